@@ -156,6 +156,6 @@ def work(case):
 
 
 def tolerance(case):
-    """The inputs, h, Y and out are bf16, sums fp32: against the layer in 64 bits the output is off by 3.0e-3 in the
-    2-norm and up to 1.4e-2 in one element, most of it from where the two intermediate roundings fall."""
-    return {"rel": 1.2e-2, "max": 5.6e-2}
+    """The inputs, h, Y and out are bf16, sums fp32.  Against the layer in 64 bits the output is off by 2.35e-3 in the
+    2-norm (the same at every size) and by up to 1.45e-2 in one element; four times that is allowed."""
+    return {"rel": 9.4e-3, "max": 5.8e-2}
