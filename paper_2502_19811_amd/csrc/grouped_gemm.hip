@@ -22,19 +22,9 @@
 #include <atomic>
 #include <mutex>
 
-#include "moe_internal.h"
+#include "moe_device.h"
 
 namespace moe {
-
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(4))) short s16x4;
-typedef __attribute__((ext_vector_type(8))) short s16x8;
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
-typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-
-enum { MODE_L0_GELU = 0, MODE_L0_SWIGLU = 1, MODE_L1 = 2 };
 
 constexpr int BK = kTileK, NS = kStages, BN = kTileN;
 #ifndef MOE_READ_GROUPS
@@ -47,13 +37,6 @@ constexpr int B_STAGE = BK * BN * 2;  // 16 KiB
 
 __device__ __forceinline__ bf16x8 lds_read_a(uint32_t addr) {
   return *(const bf16x8 __attribute__((address_space(3)))*)(uintptr_t)addr;
-}
-// Two transposing reads: lane gets B[k0..k0+3][n] and B[k0+4..k0+7][n] of its column n.
-__device__ __forceinline__ bf16x8 lds_read_b(uint32_t a0, uint32_t a1) {
-  s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(uintptr_t)a0);
-  s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(uintptr_t)a1);
-  s16x8 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-  return __builtin_bit_cast(bf16x8, v);
 }
 // Packed weights: a fragment (32 columns x 16 values of K) lies in LDS in lane order, 16 bytes per lane.
 __device__ __forceinline__ bf16x8 lds_read_b_packed(uint32_t a) {
@@ -76,48 +59,9 @@ __device__ __forceinline__ void dma16_at(const void* sbase, uint32_t voff, uint3
                  : "memory", "scc");
   }
 }
-// Tells the compiler that a pointer / integer is the same in every lane (keeps it in scalar registers).
-__device__ __forceinline__ const char* uniform(const char* ptr) {
-  const uint64_t v = (uint64_t)(uintptr_t)ptr;
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return (const char*)(uintptr_t)(((uint64_t)hi << 32) | lo);
-}
-__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
-
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
-// GELU in its erf form, 0.5 v (1 + erf(v / sqrt 2)).  erf is evaluated with the classic 5-term rational
-// approximation 1 - (a1 t + ... + a5 t^5) exp(-z^2), t = 1 / (1 + 0.3275911 z) (absolute error below 1.5e-7,
-// far under the bf16 rounding of the result); it needs a handful of registers, which matters next to 256
-// live accumulators.
-__device__ __forceinline__ float gelu_erf(float v) {
-  const float z = fabsf(v) * 0.70710678118654752f;
-  const float t = __builtin_amdgcn_rcpf(1.0f + 0.3275911f * z);
-  float poly = 1.061405429f;
-  poly = poly * t - 1.453152027f;
-  poly = poly * t + 1.421413741f;
-  poly = poly * t - 0.284496736f;
-  poly = poly * t + 0.254829592f;
-  const float erf_abs = 1.0f - poly * t * __builtin_amdgcn_exp2f(z * z * -1.4426950408889634f);
-  const float erf_v = v < 0.f ? -erf_abs : erf_abs;
-  return 0.5f * v * (1.0f + erf_v);
-}
-// v * sigmoid(v) with the hardware exp2 and reciprocal (about 1 ulp each; the result is rounded to bf16 anyway).
-__device__ __forceinline__ float silu(float v) {
-  return v * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(v * -1.4426950408889634f));
-}
-
-// Wait until *flag >= want.  Returns false if the spin limit (when set) ran out.
-__device__ __forceinline__ bool spin_until_ge(const uint32_t* flag, uint32_t want, uint32_t spin_limit) {
-  uint32_t polls = 0;
-  while (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) < want) {
-    __builtin_amdgcn_s_sleep(8);
-    if (spin_limit && ++polls >= spin_limit) return false;
-  }
-  return true;
 }
 
 // Top-k weighted reduction of one unit: kCombineChunk tokens x one 256-column panel of Y.  A thread owns 8 columns

@@ -135,6 +135,7 @@ __global__ __launch_bounds__(256) void k_index_scatter(IndexParams p) {
   __shared__ int32_t off[kMaxExperts];     // first row of each expert
   __shared__ int32_t before[kMaxExperts];  // rows of each expert owned by earlier workgroups
   __shared__ int32_t tbase[kMaxExperts];   // first M-tile of each expert (workgroup 0)
+  __shared__ int32_t tallest;              // rows of the tallest tile (workgroup 0)
   const int E = p.s.E, R = p.s.R, k = p.s.k;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int my_cnt = 0;
@@ -173,7 +174,12 @@ __global__ __launch_bounds__(256) void k_index_scatter(IndexParams p) {
     int h0 = 0, h1 = 0;
     const int my_tiles = e < E ? my_cnt / p.tile_m + tail_tiles(my_cnt % p.tile_m, p.tile_m, &h0, &h1) : 0;
     const int n_tiles = exclusive_scan_256(tbase, my_tiles);
+    if (threadIdx.x == 0) tallest = 0;
+    __syncthreads();
+    if (e < E) atomicMax(&tallest, my_cnt < p.tile_m ? my_cnt : p.tile_m);
+    __syncthreads();
     if (threadIdx.x == 0) {
+      p.ws.status[6] = tallest;
       p.ws.status[0] = 0;
       p.ws.status[1] = n_tiles;
       p.ws.status[2] = n_tiles * p.n_tiles_n0;

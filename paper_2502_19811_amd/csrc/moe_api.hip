@@ -34,6 +34,7 @@ struct moe_plan {
   int32_t spin_limit;
   int32_t phases;
   int32_t n_cu;          // 0: not queried yet
+  int32_t n_cu_set;      // 1: n_cu was set by the caller
   int32_t profile;       // 1: record events around the phases of every forward
   int32_t prof_steps;    // forwards recorded since the last reset (at most kProfSlots)
   int32_t prof_dropped;  // forwards since the last reset that found every slot taken and were not recorded
@@ -121,6 +122,31 @@ Workspace view(const moe_plan* p, void* base) {
   return w;
 }
 
+// Tiles of the table at most (a short one beside the full ones per expert, two with 256-row tiles), for the grid of the
+// decode kernel.
+int decode_slots(const Shape& s, int tile_m, int max_tiles) {
+  const int experts = s.E < s.R ? s.E : s.R;
+  int n = s.R / tile_m + (tile_m == 256 ? 2 : 1) * experts;
+  if (n > s.R) n = s.R;
+  return n < max_tiles ? n : max_tiles;
+}
+
+// log2 of the parts the 8 wavefronts of a decode workgroup split K into; pair: gate and up columns are different
+// wavefronts.  Up to kDecodeSerialK the sum is the tile kernel's, step by step.  Above, as many parts as leave a wavefront
+// 12 steps of 64 (a shorter stream is all start and end: 5 steps 217 us, 20 steps 210 us on layer1 of 64 experts of
+// F = 2560; plain weights 24, since fewer parts are longer runs of a row: 272 -> 222 us there), or fewer steps where the
+// workgroups would not go round the device twice.
+int decode_k_split(const moe_plan* p, int K, int N, bool pair, int n_slots) {
+  if (K <= kDecodeSerialK) return 0;
+  int log2 = pair ? 2 : 3;
+  while (log2 > 0 && (K / 64 >> log2) < (p->weights_packed ? 12 : 24)) {
+    const int64_t units = (int64_t)n_slots * N / (32 * (8 >> (log2 - 1)) / (pair ? 2 : 1));
+    if (units < 2 * p->n_cu) break;
+    log2--;
+  }
+  return log2;
+}
+
 int default_tile_m(const Shape& s) {
   // Tallest tile the schedule may use; the ragged end of an expert gets shorter tiles (128 / 64 rows) anyway.
   const int mean_rows = s.E > 0 ? s.R / s.E : 0;
@@ -195,6 +221,23 @@ int default_layer0_waves(const Shape& s, int ingest_gbps) {
   }
   if (waves > s.S) waves = s.S;
   return waves < 1 ? 1 : waves;
+}
+
+// Whether a GroupGEMM of n_tiles_n column tiles runs as k_decode_gemm (one pass over the weights for a few rows per
+// expert) or as the persistent tile kernel.  Measured, us per layer0 / layer1 launch, tile kernel -> decode kernel:
+//   packed, 8 experts of F = 14336     1 token 116 / 143 -> 84 / 45, 16 tokens 327 / 204 -> 317 / 164, 64: 333 / 209 -> 335 / 170,
+//                                      128 (32 rows per expert, a second part for half of them): 338 / 214 -> 525 / 256
+//   packed, 64 experts of F = 2560     1 token 68 / 46 -> 60 / 34, 48: 412 / 218 -> 394 / 210, 128 (16 rows): 418 / 222 -> 406 / 222
+//   plain, 8 experts of F = 1792       8 tokens (112 / 128 tiles) 66 / 35 -> 50 / 28, 64: 68 / 36 -> 53 / 32
+//   plain, 8 experts of F = 14336      16 tokens (896 / 128 tiles) 345 / 190 -> 366 / 190
+// So packed weights take it up to 16 rows per expert.  Plain weights, whose rows it reads in pieces of 128 bytes against
+// the tile kernel's 512, take it only where the tiles leave compute units idle.
+bool decode_path(const moe_plan* p, int n_tiles_n, int n_cu) {
+  const Shape& s = p->s;
+  if ((int64_t)s.R > (int64_t)kDecodeRowsPerExpert * s.E) return false;
+  if (!p->weights_packed && (int64_t)(s.E < s.R ? s.E : s.R) * n_tiles_n >= n_cu) return false;
+  return p->layer1_order == 0 && !p->fuse_layers && p->n_prefetch <= 0 && !p->handoff_fences && !p->alias_experts &&
+         !p->large_schedule && !p->n_cu_set;
 }
 
 bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
@@ -313,6 +356,7 @@ int moe_plan_set_option(moe_plan_t* p, const char* key, int64_t v) {
   if (!strcmp(key, "n_cu")) {
     if (v < 8 || v > 1024) return MOE_ERR_INVALID_ARG;
     p->n_cu = (int32_t)v;
+    p->n_cu_set = 1;
     return MOE_OK;
   }
   if (!strcmp(key, "block_m")) {
@@ -496,6 +540,7 @@ int forward_impl(moe_plan_t* p, const void* x, const int32_t* topk_ids, const fl
   // tile count, which bounds the per-workgroup tile counters)
   const bool one_launch = p->fuse_layers && (p->phases & 2) && (p->phases & 4) && !fused && !large;
 
+  const bool decode0 = decode_path(p, p->n_tiles_n0, p->n_cu), decode1 = decode_path(p, p->n_tiles_n1, p->n_cu);
   GemmParams a = g;
   a.A = (const char*)x;
   a.lda_bytes = (uint32_t)s.H * 2;
@@ -578,6 +623,50 @@ int forward_impl(moe_plan_t* p, const void* x, const int32_t* topk_ids, const fl
     if (launch_zero_u32(ws.arrive, (size_t)s.T * p->n_tiles_n1, st) != hipSuccess) return MOE_ERR_HIP;
   }
 
+  DecodeParams d0, d1;
+  if (decode0 || decode1) {
+    memset(&d0, 0, sizeof(d0));
+    d0.n_slots = decode_slots(s, p->tile_m, p->max_tiles);
+    d0.tile_m = s.R < p->tile_m ? s.R : p->tile_m;
+    d0.T = s.T;
+    d0.n_cu = p->n_cu;
+    d0.n_tiles = g.n_tiles;
+    d0.tallest = ws.status + 6;
+    d0.tile_expert = g.tile_expert;
+    d0.tile_row0 = g.tile_row0;
+    d0.tile_rows = g.tile_rows;
+    d0.tile_ready = g.tile_ready;
+    d0.status = g.status;
+    d0.spin_limit = g.spin_limit;
+    d0.F = s.F;
+    d1 = d0;
+    d0.A = (const char*)x;
+    d0.lda_bytes = (uint32_t)s.H * 2;
+    d0.a_rows = ws.row_token;
+    d0.B = (const char*)W1;
+    d0.b_expert_bytes = (uint64_t)s.H * s.F1 * 2;
+    d0.ldb = (uint32_t)s.F1;
+    d0.n_tiles_n = p->n_tiles_n0;
+    d0.C = ws.h;
+    d0.ldc = (uint32_t)s.F;
+    d0.K = s.H;
+    d0.N = s.F;
+    d0.seg_ready = seg_ready;
+    d0.ready_epoch = ready_epoch;
+    d0.k_split_log2 = decode_k_split(p, s.H, s.F, s.act == MOE_ACT_SWIGLU, d0.n_slots);
+    d1.A = (const char*)ws.h;
+    d1.lda_bytes = (uint32_t)s.F * 2;
+    d1.B = (const char*)W2;
+    d1.b_expert_bytes = (uint64_t)s.F * s.H * 2;
+    d1.ldb = (uint32_t)s.H;
+    d1.n_tiles_n = p->n_tiles_n1;
+    d1.C = ws.Y;
+    d1.ldc = (uint32_t)s.H;
+    d1.K = s.F;
+    d1.N = s.H;
+    d1.k_split_log2 = decode_k_split(p, s.F, s.H, false, d1.n_slots);
+  }
+
   if (one_launch) {
     FuseParams f;
     f.tile_done = ws.tile_done;
@@ -590,9 +679,11 @@ int forward_impl(moe_plan_t* p, const void* x, const int32_t* topk_ids, const fl
     if (launch_fused_layers(a, b, f, s.act, grid, st) != hipSuccess) return MOE_ERR_HIP;
     if (!mark(2)) return MOE_ERR_HIP;   // the whole launch is booked as the layer0 phase
   } else {
-    if ((p->phases & 2) && launch_layer0(a, s.act, grid0, st) != hipSuccess) return MOE_ERR_HIP;
+    if ((p->phases & 2) && (decode0 ? launch_decode_gemm(d0, 0, s.act, p->weights_packed, st) : launch_layer0(a, s.act, grid0, st)) != hipSuccess)
+      return MOE_ERR_HIP;
     if (!mark(2)) return MOE_ERR_HIP;
-    if ((p->phases & 4) && launch_layer1(b, grid1, st) != hipSuccess) return MOE_ERR_HIP;
+    if ((p->phases & 4) && (decode1 ? launch_decode_gemm(d1, 1, s.act, p->weights_packed, st) : launch_layer1(b, grid1, st)) != hipSuccess)
+      return MOE_ERR_HIP;
   }
   if (!mark(3)) return MOE_ERR_HIP;
   if ((p->phases & 8) && !(fused && (p->phases & 4)) && !in_epilogue) {

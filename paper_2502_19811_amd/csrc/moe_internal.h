@@ -15,6 +15,8 @@ constexpr int kTileN = 256;         // columns of B staged per GroupGEMM tile
 constexpr int kTileK = 32;          // depth of one LDS stage
 constexpr int kStages = 4;          // LDS stages in flight
 constexpr int kCombineChunk = 256;  // tokens per unit of combine work
+constexpr int kDecodeRowsPerExpert = 16;   // rows per expert on average up to which the decode kernel is used
+constexpr int kDecodeSerialK = 1024;       // ... and the reduction length up to which it sums K in one part
 constexpr int kXcds = 8;            // XCDs of the device: workgroup i runs on XCD i % 8
 constexpr int kScheduleTileCap = 2048;  // M-tiles up to which the multi-workgroup schedule builder is used
 
@@ -31,7 +33,7 @@ struct ItemRec {
 struct Workspace {
   int32_t* status;        // [64]  0: device status word, 1: n_tiles, 2: items of layer0, 3: items of layer1,
                           //       4: combine unit counter, 5: serial number of the last forward that saw an expert
-                          //       id out of range; per XCD: 8..15 layer0 queue heads, 16..23 layer1 queue
+                          //       id out of range; 6: rows of the tallest tile; per XCD: 8..15 layer0 queue heads, 16..23 layer1 queue
                           //       heads, 24..31 layer0 queue lengths, 32..39 layer1 queue lengths, 40..47 layer1
                           //       queue bases, 48..55 layer0 queue bases (only with contiguous layer0 queues;
                           //       otherwise layer0's queue x is list positions x, x+8, ...)
@@ -136,6 +138,39 @@ struct FuseParams {
   int32_t publish_every;    // layer0 tiles between two publications of a workgroup
 };
 
+// The GroupGEMM of small batches (decode_gemm.hip): no schedule, a workgroup is one (tile of the table, 32 rows of it,
+// columns) unit found from its index.
+struct DecodeParams {
+  const char* A;            // x (layer0) or h (layer1), bf16
+  uint32_t lda_bytes;
+  const int32_t* a_rows;    // layer0: sorted row -> row of A (gather); layer1: nullptr (identity)
+  const char* B;            // W1 or W2, plain or packed
+  uint64_t b_expert_bytes;  // plain: bytes between experts
+  uint32_t ldb;             // plain: elements per row of B
+  int32_t n_tiles_n;        // packed: column tiles of this layer
+  uint16_t* C;              // h (layer0) or Y (layer1)
+  uint32_t ldc;
+  int32_t K;                // reduction length
+  int32_t N;                // columns of C
+  int32_t F;                // expert hidden size (gate/up split of W1 columns)
+  int32_t k_split_log2;     // the 8 wavefronts of a workgroup split K into 1, 2, 4 or 8 parts
+  int32_t n_slots;          // bound on the tiles of the table
+  int32_t tile_m;           // rows of the tallest tile there can be
+  int32_t T;
+  int32_t n_groups;         // workgroups along the columns
+  int32_t n_cu;
+  const int32_t* n_tiles;   // device scalars: tiles in the table, rows of the tallest
+  const int32_t* tallest;
+  const int32_t* tile_expert;
+  const int32_t* tile_row0;
+  const int32_t* tile_rows;
+  const int32_t* tile_ready;
+  const uint32_t* seg_ready;
+  uint32_t ready_epoch;
+  uint32_t spin_limit;
+  int32_t* status;
+};
+
 struct ArrivalParams {
   int32_t S;
   int32_t seg_offsets[kMaxSegments + 1];
@@ -161,6 +196,7 @@ hipError_t launch_index_build(const IndexParams& p, hipStream_t st);
 hipError_t launch_reset_counters(const Workspace& ws, int n_tiles_n1, int max_tiles, hipStream_t st);
 hipError_t launch_layer0(const GemmParams& p, int act, int grid, hipStream_t st);
 hipError_t launch_layer1(const GemmParams& p, int grid, hipStream_t st);
+hipError_t launch_decode_gemm(const DecodeParams& p, int layer1, int act, int packed, hipStream_t st);
 hipError_t launch_fused_layers(const GemmParams& p0, const GemmParams& p1, const FuseParams& f, int act, int grid, hipStream_t st);
 hipError_t launch_combine(const CombineParams& p, hipStream_t st);
 hipError_t launch_zero_u32(uint32_t* ptr, size_t n, hipStream_t st);

@@ -1,0 +1,67 @@
+"""The GroupGEMM of small batches against the oracle, at the sizes where it changes its shape: 8 / 9 and 16 / 17 tokens
+(8, 16 and 32 rows per unit), experts with more rows than a unit holds, reduction lengths around the one up to which K is
+summed in one part and such that the parts of K differ in length, and the first batch beyond it (tile kernel)."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as wl
+from oracle import moe_oracle as orc
+
+pytestmark = pytest.mark.gpu
+
+SIZES = [
+    # T, H, F, E, k, act
+    (1, 1280, 1152, 8, 2, wl.ACT_SWIGLU),
+    (8, 1280, 1152, 8, 2, wl.ACT_SWIGLU),
+    (9, 1280, 1152, 8, 2, wl.ACT_SWIGLU),
+    (16, 1024, 1280, 8, 2, wl.ACT_GELU),
+    (17, 2304, 1280, 8, 2, wl.ACT_GELU),
+    (64, 1280, 1152, 8, 2, wl.ACT_SWIGLU),
+    (65, 1280, 1152, 8, 2, wl.ACT_SWIGLU),
+    (3, 2048, 2176, 64, 16, wl.ACT_SWIGLU),
+]
+
+
+@pytest.mark.parametrize("size", SIZES, ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("packed", [False, True], ids=["plain", "packed"])
+def test_small_batches_match_the_oracle(size, packed):
+    import gpu_harness as H
+    T, Hd, F, E, k, act = size
+    cfg = wl.MoEConfig("decode", T=T, H=Hd, F=F, E=E, k=k, act=act, S=3, seed=600 + T)
+    inp = wl.make_inputs(cfg, threads=4)
+    routed, w = orc.route_topk(inp.logits, k)
+    crowded = np.tile(np.arange(E - k, E, dtype=np.int32), (T, 1))     # every token to the same k experts: T rows each
+    for ids in (routed, crowded):
+        print(f"decode {size} packed {packed} rows of the fullest expert {np.bincount(ids.ravel()).max()}", flush=True)
+        ref = orc.moe_layer(inp.x, inp.W1, inp.W2, ids, w, act)
+        layer = H.GpuLayer(cfg, inp, ids, w, packed=packed)
+        layer.forward(); run = layer.results()
+        assert run.status == 0
+        a, b = H.error_metrics(run.out, ref)
+        print(f"  err {a:.3e} {b:.3e}", flush=True)
+        assert a <= H.REL_TOL and b <= H.REL_TOL
+        # ready flags that are all there, and no row written beyond the batch's
+        layer.out.fill_(7.0)
+        layer.forward(seg_ready=torch.ones(cfg.S, dtype=torch.int32, device="cuda"), epoch=1)
+        np.testing.assert_array_equal(layer.results().out, run.out)
+        layer.close()
+
+
+def test_small_batch_with_a_missing_flag_times_out():
+    import gpu_harness as H
+    cfg = wl.MoEConfig("decode_flag", T=12, H=1280, F=1152, E=4, k=2, act=wl.ACT_SWIGLU, S=2, seed=650)
+    inp = wl.make_inputs(cfg, threads=4)
+    ids, w = orc.route_topk(inp.logits, cfg.k)
+    layer = H.GpuLayer(cfg, inp, ids, w, {"spin_limit": 200}, packed=True)
+    flags = torch.tensor([1, 0], dtype=torch.int32, device="cuda")
+    print("decode with a flag that never arrives", flush=True)
+    layer.forward(seg_ready=flags, epoch=1)
+    assert layer.results().status == -6
+    flags[1] = 1
+    layer.forward(seg_ready=flags, epoch=1)
+    run = layer.results()
+    layer.close()
+    assert run.status == 0
+    a, b = H.error_metrics(run.out, orc.moe_layer(inp.x, inp.W1, inp.W2, ids, w, cfg.act))
+    assert a <= H.REL_TOL and b <= H.REL_TOL
