@@ -135,7 +135,6 @@ __global__ __launch_bounds__(256) void k_index_scatter(IndexParams p) {
   __shared__ int32_t off[kMaxExperts];     // first row of each expert
   __shared__ int32_t before[kMaxExperts];  // rows of each expert owned by earlier workgroups
   __shared__ int32_t tbase[kMaxExperts];   // first M-tile of each expert (workgroup 0)
-  __shared__ int32_t tallest;              // rows of the tallest tile (workgroup 0)
   const int E = p.s.E, R = p.s.R, k = p.s.k;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int my_cnt = 0;
@@ -174,12 +173,7 @@ __global__ __launch_bounds__(256) void k_index_scatter(IndexParams p) {
     int h0 = 0, h1 = 0;
     const int my_tiles = e < E ? my_cnt / p.tile_m + tail_tiles(my_cnt % p.tile_m, p.tile_m, &h0, &h1) : 0;
     const int n_tiles = exclusive_scan_256(tbase, my_tiles);
-    if (threadIdx.x == 0) tallest = 0;
-    __syncthreads();
-    if (e < E) atomicMax(&tallest, my_cnt < p.tile_m ? my_cnt : p.tile_m);
-    __syncthreads();
     if (threadIdx.x == 0) {
-      p.ws.status[6] = tallest;
       p.ws.status[0] = 0;
       p.ws.status[1] = n_tiles;
       p.ws.status[2] = n_tiles * p.n_tiles_n0;
@@ -462,7 +456,8 @@ __global__ __launch_bounds__(1024) void k_index_schedule_large(IndexParams p) {
 // loop.  The 32 workgroups of an XCD, taking consecutive items, then work on G M-tiles x about 32/G column tiles of
 // one expert wherever in the block they are, and share both operands in their L2; an expert with few rows is
 // streamed through one XCD only (its weight panels are fetched once).
-constexpr int kScheduleWgs = 8;
+constexpr int kFewItems = 128;       // items of a layer up to which they are dealt out without blocks
+constexpr int kScheduleWgs = 64;   // at most; one per 1024 items up to there (8 for 35 k items: 44 us)
 
 struct ScheduleLds {
   int32_t row0[kTileCap];
@@ -481,7 +476,7 @@ struct ScheduleLds {
   uint8_t key1[kTileCap + 4];   // height class
   uint16_t sub_first[kTileCap];       // position in ord1 of the first tile of tile i's run (same height, expert, wave)
   uint16_t blk_of[kTileCap];          // block of the tile at position i of ord1
-  int32_t scan_buf[1024];             // scratch of the prefix scans
+  int32_t scan_buf[16];               // scratch of the prefix scans
   int32_t cls_first[4];
   int32_t cls_count[3];
   int32_t queue_pos[3][kXcds];
@@ -522,24 +517,29 @@ __device__ inline void rank_sort(const uint8_t* key, uint16_t* ord, int n, int t
 }
 
 // Inclusive prefix scan over up to 2048 values, two per thread (thread t holds elements 2t and 2t+1), running maximum
-// (MAX) or running sum.  buf: LDS scratch of 1024 values.
+// (MAX) or running sum: inside the wavefronts by lane exchange, across them through 16 values of LDS (buf).
 template <bool MAX>
 __device__ inline void scan_pairs(int32_t* buf, int& v0, int& v1) {
-  const int t = threadIdx.x;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   constexpr int kNeutral = MAX ? -0x7fffffff : 0;
-  v1 = MAX ? max(v0, v1) : v0 + v1;
-  buf[t] = v1;
-  __syncthreads();
-  for (int d = 1; d < 1024; d <<= 1) {
-    const int o = t >= d ? buf[t - d] : kNeutral;
-    __syncthreads();
-    buf[t] = MAX ? max(buf[t], o) : buf[t] + o;
-    __syncthreads();
+  auto join = [](int a, int b) { return MAX ? max(a, b) : a + b; };
+  v1 = join(v0, v1);
+  int incl = v1;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int o = __shfl_up(incl, d);
+    if (lane >= d) incl = join(incl, o);
   }
-  const int before = t > 0 ? buf[t - 1] : kNeutral;
+  const int prev = __shfl_up(incl, 1);
+  int before = lane > 0 ? prev : kNeutral;
+  if (lane == 63) buf[wave] = incl;
   __syncthreads();
-  v0 = MAX ? max(before, v0) : before + v0;
-  v1 = MAX ? max(before, v1) : before + v1;
+#pragma unroll
+  for (int w = 0; w < 15; w++)
+    if (w < wave) before = join(before, buf[w]);
+  __syncthreads();
+  v0 = join(before, v0);
+  v1 = join(before, v1);
 }
 
 // Items of one layer in the locality order (see above); n_tiles_n column tiles.
@@ -621,41 +621,32 @@ __device__ inline void build_blocks(ScheduleLds& L, const uint16_t* ord1, int n_
   __syncthreads();
 }
 
-__global__ __launch_bounds__(1024) void k_index_schedule(IndexParams p) {
-  __shared__ __attribute__((aligned(16))) ScheduleLds L;
-  const int n_tiles = p.ws.status[1];
+// M-tile m as the schedule builder sees it: its table row and the segment of its last row (of token `last_token`).
+__device__ inline void note_tile(ScheduleLds& L, const IndexParams& p, const int32_t* seg_lds, int m, int expert, int row0,
+                                 int nrows, int kind, int last_token, bool publish) {
+  const int S = p.s.S, nseg = p.layer0_order == 1 ? S : 1;
+  int s = 0;
+  while (s + 1 < S && seg_lds[s + 1] <= last_token) s++;
+  L.row0[m] = row0;
+  L.rows[m] = (uint16_t)nrows;
+  L.kind[m] = (uint8_t)kind;
+  L.expert[m] = (uint8_t)expert;
+  L.ready[m] = (uint8_t)s;
+  L.key0[m] = (uint8_t)((2 - kind) * nseg + (nseg > 1 ? s : 0));
+  L.key1[m] = (uint8_t)(2 - kind);
+  atomicAdd(&L.cls_count[2 - kind], 1);
+  if (publish) p.ws.tile_ready[m] = s;
+}
+
+// The schedules of both layers from the noted tiles.  The workgroups that share the work (gtid of gthreads) all build the
+// tables; the one with first set writes the queues.  Entered with the tiles noted and a barrier behind them.
+__device__ inline void build_schedules(ScheduleLds& L, const IndexParams& p, int n_tiles, bool first, int gtid, int gthreads) {
   const int tid = threadIdx.x;
-  const int S = p.s.S;
-  const int nseg = p.layer0_order == 1 ? S : 1;
+  const int S = p.s.S, nseg = p.layer0_order == 1 ? S : 1;
   // layer0: 0 expert-major (locality order), 1 by source segment, 2 locality order inside waves of source segments
   const bool local0 = p.layer0_order != 1, local1 = p.layer1_order == 0;
   const int n_waves0 = p.layer0_order == 2 ? max(1, min(p.layer0_waves, min(S, 8))) : 1;
   const int block_m = p.block_m;   // M-tiles per block of the locality order (1..8)
-  __shared__ int32_t seg_lds[kMaxSegments + 1];
-  if (tid <= S) seg_lds[tid] = p.seg_offsets[tid];
-  if (tid < 3) L.cls_count[tid] = 0;
-  __syncthreads();
-  for (int m = tid; m < n_tiles + 4; m += 1024) {
-    if (m >= n_tiles) {
-      L.key0[m] = 0xff;
-      L.key1[m] = 0xff;
-      continue;
-    }
-    const int r0 = p.ws.tile_row0[m], nr = p.ws.tile_rows[m], kd = p.ws.tile_kind[m];
-    const int t = p.ws.row_token[r0 + nr - 1];
-    int s = 0;
-    while (s + 1 < S && seg_lds[s + 1] <= t) s++;
-    L.row0[m] = r0;
-    L.rows[m] = (uint16_t)nr;
-    L.kind[m] = (uint8_t)kd;
-    L.expert[m] = (uint8_t)p.ws.tile_expert[m];
-    L.ready[m] = (uint8_t)s;
-    L.key0[m] = (uint8_t)((2 - kd) * nseg + (nseg > 1 ? s : 0));
-    L.key1[m] = (uint8_t)(2 - kd);
-    atomicAdd(&L.cls_count[2 - kd], 1);
-    if (blockIdx.x == 0) p.ws.tile_ready[m] = s;
-  }
-  __syncthreads();
   rank_sort(L.key0, L.ord0, n_tiles, tid);
   if (nseg > 1) rank_sort(L.key1, L.ord1, n_tiles, tid);
   if (tid == 0) {
@@ -676,21 +667,37 @@ __global__ __launch_bounds__(1024) void k_index_schedule(IndexParams p) {
       const int cnt = nt == 0 ? 0 : max(0, min(chunk, nt - tid * chunk));
       pos += cnt * p.n_tiles_n1;
     }
-    if (blockIdx.x == 0 && !local1) {
+    if (first && !local1) {
       p.ws.status[32 + tid] = pos - tid * cap;
       p.ws.status[40 + tid] = tid * cap;
     }
-    if (blockIdx.x == 0 && !local0) {
+    if (first && !local0) {
       const int n0 = n_tiles * p.n_tiles_n0;
       p.ws.status[24 + tid] = tid < n0 ? (n0 - tid + kXcds - 1) / kXcds : 0;   // positions tid, tid + 8, ...
     }
   }
   __syncthreads();
   const uint16_t* ord1 = nseg > 1 ? L.ord1 : L.ord0;   // height class, then table order (expert-major)
-  const int gtid = blockIdx.x * 1024 + tid, gthreads = gridDim.x * 1024;
+  // So few items that most workgroups get none and none gets a second: there is no locality to arrange, the items are
+  // dealt out one by one (the block tables cost 4 us, of 38 us for a layer of 128 tokens and H = 256).
+  if (local0 && local1 && n_waves0 == 1 && n_tiles * max(p.n_tiles_n0, p.n_tiles_n1) <= kFewItems) {
+    auto deal = [&](ItemRec* items, int n_tiles_n, int len_at, int base_at) {
+      const int n = n_tiles * n_tiles_n;
+      auto base = [&](int x) { return x * (n / kXcds) + min(x, n % kXcds); };
+      for (int i = gtid; i < n; i += gthreads)
+        items[base(i % kXcds) + i / kXcds] = make_item_lds(L, ord1[i / n_tiles_n], i % n_tiles_n);
+      if (first && tid < kXcds) {
+        p.ws.status[len_at + tid] = base(tid + 1) - base(tid);
+        p.ws.status[base_at + tid] = base(tid);
+      }
+    };
+    deal(p.ws.items0, p.n_tiles_n0, 24, 48);
+    deal(p.ws.items1, p.n_tiles_n1, 32, 40);
+    return;
+  }
   if (local0) {
     build_blocks(L, ord1, n_tiles, block_m, n_waves0, S);
-    if (blockIdx.x == 0 && tid < kXcds) {
+    if (first && tid < kXcds) {
       p.ws.status[24 + tid] = L.q_len_t[tid] * p.n_tiles_n0;
       p.ws.status[48 + tid] = L.q_base_t[tid] * p.n_tiles_n0;
     }
@@ -705,7 +712,7 @@ __global__ __launch_bounds__(1024) void k_index_schedule(IndexParams p) {
       __syncthreads();   // the layer0 items are out: the block tables can be rebuilt without waves
       build_blocks(L, ord1, n_tiles, block_m, 1, S);
     }
-    if (blockIdx.x == 0 && tid < kXcds) {
+    if (first && tid < kXcds) {
       p.ws.status[32 + tid] = L.q_len_t[tid] * p.n_tiles_n1;
       p.ws.status[40 + tid] = L.q_base_t[tid] * p.n_tiles_n1;
     }
@@ -732,6 +739,184 @@ __global__ __launch_bounds__(1024) void k_index_schedule(IndexParams p) {
       }
     }
   }
+}
+
+__global__ __launch_bounds__(1024) void k_index_schedule(IndexParams p) {
+  __shared__ __attribute__((aligned(16))) ScheduleLds L;
+  __shared__ int32_t seg_lds[kMaxSegments + 1];
+  const int n_tiles = max(0, min(p.ws.status[1], p.max_tiles));
+  const int tid = threadIdx.x;
+  if (tid <= p.s.S) seg_lds[tid] = p.seg_offsets[tid];
+  if (tid < 3) L.cls_count[tid] = 0;
+  __syncthreads();
+  for (int m = tid; m < n_tiles + 4; m += 1024) {
+    if (m >= n_tiles) {
+      L.key0[m] = 0xff;
+      L.key1[m] = 0xff;
+      continue;
+    }
+    const int r0 = p.ws.tile_row0[m], nr = p.ws.tile_rows[m], kd = p.ws.tile_kind[m];
+    note_tile(L, p, seg_lds, m, p.ws.tile_expert[m], r0, nr, kd, p.ws.row_token[max(0, min(r0 + nr, p.s.R) - 1)], blockIdx.x == 0);
+  }
+  __syncthreads();
+  build_schedules(L, p, n_tiles, blockIdx.x == 0, blockIdx.x * 1024 + tid, gridDim.x * 1024);
+}
+
+// ---------------------------------------------------------------------------------------------
+// The whole index build of a small batch in one workgroup: the three kernels above it are 5 us each of launch and
+// start, whatever the batch (with 128 tokens, 21 us of a 43 us forward).  Wavefronts rank their runs of 64 pair ids as
+// k_index_scatter does; the runs' counts, the row order and the tile table stay in LDS.  schedule: 0 leaves the tile
+// schedules out (a forward whose GroupGEMMs do not use them).
+// ---------------------------------------------------------------------------------------------
+__global__ __launch_bounds__(1024) void k_index_small(IndexParams p, int schedule) {
+  constexpr int kRuns = kIndexSmallRows / 64, kPerWave = kRuns / 16;
+  __shared__ __attribute__((aligned(16))) ScheduleLds L;
+  __shared__ int32_t seg_lds[kMaxSegments + 1];
+  __shared__ uint16_t run_cnt[kRuns * kMaxExperts];   // [run][expert]: rows of the expert in the run, then in the runs before it
+  __shared__ int32_t token_of[kIndexSmallRows];       // row -> token
+  __shared__ int32_t cnt[kMaxExperts], off[kMaxExperts], tbase[kMaxExperts + 1];
+  const int E = p.s.E, R = p.s.R, k = p.s.k;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n_runs = (R + 63) / 64;
+  int key[kPerWave], rank[kPerWave];
+#pragma unroll
+  for (int i = 0; i < kPerWave; i++) {
+    const int q = (i * 16 + wave) * 64 + lane;
+    key[i] = q < R ? p.topk_ids[q] : -1;
+  }
+  for (int i = tid; i < n_runs * E; i += 1024) run_cnt[i] = 0;
+  if (tid <= p.s.S) seg_lds[tid] = p.seg_offsets[tid];
+  if (tid < 3) L.cls_count[tid] = 0;
+  if (tid < kMaxExperts) cnt[tid] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < kPerWave; i++) {
+    const int run = i * 16 + wave;
+    if (run >= n_runs) break;
+    const bool valid = run * 64 + lane < R;
+    int e = key[i];
+    if (valid && (unsigned)e >= (unsigned)E) {   // not an expert: reported through the status word, counted as the last expert
+      p.ws.status[5] = p.forward_serial;
+      e = E - 1;
+    }
+    uint64_t same = __ballot(valid);
+#pragma unroll
+    for (int bit = 0; bit < 8; bit++) {
+      const uint64_t b = __ballot((e >> bit) & 1);
+      same &= ((e >> bit) & 1) ? b : ~b;
+    }
+    const uint64_t below = same & ((1ull << lane) - 1ull);
+    key[i] = e;
+    rank[i] = __popcll(below);
+    if (valid && below == 0) run_cnt[run * E + e] = (uint16_t)__popcll(same);
+  }
+  __syncthreads();
+  if (tid < E) {
+    int acc = 0;
+    for (int r = 0; r < n_runs; r++) {
+      const int c = run_cnt[r * E + tid];
+      run_cnt[r * E + tid] = (uint16_t)acc;
+      acc += c;
+    }
+    cnt[tid] = acc;
+  }
+  __syncthreads();
+  // offsets and first tiles of the experts: four experts per lane of the first wavefront
+  if (wave == 0) {
+    int c[4], t[4], rows = 0, tiles = 0, tallest = 0, h0, h1;
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      c[i] = cnt[lane * 4 + i];
+      t[i] = c[i] / p.tile_m + tail_tiles(c[i] % p.tile_m, p.tile_m, &h0, &h1);
+      rows += c[i];
+      tiles += t[i];
+      tallest = max(tallest, min(c[i], p.tile_m));
+    }
+    int rows_incl = rows, tiles_incl = tiles;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int ro = __shfl_up(rows_incl, d), to = __shfl_up(tiles_incl, d);
+      if (lane >= d) {
+        rows_incl += ro;
+        tiles_incl += to;
+      }
+      tallest = max(tallest, __shfl_xor(tallest, d));
+    }
+    int ro = rows_incl - rows, to = tiles_incl - tiles;
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      off[lane * 4 + i] = ro;
+      tbase[lane * 4 + i] = to;
+      ro += c[i];
+      to += t[i];
+    }
+    if (lane == 63) {
+      tbase[kMaxExperts] = tiles_incl;
+      p.ws.status[0] = 0;
+      p.ws.status[1] = tiles_incl;
+      p.ws.status[2] = tiles_incl * p.n_tiles_n0;
+      p.ws.status[3] = tiles_incl * p.n_tiles_n1;
+      p.ws.status[4] = 0;
+      p.ws.status[6] = tallest;
+      p.ws.offsets[E] = rows_incl;
+    }
+  } else if (wave == 1) {
+    if (lane < 2 * kXcds) p.ws.status[8 + lane] = 0;   // queue heads of both layers
+  } else if (wave < 4) {
+    for (int i = tid - 128; i < p.n_tiles_n1; i += 128) p.ws.panel_done[i] = 0;
+  } else {
+    for (int i = tid - 256; i < p.max_tiles + 1; i += 768) p.ws.tile_done[i] = 0;
+  }
+  __syncthreads();
+  if (tid < E) {
+    p.ws.counts[tid] = cnt[tid];
+    p.ws.offsets[tid] = off[tid];
+  }
+#pragma unroll
+  for (int i = 0; i < kPerWave; i++) {
+    const int run = i * 16 + wave, q = run * 64 + lane;
+    if (q < R) {
+      const int e = key[i], pos = off[e] + run_cnt[run * E + e] + rank[i], t = q / k;
+      p.ws.perm[pos] = q;
+      p.ws.inv_perm[q] = pos;
+      p.ws.row_token[pos] = t;
+      token_of[pos] = t;
+    }
+  }
+  __syncthreads();
+  const int n_tiles = tbase[kMaxExperts];
+  for (int m = tid; m < n_tiles + 4; m += 1024) {
+    if (m >= n_tiles) {
+      L.key0[m] = 0xff;
+      L.key1[m] = 0xff;
+      continue;
+    }
+    int lo = 0, hi = E - 1;   // the last expert whose first tile is at most m (experts without tiles share the next one's)
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (tbase[mid] <= m) lo = mid;
+      else hi = mid - 1;
+    }
+    const int i = m - tbase[lo], full = cnt[lo] / p.tile_m;
+    int row0 = off[lo] + i * p.tile_m, rows = p.tile_m, height = p.tile_m;
+    if (i >= full) {
+      const int rem = cnt[lo] % p.tile_m;
+      int h0 = 0, h1 = 0;
+      tail_tiles(rem, p.tile_m, &h0, &h1);
+      row0 = off[lo] + full * p.tile_m + (i > full ? h0 : 0);
+      height = i > full ? h1 : h0;
+      rows = min(height, i > full ? rem - h0 : rem);
+    }
+    const int kind = height == 256 ? 2 : (height == 128 ? 1 : 0);
+    p.ws.tile_expert[m] = lo;
+    p.ws.tile_row0[m] = row0;
+    p.ws.tile_rows[m] = rows;
+    p.ws.tile_kind[m] = kind;
+    note_tile(L, p, seg_lds, m, lo, row0, rows, kind, token_of[row0 + rows - 1], true);
+  }
+  if (!schedule) return;
+  __syncthreads();
+  build_schedules(L, p, n_tiles, true, tid, 1024);
 }
 
 __global__ void k_tile_heights(const int32_t* __restrict__ kind, int32_t* __restrict__ height, int n) {
@@ -803,15 +988,29 @@ hipError_t launch_reset_counters(const Workspace& ws, int n_tiles_n1, int max_ti
   return hipGetLastError();
 }
 
-hipError_t launch_index_build(const IndexParams& p, hipStream_t st) {
+hipError_t launch_index_schedule(const IndexParams& p, hipStream_t st) {
+  if (!uses_large_schedule(p.max_tiles, p.force_large_schedule)) {
+    const int64_t items = (int64_t)(p.s.R / p.tile_m + p.s.E) * (p.n_tiles_n0 + p.n_tiles_n1);
+    const int wgs = (int)(items / 1024 < 1 ? 1 : (items / 1024 > kScheduleWgs ? kScheduleWgs : items / 1024));
+    hipLaunchKernelGGL(k_index_schedule, dim3(wgs), dim3(1024), 0, st, p);
+  } else {
+    hipLaunchKernelGGL(k_index_schedule_large, dim3(1), dim3(1024), 0, st, p);
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_index_build(const IndexParams& p, bool schedule, hipStream_t st) {
   if (p.s.R == 0) return hipSuccess;
+  // one workgroup while it ends before the three kernels would (it then writes the item records alone)
+  const bool large = uses_large_schedule(p.max_tiles, p.force_large_schedule);
+  if (p.s.R <= kIndexSmallRows && !large &&
+      (!schedule || (int64_t)p.max_tiles * (p.n_tiles_n0 + p.n_tiles_n1) <= kIndexSmallItems)) {
+    hipLaunchKernelGGL(k_index_small, dim3(1), dim3(1024), 0, st, p, schedule ? 1 : 0);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_index_hist, dim3(p.n_blocks), dim3(256), 0, st, p);
   hipLaunchKernelGGL(k_index_scatter, dim3(p.n_blocks), dim3(256), 0, st, p);
-  if (!uses_large_schedule(p.max_tiles, p.force_large_schedule))
-    hipLaunchKernelGGL(k_index_schedule, dim3(kScheduleWgs), dim3(1024), 0, st, p);
-  else
-    hipLaunchKernelGGL(k_index_schedule_large, dim3(1), dim3(1024), 0, st, p);
-  return hipGetLastError();
+  return launch_index_schedule(p, st);
 }
 
 }  // namespace moe

@@ -30,6 +30,7 @@ struct moe_plan {
   int32_t layer0_waves;          // 0: from the table below
   int32_t expected_ingest_gbps;  // 0: unknown
   int32_t last_layer0_order;     // what the last forward ran with (for moe_get_schedule)
+  int32_t schedule_owed;         // 1: the last index build left the tile schedules out (its GroupGEMMs run without them)
   int32_t layer1_order;
   int32_t spin_limit;
   int32_t phases;
@@ -457,6 +458,26 @@ int moe_route_topk(const float* logits, int32_t T, int32_t E, int32_t k, int32_t
 
 namespace {
 
+IndexParams index_params(const moe_plan* p, const Workspace& ws, const int32_t* topk_ids, int order0) {
+  IndexParams ip;
+  memset(&ip, 0, sizeof(ip));
+  ip.s = p->s;
+  ip.ws = ws;
+  ip.topk_ids = topk_ids;
+  ip.n_blocks = p->n_index_blocks;
+  ip.tile_m = p->tile_m;
+  ip.n_tiles_n0 = p->n_tiles_n0;
+  ip.n_tiles_n1 = p->n_tiles_n1;
+  ip.layer0_order = order0;
+  ip.layer0_waves = p->layer0_waves > 0 ? p->layer0_waves : default_layer0_waves(p->s, p->expected_ingest_gbps);
+  ip.layer1_order = p->layer1_order == 1 ? 1 : 0;   // only the in-kernel panel reduction needs the panel-major order
+  ip.max_tiles = p->max_tiles;
+  ip.force_large_schedule = p->large_schedule;
+  ip.block_m = p->block_m;
+  memcpy(ip.seg_offsets, p->seg_offsets, sizeof(int32_t) * (p->s.S + 1));
+  return ip;
+}
+
 int forward_impl(moe_plan_t* p, const void* x, const int32_t* topk_ids, const float* topk_weights, const void* W1,
                  const void* W2, int32_t act, void* out, void* workspace, size_t workspace_bytes,
                  const uint32_t* seg_ready, uint32_t ready_epoch, void* hip_stream) {
@@ -481,10 +502,10 @@ int forward_impl(moe_plan_t* p, const void* x, const int32_t* topk_ids, const fl
   // segments (Fig. 5).  The one-workgroup builder for very large tile tables knows orders 0 and 1 only.
   const bool large = uses_large_schedule(p->max_tiles, p->large_schedule);
   int order0 = p->layer0_order >= 0 ? p->layer0_order : (seg_ready ? 2 : 0);
-  const int waves0 = p->layer0_waves > 0 ? p->layer0_waves : default_layer0_waves(s, p->expected_ingest_gbps);
   if (order0 == 2 && large) order0 = 1;
   if (p->phases & 1) p->last_layer0_order = order0;
   else order0 = p->last_layer0_order;   // the schedules of the last index build are run again
+  const bool decode0 = decode_path(p, p->n_tiles_n0, p->n_cu), decode1 = decode_path(p, p->n_tiles_n1, p->n_cu);
   // a forward beyond the last event slot is not recorded (and counted as dropped) rather than overwriting an earlier one
   hipEvent_t* ev = (p->profile && p->prof_steps < kProfSlots) ? p->ev[p->prof_steps] : nullptr;
   if (p->profile && !ev) p->prof_dropped++;
@@ -492,25 +513,15 @@ int forward_impl(moe_plan_t* p, const void* x, const int32_t* topk_ids, const fl
   if (!mark(0)) return MOE_ERR_HIP;
 
   if (p->phases & 1) {
-    IndexParams ip;
-    memset(&ip, 0, sizeof(ip));
-    ip.s = s;
-    ip.ws = ws;
-    ip.topk_ids = topk_ids;
-    ip.n_blocks = p->n_index_blocks;
-    ip.tile_m = p->tile_m;
-    ip.n_tiles_n0 = p->n_tiles_n0;
-    ip.n_tiles_n1 = p->n_tiles_n1;
-    ip.layer0_order = order0;
-    ip.layer0_waves = waves0;
-    ip.layer1_order = p->layer1_order == 1 ? 1 : 0;   // only the in-kernel panel reduction needs the panel-major order
-    ip.max_tiles = p->max_tiles;
-    ip.force_large_schedule = p->large_schedule;
-    ip.block_m = p->block_m;
+    IndexParams ip = index_params(p, ws, topk_ids, order0);
     ip.forward_serial = ++p->serial;
-    memcpy(ip.seg_offsets, p->seg_offsets, sizeof(int32_t) * (s.S + 1));
-    if (launch_index_build(ip, st) != hipSuccess) return MOE_ERR_HIP;
+    p->schedule_owed = decode0 && decode1;
+    if (launch_index_build(ip, !p->schedule_owed, st) != hipSuccess) return MOE_ERR_HIP;
   } else {
+    if (p->schedule_owed && !(decode0 && decode1)) {
+      if (launch_index_schedule(index_params(p, ws, topk_ids, order0), st) != hipSuccess) return MOE_ERR_HIP;
+      p->schedule_owed = 0;
+    }
     // the schedules of the last index build on this workspace are run again: their queue heads and counters start over
     if (launch_reset_counters(ws, p->n_tiles_n1, p->max_tiles, st) != hipSuccess) return MOE_ERR_HIP;
   }
@@ -540,7 +551,6 @@ int forward_impl(moe_plan_t* p, const void* x, const int32_t* topk_ids, const fl
   // tile count, which bounds the per-workgroup tile counters)
   const bool one_launch = p->fuse_layers && (p->phases & 2) && (p->phases & 4) && !fused && !large;
 
-  const bool decode0 = decode_path(p, p->n_tiles_n0, p->n_cu), decode1 = decode_path(p, p->n_tiles_n1, p->n_cu);
   GemmParams a = g;
   a.A = (const char*)x;
   a.lda_bytes = (uint32_t)s.H * 2;
@@ -830,6 +840,9 @@ int moe_get_schedule(const moe_plan_t* p, const void* workspace, int32_t layer, 
   Workspace ws = view(p, const_cast<void*>(workspace));
   hipStream_t st = (hipStream_t)hip_stream;
   int32_t status[64];
+  if (p->schedule_owed &&   // (the forward had no use for it)
+      launch_index_schedule(index_params(p, ws, nullptr, p->last_layer0_order), st) != hipSuccess)
+    return MOE_ERR_HIP;
   if (hipMemcpyAsync(status, ws.status, sizeof(status), hipMemcpyDeviceToHost, st) != hipSuccess) return MOE_ERR_HIP;
   if (items) {
     const size_t bytes = (size_t)moe_plan_schedule_capacity(p, layer) * sizeof(ItemRec);

@@ -11,6 +11,11 @@ constexpr int kMaxExperts = 256;
 constexpr int kMaxTopK = 16;
 constexpr int kMaxSegments = 64;
 constexpr int kIndexChunk = 1024;   // (token, slot) pairs handled by one workgroup of the index build
+// Pairs, and items of both schedules, up to which the index build is one workgroup.  us, one workgroup against three
+// kernels: 256 pairs 9 / 17, 1018 pairs and 3 k items 14 / 26, 4000 pairs of 64 experts 25 / 28 (its scatter and its item
+// records are then as slow as the launches it saves).
+constexpr int kIndexSmallRows = 4096;
+constexpr int kIndexSmallItems = 8192;
 constexpr int kTileN = 256;         // columns of B staged per GroupGEMM tile
 constexpr int kTileK = 32;          // depth of one LDS stage
 constexpr int kStages = 4;          // LDS stages in flight
@@ -33,7 +38,7 @@ struct ItemRec {
 struct Workspace {
   int32_t* status;        // [64]  0: device status word, 1: n_tiles, 2: items of layer0, 3: items of layer1,
                           //       4: combine unit counter, 5: serial number of the last forward that saw an expert
-                          //       id out of range; 6: rows of the tallest tile; per XCD: 8..15 layer0 queue heads, 16..23 layer1 queue
+                          //       id out of range; 6: rows of the tallest tile (written for small batches); per XCD: 8..15 layer0 queue heads, 16..23 layer1 queue
                           //       heads, 24..31 layer0 queue lengths, 32..39 layer1 queue lengths, 40..47 layer1
                           //       queue bases, 48..55 layer0 queue bases (only with contiguous layer0 queues;
                           //       otherwise layer0's queue x is list positions x, x+8, ...)
@@ -192,7 +197,8 @@ struct CombineParams {
 
 // kernel launchers (defined in the .hip files)
 hipError_t launch_route_topk(const float* logits, int T, int E, int k, int32_t* ids, float* w, hipStream_t st);
-hipError_t launch_index_build(const IndexParams& p, hipStream_t st);
+hipError_t launch_index_build(const IndexParams& p, bool schedule, hipStream_t st);
+hipError_t launch_index_schedule(const IndexParams& p, hipStream_t st);
 hipError_t launch_reset_counters(const Workspace& ws, int n_tiles_n1, int max_tiles, hipStream_t st);
 hipError_t launch_layer0(const GemmParams& p, int act, int grid, hipStream_t st);
 hipError_t launch_layer1(const GemmParams& p, int grid, hipStream_t st);
