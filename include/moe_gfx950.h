@@ -89,7 +89,8 @@ int moe_plan_destroy(moe_plan_t *plan);
  *                  M-tiles sorted by the segment they wait for, all column tiles of an M-tile in a row);
  *                  2 = waves: the S source segments are grouped into "layer0_waves" waves, the tiles are
  *                  segment-major across waves and weight-panel-major inside a wave; -1 (default) = chosen by
- *                  every forward: 0 when seg_ready is NULL, 2 when ready flags are in use
+ *                  every forward: 0 when seg_ready is NULL or every segment has arrived by the time the forward builds
+ *                  its schedule, else 2
  *   "layer0_waves" 1..8 waves of order 2 (1 is order 0); 0 (default) = looked up from the shape and
  *                  "expected_ingest_gbps" (reading the option back returns the number in effect)
  *   "expected_ingest_gbps" rate in GB/s at which the caller expects the source segments to arrive (0 = unknown,

@@ -515,6 +515,10 @@ int forward_impl(moe_plan_t* p, const void* x, const int32_t* topk_ids, const fl
   if (p->phases & 1) {
     IndexParams ip = index_params(p, ws, topk_ids, order0);
     ip.forward_serial = ++p->serial;
+    if (p->layer0_order < 0) {   // the order is this library's choice
+      ip.seg_ready = seg_ready;
+      ip.ready_epoch = ready_epoch;
+    }
     p->schedule_owed = decode0 && decode1;
     if (launch_index_build(ip, !p->schedule_owed, st) != hipSuccess) return MOE_ERR_HIP;
   } else {

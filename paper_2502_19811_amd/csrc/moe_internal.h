@@ -38,7 +38,7 @@ struct ItemRec {
 struct Workspace {
   int32_t* status;        // [64]  0: device status word, 1: n_tiles, 2: items of layer0, 3: items of layer1,
                           //       4: combine unit counter, 5: serial number of the last forward that saw an expert
-                          //       id out of range; 6: rows of the tallest tile (written for small batches); per XCD: 8..15 layer0 queue heads, 16..23 layer1 queue
+                          //       id out of range; 6: rows of the tallest tile (written for small batches); 7: waves of the layer0 schedule; per XCD: 8..15 layer0 queue heads, 16..23 layer1 queue
                           //       heads, 24..31 layer0 queue lengths, 32..39 layer1 queue lengths, 40..47 layer1
                           //       queue bases, 48..55 layer0 queue bases (only with contiguous layer0 queues;
                           //       otherwise layer0's queue x is list positions x, x+8, ...)
@@ -77,6 +77,8 @@ struct IndexParams {
   int32_t n_tiles_n0, n_tiles_n1;
   int32_t layer0_order, layer1_order;   // layer0: 0 expert-major, 1 by source segment, 2 waves of segments
   int32_t layer0_waves;                 // order 2: waves the source segments are grouped into (1..8)
+  const uint32_t* seg_ready;     // not null: one wave once every segment is there (waves chosen by the library)
+  uint32_t ready_epoch;
   int32_t max_tiles;             // bound on the M-tiles of this plan
   int32_t force_large_schedule;  // 1: build the schedules with the one-workgroup kernel whatever the size
   int32_t block_m;               // M-tiles per block of the locality order (1..8)

@@ -40,3 +40,28 @@ def test_index_outputs_and_schedules_of_small_batches(T, E, k, tile_m):
         layer.forward()
         assert layer.results().status == -1
         layer.close()
+
+
+@pytest.mark.parametrize("T", [600, 3000])
+def test_the_schedule_of_a_flagged_forward_follows_what_has_arrived(T):
+    """All segments there when the schedule is built: the order of resident input.  One missing: waves of segments."""
+    import gpu_harness as H
+    import paper_2502_19811_amd as moe
+    cfg = wl.MoEConfig("arrived", T=T, H=512, F=2560, E=8, k=2, act=wl.ACT_SWIGLU, S=8, seed=701)
+    inp = wl.make_inputs(cfg, threads=2, weights=False)
+    ids, w = orc.route_topk(inp.logits, cfg.k)
+    layer = H.GpuLayer(cfg, inp, ids, w, {"phases": 1, "block_m": 2, "tile_m": 64})
+    n_waves = moe.moe_plan_get_option(layer.plan, "layer0_waves")
+    layer.forward()
+    resident, queues = layer.schedule(0)
+    flags = torch.full((cfg.S,), 4, dtype=torch.int32, device="cuda")
+    layer.forward(seg_ready=flags, epoch=4)
+    there, there_queues = layer.schedule(0)
+    assert there_queues == queues
+    for first, count, stride in queues:
+        np.testing.assert_array_equal(there[first:first + count * stride:stride], resident[first:first + count * stride:stride])
+    flags[5] = 3
+    layer.forward(seg_ready=flags, epoch=4)
+    items, queues = layer.schedule(0)
+    H.check_schedule(items, queues, layer.results().tiles, cfg.F // 128, waves=(n_waves, cfg.S))
+    layer.close()
