@@ -7,7 +7,10 @@
 //    GEMM workgroup or a data-movement workgroup, chosen by its index (the division point of Section 3.2.2); the
 //    data movement there is to do on one GPU: reducing finished column panels of layer1, prefetching weight panels;
 //  * a GEMM workgroup is 4 wavefronts, one per SIMD; a tile is BM x 256 outputs with BM = 256, 128 or 64, and
-//    accumulates in fp32 with v_mfma_f32_32x32x16_bf16;
+//    accumulates in fp32 with v_mfma_f32_16x16x32_bf16.  What bounds the kernel is the power limit, and per flop this one draws
+//    less than v_mfma_f32_32x32x16_bf16 (half the accumulator traffic; register-only loops: 2061 against 1835 TFLOP/s).  8192
+//    tokens of the Mixtral-shaped layer, 32x32x16 -> 16x16x32 and direct epilogue: main loop 91 -> 82 us per layer0
+//    tile (1140 cycles per K step in both, 1.60 -> 1.78 GHz), epilogue 5.4 -> 4.2 us, the layer 4338 -> 4077 us;
 //  * operands go global -> LDS directly (global_load_lds_dwordx4, 16 bytes per lane, no registers in between):
 //    B through a ring of 4 stages of depth 32, A through a ring of 5 blocks of half the tile's rows by depth 64, so
 //    that a load of A fetches whole 128-byte lines (8 rows per instruction); rows of A are gathered through
@@ -27,11 +30,6 @@
 namespace moe {
 
 constexpr int BK = kTileK, NS = kStages, BN = kTileN;
-#ifndef MOE_READ_GROUPS
-#define MOE_READ_GROUPS 2
-#endif
-constexpr int kReadGroups = MOE_READ_GROUPS;        // of the 4 groups of a half step, how many carry the LDS reads
-constexpr int kFragsPerGroup = 4 / kReadGroups;     // fragments (of at most 4 per operand) requested per such group
 constexpr int kMaxPanels = 128;   // column panels whose publication can be batched per workgroup
 constexpr int B_STAGE = BK * BN * 2;  // 16 KiB
 
@@ -42,6 +40,13 @@ __device__ __forceinline__ bf16x8 lds_read_a(uint32_t addr) {
 __device__ __forceinline__ bf16x8 lds_read_b_packed(uint32_t a) {
   return *(const bf16x8 __attribute__((address_space(3)))*)(uintptr_t)a;
 }
+// acc += B A with the accumulator staying where it is.  The instruction's result may go elsewhere than its addend came from;
+// with all 256 accumulation registers taken the register allocator uses that, outside the loop, to move half of a
+// 256-row tile's accumulators to vector registers and back (300 moves per tile).  The compiler does not know this for an
+// MFMA: whoever reads the accumulator next waits for it (the next MFMA on it is 32 away at least).
+__device__ __forceinline__ void mfma_in_place(f32x4& acc, bf16x8 b, bf16x8 a) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(b), "v"(a));
+}
 // 16 bytes per lane from sbase + voff straight into LDS at lds_base + lane * 16.  Written as asm so that the
 // compiler's wait-count pass does not serialise later LDS reads behind it; completion is awaited by hand
 // with s_waitcnt vmcnt.
@@ -49,15 +54,21 @@ __device__ __forceinline__ void dma16(const void* sbase, uint32_t voff, uint32_t
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds_base)
                : "memory");
 }
-// The same with the LDS address given as a base in a scalar register plus a constant: the addition writes M0 itself.
+// The same in two instructions with an MFMA between them (M0 wants a cycle before it is used): the LDS address, a base in a
+// scalar register plus a constant, and the load.  Nothing between the two may touch M0.
 template <int OFF>
-__device__ __forceinline__ void dma16_at(const void* sbase, uint32_t voff, uint32_t lds_base) {
-  if constexpr (OFF == 0) {
-    dma16(sbase, voff, lds_base);
-  } else {
-    asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds_base), "n"(OFF)
-                 : "memory", "scc");
-  }
+__device__ __forceinline__ void dma16_address(uint32_t lds_base) {
+  if constexpr (OFF == 0) asm volatile("s_mov_b32 m0, %0" ::"s"(lds_base) : "memory");
+  else asm volatile("s_add_u32 m0, %0, %1" ::"s"(lds_base), "n"(OFF) : "memory", "scc");
+}
+__device__ __forceinline__ void dma16_load(const void* sbase, uint32_t voff) {
+  asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase) : "memory");
+}
+// Waits until at most N LDS reads are outstanding, in a form the compiler knows: it adds no waits of its own for the
+// fragments that have landed by then (one in front of every fragment's first MFMA otherwise).
+template <int N>
+__device__ __forceinline__ void wait_lds_reads() {
+  __builtin_amdgcn_s_waitcnt(0xc07f | (N << 8));
 }
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
@@ -385,13 +396,13 @@ struct LoadState {
 constexpr int kDeepStages = 6;
 constexpr int a_block_bytes(int bm) { return bm * 64; }
 constexpr int b_ring_offset(int bm, int nsx) { return (nsx + 1) * a_block_bytes(bm); }
-// The epilogue stages C in 32 KiB that are free at the end of a tile even when the successor's first loads are under
-// way (A blocks 0..2, B stages 0..2): A blocks 3 and 4 of a 256-row tile, the space behind the rings otherwise.
-constexpr int staging_offset(int bm, int nsx) { return bm == 256 ? 3 * a_block_bytes(bm) : b_ring_offset(bm, nsx) + nsx * B_STAGE; }
-constexpr int kLdsBytesShallow = b_ring_offset(256, NS) + NS * B_STAGE;   // 144 KiB; covers the smaller tiles' layouts with NSX = 4 too
-constexpr int kLdsBytes = staging_offset(64, kDeepStages) + 32768;         // 156 KiB: the 64-row tiles with 6 stages
-static_assert(staging_offset(128, NS) + 32768 <= kLdsBytesShallow && staging_offset(64, NS) + 32768 <= kLdsBytesShallow, "staging fits");
-static_assert(kLdsBytes >= kLdsBytesShallow && kLdsBytes <= 160 * 1024 - 2048, "LDS of a compute unit, less the kernels' static variables");
+// The reduction in the layer1 epilogue lists its tokens in 2 KiB that are free at the end of a tile even when the successor's
+// first loads are under way (A blocks 0..2, B stages 0..2): A block 3 of a 256-row tile, the space behind the rings otherwise.
+constexpr int kListBytes = 2048;
+constexpr int list_offset(int bm, int nsx) { return bm == 256 ? 3 * a_block_bytes(bm) : b_ring_offset(bm, nsx) + nsx * B_STAGE; }
+constexpr int kLdsBytes = b_ring_offset(256, NS) + NS * B_STAGE;   // 144 KiB; covers the smaller tiles' layouts too
+static_assert(list_offset(128, NS) + kListBytes <= kLdsBytes && list_offset(64, kDeepStages) + kListBytes <= kLdsBytes, "the list fits");
+static_assert(kLdsBytes <= 160 * 1024 - 16384, "LDS of a compute unit, less the kernels' static variables");
 
 // Rows of A the lane loads for a tile of the given height class: LA = 1, 2 or 4 loads per block and two blocks (row
 // halves) per tile; a load covers 8 rows, 8 lanes per row.  arow[h * LA + j]: row half h, load j.
@@ -438,8 +449,8 @@ __device__ __forceinline__ void setup_and_issue(const GemmParams& p, uint32_t ld
     }
     const int kr = (w * LB + j) * 2 + (lane >> 5);
     const int cpb = lane & 31;
-    const int blk = (cpb >> 2) ^ ((kr & 3) | (((kr >> 3) & 1) << 2));
-    const int c8 = (blk * 4 + (cpb & 3)) * 8;  // column of the tile this lane fetches
+    const int blk = (cpb >> 1) ^ ((kr & 3) | (((kr >> 3) & 1) << 2));   // 16-column blocks, XOR-swizzled by row
+    const int c8 = (blk * 2 + (cpb & 1)) * 8;  // column of the tile this lane fetches
     int gcol;
     if (MODE == MODE_L0_SWIGLU) {
       // a wavefront's 32*NT columns are [gate | up] of the same 16*NT hidden units
@@ -502,7 +513,7 @@ __device__ __forceinline__ bool segment_ready(const GemmParams& p, const Tile& t
 
 // One tile of BM = WM*MT*32 rows by 256 columns: address set-up and first loads, main loop, epilogue.  While the
 // tile runs the workgroup finds out what its next tile is without waiting for any of the round trips: the queue
-// atomic is issued up front; once the last operand load has landed (48 MFMAs before the end) its result is shared
+// atomic is issued up front; once the last operand load has landed (a step and a half before the end) its result is shared
 // through LDS and the item record is requested.  A tile followed by one of the same height also starts the
 // successor's first operand stages during its own epilogue (next.pre = 1); otherwise only the rows of A the next
 // tile gathers are requested, after the epilogue.  next.idx = -1: no further tile.
@@ -517,11 +528,10 @@ __device__ __forceinline__ void run_tile(const GemmParams& p, char* smem, volati
   constexpr int B_RING = b_ring_offset(BM, NSX);
   constexpr int AB = NSX + 1;     // blocks of the A ring
   constexpr int LEAD = NSX - 1;   // K steps the loads run ahead; odd, so that the steps without loads at the end start on an odd step
-  static_assert(LEAD % 2 == 1 && (BM != 256 || NSX == NS), "see staging_offset: the 256-row epilogue stages in A blocks 3 and 4");
+  static_assert(LEAD % 2 == 1 && (BM != 256 || NSX == NS), "see list_offset: A block 3 of a 256-row tile is free at its end");
   constexpr int LA = BM / 64;  // A loads per lane per K step (one block)
   constexpr int LB = 4;        // B loads per lane per K step (one stage)
   constexpr int LS = LA + LB;
-  constexpr int FPB = BM / 64; // 32-row fragments per A block
 
 #ifdef MOE_TILE_TRACE
   uint64_t tt0 = 0, tt1 = 0, tt2 = 0, tt3 = 0, tc_loop = 0, tc_sync = 0, tc_mark = 0;
@@ -535,32 +545,26 @@ __device__ __forceinline__ void run_tile(const GemmParams& p, char* smem, volati
   const int lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = w / WN, wn = w % WN;
-  const int g = lane >> 4, j16 = lane & 15;
+  const int g = lane >> 4, j16 = lane & 15;   // (also of the MFMA's operands: K group and row / column of a fragment)
   const int row0 = uniform(cur.rec.row0), nrows = uniform(cur.rec.nrows), n_tile = uniform(cur.rec.n_tile);
   const int col0 = (MODE == MODE_L0_SWIGLU) ? n_tile * (BN / 2) : n_tile * BN;
 
-  // LDS read addresses: a_rd[parity of the K step][16-deep half of the step] inside an A block, b_rd inside a B stage
-  uint32_t a_rd[2][2], b_rd[NT];
+  // LDS read addresses of a lane: a_rd[parity of the K step] inside an A block (fragment 0: 16 rows by 32 values of K, the
+  // lane's row is lane % 16 and its 8 values of K are those at lane / 16), b_rd inside a B stage (fragment 0 of the wavefront)
+  uint32_t a_rd[2], b_rd;
   {
-    const int l = lane & 31;
-    const int s = (l >> 1) & 7;
+    const int s = (j16 >> 1) & 7;
 #pragma unroll
-    for (int sub = 0; sub < 2; sub++)
-#pragma unroll
-      for (int kk = 0; kk < 2; kk++) a_rd[sub][kk] = lds0 + l * 128 + (((sub * 4 + kk * 2 + (lane >> 5)) ^ s) << 4);
-    const int swz = (j16 >> 2) | ((g >> 1) << 2);
-    const int krow = 8 * (g >> 1) + (j16 >> 2);
-#pragma unroll
-    for (int nt = 0; nt < NT; nt++) {
-      if (PK) {
-        // column block of the packed tile this wavefront's block nt is: SwiGLU tiles hold [4 gate | 4 up] blocks of the
-        // same 128 hidden units, of which a wavefront takes the gate and up blocks of its own units
-        // (block nt lies a constant number of KiB behind block 0: b_block_offset below)
-        const int c = MODE == MODE_L0_SWIGLU ? (nt / (NT / 2)) * 4 + wn * (NT / 2) + nt % (NT / 2) : wn * NT + nt;
-        b_rd[nt] = lds0 + B_RING + c * 1024 + lane * 16;
-      } else {
-        b_rd[nt] = lds0 + B_RING + krow * 512 + (((wn * NT + nt) ^ swz) << 6) + (16 * (g & 1) + 4 * (j16 & 3)) * 2;
-      }
+    for (int sub = 0; sub < 2; sub++) a_rd[sub] = lds0 + j16 * 128 + (((sub * 4 + g) ^ s) << 4);
+    if (PK) {
+      // column block of the packed tile this wavefront's columns begin with: SwiGLU tiles hold [4 gate | 4 up] blocks of the
+      // same 128 hidden units, of which a wavefront takes the gate and up blocks of its own units (see b_frag_offset)
+      const int c = MODE == MODE_L0_SWIGLU ? wn * (NT / 2) : wn * NT;
+      b_rd = lds0 + B_RING + c * 1024 + (g >> 1) * (B_STAGE / 2) + (g & 1) * 512 + j16 * 16;
+    } else {
+      const int krow = 8 * g + (j16 >> 2);
+      const int swz = (j16 >> 2) | ((g & 1) << 2);
+      b_rd = lds0 + B_RING + krow * 512 + (((wn * NT * 2) ^ swz) << 5) + (j16 & 3) * 8;
     }
   }
   // Measurement aid: the fences a tile-granular hand-off between the two GroupGEMMs would need (a layer1 tile
@@ -573,9 +577,11 @@ __device__ __forceinline__ void run_tile(const GemmParams& p, char* smem, volati
   const char* Bb = uniform(ls.Bb);
   const size_t bstep = PK ? (size_t)B_STAGE : (size_t)BK * p.ldb * 2;
 
-  // Not cleared: the MFMAs of the tile's first half step take a zero constant as their addend instead (clearing 256
+  // Not cleared: the MFMAs of the tile's first K step take a zero constant as their addend instead (clearing 256
   // accumulator registers is 256 instructions, 0.8 us of a tile with the matrix cores idle).
-  f32x16 acc[MT][NT];
+  constexpr int MA = 2 * MT, NB = 2 * NT;     // 16-row and 16-column blocks of the wavefront
+  constexpr int HA = MA / 2, HB = NB / 2;     // ... of a half of them
+  f32x4 acc[MA][NB];
 
   // Per K step and lane: LA loads of A (block kt+LEAD: the other half of the rows than the block before, 64 values of K)
   // and LB loads of B (stage kt+LEAD).  The loads are issued one at a time between groups of MFMAs: a burst would fill
@@ -630,130 +636,145 @@ __device__ __forceinline__ void run_tile(const GemmParams& p, char* smem, volati
   ring.bdst = (uint32_t)LEAD * B_STAGE;
   next_ring = ring;
   const char* a_src = Ab + ((LEAD - 1) / 2) * 128;   // what the A block of an even step is loaded from; + 128: of the odd step after it
-  // where fragment q (32 rows) of this wavefront sits: row half and offset inside the block
-  auto frag_off = [&](const uint32_t (&blk)[2], int q) {
-    const int f = wm * MT + q;   // WM == 2: f / FPB == wm for every q
-    return (WM == 2 ? (wm ? blk[1] : blk[0]) : blk[f / FPB]) + (uint32_t)(f % FPB) * (32 * 128);
+  // The read addresses of a K step as one per-lane base per operand (64-row tiles: the two halves of the rows lie in two A
+  // blocks) plus constants that go into the instructions' offset fields.
+  //   A: fragment f of a half is f * 2 KiB further on; 128- and 256-row tiles: a wavefront's rows fill one block
+  //   B (packed): fragment f is b_frag_offset(f) further on; plain: the bits of f that the row's swizzle is XORed into
+  struct StepBases { uint32_t a_lo, a_hi, b; };
+  auto step_bases = [&](uint32_t blk0, uint32_t blk1, uint32_t b_off, int parity) {
+    StepBases sb;
+    sb.a_lo = (WM == 2 ? (wm ? blk1 : blk0) : blk0) + a_rd[parity];
+    sb.a_hi = WM == 2 ? sb.a_lo + (uint32_t)HA * 2048 : blk1 + a_rd[parity];
+    sb.b = b_off + b_rd;
+    return sb;
   };
-  // The read addresses of a half step as one per-lane base per operand plus constants that go into the instructions'
-  // offset fields: one address addition per operand and half step instead of one per fragment.
-  //   A: the block (or, 64-row tiles, the two blocks) the wavefront's fragments lie in; fragment q is q * 4 KiB further on
-  //   B (packed): block 0 of the wavefront; block nt is b_block_offset(nt) further on
-  struct HalfBases { uint32_t a[2], b; };
-  auto half_bases = [&](const uint32_t (&blk)[2], uint32_t b_off, int rd_par, int rd_kk) {
-    HalfBases hb;
-    hb.a[0] = (WM == 2 ? (wm ? blk[1] : blk[0]) : blk[0]) + a_rd[rd_par][rd_kk];
-    hb.a[1] = WM == 2 ? hb.a[0] : blk[1] + a_rd[rd_par][rd_kk];
-    hb.b = b_off + b_rd[0] + rd_kk * (B_STAGE / 2);
-    return hb;
+  auto b_frag_offset = [](int f) {
+    const int nt = f >> 1;
+    return (uint32_t)(MODE == MODE_L0_SWIGLU ? (nt / (NT / 2)) * 4 + nt % (NT / 2) : nt) * 1024 + (uint32_t)(f & 1) * 256;
   };
-  auto a_frag_addr = [&](const HalfBases& hb, int q) {
-    // WM == 2: f = wm * MT + q lies in block wm at position q (MT == FPB); WM == 1: fragment q is block q / FPB
-    return WM == 2 ? hb.a[0] + (uint32_t)q * (32 * 128) : hb.a[q / FPB] + (uint32_t)(q % FPB) * (32 * 128);
+  static_assert(WM == 1 || 2 * MT * 16 * WM == BM, "a wavefront's rows fill one A block");
+  auto read_b = [&](uint32_t base, int f) {
+    if constexpr (PK) return lds_read_b_packed(base + b_frag_offset(f));
+    const uint32_t at = base ^ (uint32_t)(f << 5);
+    return lds_read_b(at, at + 4 * 512);
   };
-  auto b_block_offset = [](int nt) {
-    return (uint32_t)(MODE == MODE_L0_SWIGLU ? (nt / (NT / 2)) * 4 + nt % (NT / 2) : nt) * 1024;
-  };
-  static_assert(WM == 1 || MT == FPB, "a wavefront's fragments fill one A block");
-  bf16x8 af[2][MT], bfr[2][NT];
-  // Group q (of 4) of a half step: the LDS reads of fragment q for the next half step and a quarter of the MFMAs
-  // of this one.  blk / b_off / rd_par / rd_kk: A blocks, B stage, parity and 16-deep half of the step read from.
-  auto group = [&](int cb, int nb, const HalfBases& hb, uint32_t b_off, int rd_kk, int q, auto first) {
-    constexpr bool FIRST = decltype(first)::value;   // the tile's first half step: nothing accumulated yet
-    constexpr int PER = MT * NT / 4;
-    // The fragments of the next half step are all requested in the first kReadGroups groups, so that they are back
-    // well before the half step ends: the workgroup barrier between the halves waits for every outstanding LDS
-    // read, and a read issued just before it would stall all four matrix pipes for an LDS round trip.
-    int n_reads = 0;
+  // A K step of a wavefront is MA x NB MFMAs of 16 x 16 x 32, taken as four quadrants of the blocks in an order that
+  // changes one operand's half at a time and alternates between even and odd steps:
+  //   even: (A lo, B lo) (A lo, B hi) | (A hi, B hi) (A hi, B lo)      odd: B lo and hi swapped
+  // A half of an operand is then dead two quadrants before its successor is needed, so that one register set of
+  // fragments is enough: quadrant 0 reads this step's other half of B and A hi, quadrant 2 the next step's A lo, quadrant 3
+  // the half of B that the next step begins with.  Between quadrants 1 and 2 lies the workgroup barrier, with every read of
+  // this step long returned.
+  bf16x8 af[MA], bfr[NB];
+  StepBases now, nxt;
+  now = step_bases(ring.a0, ring.a1, ring.b, 0);
+  nxt = now;
+  // Group gi (of 8, two per quadrant) of a K step of parity PAR: its MFMAs with its LDS reads between them, one per MFMA.
+  // reads_next: false in the last step of the tile.
+  using First = std::integral_constant<int, 0>;    // the tile's first step: nothing accumulated yet
+  using Middle = std::integral_constant<int, 1>;
+  using Last = std::integral_constant<int, 2>;     // one of the last LEAD steps (see mfma_in_place)
+  // side: scalar work for the step to come, spread between the MFMAs.  load: the group's operand load.
+  // In-order issue and 16 cycles per MFMA: what stands between two MFMAs should be three instructions at most, so the
+  // reads come behind the first MFMAs, the load behind the reads, in two parts.
+  constexpr int PER = HA * HB / 2;                              // MFMAs of a group
+  constexpr int kLoadAt = PER == 8 ? 5 : (PER == 4 ? 2 : 1);   // ... ahead of the load
+  auto group = [&](auto par, auto gi, auto where, bool reads_next, auto side, auto load_address, auto load) {
+    constexpr int PAR = decltype(par)::value, G = decltype(gi)::value, Q = G / 2;
+    constexpr int WHERE = decltype(where)::value;
+    constexpr int a0 = (Q >= 2) * HA, b0 = ((Q == 0 || Q == 3) ? PAR : 1 - PAR) * HB;
+    constexpr int bx = (1 - PAR) * HB;               // the half of B this step ends and the next one begins without ...
+    constexpr int READS = G == 0 || G == 6 ? (PK ? HB : 2 * HB) : (G == 1 || G == 4 ? HA : 0);
+    constexpr int TAKE = READS > kLoadAt ? (READS + kLoadAt - 1) / kLoadAt : 1;   // reads behind one MFMA
+    const int n_reads = G < 4 || reads_next ? READS : 0;
+    if constexpr (G == 0) {
+      wait_lds_reads<PK ? HB / 2 : HB>();            // A lo and half of the columns of quadrant 0
 #pragma unroll
-    for (int f = q * kFragsPerGroup; f < (q + 1) * kFragsPerGroup; f++) {
-      if (q < kReadGroups && f < MT) {
-        af[nb][f] = lds_read_a(a_frag_addr(hb, f));
-        n_reads += 1;
-      }
-      if (q < kReadGroups && f < NT) {
-        if (PK) bfr[nb][f] = lds_read_b_packed(hb.b + b_block_offset(f));
-        else bfr[nb][f] = lds_read_b(b_off + b_rd[f] + rd_kk * 16 * 512, b_off + b_rd[f] + (rd_kk * 16 + 4) * 512);
-        n_reads += PK ? 1 : 2;
-      }
+      for (int f = 0; f < HB; f++) bfr[bx + f] = read_b(now.b, bx + f);
+    } else if constexpr (G == 1) {
+#pragma unroll
+      for (int f = 0; f < HA; f++) af[HA + f] = lds_read_a(now.a_hi + f * 2048);
+    } else if constexpr (G == 2) {
+      wait_lds_reads<HA>();                          // the columns of quadrant 1
+    } else if constexpr (G == 4) {
+      if (reads_next) {
+#pragma unroll
+        for (int f = 0; f < HA; f++) af[f] = lds_read_a(nxt.a_lo + f * 2048);
+        }
+    } else if constexpr (G == 6) {
+      if (reads_next) {
+#pragma unroll
+        for (int f = 0; f < HB; f++) bfr[bx + f] = read_b(nxt.b, bx + f);
+        }
     }
+    side();
+    auto multiply = [&](auto lo, auto hi) {
 #pragma unroll
-    for (int i = 0; i < PER; i++) {
-      const int m = q * PER + i, mt = m / NT, nt = m % NT;
-      if constexpr (FIRST) acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[cb][nt], af[cb][mt], (f32x16){0}, 0, 0, 0);
-      else acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[cb][nt], af[cb][mt], acc[mt][nt], 0, 0, 0);
-    }
+      for (int i = decltype(lo)::value; i < decltype(hi)::value; i++) {
+        // the operand half that was read last is the outer one: its fragments are needed one by one
+        const int m = (G & 1) * PER + i, ma = a0 + (Q < 2 ? m % HA : m / HB), nb = b0 + (Q < 2 ? m / HA : m % HB);
+        if constexpr (WHERE == Last::value && MA * NB == 64) mfma_in_place(acc[ma][nb], bfr[nb], af[ma]);
+        else if constexpr (WHERE == First::value) acc[ma][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[nb], af[ma], (f32x4){0}, 0, 0, 0);
+        else acc[ma][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[nb], af[ma], acc[ma][nb], 0, 0, 0);
+      }
+    };
+    using L0 = std::integral_constant<int, 0>;
+    using L1 = std::integral_constant<int, kLoadAt>;
+    using L2 = std::integral_constant<int, kLoadAt + 1>;
+    using L3 = std::integral_constant<int, PER>;
+    multiply(L0{}, L1{});
 #pragma unroll
-    for (int i = 0; i < PER; i++) {
+    for (int i = 0; i < kLoadAt; i++) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      if (i < n_reads) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-    }
-#pragma unroll
-    for (int i = PER; i < 12; i++)
-      if (i < n_reads) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-  };
-  // read addresses of the half step about to begin (first half of step 0) and of the one after it
-  HalfBases hb_first, hb_second;
-  {
-    const uint32_t blk0[2] = {ring.a0, ring.a1};
-    hb_first = half_bases(blk0, ring.b, 0, 1);
-    hb_second = hb_first;
-  }
-  // first half of K step kt (parity PAR): MFMAs of its first 16 values of K, fragments of its second 16, A block kt+LEAD
-  auto half1 = [&](auto par, bool do_issue, auto first) {
-    constexpr int PAR = decltype(par)::value;
-    const uint32_t blk[2] = {ring.a0, ring.a1};
-    const uint32_t b_off = ring.b;
-    const char* src = a_src + PAR * 128;
-    const uint32_t dst = lds0 + ring.adst + w * LA * 1024;
-    const HalfBases hb = hb_first;   // worked out under the MFMAs of the half step before
-    (void)blk;
-#pragma unroll
-    for (int q = 0; q < 4; q++) {
-      if (q > 0) __builtin_amdgcn_sched_barrier(0);   // the loads stay where they are written: one per group
-      if (q == 3) {   // under this group's MFMAs: the A ring's next positions, and the read addresses of the second half
-        advance_a(ring, next_ring, std::integral_constant<int, 1 - PAR>{});
-        const uint32_t blk2[2] = {ring.an0, ring.an1};
-        hb_second = half_bases(blk2, ring.bn, 1 - PAR, 0);
-      }
-      group(0, 1, hb, b_off, 1, q, first);
-      // (behind the group's MFMAs, so that a half step begins with an MFMA and not with the load's set-up)
-      if (do_issue && q < LA) {
-        const uint32_t off = ls.aoff[((PAR + LEAD) & 1) * LA + q];
-        if (q == 0) dma16_at<0>(src, off, dst);
-        else if (q == 1) dma16_at<1024>(src, off, dst);
-        else if (q == 2) dma16_at<2048>(src, off, dst);
-        else dma16_at<3072>(src, off, dst);
-      }
-    }
-  };
-  // second half: MFMAs of the second 16 values, fragments of the first 16 of step kt+1, B stage kt+LEAD; the last
-  // groups of both halves also work out where the next step finds its operands, so that this is done under MFMAs
-  auto half2 = [&](auto par, bool do_issue) {
-    constexpr int PAR = decltype(par)::value;
-    const uint32_t blk[2] = {ring.an0, ring.an1};
-    const uint32_t b_off = ring.bn;
-    const uint32_t dst = lds0 + B_RING + ring.bdst + w * LB * 1024;
-    const HalfBases hb = hb_second;
-    (void)blk;
-#pragma unroll
-    for (int q = 0; q < 4; q++) {
-      if (q > 0) __builtin_amdgcn_sched_barrier(0);
-      if (q == 3) {   // the B ring's next positions, and the read addresses of the next step's first half
-        advance_b(ring, next_ring);
-        const uint32_t blk1[2] = {next_ring.a0, next_ring.a1};
-        hb_first = half_bases(blk1, next_ring.b, 1 - PAR, 1);
-      }
-      group(1, 0, hb, b_off, 0, q, std::false_type{});
-      if (do_issue && q < LB) {
-        if (q == 0) dma16_at<0>(Bb, ls.boff[q], dst);
-        else if (q == 1) dma16_at<1024>(Bb, ls.boff[q], dst);
-        else if (q == 2) dma16_at<2048>(Bb, ls.boff[q], dst);
-        else dma16_at<3072>(Bb, ls.boff[q], dst);
-      }
+      if (i * TAKE < n_reads) __builtin_amdgcn_sched_group_barrier(0x100, TAKE, 0);
+      else __builtin_amdgcn_sched_group_barrier(0x006, 2, 0);
     }
     __builtin_amdgcn_sched_barrier(0);
+    load_address();
+    __builtin_amdgcn_sched_barrier(0);
+    multiply(L1{}, L2{});
+    __builtin_amdgcn_sched_barrier(0);
+    load();
+    __builtin_amdgcn_sched_barrier(0);
+    multiply(L2{}, L3{});
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // first half of K step kt (parity PAR): quadrants 0 and 1, and the loads of A block kt+LEAD
+  auto half1 = [&](auto par, bool do_issue, auto where) {
+    constexpr int PAR = decltype(par)::value;
+    const char* src = a_src + PAR * 128;
+    const uint32_t dst = lds0 + ring.adst + w * LA * 1024;
+    auto part = [&](auto gi) {
+      constexpr int q = decltype(gi)::value;
+      const bool load = do_issue && q < LA;
+      group(par, gi, where, true,
+            [&]() {
+              if (q == 2) nxt = step_bases(ring.an0, ring.an1, ring.bn, 1 - PAR);   // where the next step reads
+              if (q == 3) advance_a(ring, next_ring, std::integral_constant<int, 1 - PAR>{});   // the A ring's next positions
+            },
+            [&]() { if (load) dma16_address<q * 1024>(dst); },
+            [&]() { if (load) dma16_load(src, ls.aoff[((PAR + LEAD) & 1) * LA + (q < LA ? q : 0)]); });
+    };
+    part(std::integral_constant<int, 0>{});
+    part(std::integral_constant<int, 1>{});
+    part(std::integral_constant<int, 2>{});
+    part(std::integral_constant<int, 3>{});
+  };
+  // second half: quadrants 2 and 3, and the loads of B stage kt+LEAD
+  auto half2 = [&](auto par, bool do_issue, auto where, bool reads_next) {
+    constexpr int PAR = decltype(par)::value;
+    const uint32_t dst = lds0 + B_RING + ring.bdst + w * LB * 1024;
+    auto part = [&](auto gi) {
+      constexpr int q = decltype(gi)::value - 4;
+      group(par, gi, where, reads_next, [&]() { if (q == 3) advance_b(ring, next_ring); },   // the B ring's next positions
+            [&]() { if (do_issue) dma16_address<q * 1024>(dst); }, [&]() { if (do_issue) dma16_load(Bb, ls.boff[q]); });
+    };
+    part(std::integral_constant<int, 4>{});
+    part(std::integral_constant<int, 5>{});
+    part(std::integral_constant<int, 6>{});
+    part(std::integral_constant<int, 7>{});
     ring = next_ring;
+    now = nxt;
     if (PAR == 1) a_src += 128;
   };
 
@@ -771,75 +792,81 @@ __device__ __forceinline__ void run_tile(const GemmParams& p, char* smem, volati
   if (kCanPre && flags_on && tid < p.n_segments)
     flag_v = __hip_atomic_load(&p.seg_ready[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 
+  // Blocks of 16 rows that the epilogue of the tile before stored ahead of this tile's first loads (layer0: while the
+  // gather rows of this tile came back), and the stores it issued behind them: younger than those loads, they need not be
+  // waited for with them.
+  constexpr int kPreBlock = MODE == MODE_L1 ? 0 : 2;
+  constexpr int kPreStores = (MA - kPreBlock) * ((MODE == MODE_L0_SWIGLU) ? NB / 4 : NB / 2);
   const int nk = p.K / BK;  // even and >= 4 (checked on the host)
   // A blocks 0 and 1 and B stage 0 landed?  Everything issued after them (A blocks 2 .. LEAD-1, B stages 1 .. LEAD-1, and
-  // whatever the previous tile's epilogue stored) may still be outstanding; loads return in order.
-  wait_vmcnt<(LEAD - 2) * LA + (LEAD - 1) * LB>();
+  // what the previous tile's epilogue stored behind them) may still be outstanding; memory operations return in order.
+  const bool started_early = cur.pre != 0;
+  if (started_early) wait_vmcnt<(LEAD - 2) * LA + (LEAD - 1) * LB + kPreStores>();
+  else wait_vmcnt<(LEAD - 2) * LA + (LEAD - 1) * LB>();
   block_barrier();
   MOE_TRACE_STAMP(tt1);
   MOE_TRACE_CYCLES(tc_loop);
-  {
-    const uint32_t blk[2] = {ring.a0, ring.a1};
 #pragma unroll
-    for (int mt = 0; mt < MT; mt++) af[0][mt] = lds_read_a(frag_off(blk, mt) + a_rd[0][0]);
-  }
+  for (int f = 0; f < HA; f++) af[f] = lds_read_a(now.a_lo + f * 2048);
 #pragma unroll
-  for (int nt = 0; nt < NT; nt++) bfr[0][nt] = PK ? lds_read_b_packed(b_rd[nt]) : lds_read_b(b_rd[nt], b_rd[nt] + 4 * 512);
+  for (int f = 0; f < HB; f++) bfr[f] = read_b(now.b, f);
 
   int kt = 0;
-  auto step = [&](auto par, auto first) {
-    half1(par, true, first);
+  auto step = [&](auto par, auto where) {
+    half1(par, true, where);
     // B stage kt+1 and the A blocks of step kt+1 (up to block kt+2) have landed for this lane; younger, in issue
     // order: B stage kt+2, blocks and stages kt+3 .. kt+LEAD-1, A block kt+LEAD: LEAD-2 steps' worth of loads.
     // After the barrier they have for all, and all are done reading step kt.  The scheduler must not move MFMAs of the
     // first half behind the barrier: they are what covers the latency of the half's LDS reads before the wait.
     __builtin_amdgcn_sched_barrier(0);
     MOE_TRACE_CYCLES(tc_mark);
-    wait_vmcnt<(LEAD - 2) * LS>();
+    if (decltype(where)::value == First::value && started_early) wait_vmcnt<(LEAD - 2) * LS + kPreStores>();
+    else wait_vmcnt<(LEAD - 2) * LS>();
+    wait_lds_reads<0>();
     block_barrier();
     MOE_TRACE_ADD_CYCLES(tc_sync, tc_mark);
     __builtin_amdgcn_sched_barrier(0);
-    half2(par, true);
+    half2(par, true, where, true);
     Bb += bstep;
     kt++;
   };
   const int kt_end = nk - LEAD;   // odd; at least 1 (the caller picks NSX so that nk > LEAD)
-  step(P0{}, std::true_type{});   // kt_end is odd: an even number of steps with loads follows
+  step(P0{}, First{});   // kt_end is odd: an even number of steps with loads follows
   while (kt + 2 <= kt_end) {
-    step(P1{}, std::false_type{});
-    step(P0{}, std::false_type{});
+    step(P1{}, Middle{});
+    step(P0{}, Middle{});
   }
 
   // The last LEAD steps (parities 1, 0, ..., 1) issue nothing.  With r steps still to come after the current one, what
   // is younger than the loads the step waits for is B stage kt+2 and the blocks and stages of the r-2 steps after it.
   static_assert(LEAD == 3 || LEAD == 5, "the steps without loads are written out for these two");
   if constexpr (LEAD == 5) {
-    half1(P1{}, false, std::false_type{});
+    half1(P1{}, false, Last{});
     __builtin_amdgcn_sched_barrier(0);
     wait_vmcnt<LB + 2 * LS>();
     block_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    half2(P1{}, false);
+    half2(P1{}, false, Last{}, true);
     kt++;
-    half1(P0{}, false, std::false_type{});
+    half1(P0{}, false, Last{});
     __builtin_amdgcn_sched_barrier(0);
     wait_vmcnt<LB + LS>();
     block_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    half2(P0{}, false);
+    half2(P0{}, false, Last{}, true);
     kt++;
   }
-  half1(P1{}, false, std::false_type{});
+  half1(P1{}, false, Last{});
   wait_vmcnt<LB>();   // younger than the last A block: the last B stage
   block_barrier();
-  half2(P1{}, false);
+  half2(P1{}, false, Last{}, true);
   kt++;
-  half1(P0{}, false, std::false_type{});
+  half1(P0{}, false, Last{});
   wait_vmcnt<0>();
   // No operand load is in flight any more, so memory operations the compiler waits for by itself no longer stall
   // behind them: thread 0 turns its queue ticket into a list position (stealing from other XCDs if its own queue is
   // used up) and hands it to the workgroup across the barrier; everybody then asks for the item record, whose
-  // latency the remaining 48 MFMAs cover.
+  // latency the remaining step and a half covers.
   uint64_t ready_mask = ~0ull;
   if (kCanPre && flags_on) ready_mask = __ballot(tid < p.n_segments && flag_v >= p.ready_epoch);
   if (tid == 0) {
@@ -856,14 +883,14 @@ __device__ __forceinline__ void run_tile(const GemmParams& p, char* smem, volati
     ready_mask = (uint32_t)uniform((int)lds_mask[0]) | ((uint64_t)(uint32_t)uniform((int)lds_mask[1]) << 32);
   ItemRec raw_rec;
   if (next.idx >= 0) raw_rec = p.items[next.idx];
-  half2(P0{}, false);
+  half2(P0{}, false, Last{}, true);
   kt++;
-  half1(P1{}, false, std::false_type{});
-#pragma unroll
-  for (int mt = 0; mt < MT; mt++)
-#pragma unroll
-    for (int nt = 0; nt < NT; nt++)
-      acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[1][nt], af[1][mt], acc[mt][nt], 0, 0, 0);
+  half1(P1{}, false, Last{});
+  half2(P1{}, false, Last{}, false);
+  if constexpr (MA * NB == 64) {
+    asm volatile("s_nop 15\n\ts_nop 3" ::: "memory");   // the last results are there (the compiler does not see MFMAs in mfma_in_place)
+    __builtin_amdgcn_sched_barrier(0);
+  }
 
   // The previous tile is published only now: its stores have drained during this tile's main loop, so the release
   // does not wait for them (publishing right after the stores would stall the next tile behind the store burst).
@@ -887,89 +914,67 @@ __device__ __forceinline__ void run_tile(const GemmParams& p, char* smem, volati
   if (kCanPre && do_pre) load_arows<MODE>(p, next, lane, w);
 
   // Epilogue.  The MFMAs ran with the operands swapped (B fragment first), so a lane holds, for output row
-  // lane & 31 of each 32x32 block, the columns 8*(i/4) + 4*(lane/32) + i%4: four consecutive columns per group of
-  // four accumulator registers.  The wavefront's part of the tile goes out in pieces of 32 rows x 128 bytes (64 bytes
-  // where the wavefront has a single 32-column block of output): a piece
-  // is staged in LDS as bf16 (8-byte writes, 16-byte chunks XOR-swizzled by row) and written out in full 16-byte
-  // chunks, 8 rows of 128 bytes per store instruction; 2-byte stores straight from the accumulators cost a tenth of
-  // the tile's time.  Two staging buffers per wavefront: while piece s is converted and staged, the chunks of piece
-  // s-1 are on their way back from LDS, so that only the first and the last piece pay an LDS round trip.
-  constexpr int OUT_NT = (MODE == MODE_L0_SWIGLU) ? NT / 2 : NT;   // 32-column blocks of output per wavefront
-  constexpr int PW = OUT_NT >= 2 ? 2 : 1;                           // 32-column blocks per piece
-  constexpr int PH = OUT_NT / PW;                                   // pieces per 32-row block
-  constexpr int PRB = PW * 64;                                      // bytes per staged row of a piece
-  constexpr int PNC = PRB / 16;                                     // 16-byte chunks per staged row
-  constexpr int RPB = 256 / PRB;                                    // rows per 256 bytes of LDS banks
-  constexpr int NST = 32 * PNC / 64;                                // 16-byte stores per lane and piece
-  constexpr int NPIECE = MT * PH;
-  static_assert(OUT_NT % PW == 0, "pieces tile the wavefront's columns");
-  const uint32_t cbase = lds0 + staging_offset(BM, NSX) + w * (2 * 32 * PRB);   // 2 buffers x 32 rows x 128 bytes per wavefront
+  // lane % 16 of each 16x16 block, the four consecutive columns from 4 * (lane / 16) on.  Two neighbouring blocks become one
+  // 16-byte store per lane -- 16 rows of 64 bytes -- by exchanging quarter rows between them (v_permlane16_swap): lanes
+  // 16 .. 31 and 48 .. 63 end up with the second block, and a lane with the 8 columns from 8 * (lane / 32) on of its block.
+  // (Staged through LDS for rows of 128 bytes the epilogue of a layer1 tile took 4.5 us: round trips and address
+  // arithmetic that one wavefront per SIMD cannot hide.)
+  constexpr int OUT_NB = (MODE == MODE_L0_SWIGLU) ? NB / 2 : NB;   // 16-column blocks of output per wavefront
+  static_assert(OUT_NB % 2 == 0, "blocks are stored in pairs");
   int lane_e = lane;   // opaque again: the epilogue's addresses are computed here, not before the main loop
   asm volatile("" : "+v"(lane_e));
   const int col_base = (MODE == MODE_L0_SWIGLU) ? col0 + wn * (NT * 16) : col0 + wn * (NT * 32);
-  const bool full = nrows == BM;
-  // converts piece s (row block s / PH, column blocks 2 * (s % PH) and the next) and stages it in buffer s & 1
-  auto stage_piece = [&](int s) {
-    const int mt = s / PH, nt0 = (s % PH) * PW;
-    const int m = lane_e & 31, half = lane_e >> 5;
-    const uint32_t row_addr = cbase + (s & 1) * (32 * PRB) + m * PRB + half * 8;
-    const int sw = (m / RPB) & (PNC - 1);
+  // The wavefront's rows as a buffer that ends with the tile's last row: what lies behind it is not stored, without a branch,
+  // so that the number of stores is the same for every tile (kPreStores).
+  const int first_row = wm * (MT * 32);
+  const uint32_t row_bytes = p.ldc * 2;
+  const __amdgpu_buffer_rsrc_t c_rows = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)uniform((const char*)(p.C + (size_t)(row0 + first_row) * p.ldc + col_base)), 0,
+      uniform(nrows > first_row ? (int)((nrows - first_row) * row_bytes) : 0), 0x00020000);
+  uint32_t c_off = (lane_e & 15) * row_bytes + ((lane_e >> 4) & 1) * 32 + (lane_e >> 5) * 16;
 #pragma unroll
-    for (int n2 = 0; n2 < PW; n2++) {
-      const int nt = nt0 + n2;
-      if (MODE == MODE_L0_GELU) __builtin_amdgcn_sched_barrier(0);  // bounds the live activation temporaries
-#pragma unroll
-      for (int qd = 0; qd < 4; qd++) {
-        float v[4];
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-          if (MODE == MODE_L0_SWIGLU) v[i] = silu(acc[mt][nt][qd * 4 + i]) * acc[mt][nt + NT / 2][qd * 4 + i];
-          else if (MODE == MODE_L0_GELU) v[i] = gelu_erf(acc[mt][nt][qd * 4 + i]);
-          else v[i] = acc[mt][nt][qd * 4 + i];
-        }
-        bf16x2 lo = {(__bf16)v[0], (__bf16)v[1]}, hi = {(__bf16)v[2], (__bf16)v[3]};
-        u32x2 pk = {__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
-        const int chunk = n2 * 4 + qd;
-        *(u32x2 __attribute__((address_space(3)))*)(uintptr_t)(row_addr + ((chunk ^ sw) << 4)) = pk;
-      }
-    }
-  };
-  // reads the 16-byte chunks of piece s this lane stores (rows it * 8 + lane / 8, chunk lane % 8)
-  auto fetch_piece = [&](int s, u32x4* v) {
-    const int c = lane_e % PNC;
-#pragma unroll
-    for (int it = 0; it < NST; it++) {
-      const int r = it * (64 / PNC) + lane_e / PNC;
-      v[it] = *(const u32x4 __attribute__((address_space(3)))*)(uintptr_t)(
-          cbase + (s & 1) * (32 * PRB) + r * PRB + ((c ^ ((r / RPB) & (PNC - 1))) << 4));
-    }
-  };
-  auto store_piece = [&](int s, const u32x4* v) {
-    const int mt = s / PH, ph = s % PH;
-    const int c = lane_e % PNC;
-#pragma unroll
-    for (int it = 0; it < NST; it++) {
-      const int grow = wm * (MT * 32) + mt * 32 + it * (64 / PNC) + lane_e / PNC;
-      u32x4* dst = (u32x4*)(p.C + (size_t)(row0 + grow) * p.ldc + col_base + ph * (PW * 32) + c * 8);
-      if (full) *dst = v[it];
-      else if (grow < nrows) *dst = v[it];
-    }
-  };
-  stage_piece(0);
-#pragma unroll
-  for (int s = 1; s <= NPIECE; s++) {
-    __builtin_amdgcn_sched_barrier(0);   // one piece at a time: keeps the address temporaries few
-    u32x4 v[NST];
-    fetch_piece(s - 1, v);
-    if (s < NPIECE) stage_piece(s);
-    store_piece(s - 1, v);
+  for (int ma = 0; ma < MA; ma++) {
+    __builtin_amdgcn_sched_barrier(0);   // one block of rows at a time: keeps the temporaries few
     if constexpr (kCanPre) {
-      if (s == PH && do_pre) {   // the first 32-row block is out
+      if (ma == kPreBlock && do_pre) {
         if (flags_on) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "");
         LoadState ls_next;
         setup_and_issue<WM, MT, NT, MODE, PK, NSX>(p, lds0, next, ls_next, lane_e, w, true);
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
+    // (read out here: the compiler would otherwise move all accumulators to vector registers first, more than there are)
+#pragma unroll
+    for (int nb = 0; nb < NB; nb++) asm volatile("" : "+a"(acc[ma][nb]));
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int pr = 0; pr < OUT_NB / 2; pr++) {
+      if (MODE == MODE_L0_GELU) __builtin_amdgcn_sched_barrier(0);  // bounds the live activation temporaries
+      uint32_t d[2][2];
+#pragma unroll
+      for (int b = 0; b < 2; b++) {
+        const int nb = 2 * pr + b;
+        float v[4];
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+          if (MODE == MODE_L0_SWIGLU) v[i] = silu(acc[ma][nb][i]) * acc[ma][nb + NB / 2][i];
+          else if (MODE == MODE_L0_GELU) v[i] = gelu_erf(acc[ma][nb][i]);
+          else v[i] = acc[ma][nb][i];
+        }
+        const bf16x2 lo = {(__bf16)v[0], (__bf16)v[1]}, hi = {(__bf16)v[2], (__bf16)v[3]};
+        d[b][0] = __builtin_bit_cast(uint32_t, lo);
+        d[b][1] = __builtin_bit_cast(uint32_t, hi);
+      }
+      u32x4 o;
+#pragma unroll
+      for (int j = 0; j < 2; j++) {
+        const auto x = __builtin_amdgcn_permlane16_swap(d[0][j], d[1][j], false, false);
+        o[j] = x[0];
+        o[2 + j] = x[1];
+      }
+      __builtin_amdgcn_raw_buffer_store_b128(o, c_rows, c_off + pr * 64, 0, 0);
+    }
+    c_off += 16 * row_bytes;
   }
   if (MODE == MODE_L1 && p.fused_combine) {
     if (p.batch_publish) {
@@ -986,8 +991,8 @@ __device__ __forceinline__ void run_tile(const GemmParams& p, char* smem, volati
   // Nobody waits for anybody; the price is one device-wide release per tile (the rows must be visible before they are
   // announced) and one acquire.
   if (MODE == MODE_L1 && p.epilogue_combine) {
-    volatile int32_t* last_list = (volatile int32_t*)(smem + staging_offset(BM, NSX));   // the staging area is free again
-    int32_t* last_count = (int32_t*)(smem + staging_offset(BM, NSX) + 256 * 4);
+    volatile int32_t* last_list = (volatile int32_t*)(smem + list_offset(BM, NSX));   // free, see list_offset
+    int32_t* last_count = (int32_t*)(smem + list_offset(BM, NSX) + 256 * 4);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     __syncthreads();
     if (tid == 0) *last_count = 0;
@@ -1028,7 +1033,7 @@ __device__ __forceinline__ void run_tile(const GemmParams& p, char* smem, volati
         *(u32x4*)(p.out + (size_t)t * p.H + col) = o;
       }
     }
-    __syncthreads();   // the list is read out before the next tile's epilogue reuses the staging area
+    __syncthreads();   // the list is read out before the next tile's epilogue writes it
   }
   // rows of A the next tile gathers (requested only now: held across the epilogue they push it into spilling)
   if (next.idx >= 0 && !do_pre) load_arows<MODE>(p, next, lane, w);
@@ -1296,7 +1301,7 @@ static hipError_t allow_large_lds(const void* kern, int lds_bytes) {
 
 template <int MODE0, bool PK>
 static hipError_t launch_fused(const GemmParams& p0, const GemmParams& p1, const FuseParams& f, int grid, hipStream_t st) {
-  constexpr int lds = kLdsBytesShallow;   // (its per-M-tile counters take 8 KiB of LDS; every tile height runs with 4 stages)
+  constexpr int lds = kLdsBytes;
   auto kern = k_fused_layers<MODE0, PK>;
   hipError_t e = allow_large_lds((const void*)kern, lds);
   if (e != hipSuccess) return e;
