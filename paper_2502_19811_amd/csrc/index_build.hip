@@ -88,19 +88,16 @@ __global__ __launch_bounds__(256) void k_index_hist(IndexParams p) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Tiling of an expert's rows: as many tiles of tile_m rows as fit, then the remainder is cut so that little
-// of a tile is padding: with tile_m = 256 a remainder of up to 64 rows becomes one 64-row tile, up to 128 one
-// 128-row tile, up to 192 a 128-row and a 64-row tile, more one ragged 256-row tile (tile_m = 128: 64 or 128).
+// Tiling of an expert's rows: as many tiles of tile_m rows as fit, then one tile for the remainder, of the lowest
+// height that holds it.  (A remainder of 129 to 192 rows is not split into a 128- and a 64-row tile, for all that the ragged
+// tile pads it: tiles of different heights lie apart in the queues, tall ones first, so every height streams its
+// experts' weights from HBM once more, which costs what the matrix cores need for about 240 rows.  160 rows for each of 16
+// experts with F = 6400: 941 -> 611 us, 400 rows 1385 -> 1022.)
 // ---------------------------------------------------------------------------------------------
-__device__ inline int tail_tiles(int rem, int tile_m, int* h0, int* h1) {
-  // heights (kernel variant) of the tiles that cover a remainder of rem rows; returns their number (0..2)
+__device__ inline int tail_height(int rows, int tile_m) {   // height of the tile that holds the remainder; 0: there is none
+  const int rem = rows % tile_m;
   if (rem == 0) return 0;
-  if (tile_m == 64) { *h0 = 64; return 1; }
-  if (rem <= 64) { *h0 = 64; return 1; }
-  if (rem <= 128 || tile_m == 128) { *h0 = 128; return 1; }
-  if (rem <= 192) { *h0 = 128; *h1 = 64; return 2; }
-  *h0 = 256;
-  return 1;
+  return rem <= 64 || tile_m == 64 ? 64 : (rem <= 128 || tile_m == 128 ? 128 : 256);
 }
 
 // Exclusive prefix sum over 256 values in LDS (one per thread of the workgroup); returns the total.
@@ -182,8 +179,8 @@ __global__ __launch_bounds__(256) void k_index_scatter(IndexParams p) {
   const int total_rows = exclusive_scan_256(off, my_cnt);
   if (blockIdx.x == 0) {
     const int e = threadIdx.x;
-    int h0 = 0, h1 = 0;
-    const int my_tiles = e < E ? my_cnt / p.tile_m + tail_tiles(my_cnt % p.tile_m, p.tile_m, &h0, &h1) : 0;
+    const int tail = e < E ? tail_height(my_cnt, p.tile_m) : 0;
+    const int my_tiles = e < E ? my_cnt / p.tile_m + (tail > 0) : 0;
     const int n_tiles = exclusive_scan_256(tbase, my_tiles);
     const int waves = wave == 0 ? waves_now(p, lane) : 0;
     if (threadIdx.x == 0) {
@@ -210,17 +207,11 @@ __global__ __launch_bounds__(256) void k_index_scatter(IndexParams p) {
         p.ws.tile_rows[ti] = p.tile_m;
         p.ws.tile_kind[ti] = kind_full;
       }
-      const int h[2] = {h0, h1};
-      const int nt = my_tiles - nfull;
-      int left = my_cnt % p.tile_m;
-      for (int i = 0; i < nt; i++, ti++) {
-        const int rows = left < h[i] ? left : h[i];
+      if (tail > 0) {
         p.ws.tile_expert[ti] = e;
         p.ws.tile_row0[ti] = row;
-        p.ws.tile_rows[ti] = rows;
-        p.ws.tile_kind[ti] = h[i] == 256 ? 2 : (h[i] == 128 ? 1 : 0);
-        row += rows;
-        left -= rows;
+        p.ws.tile_rows[ti] = my_cnt % p.tile_m;
+        p.ws.tile_kind[ti] = tail == 256 ? 2 : (tail == 128 ? 1 : 0);
       }
     }
   }
@@ -838,11 +829,11 @@ __global__ __launch_bounds__(1024) void k_index_small(IndexParams p, int schedul
   __syncthreads();
   // offsets and first tiles of the experts: four experts per lane of the first wavefront
   if (wave == 0) {
-    int c[4], t[4], rows = 0, tiles = 0, tallest = 0, h0, h1;
+    int c[4], t[4], rows = 0, tiles = 0, tallest = 0;
 #pragma unroll
     for (int i = 0; i < 4; i++) {
       c[i] = cnt[lane * 4 + i];
-      t[i] = c[i] / p.tile_m + tail_tiles(c[i] % p.tile_m, p.tile_m, &h0, &h1);
+      t[i] = c[i] / p.tile_m + (c[i] % p.tile_m > 0);
       rows += c[i];
       tiles += t[i];
       tallest = max(tallest, min(c[i], p.tile_m));
@@ -915,14 +906,11 @@ __global__ __launch_bounds__(1024) void k_index_small(IndexParams p, int schedul
       else hi = mid - 1;
     }
     const int i = m - tbase[lo], full = cnt[lo] / p.tile_m;
-    int row0 = off[lo] + i * p.tile_m, rows = p.tile_m, height = p.tile_m;
+    const int row0 = off[lo] + i * p.tile_m;
+    int rows = p.tile_m, height = p.tile_m;
     if (i >= full) {
-      const int rem = cnt[lo] % p.tile_m;
-      int h0 = 0, h1 = 0;
-      tail_tiles(rem, p.tile_m, &h0, &h1);
-      row0 = off[lo] + full * p.tile_m + (i > full ? h0 : 0);
-      height = i > full ? h1 : h0;
-      rows = min(height, i > full ? rem - h0 : rem);
+      rows = cnt[lo] % p.tile_m;
+      height = tail_height(cnt[lo], p.tile_m);
     }
     const int kind = height == 256 ? 2 : (height == 128 ? 1 : 0);
     p.ws.tile_expert[m] = lo;

@@ -123,11 +123,10 @@ Workspace view(const moe_plan* p, void* base) {
   return w;
 }
 
-// Tiles of the table at most (a short one beside the full ones per expert, two with 256-row tiles), for the grid of the
-// decode kernel.
+// Tiles of the table at most (a short one beside the full ones per expert), for the grid of the decode kernel.
 int decode_slots(const Shape& s, int tile_m, int max_tiles) {
   const int experts = s.E < s.R ? s.E : s.R;
-  int n = s.R / tile_m + (tile_m == 256 ? 2 : 1) * experts;
+  int n = s.R / tile_m + experts;
   if (n > s.R) n = s.R;
   return n < max_tiles ? n : max_tiles;
 }
@@ -148,12 +147,23 @@ int decode_k_split(const moe_plan* p, int K, int N, bool pair, int n_slots) {
   return log2;
 }
 
+// Tallest tile the schedule may use (an expert's remainder gets a shorter one anyway).  A tile streams its column's weights
+// whatever its height, so 256 rows -- except where the items of layer0 then are one round or less on the device: the
+// lowest height whose items still are one round spreads them over more compute units.  The rows of an expert are taken as the
+// mean plus a standard deviation.  us per forward with 64 / 128 / 256, 14 column tiles and 8 experts (F = 1792): 112 rows
+// per expert 127 / 136 / 136, 192 rows 184 / 143 / 153, 320 rows 248 / 215 / 180; 50 column tiles and 16 experts (F = 6400): 80
+// rows 592 / 508 / 510, 160 rows 801 / 939 / 611, 400 rows 1692 / 1334 / 1046.  Many rows in few columns (4 experts, 2 column
+// tiles, 1024 rows: 50 / 47 / 51) do better with 128.
 int default_tile_m(const Shape& s) {
-  // Tallest tile the schedule may use; the ragged end of an expert gets shorter tiles (128 / 64 rows) anyway.
-  const int mean_rows = s.E > 0 ? s.R / s.E : 0;
-  if (mean_rows >= 256) return 256;
-  if (mean_rows >= 128) return 128;
-  return 64;
+  const int experts = s.E < s.R ? s.E : s.R;
+  if (experts <= 0) return 256;
+  const int n_tiles_n0 = s.act == MOE_ACT_SWIGLU ? s.F / (kTileN / 2) : s.F / kTileN;
+  int rows = s.R / experts, dev = 0;
+  while (dev * dev < rows) dev++;
+  rows += dev;
+  for (int tile_m = rows > 512 ? 128 : 64; tile_m < 256; tile_m *= 2)
+    if ((int64_t)experts * n_tiles_n0 * ((rows + tile_m - 1) / tile_m) <= kDefaultCus) return tile_m;
+  return 256;
 }
 
 // Division point between GEMM and data-movement workgroups of the layer1 kernel (Section 3.2.2): looked up, as the

@@ -22,6 +22,7 @@ constexpr int kStages = 4;          // LDS stages in flight
 constexpr int kCombineChunk = 256;  // tokens per unit of combine work
 constexpr int kDecodeRowsPerExpert = 16;   // rows per expert on average up to which the decode kernel is used
 constexpr int kDecodeSerialK = 1024;       // ... and the reduction length up to which it sums K in one part
+constexpr int kDefaultCus = 256;    // compute units a plan assumes before it has seen the device
 constexpr int kXcds = 8;            // XCDs of the device: workgroup i runs on XCD i % 8
 constexpr int kScheduleTileCap = 2048;  // M-tiles up to which the multi-workgroup schedule builder is used
 
