@@ -1379,34 +1379,69 @@ hipError_t launch_pack_weights(const void* B, void* out, int E, int K, int ldb, 
 }
 
 // ---------------------------------------------------------------------------------------------
-// Stand-alone top-k weighted reduction (used when the layer1 kernel runs without data-movement workgroups).
+// Stand-alone top-k weighted reduction (used when the layer1 kernel runs without data-movement workgroups).  HBM-bound: 32
+// lanes own 256 columns of TOKENS tokens and request the rows of all of them before any is used (8 in flight per lane; walked
+// one row at a time, index and row a dependent pair of loads each, 8192 tokens with k = 4 and H = 2048 took 35.5 us, 4.7
+// TB/s; now 28.8, 5.8 TB/s).  K = 0: any other k, one row at a time.
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_combine(CombineParams p) {
-  const int cols8 = p.H / 8;
-  const size_t total = (size_t)p.T * cols8;
-  for (size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (size_t)gridDim.x * 256) {
-    const int t = (int)(idx / cols8);
-    const size_t col = (idx % cols8) * 8;
-    float acc[8];
+constexpr int combine_tokens(int k) { return k == 1 || k == 2 ? 4 : (k == 4 ? 2 : 1); }
+constexpr int kCombineResident = 2048;   // workgroups the device holds at once; up to there one token per 32 lanes (more to start)
+template <int K, int TOKENS>
+__global__ __launch_bounds__(256) void k_combine(CombineParams p, int n_panels, int n_units) {
+  constexpr int KK = K > 0 ? K : 1;
+  const int u = blockIdx.x * 8 + (threadIdx.x >> 5);
+  if (u >= n_units) return;
+  const int group = u / n_panels;
+  const size_t col = (size_t)(u - group * n_panels) * BN + (threadIdx.x & 31) * 8;
+  const int t0 = group * TOKENS, k = K > 0 ? K : p.k;
+  float acc[TOKENS][8];
+  auto add = [&](float (&a)[8], float w, const u32x4& v) {
 #pragma unroll
-    for (int c = 0; c < 8; c++) acc[c] = 0.f;
-    for (int j = 0; j < p.k; j++) {
-      const int row = p.inv_perm[t * p.k + j];
-      const float w = p.topk_weights[t * p.k + j];
-      const u32x4 v = *(const u32x4*)(p.Y + (size_t)row * p.H + col);
+    for (int c = 0; c < 4; c++) {
+      a[2 * c] += w * __uint_as_float(v[c] << 16);
+      a[2 * c + 1] += w * __uint_as_float(v[c] & 0xffff0000u);
+    }
+  };
 #pragma unroll
-      for (int c = 0; c < 4; c++) {
-        acc[2 * c] += w * __uint_as_float(v[c] << 16);
-        acc[2 * c + 1] += w * __uint_as_float(v[c] & 0xffff0000u);
+  for (int i = 0; i < TOKENS; i++)
+#pragma unroll
+    for (int c = 0; c < 8; c++) acc[i][c] = 0.f;
+  if constexpr (K > 0) {
+    int row[TOKENS][KK];
+    float w[TOKENS][KK];
+    u32x4 v[TOKENS][KK];
+#pragma unroll
+    for (int i = 0; i < TOKENS; i++) {
+      const int t = min(t0 + i, p.T - 1);
+#pragma unroll
+      for (int j = 0; j < KK; j++) {
+        row[i][j] = p.inv_perm[t * KK + j];
+        w[i][j] = p.topk_weights[t * KK + j];
       }
     }
+#pragma unroll
+    for (int i = 0; i < TOKENS; i++)
+#pragma unroll
+      for (int j = 0; j < KK; j++) v[i][j] = *(const u32x4*)(p.Y + (size_t)row[i][j] * p.H + col);
+    __builtin_amdgcn_sched_barrier(0);   // all requested by here
+#pragma unroll
+    for (int i = 0; i < TOKENS; i++)
+#pragma unroll
+      for (int j = 0; j < KK; j++) add(acc[i], w[i][j], v[i][j]);
+  } else {
+    for (int j = 0; j < k; j++)
+      add(acc[0], p.topk_weights[t0 * k + j], *(const u32x4*)(p.Y + (size_t)p.inv_perm[t0 * k + j] * p.H + col));
+  }
+#pragma unroll
+  for (int i = 0; i < TOKENS; i++) {
+    if (t0 + i >= p.T) break;
     u32x4 o;
 #pragma unroll
     for (int c = 0; c < 4; c++) {
-      bf16x2 pr = {(__bf16)acc[2 * c], (__bf16)acc[2 * c + 1]};
+      const bf16x2 pr = {(__bf16)acc[i][2 * c], (__bf16)acc[i][2 * c + 1]};
       o[c] = __builtin_bit_cast(uint32_t, pr);
     }
-    *(u32x4*)(p.out + (size_t)t * p.H + col) = o;
+    *(u32x4*)(p.out + (size_t)(t0 + i) * p.H + col) = o;
   }
 }
 
@@ -1422,13 +1457,25 @@ hipError_t launch_zero_u32(uint32_t* ptr, size_t n, hipStream_t st) {
   return hipGetLastError();
 }
 
+template <int K, int TOKENS = combine_tokens(K)>
+static hipError_t launch_combine_k(const CombineParams& p, hipStream_t st) {
+  const int n_panels = p.H / BN, n_units = (p.T + TOKENS - 1) / TOKENS * n_panels;   // (T * H < 2^31)
+  if constexpr (TOKENS > 1) {
+    if (p.T * n_panels <= 8 * kCombineResident) return launch_combine_k<K, 1>(p, st);
+  }
+  hipLaunchKernelGGL((k_combine<K, TOKENS>), dim3((n_units + 7) / 8), dim3(256), 0, st, p, n_panels, n_units);
+  return hipGetLastError();
+}
+
 hipError_t launch_combine(const CombineParams& p, hipStream_t st) {
   if (p.T == 0) return hipSuccess;
-  const size_t total = (size_t)p.T * (p.H / 8);
-  int grid = (int)((total + 255) / 256);
-  if (grid > 256 * 16) grid = 256 * 16;
-  hipLaunchKernelGGL(k_combine, dim3(grid), dim3(256), 0, st, p);
-  return hipGetLastError();
+  switch (p.k) {
+    case 1: return launch_combine_k<1>(p, st);
+    case 2: return launch_combine_k<2>(p, st);
+    case 4: return launch_combine_k<4>(p, st);
+    case 8: return launch_combine_k<8>(p, st);
+    default: return launch_combine_k<0>(p, st);
+  }
 }
 
 }  // namespace moe
