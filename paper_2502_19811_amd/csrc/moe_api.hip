@@ -294,6 +294,16 @@ int moe_plan_create(moe_plan_t** plan, const moe_shape_t* shape, const int32_t* 
   p->phases = 15;
   p->n_cu = 0;
   layout(p);
+  if (p->tile_m < 256 && p->total_bytes > kStaticScratchBytes) {
+    // short tiles have larger tables: they must not be what keeps a plan out of the library's own workspace
+    const int32_t tile_m = p->tile_m;
+    p->tile_m = 256;
+    layout(p);
+    if (p->total_bytes > kStaticScratchBytes) {
+      p->tile_m = tile_m;
+      layout(p);
+    }
+  }
   *plan = p;
   return MOE_OK;
 }
