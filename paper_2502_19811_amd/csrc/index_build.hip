@@ -150,8 +150,10 @@ __global__ __launch_bounds__(256) void k_index_scatter(IndexParams p) {
   __shared__ int32_t off[kMaxExperts];     // first row of each expert
   __shared__ int32_t before[kMaxExperts];  // rows of each expert owned by earlier workgroups
   __shared__ int32_t tbase[kMaxExperts];   // first M-tile of each expert (workgroup 0)
+  __shared__ int32_t tallest;              // rows of the tallest M-tile (workgroup 0)
   const int E = p.s.E, R = p.s.R, k = p.s.k;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (threadIdx.x == 0) tallest = 0;
   int my_cnt = 0;
   {
     const int e = threadIdx.x;   // E <= 256 = threads
@@ -187,6 +189,7 @@ __global__ __launch_bounds__(256) void k_index_scatter(IndexParams p) {
     const int e = threadIdx.x;
     const int tail = e < E ? tail_height(my_cnt, p.tile_m) : 0;
     const int my_tiles = e < E ? my_cnt / p.tile_m + (tail > 0) : 0;
+    if (my_tiles > 0) atomicMax(&tallest, min(my_cnt, p.tile_m));   // (exclusive_scan_256 has barriers on both sides of it)
     const int n_tiles = exclusive_scan_256(tbase, my_tiles);
     const int waves = wave == 0 ? waves_now(p, lane) : 0;
     if (threadIdx.x == 0) {
@@ -196,6 +199,7 @@ __global__ __launch_bounds__(256) void k_index_scatter(IndexParams p) {
       p.ws.status[2] = n_tiles * p.n_tiles_n0;
       p.ws.status[3] = n_tiles * p.n_tiles_n1;
       p.ws.status[4] = 0;
+      p.ws.status[6] = tallest;
       p.ws.offsets[E] = total_rows;
     }
     if (threadIdx.x < 2 * kXcds) p.ws.status[8 + threadIdx.x] = 0;   // queue heads of both layers

@@ -39,7 +39,7 @@ struct ItemRec {
 struct Workspace {
   int32_t* status;        // [64]  0: device status word, 1: n_tiles, 2: items of layer0, 3: items of layer1,
                           //       4: combine unit counter, 5: serial number of the last forward that saw an expert
-                          //       id out of range; 6: rows of the tallest tile (written for small batches); 7: waves of the layer0 schedule; per XCD: 8..15 layer0 queue heads, 16..23 layer1 queue
+                          //       id out of range; 6: rows of the tallest tile; 7: waves of the layer0 schedule; per XCD: 8..15 layer0 queue heads, 16..23 layer1 queue
                           //       heads, 24..31 layer0 queue lengths, 32..39 layer1 queue lengths, 40..47 layer1
                           //       queue bases, 48..55 layer0 queue bases (only with contiguous layer0 queues;
                           //       otherwise layer0's queue x is list positions x, x+8, ...)

@@ -65,3 +65,30 @@ def test_small_batch_with_a_missing_flag_times_out():
     assert run.status == 0
     a, b = H.error_metrics(run.out, orc.moe_layer(inp.x, inp.W1, inp.W2, ids, w, cfg.act))
     assert a <= H.REL_TOL and b <= H.REL_TOL
+
+
+@pytest.mark.parametrize("fill", [0, 0xFF])
+@pytest.mark.parametrize("Hd,F", [(256, 2048), (4096, 128)], ids=["layer1_alone", "layer0_alone"])
+def test_one_layer_alone_in_small_batches(Hd, F, fill):
+    """Plain weights of 256 experts: one GroupGEMM has fewer tiles than the device has compute units and the other more, and
+    both schedules together are more items than the one-workgroup index build takes.  Nothing may depend on what the
+    workspace held before."""
+    import gpu_harness as H
+    cfg = wl.MoEConfig("decode_mixed", T=2, H=Hd, F=F, E=256, k=8, act=wl.ACT_SWIGLU, S=1, seed=660)
+    inp = wl.make_inputs(cfg, threads=2, weights=False)
+    ids, w = orc.route_topk(inp.logits, cfg.k)
+    used = np.unique(ids)
+    inp.W1 = np.zeros((cfg.E, Hd, 2 * F), np.uint16)
+    inp.W2 = np.zeros((cfg.E, F, Hd), np.uint16)
+    inp.W1[used] = wl.normal_bf16((used.size, Hd, 2 * F), 661, 1, Hd ** -0.5)
+    inp.W2[used] = wl.normal_bf16((used.size, F, Hd), 661, 2, F ** -0.5)
+    ref = orc.moe_layer(inp.x, inp.W1, inp.W2, ids, w, cfg.act)
+    layer = H.GpuLayer(cfg, inp, ids, w)
+    layer.ws.fill_(fill)
+    print(f"decode mixed H {Hd} F {F} workspace filled with {fill}", flush=True)
+    layer.forward()
+    run = layer.results()
+    layer.close()
+    assert run.status == 0
+    a, b = H.error_metrics(run.out, ref)
+    assert a <= H.REL_TOL and b <= H.REL_TOL, f"{a:.3e} {b:.3e}"
