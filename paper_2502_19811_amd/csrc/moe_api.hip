@@ -242,9 +242,11 @@ int default_layer0_waves(const Shape& s, int ingest_gbps) {
 //   plain, 8 experts of F = 1792       8 tokens (112 / 128 tiles) 66 / 35 -> 50 / 28, 64: 68 / 36 -> 53 / 32
 //   plain, 8 experts of F = 14336      16 tokens (896 / 128 tiles) 345 / 190 -> 366 / 190
 // So packed weights take it up to 16 rows per expert.  Plain weights, whose rows it reads in pieces of 128 bytes against
-// the tile kernel's 512, take it only where the tiles leave compute units idle.
-bool decode_path(const moe_plan* p, int n_tiles_n, int n_cu) {
+// the tile kernel's 512, take it only where the tiles leave compute units idle.  It addresses an expert's matrix (K rows of ldb
+// columns) with 32-bit byte offsets; the tile kernel has no such limit.
+bool decode_path(const moe_plan* p, int n_tiles_n, int64_t K, int64_t ldb, int n_cu) {
   const Shape& s = p->s;
+  if (K * ldb * 2 >= 1ll << 32) return false;
   if ((int64_t)s.R > (int64_t)kDecodeRowsPerExpert * s.E) return false;
   if (!p->weights_packed && (int64_t)(s.E < s.R ? s.E : s.R) * n_tiles_n >= n_cu) return false;
   return p->layer1_order == 0 && !p->fuse_layers && p->n_prefetch <= 0 && !p->handoff_fences && !p->alias_experts &&
@@ -525,7 +527,7 @@ int forward_impl(moe_plan_t* p, const void* x, const int32_t* topk_ids, const fl
   if (order0 == 2 && large) order0 = 1;
   if (p->phases & 1) p->last_layer0_order = order0;
   else order0 = p->last_layer0_order;   // the schedules of the last index build are run again
-  const bool decode0 = decode_path(p, p->n_tiles_n0, p->n_cu), decode1 = decode_path(p, p->n_tiles_n1, p->n_cu);
+  const bool decode0 = decode_path(p, p->n_tiles_n0, s.H, s.F1, p->n_cu), decode1 = decode_path(p, p->n_tiles_n1, s.F, s.H, p->n_cu);
   // a forward beyond the last event slot is not recorded (and counted as dropped) rather than overwriting an earlier one
   hipEvent_t* ev = (p->profile && p->prof_steps < kProfSlots) ? p->ev[p->prof_steps] : nullptr;
   if (p->profile && !ev) p->prof_dropped++;

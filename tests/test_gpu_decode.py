@@ -92,3 +92,35 @@ def test_one_layer_alone_in_small_batches(Hd, F, fill):
     assert run.status == 0
     a, b = H.error_metrics(run.out, ref)
     assert a <= H.REL_TOL and b <= H.REL_TOL, f"{a:.3e} {b:.3e}"
+
+
+def test_an_expert_of_more_than_4_gib():
+    """Two tokens of one expert whose W1 is 16 GiB: beyond what 32-bit byte offsets inside an expert reach.  Checked against a plain
+    product in fp32 of the same tensors."""
+    import gpu_harness as H
+    import paper_2502_19811_amd as moe
+    T, Hd, F = 2, 131840, 32640
+    g = torch.Generator(device="cuda")
+    g.manual_seed(680)
+
+    def normal(shape, std):
+        return torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=g)
+
+    x, W1, W2 = normal((T, Hd), 1.0), normal((1, Hd, 2 * F), Hd ** -0.5), normal((1, F, Hd), F ** -0.5)
+    a = torch.zeros((T, 2 * F), device="cuda")
+    for k in range(0, Hd, 8240):
+        a += x[:, k:k + 8240].float() @ W1[0, k:k + 8240].float()
+    h = (torch.nn.functional.silu(a[:, :F]) * a[:, F:]).to(torch.bfloat16)
+    ref = torch.zeros((T, Hd), device="cuda")
+    for k in range(0, F, 4080):
+        ref += h[:, k:k + 4080].float() @ W2[0, k:k + 4080].float()
+    plan = moe.moe_plan_create(T, Hd, F, 1, 1, 1, moe.MOE_ACT_SWIGLU, [0, T])
+    ws = torch.zeros(moe.moe_plan_workspace_bytes(plan), dtype=torch.uint8, device="cuda")
+    ids, w = torch.zeros((T, 1), dtype=torch.int32, device="cuda"), torch.ones((T, 1), device="cuda")
+    out = torch.zeros((T, Hd), dtype=torch.bfloat16, device="cuda")
+    print("decode, expert of 16 GiB", flush=True)
+    moe.moe_layer_forward(plan, x, ids, w, W1, W2, moe.MOE_ACT_SWIGLU, out, ws)
+    assert moe.moe_last_device_status(plan, ws) == 0
+    moe.moe_plan_destroy(plan)
+    a, b = H.error_metrics(H.bf16_to_np(out), ref.double().cpu().numpy())
+    assert a <= H.REL_TOL and b <= H.REL_TOL, f"{a:.3e} {b:.3e}"
