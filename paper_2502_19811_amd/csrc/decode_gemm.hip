@@ -3,30 +3,31 @@
 // What bounds it is the stream of weights from HBM: every expert that some token picked is read once for a handful of
 // rows.  The persistent tile kernel (grouped_gemm.hip) keeps that stream going only while it has a 64 x 256 tile or two
 // per compute unit; with few rows there are few tiles (layer1 of one token of 8 experts, H = 4096: 32), and the rest of
-// the chip idles.  Here the unit is 32 columns (plain weights: 64) of one expert by up to 32 rows:
-//  * a workgroup is 8 wavefronts that share the columns and split K, so that even one token's layer1 is 256 units; the
-//    parts of K meet in LDS at the end, in a fixed order;
-//  * a wavefront keeps a ring of operands in registers, loaded two or three 64-deep steps ahead, and meets the others
-//    only at the end of a unit; its rows of A go through a private piece of LDS (8 whole lines per load instruction, then
-//    one ds_read_b128 per fragment: read as fragments from memory, 32 rows apart, they took a third longer at 8 rows);
-//  * the first loads of the next unit are issued before the parts of this one meet, and two workgroups share a compute
-//    unit (128 registers a wavefront), so that the stream does not stop at the ends of units;
-//  * packed weights arrive in MFMA operand order (one 1 KiB load is one fragment).  Plain weights are loaded as they lie
-//    (rows of K, whole 128-byte lines) and transposed through LDS with ds_read_b64_tr_b16;
-//  * there is no schedule: workgroups walk the units with a fixed stride.  (A workgroup per unit cost 220 us on layer0 +
-//    layer1 of 32 tokens of the Mixtral-shaped layer, where every other workgroup finds no rows and returns: those keep
-//    waiting ones from starting.)
-// Measured on that shape with packed weights, both layers, tile kernel -> this one: 1 token 259 -> 128 us (704 MB: 5.5
-// TB/s), 16 tokens 531 -> 482 us (2.8 GB: 5.8 TB/s; a copy of 1 GiB moves 4.4 TB/s, half of it writes).
+// the chip idles.  Here the unit of work is one wavefront's: 16 to 64 columns of one expert by up to 32 rows.
+//  * A wavefront sums all of K, 32 values at a time with the tile kernel's instruction in the tile kernel's order: an output has
+//    the same bits whichever kernel computes it, whatever the batch around it.  (K split over 8 wavefronts that added their
+//    parts up had not, and was not faster: below.)
+//  * It keeps a ring of operands in registers, loaded 2 to 8 steps of 64 values of K ahead, and meets nobody; its rows of A go
+//    through a private piece of LDS (8 whole lines per load instruction, then one ds_read_b128 per fragment: read as
+//    fragments from memory they took a third longer at 8 rows).
+//  * The first loads of the next unit are issued before this one is written, and several wavefronts share a SIMD, so that the
+//    stream does not stop at the ends of units.
+//  * Packed weights arrive in MFMA operand order (a fragment is 4 pieces of 256 bytes).  With SwiGLU a wavefront has the gate and
+//    the up columns of its hidden units.  Plain weights are loaded as they lie (rows of K, whole 128-byte lines) and
+//    transposed through LDS with ds_read_b64_tr_b16; with SwiGLU the two wavefronts of a workgroup take gate and up and
+//    exchange halves at the end (in 64-byte pieces, both in one wavefront: 61 us against 47 on layer0 of 33 tokens, F = 1792).
+//  * There is no schedule: wavefronts walk the units with a fixed stride.
+// us for both layers, tile kernel -> K in 8 parts -> this one: Mixtral-shaped packed, 1 token 259 -> 130 -> 133 (704 MB: 5.3
+// TB/s), 16 tokens 530 -> 485 -> 484 (2.8 GB: 5.8 TB/s; a copy of 1 GiB moves 4.4 TB/s, half of it writes); 64 experts of
+// F = 2560, 48 tokens 634 -> 615 -> 623; plain, 8 experts of F = 1792, 33 tokens 102 -> 82 -> 74.
 #include "moe_device.h"
 
 namespace moe {
 
-constexpr int kDecodeWaves = 8;
+constexpr int kDecodeWaves = 2;                    // of a workgroup
 constexpr int kStageBytes = kTileK * kTileN * 2;   // packed weights: one K step of one column tile
 constexpr int kPlainPitch = 144;                   // bytes between rows of K in the transposing buffer (64 columns + padding)
 constexpr int kStepK = 64;                         // K of one ring slot: a whole 128-byte line of every row of A
-constexpr int kABytes = 32 * kStepK * 2;           // a wavefront's rows of A for one step, in LDS
 
 // The memory from ptr on (the same in every lane) as a buffer: loads then take one 32-bit offset per lane and one scalar
 // offset, and no 64-bit address per load sits in vector registers.
@@ -34,17 +35,23 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer(const char* ptr) {
   return __builtin_amdgcn_make_buffer_rsrc((void*)uniform(ptr), 0, -1, 0x00020000);
 }
 
-// NB: 32-column blocks of a wavefront; RB: 8-row groups of A that are loaded (a unit is up to 8 RB rows); U: steps in flight.
-template <int MODE, bool PK, int NB, int RB, int U>
-__global__ __launch_bounds__(kDecodeWaves * 64) __attribute__((amdgpu_waves_per_eu(PK ? 4 : 2))) void k_decode_gemm(DecodeParams p) {
-  static_assert(PK || NB == 2, "plain weights are loaded in whole 128-byte lines: 64 columns");
-  constexpr bool kPair = MODE == MODE_L0_SWIGLU;       // gate and up columns of the same hidden units meet in the workgroup
+// NB: 16-column blocks of weights of a wavefront (SwiGLU: half of them gate, half up columns of the same hidden units);
+// RB: 8-row groups of A that are loaded (a unit is up to 8 RB rows); U: steps in flight; EU: wavefronts a SIMD holds.
+template <int MODE, bool PK, int NB, int RB, int U, int EU>
+__global__ __launch_bounds__(kDecodeWaves * 64) __attribute__((amdgpu_waves_per_eu(EU))) void k_decode_gemm(DecodeParams p) {
+  constexpr bool kPair = MODE == MODE_L0_SWIGLU;
   constexpr int ROWS = 8 * RB;
-  constexpr int CW = NB * 32;                          // columns of a wavefront
-  constexpr int PITCH = CW + 4;                        // floats between rows of a partial result
-  constexpr int NBL = NB * 4;                          // 16-byte loads of B per lane and step
+  constexpr int RR = (RB + 1) / 2;                     // 16-row blocks
+  constexpr bool kInWave = kPair && PK;                // gate and up columns of a hidden unit in one wavefront ...
+  constexpr bool kTwoWaves = kPair && !PK;             // ... or in the workgroup's two
+  constexpr int OB = kInWave ? NB / 2 : NB;            // 16-column blocks of C of a unit
+  constexpr int NBL = NB * 2;                          // 16-byte loads of B per lane and step
+  constexpr int kABytes = RR * 16 * kStepK * 2;        // rows of A of one step, in LDS
   constexpr int kWaveBytes = kABytes + (PK ? 0 : kTileK * kPlainPitch);   // operands on their way through LDS
-  __shared__ __attribute__((aligned(16))) float part[kDecodeWaves * ROWS * PITCH];
+  constexpr bool kAhead = U >= 4 && (RB == 1 || !PK);  // a step's rows of A go through LDS a step ahead
+  static_assert(PK || NB == 4 || (NB == 2 && !kPair), "plain weights: rows of K in pieces of 64 or 128 bytes");
+  static_assert(!kAhead || U % 2 == 0, "the fragments of A alternate between two sets of registers");
+  __shared__ __attribute__((aligned(16))) f32x4 swap_lds[kTwoWaves ? 2 : 1][2][kTwoWaves ? RR * 2 : 1][kTwoWaves ? 64 : 1];
   __shared__ __attribute__((aligned(128))) char operands[kDecodeWaves * kWaveBytes];
   __shared__ int ok_lds;
 
@@ -64,19 +71,12 @@ __global__ __launch_bounds__(kDecodeWaves * 64) __attribute__((amdgpu_waves_per_
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "");
   }
 
-  // this wavefront's part of K and its columns
-  const int ks = 1 << p.k_split_log2;
-  const int kw = w & (ks - 1), cw = w >> p.k_split_log2;
-  const int n_cw = kDecodeWaves >> p.k_split_log2;       // column groups of the workgroup
-  const int n_units = kPair ? n_cw / 2 : n_cw;           // ... of its output
-  const int half = kPair && cw >= n_units;               // 1: up columns
+  // Units: (row part, tile, columns), the parts slowest and the columns fastest.  Wavefronts take them in turn.
   const int nk = p.K / kStepK;
-  const int k_lo = kw * nk >> p.k_split_log2, k_hi = (kw + 1) * nk >> p.k_split_log2;
-  const int wave_col = (half ? cw - n_units : cw) * CW;
-
-  // Units: (row part, tile, columns), the parts slowest and the columns fastest.  Workgroups take them in turn.
+  const int n_groups = p.N / (OB * 16);
   const int n_parts = (*p.tallest + ROWS - 1) / ROWS;
-  const int per_part = n_tiles * p.n_groups, n_wg_units = per_part * n_parts;
+  const int per_part = n_tiles * n_groups, n_units = per_part * n_parts;
+  const int stride = kTwoWaves ? gridDim.x : gridDim.x * kDecodeWaves;
   struct Unit {
     int index, cg, row0, nrows, expert;
     uint32_t a_off[RB];          // per lane: rows 8 g + lane / 8 of A, 16 bytes at lane % 8 of a line
@@ -84,12 +84,12 @@ __global__ __launch_bounds__(kDecodeWaves * 64) __attribute__((amdgpu_waves_per_
   auto find = [&](int index) {   // the first unit with rows from this one on
     Unit t;
     t.nrows = 0;
-    for (; index < n_wg_units; index += gridDim.x) {
+    for (; index < n_units; index += stride) {
       const int sub = index / per_part, in_part = index % per_part;
-      const int slot = in_part / p.n_groups;
+      const int slot = in_part / n_groups;
       const int rows = p.tile_rows[slot] - sub * ROWS;
       if (rows <= 0) continue;
-      t.cg = in_part % p.n_groups;
+      t.cg = in_part % n_groups;
       t.row0 = p.tile_row0[slot] + sub * ROWS;
       t.nrows = rows < ROWS ? rows : ROWS;
       t.expert = p.tile_expert[slot];
@@ -107,164 +107,201 @@ __global__ __launch_bounds__(kDecodeWaves * 64) __attribute__((amdgpu_waves_per_
   };
 
   u32x4 areg[U][RB], breg[U][NBL];
-  __amdgpu_buffer_rsrc_t a_buf, b_buf;
+  const __amdgpu_buffer_rsrc_t a_buf = buffer(p.A);
+  __amdgpu_buffer_rsrc_t b_buf;
   uint32_t a_off[RB];
-  int n = 0;                                             // steps of this wavefront
-  const uint32_t b_off = PK ? lane * 16 : (lane >> 3) * p.ldb * 2 + (lane & 7) * 16;
-  const uint32_t b_row8 = p.ldb * 2 * 8;                 // plain: 8 rows of K
+  const int g16 = lane >> 4, j16 = lane & 15;
+  // Packed: the operand of one MFMA (32 values of K of 16 columns) is 4 pieces of 256 bytes, one per 8 values of K.
+  // Plain: a load takes 8 rows of K (128-byte lines), or 16 rows (64 bytes) where the wavefront has 32 columns of a matrix.
+  constexpr int kLineCols = NB * 16, kLineLanes = kLineCols / 8, kLineRows = 64 / kLineLanes;
+  const uint32_t b_off = PK ? (g16 >> 1) * (kStageBytes / 2) + (g16 & 1) * 512 + j16 * 16
+                            : (lane / kLineLanes) * p.ldb * 2 + (lane % kLineLanes) * 16;
+  const uint32_t b_rows = p.ldb * 2 * kLineRows;
   const uint32_t b_step = PK ? 2 * kStageBytes : p.ldb * 2 * kStepK;
   auto load = [&](int u, int st) {
     const uint32_t bs = (uint32_t)st * b_step;
-    // packed: fragment (K 16 kk .. + 15, block nb) at kk * NB + nb; plain: rows 8 j .. + 7 of K at j
+    auto load_a = [&]() {
+#pragma unroll
+      for (int g = 0; g < RB; g++) areg[u][g] = __builtin_amdgcn_raw_buffer_load_b128(a_buf, a_off[g], st * (kStepK * 2), 0);
+    };
+    if (kAhead) load_a();
 #pragma unroll
     for (int j = 0; j < NBL; j++) {
-      const uint32_t at = PK ? bs + (j / NB) * (kStageBytes / 2) + (j % NB) * 1024 : bs + j * b_row8;
+      uint32_t at;
+      if (PK) {   // (32 values of K j / NB, block j % NB)
+        const int nb = j % NB;
+        at = bs + (j / NB) * kStageBytes + (nb / OB) * 4096 + ((nb % OB) >> 1) * 1024 + (nb & (OB > 1 ? 1 : 0)) * 256;
+      } else {
+        at = bs + j * b_rows;
+      }
       breg[u][j] = __builtin_amdgcn_raw_buffer_load_b128(b_buf, b_off, at, 0);
     }
-#pragma unroll
-    for (int g = 0; g < RB; g++) areg[u][g] = __builtin_amdgcn_raw_buffer_load_b128(a_buf, a_off[g], st * (kStepK * 2), 0);
+    if (!kAhead) load_a();
   };
   // addresses of a unit and its first loads (past the last step: the last step again, it is in the caches; a load under
   // a condition would make the compiler wait for more than it has to at every use)
   auto start = [&](const Unit& t) {
-    const int out_col = t.cg * n_units * CW + wave_col;
-    n = out_col < p.N ? k_hi - k_lo : 0;
-    if (n == 0) return;
+    const int col = t.cg * (OB * 16);   // of C
 #pragma unroll
     for (int g = 0; g < RB; g++) a_off[g] = t.a_off[g];
-    a_buf = buffer(p.A + (size_t)k_lo * (kStepK * 2));
-    if (PK) {
-      const int blk = out_col / 32;
-      const int tile = kPair ? blk >> 2 : blk >> 3;
-      const int c = kPair ? (blk & 3) + half * 4 : blk & 7;
-      b_buf = buffer(p.B + (((uint64_t)t.expert * p.n_tiles_n + tile) * nk + k_lo) * (2 * kStageBytes) + c * 1024);
+    if (PK) {   // column tiles of 256 columns (SwiGLU: 128 gate and the 128 up columns of the same units)
+      const int tile = kPair ? col >> 7 : col >> 8, in_tile = kPair ? col & 127 : col & 255;
+      b_buf = buffer(p.B + ((uint64_t)t.expert * p.n_tiles_n + tile) * nk * (2 * kStageBytes) + (in_tile >> 5) * 1024 + ((in_tile >> 4) & 1) * 256);
     } else {
-      b_buf = buffer(p.B + (uint64_t)t.expert * p.b_expert_bytes + ((uint64_t)k_lo * kStepK * p.ldb + half * p.F + out_col) * 2);
+      b_buf = buffer(p.B + (uint64_t)t.expert * p.b_expert_bytes + ((uint64_t)(kTwoWaves ? w * p.F : 0) + col) * 2);
     }
 #pragma unroll
-    for (int u = 0; u < U; u++) load(u, min(u, n - 1));
+    for (int u = 0; u < U; u++) load(u, min(u, nk - 1));
   };
 
   // LDS positions: A rows of 128 bytes, the 16-byte chunks swizzled by row; plain B rows of 64 columns
   const uint32_t lds_a = (uint32_t)(uintptr_t)operands + w * kWaveBytes, lds_b = lds_a + kABytes;
-  const int row8 = lane >> 3, c8 = lane & 7, g16 = lane >> 4, j16 = lane & 15;
+  const int row8 = lane >> 3, c8 = lane & 7;
   const uint32_t a_wr = lds_a + row8 * 128 + ((c8 ^ ((row8 >> 1) & 3)) << 4);   // + 1 KiB per 8-row group, chunks ^ 4 in odd ones
-  const uint32_t a_rd = lds_a + (lane & 31) * 128;
-  const int s = ((lane & 31) >> 1) & 7;
-  const uint32_t tr_wr = lds_b + row8 * kPlainPitch + c8 * 16;
-  const uint32_t tr_rd = lds_b + (8 * (g16 >> 1) + (j16 >> 2)) * kPlainPitch + (16 * (g16 & 1) + 4 * (j16 & 3)) * 2;
-  f32x16 acc[NB];
-  auto multiply = [&](int u) {
+  const uint32_t a_rd = lds_a + j16 * 128;
+  const int s = (j16 >> 1) & 7;
+  const uint32_t tr_wr = lds_b + (lane / kLineLanes) * kPlainPitch + (lane % kLineLanes) * 16;
+  const uint32_t tr_rd = lds_b + (8 * g16 + (j16 >> 2)) * kPlainPitch + (j16 & 3) * 8;
+  f32x4 acc[RR][NB];
+  bf16x8 af[kAhead ? 2 : 1][2][RR];
+  auto through_lds = [&](int u, int set) {   // the rows of A of ring slot u, as fragments
 #pragma unroll
     for (int g = 0; g < RB; g++)
       *(u32x4 __attribute__((address_space(3)))*)(uintptr_t)((a_wr ^ ((g & 1) << 6)) + g * 1024) = areg[u][g];
 #pragma unroll
-    for (int kk = 0; kk < 4; kk++) {
-      if (!PK && (kk & 1) == 0) {
+    for (int kk = 0; kk < 2; kk++)
 #pragma unroll
-        for (int j = 0; j < 4; j++)
-          *(u32x4 __attribute__((address_space(3)))*)(uintptr_t)(tr_wr + j * 8 * kPlainPitch) = breg[u][kk * 2 + j];
+      for (int r = 0; r < RR; r++)
+        af[set][kk][r] = *(const bf16x8 __attribute__((address_space(3)))*)(uintptr_t)(a_rd + r * 2048 + (((kk * 4 + g16) ^ s) << 4));
+  };
+  auto multiply = [&](int u) {
+    if (kAhead) through_lds((u + 1) % U, (u + 1) & 1);
+    else through_lds(u, 0);
+#pragma unroll
+    for (int kk = 0; kk < 2; kk++) {
+      if (!PK) {   // 32 rows of K
+#pragma unroll
+        for (int j = 0; j < NBL / 2; j++)
+          *(u32x4 __attribute__((address_space(3)))*)(uintptr_t)(tr_wr + j * kLineRows * kPlainPitch) = breg[u][kk * (NBL / 2) + j];
       }
-      const bf16x8 a = *(const bf16x8 __attribute__((address_space(3)))*)(uintptr_t)(a_rd + (((kk * 2 + (lane >> 5)) ^ s) << 4));
 #pragma unroll
       for (int nb = 0; nb < NB; nb++) {
         bf16x8 b;
         if (PK) {
           b = __builtin_bit_cast(bf16x8, breg[u][kk * NB + nb]);
         } else {
-          const uint32_t at = tr_rd + (kk & 1) * 16 * kPlainPitch + nb * 64;
+          const uint32_t at = tr_rd + nb * 32;
           b = lds_read_b(at, at + 4 * kPlainPitch);
         }
-        acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, a, acc[nb], 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < RR; r++)
+          acc[r][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, af[kAhead ? u & 1 : 0][kk][r], acc[r][nb], 0, 0, 0);
       }
     }
   };
 
-  Unit cur = find(blockIdx.x);
-  if (cur.index < n_wg_units) start(cur);
-  while (cur.index < n_wg_units) {
+  Unit cur = find(kTwoWaves ? blockIdx.x : blockIdx.x * kDecodeWaves + w);
+  int turn = 0;
+  if (cur.index < n_units) start(cur);
+  while (cur.index < n_units) {
 #pragma unroll
-    for (int nb = 0; nb < NB; nb++) acc[nb] = (f32x16){0};
-    const Unit next = find(cur.index + gridDim.x);   // asked for now: its table entries are back when they are needed
-    if (n > 0) {
-      int st = 0;
+    for (int r = 0; r < RR; r++)
+#pragma unroll
+      for (int nb = 0; nb < NB; nb++) acc[r][nb] = (f32x4){0};
+    const Unit next = find(cur.index + stride);   // asked for now: its table entries are back when they are needed
+    if (kAhead) through_lds(0, 0);
+    int st = 0;
 #pragma unroll 1
-      do {
+    do {
 #pragma unroll
-        for (int u = 0; u < U; u++) {
-          __builtin_amdgcn_sched_barrier(0);   // a step's loads reuse the registers just consumed
-          if (st + u < n) multiply(u);
-          __builtin_amdgcn_sched_barrier(0);
-          load(u, min(st + u + U, n - 1));
-        }
-        st += U;
-      } while (st < n);
-    }
-    // the next unit's first loads are under way while this one's parts meet
-    if (next.index < n_wg_units) start(next);
-
-    // the parts of K meet in LDS; a lane holds, of row lane & 31, the columns 8*(i/4) + 4*(lane/32) + i%4 of each block
-    __syncthreads();   // the partial results of the unit before are read out
-    if ((lane & 31) < cur.nrows) {
-      float* dst = part + (w * ROWS + (lane & 31)) * PITCH + (lane >> 5) * 4;
-#pragma unroll
-      for (int nb = 0; nb < NB; nb++)
-#pragma unroll
-        for (int i = 0; i < 4; i++)
-          *(float4*)(dst + nb * 32 + i * 8) = make_float4(acc[nb][4 * i], acc[nb][4 * i + 1], acc[nb][4 * i + 2], acc[nb][4 * i + 3]);
-    }
-    __syncthreads();
-    const int total = n_units * cur.nrows * (CW / 4);
-    for (int v = tid; v < total; v += kDecodeWaves * 64) {
-      const int c4 = v % (CW / 4), ur = v / (CW / 4), rr = ur % cur.nrows, u = ur / cur.nrows;
-      const int col = (cur.cg * n_units + u) * CW + c4 * 4;
-      if (col >= p.N) continue;
-      auto sum = [&](int column_group) {
-        const float* src = part + ((column_group << p.k_split_log2) * ROWS + rr) * PITCH + c4 * 4;
-        float4 t = *(const float4*)src;
-        for (int i = 1; i < ks; i++) {
-          const float4 o = *(const float4*)(src + i * ROWS * PITCH);
-          t.x += o.x; t.y += o.y; t.z += o.z; t.w += o.w;
-        }
-        return t;
-      };
-      const float4 t = sum(u);
-      float o[4] = {t.x, t.y, t.z, t.w};
-      if (kPair) {
-        const float4 t2 = sum(u + n_units);
-        const float up[4] = {t2.x, t2.y, t2.z, t2.w};
-#pragma unroll
-        for (int i = 0; i < 4; i++) o[i] = silu(o[i]) * up[i];
-      } else if (MODE == MODE_L0_GELU) {
-#pragma unroll
-        for (int i = 0; i < 4; i++) o[i] = gelu_erf(o[i]);
+      for (int u = 0; u < U; u++) {
+        __builtin_amdgcn_sched_barrier(0);   // a step's loads reuse the registers just consumed
+        if (st + u < nk) multiply(u);
+        __builtin_amdgcn_sched_barrier(0);
+        load(u, min(st + u + U, nk - 1));
       }
-      const bf16x2 lo = {(__bf16)o[0], (__bf16)o[1]}, hi = {(__bf16)o[2], (__bf16)o[3]};
-      const u32x2 pk = {__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
-      *(u32x2*)(p.C + (size_t)(cur.row0 + rr) * p.ldc + col) = pk;
+      st += U;
+    } while (st < nk);
+    // the next unit's first loads are under way while this one is written
+    if (next.index < n_units) start(next);
+
+    // SwiGLU of plain weights: wavefront 0 gives the gate columns of the upper blocks away and gets the up columns of the
+    // lower ones, wavefront 1 the reverse.
+    if constexpr (kTwoWaves) {
+#pragma unroll
+      for (int r = 0; r < RR; r++)
+#pragma unroll
+        for (int i = 0; i < 2; i++) swap_lds[turn][w][r * 2 + i][lane] = w == 0 ? acc[r][2 + i] : acc[r][i];
+      __syncthreads();   // (this turn's buffer is written again two units on, behind the next unit's barrier)
     }
+    // a lane holds, of row lane % 16 of a block, the 4 columns from 4 (lane / 16) on
+#pragma unroll
+    for (int r = 0; r < RR; r++) {
+      const int row = r * 16 + j16;
+      uint16_t* dst = p.C + (size_t)(cur.row0 + row) * p.ldc + cur.cg * (OB * 16) + (kTwoWaves ? w * 32 : 0) + g16 * 4;
+#pragma unroll
+      for (int nb = 0; nb < (kTwoWaves ? 2 : OB); nb++) {
+        f32x4 v = acc[r][nb], up = v;
+        if constexpr (kInWave) up = acc[r][nb + OB];
+        if constexpr (kTwoWaves) {
+          const f32x4 other = swap_lds[turn][w ^ 1][r * 2 + nb][lane];
+          up = w == 0 ? other : acc[r][2 + nb];
+          v = w == 0 ? v : other;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+          if (kPair) v[i] = silu(v[i]) * up[i];
+          else if (MODE == MODE_L0_GELU) v[i] = gelu_erf(v[i]);
+        }
+        const bf16x2 lo = {(__bf16)v[0], (__bf16)v[1]}, hi = {(__bf16)v[2], (__bf16)v[3]};
+        const u32x2 pk = {__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
+        if (row < cur.nrows) *(u32x2*)(dst + nb * 16) = pk;
+      }
+    }
+    turn ^= 1;
     cur = next;
   }
 }
 
-template <int MODE, bool PK, int RB>
-static hipError_t launch_decode(DecodeParams p, hipStream_t st) {
-  constexpr int NB = PK ? 1 : 2, U = PK ? (RB == 4 ? 2 : 3) : 2;
-  const int units_per_wg = (kDecodeWaves >> p.k_split_log2) / (MODE == MODE_L0_SWIGLU ? 2 : 1);
-  p.n_groups = (p.N + units_per_wg * NB * 32 - 1) / (units_per_wg * NB * 32);
-  const int64_t units = (int64_t)p.n_slots * p.n_groups * ((p.tile_m + 8 * RB - 1) / (8 * RB));
-  const int64_t resident = (int64_t)p.n_cu * (PK ? 2 : 1);
-  hipLaunchKernelGGL((k_decode_gemm<MODE, PK, NB, RB, U>), dim3((unsigned)(units < resident ? units : resident)),
-                     dim3(kDecodeWaves * 64), 0, st, p);
+template <int MODE, bool PK, int NB, int RB, int U, int EU>
+static hipError_t launch_decode(const DecodeParams& p, hipStream_t st) {
+  constexpr bool kTwoWaves = MODE == MODE_L0_SWIGLU && !PK, kInWave = MODE == MODE_L0_SWIGLU && PK;
+  const int64_t units = (int64_t)p.n_slots * (p.N / (NB * 16 / (kInWave ? 2 : 1))) * ((p.tile_m + 8 * RB - 1) / (8 * RB));
+  const int64_t wgs = kTwoWaves ? units : (units + 1) / 2, resident = (int64_t)p.n_cu * (4 * EU / kDecodeWaves);
+  const int64_t rounds = (wgs + resident - 1) / resident;   // all workgroups get as many units, or one less
+  hipLaunchKernelGGL((k_decode_gemm<MODE, PK, NB, RB, U, EU>), dim3((unsigned)((wgs + rounds - 1) / rounds)), dim3(kDecodeWaves * 64), 0, st, p);
   return hipGetLastError();
+}
+
+// Columns of a wavefront, ring depth and wavefronts per SIMD by what fits the registers and measured best, us per launch:
+//   packed, up to 8 rows    SwiGLU 4 steps x 4 wavefronts 86, 6 x 2 87, 3 x 4 87; layer1 (512 wavefronts in all for one token) 16 columns
+//                           each, 8 x 2 44, 4 x 4 52; 32 columns 4 x 4 66   (1 token, Mixtral-shaped)
+//   packed, 9 to 16 rows    4 x 4 309 / 159, 2 x 4 319 / 159 (16 tokens)
+//   packed, more            SwiGLU 3 x 3 402, 2 x 4 411; layer1 32 columns 2 x 4 219, 6 x 2 222 (48 tokens, 64 experts of F = 2560)
+//   plain, SwiGLU           3 x 2 25, 2 x 2 33 (4 tokens); 4 x 1 47, 3 x 2 50 (33 tokens, 8 experts of F = 1792)
+// Plain weights without SwiGLU: 64 columns, whole lines (12 tokens, F = 2560, weights from HBM: layer1 33 us against 46 in
+// 64-byte pieces), but 32 where the wavefronts of 64 would leave compute units idle (one token, 120 wavefronts of 64 columns: layer1
+// of F = 1792 19 -> 16; 4 tokens of GELU layer0, 147: 33 -> 26, 210: 37 / 37, 252 and cold: 44 -> 67).
+template <int MODE, int RB>
+static hipError_t launch_decode_depth(const DecodeParams& p, int packed, hipStream_t st) {
+  constexpr bool kPair = MODE == MODE_L0_SWIGLU;
+  if (packed) {
+    if constexpr (RB == 1) return launch_decode<MODE, true, (kPair ? 2 : 1), 1, (kPair ? 4 : 8), (kPair ? 4 : 2)>(p, st);
+    else if constexpr (RB == 2) return launch_decode<MODE, true, (kPair ? 2 : 1), 2, 4, 4>(p, st);
+    else return launch_decode<MODE, true, 2, 4, (kPair ? 3 : 2), (kPair ? 3 : 4)>(p, st);
+  }
+  if constexpr (!kPair) {
+    if (p.experts * (p.N / 64) < 0.75f * p.n_cu) return launch_decode<MODE, false, 2, RB, (RB == 1 ? 6 : 4), 2>(p, st);
+  }
+  return launch_decode<MODE, false, 4, RB, (RB == 1 ? 3 : 4), (RB == 4 ? 1 : 2)>(p, st);
 }
 
 template <int MODE>
 static hipError_t launch_decode_rows(const DecodeParams& p, int packed, hipStream_t st) {
   // rows a unit holds: what most experts of the batch stay under
-  if (p.T <= 8) return packed ? launch_decode<MODE, true, 1>(p, st) : launch_decode<MODE, false, 1>(p, st);
-  if (p.T <= 16) return packed ? launch_decode<MODE, true, 2>(p, st) : launch_decode<MODE, false, 2>(p, st);
-  return packed ? launch_decode<MODE, true, 4>(p, st) : launch_decode<MODE, false, 4>(p, st);
+  if (p.T <= 8) return launch_decode_depth<MODE, 1>(p, packed, st);
+  if (p.T <= 16) return launch_decode_depth<MODE, 2>(p, packed, st);
+  return launch_decode_depth<MODE, 4>(p, packed, st);
 }
 
 hipError_t launch_decode_gemm(const DecodeParams& p, int layer1, int act, int packed, hipStream_t st) {

@@ -1,4 +1,5 @@
 // Host side of libmoe_gfx950: plan object, workspace layout, and the extern "C" entry points.
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
@@ -131,21 +132,8 @@ int decode_slots(const Shape& s, int tile_m, int max_tiles) {
   return n < max_tiles ? n : max_tiles;
 }
 
-// log2 of the parts the 8 wavefronts of a decode workgroup split K into; pair: gate and up columns are different
-// wavefronts.  Up to kDecodeSerialK the sum is the tile kernel's, step by step.  Above, as many parts as leave a wavefront
-// 12 steps of 64 (a shorter stream is all start and end: 5 steps 217 us, 20 steps 210 us on layer1 of 64 experts of
-// F = 2560; plain weights 24, since fewer parts are longer runs of a row: 272 -> 222 us there), or fewer steps where the
-// workgroups would not go round the device twice.
-int decode_k_split(const moe_plan* p, int K, int N, bool pair, int n_slots) {
-  if (K <= kDecodeSerialK) return 0;
-  int log2 = pair ? 2 : 3;
-  while (log2 > 0 && (K / 64 >> log2) < (p->weights_packed ? 12 : 24)) {
-    const int64_t units = (int64_t)n_slots * N / (32 * (8 >> (log2 - 1)) / (pair ? 2 : 1));
-    if (units < 2 * p->n_cu) break;
-    log2--;
-  }
-  return log2;
-}
+// Experts that have rows when the pairs are spread evenly.
+float expected_experts(const Shape& s) { return (float)(s.E * (1.0 - pow(1.0 - 1.0 / s.E, s.R))); }
 
 // Tallest tile the schedule may use (an expert's remainder gets a shorter one anyway).  A tile streams its column's weights
 // whatever its height, so 256 rows -- except where the items of layer0 then are one round or less on the device: the
@@ -236,19 +224,20 @@ int default_layer0_waves(const Shape& s, int ingest_gbps) {
 
 // Whether a GroupGEMM of n_tiles_n column tiles runs as k_decode_gemm (one pass over the weights for a few rows per
 // expert) or as the persistent tile kernel.  Measured, us per layer0 / layer1 launch, tile kernel -> decode kernel:
-//   packed, 8 experts of F = 14336     1 token 116 / 143 -> 84 / 45, 16 tokens 327 / 204 -> 317 / 164, 64: 333 / 209 -> 335 / 170,
+//   packed, 8 experts of F = 14336     1 token 120 / 144 -> 89 / 44, 16 tokens 328 / 202 -> 320 / 160, 64: 336 / 208 -> 343 / 167,
 //                                      128 (32 rows per expert, a second part for half of them): 338 / 214 -> 525 / 256
-//   packed, 64 experts of F = 2560     1 token 68 / 46 -> 60 / 34, 48: 412 / 218 -> 394 / 210, 128 (16 rows): 418 / 222 -> 406 / 222
-//   plain, 8 experts of F = 1792       8 tokens (112 / 128 tiles) 66 / 35 -> 50 / 28, 64: 68 / 36 -> 53 / 32
-//   plain, 8 experts of F = 14336      16 tokens (896 / 128 tiles) 345 / 190 -> 366 / 190
+//   packed, 64 experts of F = 2560     1 token 67 / 45 -> 59 / 31, 48: 415 / 219 -> 404 / 219, 128 (16 rows): 424 / 224 -> 434 / 236
+//   plain, 8 experts, H = 4096, 64 tokens   F = 1792 (112 / 128 tiles) 68 / 36 -> 48 / 27, 2560 (160 / 128) 76 / 43 -> 98 / 36,
+//                                      3072 (192 / 128) 83 / 49 -> 98 / 41; GELU, F = 3072 (96 / 128) 63 / 49 -> 47 / 43
 // So packed weights take it up to 16 rows per expert.  Plain weights, whose rows it reads in pieces of 128 bytes against
-// the tile kernel's 512, take it only where the tiles leave compute units idle.  It addresses an expert's matrix (K rows of ldb
-// columns) with 32-bit byte offsets; the tile kernel has no such limit.
-bool decode_path(const moe_plan* p, int n_tiles_n, int64_t K, int64_t ldb, int n_cu) {
+// the tile kernel's 512, take it only where the tiles leave compute units idle -- half of them in layer0 with SwiGLU, whose
+// gate and up pieces lie apart.  It addresses an expert's matrix (K rows of ldb columns) with 32-bit byte offsets; the tile
+// kernel has no such limit.
+bool decode_path(const moe_plan* p, int n_tiles_n, int64_t K, int64_t ldb, bool pair, int n_cu) {
   const Shape& s = p->s;
   if (K * ldb * 2 >= 1ll << 32) return false;
   if ((int64_t)s.R > (int64_t)kDecodeRowsPerExpert * s.E) return false;
-  if (!p->weights_packed && (int64_t)(s.E < s.R ? s.E : s.R) * n_tiles_n >= n_cu) return false;
+  if (!p->weights_packed && expected_experts(s) * n_tiles_n * (pair ? 2 : 1) >= n_cu) return false;
   return p->layer1_order == 0 && !p->fuse_layers && p->n_prefetch <= 0 && !p->handoff_fences && !p->alias_experts &&
          !p->large_schedule && !p->n_cu_set;
 }
@@ -527,7 +516,8 @@ int forward_impl(moe_plan_t* p, const void* x, const int32_t* topk_ids, const fl
   if (order0 == 2 && large) order0 = 1;
   if (p->phases & 1) p->last_layer0_order = order0;
   else order0 = p->last_layer0_order;   // the schedules of the last index build are run again
-  const bool decode0 = decode_path(p, p->n_tiles_n0, s.H, s.F1, p->n_cu), decode1 = decode_path(p, p->n_tiles_n1, s.F, s.H, p->n_cu);
+  const bool decode0 = decode_path(p, p->n_tiles_n0, s.H, s.F1, s.act == MOE_ACT_SWIGLU, p->n_cu);
+  const bool decode1 = decode_path(p, p->n_tiles_n1, s.F, s.H, false, p->n_cu);
   // a forward beyond the last event slot is not recorded (and counted as dropped) rather than overwriting an earlier one
   hipEvent_t* ev = (p->profile && p->prof_steps < kProfSlots) ? p->ev[p->prof_steps] : nullptr;
   if (p->profile && !ev) p->prof_dropped++;
@@ -666,6 +656,7 @@ int forward_impl(moe_plan_t* p, const void* x, const int32_t* topk_ids, const fl
     d0.tile_m = s.R < p->tile_m ? s.R : p->tile_m;
     d0.T = s.T;
     d0.n_cu = p->n_cu;
+    d0.experts = expected_experts(s);
     d0.n_tiles = g.n_tiles;
     d0.tallest = ws.status + 6;
     d0.tile_expert = g.tile_expert;
@@ -689,7 +680,6 @@ int forward_impl(moe_plan_t* p, const void* x, const int32_t* topk_ids, const fl
     d0.N = s.F;
     d0.seg_ready = seg_ready;
     d0.ready_epoch = ready_epoch;
-    d0.k_split_log2 = decode_k_split(p, s.H, s.F, s.act == MOE_ACT_SWIGLU, d0.n_slots);
     d1.A = (const char*)ws.h;
     d1.lda_bytes = (uint32_t)s.F * 2;
     d1.B = (const char*)W2;
@@ -700,7 +690,6 @@ int forward_impl(moe_plan_t* p, const void* x, const int32_t* topk_ids, const fl
     d1.ldc = (uint32_t)s.H;
     d1.K = s.F;
     d1.N = s.H;
-    d1.k_split_log2 = decode_k_split(p, s.F, s.H, false, d1.n_slots);
   }
 
   if (one_launch) {

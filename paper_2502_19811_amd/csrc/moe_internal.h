@@ -21,7 +21,6 @@ constexpr int kTileK = 32;          // depth of one LDS stage
 constexpr int kStages = 4;          // LDS stages in flight
 constexpr int kCombineChunk = 256;  // tokens per unit of combine work
 constexpr int kDecodeRowsPerExpert = 16;   // rows per expert on average up to which the decode kernel is used
-constexpr int kDecodeSerialK = 1024;       // ... and the reduction length up to which it sums K in one part
 constexpr int kDefaultCus = 256;    // compute units a plan assumes before it has seen the device
 constexpr int kXcds = 8;            // XCDs of the device: workgroup i runs on XCD i % 8
 constexpr int kScheduleTileCap = 2048;  // M-tiles up to which the multi-workgroup schedule builder is used
@@ -146,8 +145,8 @@ struct FuseParams {
   int32_t publish_every;    // layer0 tiles between two publications of a workgroup
 };
 
-// The GroupGEMM of small batches (decode_gemm.hip): no schedule, a workgroup is one (tile of the table, 32 rows of it,
-// columns) unit found from its index.
+// The GroupGEMM of small batches (decode_gemm.hip): no schedule, wavefronts walk the (rows of a tile of the table, columns)
+// units with a fixed stride.
 struct DecodeParams {
   const char* A;            // x (layer0) or h (layer1), bf16
   uint32_t lda_bytes;
@@ -161,11 +160,10 @@ struct DecodeParams {
   int32_t K;                // reduction length
   int32_t N;                // columns of C
   int32_t F;                // expert hidden size (gate/up split of W1 columns)
-  int32_t k_split_log2;     // the 8 wavefronts of a workgroup split K into 1, 2, 4 or 8 parts
   int32_t n_slots;          // bound on the tiles of the table
+  float experts;            // experts that even routing gives rows
   int32_t tile_m;           // rows of the tallest tile there can be
   int32_t T;
-  int32_t n_groups;         // workgroups along the columns
   int32_t n_cu;
   const int32_t* n_tiles;   // device scalars: tiles in the table, rows of the tallest
   const int32_t* tallest;

@@ -1,6 +1,6 @@
 """The GroupGEMM of small batches against the oracle, at the sizes where it changes its shape: 8 / 9 and 16 / 17 tokens
-(8, 16 and 32 rows per unit), experts with more rows than a unit holds, reduction lengths around the one up to which K is
-summed in one part and such that the parts of K differ in length, and the first batch beyond it (tile kernel)."""
+(8, 16 and 32 rows per unit), experts with more rows than a unit holds, reduction lengths that the ring of operands does not
+divide, and the first batch beyond it (tile kernel)."""
 import numpy as np
 import pytest
 import torch
@@ -124,3 +124,35 @@ def test_an_expert_of_more_than_4_gib():
     moe.moe_plan_destroy(plan)
     a, b = H.error_metrics(H.bf16_to_np(out), ref.double().cpu().numpy())
     assert a <= H.REL_TOL and b <= H.REL_TOL, f"{a:.3e} {b:.3e}"
+
+
+def _bits(layer):
+    layer.forward()
+    run = layer.results()
+    assert run.status == 0
+    return layer.out.view(torch.int16).cpu().numpy().copy(), run
+
+
+@pytest.mark.parametrize("T,act", [(1, wl.ACT_SWIGLU), (7, wl.ACT_SWIGLU), (12, wl.ACT_GELU), (33, wl.ACT_SWIGLU)])
+def test_a_small_batch_has_the_bits_of_every_other_way_to_compute_it(T, act):
+    """Reductions longer than 1024: packed and plain weights, the options that bypass the kernel of small batches, and a larger
+    batch around the same tokens all sum in the same order."""
+    import gpu_harness as H
+    cfg = wl.MoEConfig("decode_bits", T=T, H=2304, F=1792, E=8, k=2, act=act, S=1, seed=670)
+    big = wl.scaled(cfg, T=300)
+    inp_big = wl.make_inputs(big, threads=4)
+    ids_big, w_big = orc.route_topk(inp_big.logits, cfg.k)
+    ids, w = ids_big[:T].copy(), w_big[:T].copy()
+    inp = wl.MoEInputs(cfg, inp_big.x[:T].copy(), inp_big.W1, inp_big.W2, inp_big.logits[:T], np.array([0, T], np.int32))
+    layer = H.GpuLayer(big, inp_big, ids_big, w_big)
+    want = _bits(layer)[0][:T]
+    layer.close()
+    for packed in (False, True):
+        for opts in ({}, {"n_cu": 256}, {"layer1_order": 1}, {"fuse_layers": 1}, {"large_schedule": 1}, {"handoff_fences": 1}):
+            print(f"decode bits T {T} act {act} packed {packed} {opts}", flush=True)
+            layer = H.GpuLayer(cfg, inp, ids, w, opts, packed=packed)
+            got, run = _bits(layer)
+            layer.close()
+            np.testing.assert_array_equal(got, want)
+    a, b = H.error_metrics(run.out, orc.moe_layer(inp.x, inp.W1, inp.W2, ids, w, act))
+    assert a <= H.REL_TOL and b <= H.REL_TOL
