@@ -16,7 +16,12 @@
 //    the up columns of its hidden units.  Plain weights are loaded as they lie (rows of K, whole 128-byte lines) and
 //    transposed through LDS with ds_read_b64_tr_b16; with SwiGLU the two wavefronts of a workgroup take gate and up and
 //    exchange halves at the end (in 64-byte pieces, both in one wavefront: 61 us against 47 on layer0 of 33 tokens, F = 1792).
-//  * There is no schedule: wavefronts walk the units with a fixed stride.
+//  * There is no schedule: wavefronts walk the units with a fixed stride.  An expert with more rows than a unit holds is several
+//    units per columns, next to each other on one XCD, so that its weights come from HBM once.  (With the parts of all experts
+//    one after the other they came once per part: 128 tokens of 64 experts, popularity falling as rank^-1.2, 450 / 247 us per
+//    layer0 / layer1 launch, now 390 / 200; the tile kernel 335 / 182.  256 tokens of 64 experts of F = 1408 116 / 131 ->
+//    96 / 52, tile kernel 95 / 51.)  The row blocks and rows of A that a unit does not have cost nothing: no MFMA, loads
+//    beyond the end of the buffer.
 // us for both layers, tile kernel -> K in 8 parts -> this one: Mixtral-shaped packed, 1 token 259 -> 130 -> 133 (704 MB: 5.3
 // TB/s), 16 tokens 530 -> 485 -> 484 (2.8 GB: 5.8 TB/s; a copy of 1 GiB moves 4.4 TB/s, half of it writes); 64 experts of
 // F = 2560, 48 tokens 634 -> 615 -> 623; plain, 8 experts of F = 1792, 33 tokens 102 -> 82 -> 74.
@@ -25,14 +30,18 @@
 namespace moe {
 
 constexpr int kDecodeWaves = 2;                    // of a workgroup
+constexpr int kUnitChunk = 2;                      // consecutive units on one XCD
+constexpr uint32_t kRowsEnd = 1u << 31;            // no row of A has an offset of this or more; past it a load returns zeros
+constexpr int kDecodeTileCap = 384;                // tiles of a batch the kernel is used for: at most 4096 / 64 full ones and 256 others
+static_assert(kDecodeTileCap % 64 == 0 && kDecodeTileCap >= kDecodeRowsPerExpert * kMaxExperts / 64 + kMaxExperts, "tiles of the largest batch");
 constexpr int kStageBytes = kTileK * kTileN * 2;   // packed weights: one K step of one column tile
 constexpr int kPlainPitch = 144;                   // bytes between rows of K in the transposing buffer (64 columns + padding)
 constexpr int kStepK = 64;                         // K of one ring slot: a whole 128-byte line of every row of A
 
 // The memory from ptr on (the same in every lane) as a buffer: loads then take one 32-bit offset per lane and one scalar
 // offset, and no 64-bit address per load sits in vector registers.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer(const char* ptr) {
-  return __builtin_amdgcn_make_buffer_rsrc((void*)uniform(ptr), 0, -1, 0x00020000);
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer(const char* ptr, uint32_t bytes = 0xffffffff) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)uniform(ptr), 0, bytes, 0x00020000);
 }
 
 // NB: 16-column blocks of weights of a wavefront (SwiGLU: half of them gate, half up columns of the same hidden units);
@@ -53,10 +62,11 @@ __global__ __launch_bounds__(kDecodeWaves * 64) __attribute__((amdgpu_waves_per_
   static_assert(!kAhead || U % 2 == 0, "the fragments of A alternate between two sets of registers");
   __shared__ __attribute__((aligned(16))) f32x4 swap_lds[kTwoWaves ? 2 : 1][2][kTwoWaves ? RR * 2 : 1][kTwoWaves ? 64 : 1];
   __shared__ __attribute__((aligned(128))) char operands[kDecodeWaves * kWaveBytes];
+  __shared__ int32_t unit0[kDecodeWaves][kDecodeTileCap];
   __shared__ int ok_lds;
 
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int n_tiles = *p.n_tiles;
+  const int n_tiles = min(*p.n_tiles, kDecodeTileCap);
   if (MODE != MODE_L1 && p.seg_ready != nullptr) {
     // a small batch waits for every segment its tiles need before it starts on the first
     if (tid == 0) ok_lds = 1;
@@ -71,43 +81,58 @@ __global__ __launch_bounds__(kDecodeWaves * 64) __attribute__((amdgpu_waves_per_
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "");
   }
 
-  // Units: (row part, tile, columns), the parts slowest and the columns fastest.  Wavefronts take them in turn.
+  // Units: (tile, columns, row part), the parts fastest.  unit0[i]: the units of the tiles before tile i.
   const int nk = p.K / kStepK;
   const int n_groups = p.N / (OB * 16);
-  const int n_parts = (*p.tallest + ROWS - 1) / ROWS;
-  const int per_part = n_tiles * n_groups, n_units = per_part * n_parts;
-  const int stride = kTwoWaves ? gridDim.x : gridDim.x * kDecodeWaves;
+  int n_units = 0;
+#pragma unroll 1
+  for (int i0 = 0; i0 < n_tiles; i0 += 64) {
+    const int rows = i0 + lane < n_tiles ? p.tile_rows[i0 + lane] : 0;
+    int incl = (rows + ROWS - 1) / ROWS * n_groups;
+    const int mine = incl;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int o = __shfl_up(incl, d);
+      if (lane >= d) incl += o;
+    }
+    unit0[w][i0 + lane] = n_units + incl - mine;
+    n_units += uniform(__shfl(incl, 63));
+  }
+  // Chunks of kUnitChunk consecutive units go to the XCDs in turn, so that the parts of an expert's rows read its weights at the
+  // same time through one L2; inside an XCD its wavefronts (SwiGLU of plain weights: workgroups) take the units in turn.
+  const int xcd = blockIdx.x % kXcds;
+  const int stride = (gridDim.x / kXcds) * (kTwoWaves ? 1 : kDecodeWaves);
   struct Unit {
-    int index, cg, row0, nrows, expert;
+    int turn, cg, row0, nrows, expert;   // nrows = 0: there is no further unit
     uint32_t a_off[RB];          // per lane: rows 8 g + lane / 8 of A, 16 bytes at lane % 8 of a line
   };
-  auto find = [&](int index) {   // the first unit with rows from this one on
+  auto find = [&](int turn) {
     Unit t;
+    t.turn = turn;
     t.nrows = 0;
-    for (; index < n_units; index += stride) {
-      const int sub = index / per_part, in_part = index % per_part;
-      const int slot = in_part / n_groups;
-      const int rows = p.tile_rows[slot] - sub * ROWS;
-      if (rows <= 0) continue;
-      t.cg = in_part % n_groups;
-      t.row0 = p.tile_row0[slot] + sub * ROWS;
-      t.nrows = rows < ROWS ? rows : ROWS;
+    const int index = (turn / kUnitChunk * kXcds + xcd) * kUnitChunk + turn % kUnitChunk;
+    if (index < n_units) {
+      int slot = -1;   // the last tile whose units begin at this one or before (every tile has some)
+      for (int i0 = 0; i0 < n_tiles; i0 += 64) slot += __popcll(__ballot(i0 + lane < n_tiles && unit0[w][i0 + lane] <= index));
+      slot = uniform(slot);
+      const int in_tile = index - uniform(unit0[w][slot]), rows = p.tile_rows[slot], parts = (rows + ROWS - 1) / ROWS;
+      const int part = in_tile % parts;
+      t.cg = in_tile / parts;
+      t.row0 = p.tile_row0[slot] + part * ROWS;
+      t.nrows = min(rows - part * ROWS, ROWS);
       t.expert = p.tile_expert[slot];
-      break;
-    }
-    t.index = index;
-    if (t.nrows > 0) {
 #pragma unroll
       for (int g = 0; g < RB; g++) {
-        const int r = t.row0 + min(g * 8 + (lane >> 3), t.nrows - 1);   // rows past the end: the last row again
+        const int in_unit = g * 8 + (lane >> 3), r = t.row0 + min(in_unit, t.nrows - 1);
         t.a_off[g] = (uint32_t)(MODE != MODE_L1 ? p.a_rows[r] : r) * p.lda_bytes + (lane & 7) * 16;
+        if (in_unit >= t.nrows) t.a_off[g] = kRowsEnd;
       }
     }
     return t;
   };
 
   u32x4 areg[U][RB], breg[U][NBL];
-  const __amdgpu_buffer_rsrc_t a_buf = buffer(p.A);
+  const __amdgpu_buffer_rsrc_t a_buf = buffer(p.A, kRowsEnd);
   __amdgpu_buffer_rsrc_t b_buf;
   uint32_t a_off[RB];
   const int g16 = lane >> 4, j16 = lane & 15;
@@ -174,9 +199,10 @@ __global__ __launch_bounds__(kDecodeWaves * 64) __attribute__((amdgpu_waves_per_
       for (int r = 0; r < RR; r++)
         af[set][kk][r] = *(const bf16x8 __attribute__((address_space(3)))*)(uintptr_t)(a_rd + r * 2048 + (((kk * 4 + g16) ^ s) << 4));
   };
-  auto multiply = [&](int u) {
+  auto multiply = [&](int u, int rows_now) {
     if (kAhead) through_lds((u + 1) % U, (u + 1) & 1);
     else through_lds(u, 0);
+    bf16x8 b[2][NB];
 #pragma unroll
     for (int kk = 0; kk < 2; kk++) {
       if (!PK) {   // 32 rows of K
@@ -186,29 +212,35 @@ __global__ __launch_bounds__(kDecodeWaves * 64) __attribute__((amdgpu_waves_per_
       }
 #pragma unroll
       for (int nb = 0; nb < NB; nb++) {
-        bf16x8 b;
         if (PK) {
-          b = __builtin_bit_cast(bf16x8, breg[u][kk * NB + nb]);
+          b[kk][nb] = __builtin_bit_cast(bf16x8, breg[u][kk * NB + nb]);
         } else {
           const uint32_t at = tr_rd + nb * 32;
-          b = lds_read_b(at, at + 4 * kPlainPitch);
+          b[kk][nb] = lds_read_b(at, at + 4 * kPlainPitch);
         }
-#pragma unroll
-        for (int r = 0; r < RR; r++)
-          acc[r][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, af[kAhead ? u & 1 : 0][kk][r], acc[r][nb], 0, 0, 0);
       }
+    }
+#pragma unroll
+    for (int r = 0; r < RR; r++) {
+      if (r > 0 && rows_now <= 16 * r) break;
+#pragma unroll
+      for (int kk = 0; kk < 2; kk++)
+#pragma unroll
+        for (int nb = 0; nb < NB; nb++)
+          acc[r][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[kk][nb], af[kAhead ? u & 1 : 0][kk][r], acc[r][nb], 0, 0, 0);
     }
   };
 
-  Unit cur = find(kTwoWaves ? blockIdx.x : blockIdx.x * kDecodeWaves + w);
+  const int first = kTwoWaves ? blockIdx.x / kXcds : blockIdx.x / kXcds * kDecodeWaves + w;
+  Unit cur = find(first);
+  if (cur.nrows > 0) start(cur);
   int turn = 0;
-  if (cur.index < n_units) start(cur);
-  while (cur.index < n_units) {
+  while (cur.nrows > 0) {
 #pragma unroll
     for (int r = 0; r < RR; r++)
 #pragma unroll
       for (int nb = 0; nb < NB; nb++) acc[r][nb] = (f32x4){0};
-    const Unit next = find(cur.index + stride);   // asked for now: its table entries are back when they are needed
+    const Unit next = find(cur.turn + stride);   // asked for now: its table entries are back when they are needed
     if (kAhead) through_lds(0, 0);
     int st = 0;
 #pragma unroll 1
@@ -216,14 +248,14 @@ __global__ __launch_bounds__(kDecodeWaves * 64) __attribute__((amdgpu_waves_per_
 #pragma unroll
       for (int u = 0; u < U; u++) {
         __builtin_amdgcn_sched_barrier(0);   // a step's loads reuse the registers just consumed
-        if (st + u < nk) multiply(u);
+        if (st + u < nk) multiply(u, cur.nrows);
         __builtin_amdgcn_sched_barrier(0);
         load(u, min(st + u + U, nk - 1));
       }
       st += U;
     } while (st < nk);
     // the next unit's first loads are under way while this one is written
-    if (next.index < n_units) start(next);
+    if (next.nrows > 0) start(next);
 
     // SwiGLU of plain weights: wavefront 0 gives the gate columns of the upper blocks away and gets the up columns of the
     // lower ones, wavefront 1 the reverse.
@@ -266,10 +298,13 @@ __global__ __launch_bounds__(kDecodeWaves * 64) __attribute__((amdgpu_waves_per_
 template <int MODE, bool PK, int NB, int RB, int U, int EU>
 static hipError_t launch_decode(const DecodeParams& p, hipStream_t st) {
   constexpr bool kTwoWaves = MODE == MODE_L0_SWIGLU && !PK, kInWave = MODE == MODE_L0_SWIGLU && PK;
-  const int64_t units = (int64_t)p.n_slots * (p.N / (NB * 16 / (kInWave ? 2 : 1))) * ((p.tile_m + 8 * RB - 1) / (8 * RB));
-  const int64_t wgs = kTwoWaves ? units : (units + 1) / 2, resident = (int64_t)p.n_cu * (4 * EU / kDecodeWaves);
-  const int64_t rounds = (wgs + resident - 1) / resident;   // all workgroups get as many units, or one less
-  hipLaunchKernelGGL((k_decode_gemm<MODE, PK, NB, RB, U, EU>), dim3((unsigned)((wgs + rounds - 1) / rounds)), dim3(kDecodeWaves * 64), 0, st, p);
+  constexpr int kUnitWaves = kTwoWaves ? kDecodeWaves : 1;   // wavefronts per unit
+  const int64_t n_groups = p.N / (NB * 16 / (kInWave ? 2 : 1));
+  // no more wavefronts than can be resident, or than there can be units (an expert's last part is not full)
+  const int64_t most = ((int64_t)p.R / (8 * RB) + p.n_slots) * n_groups, resident = (int64_t)p.n_cu * 4 * EU / kUnitWaves;
+  const int64_t per_xcd = ((most < resident ? most : resident) + kXcds * kUnitChunk - 1) / (kXcds * kUnitChunk) * kUnitChunk;
+  const unsigned grid = (unsigned)(per_xcd * kUnitWaves / kDecodeWaves) * kXcds;
+  hipLaunchKernelGGL((k_decode_gemm<MODE, PK, NB, RB, U, EU>), dim3(grid), dim3(kDecodeWaves * 64), 0, st, p);
   return hipGetLastError();
 }
 
@@ -277,7 +312,8 @@ static hipError_t launch_decode(const DecodeParams& p, hipStream_t st) {
 //   packed, up to 8 rows    SwiGLU 4 steps x 4 wavefronts 86, 6 x 2 87, 3 x 4 87; layer1 (512 wavefronts in all for one token) 16 columns
 //                           each, 8 x 2 44, 4 x 4 52; 32 columns 4 x 4 66   (1 token, Mixtral-shaped)
 //   packed, 9 to 16 rows    4 x 4 309 / 159, 2 x 4 319 / 159 (16 tokens)
-//   packed, more            SwiGLU 3 x 3 402, 2 x 4 411; layer1 32 columns 2 x 4 219, 6 x 2 222 (48 tokens, 64 experts of F = 2560)
+//   packed, more            SwiGLU 3 x 3 404, 2 x 4 395, with skewed routing 390 / 414; layer1 32 columns 2 x 4 213, 3 x 3 208, 4 x 2 206, 16 columns 3 x 4 225 (48 tokens,
+//                           64 experts of F = 2560; skewed: 128 tokens, popularity falling as rank^-1.2, layer1 210 / 209 / 208 / 259)
 //   plain, SwiGLU           3 x 2 25, 2 x 2 33 (4 tokens); 4 x 1 47, 3 x 2 50 (33 tokens, 8 experts of F = 1792)
 // Plain weights without SwiGLU: 64 columns, whole lines (12 tokens, F = 2560, weights from HBM: layer1 33 us against 46 in
 // 64-byte pieces), but 32 where the wavefronts of 64 would leave compute units idle (one token, 120 wavefronts of 64 columns: layer1
@@ -287,7 +323,7 @@ static hipError_t launch_decode_depth(const DecodeParams& p, int packed, hipStre
   constexpr bool kPair = MODE == MODE_L0_SWIGLU;
   if (packed) {
     if constexpr (RB == 1) return launch_decode<MODE, true, (kPair ? 2 : 1), 1, (kPair ? 4 : 8), (kPair ? 4 : 2)>(p, st);
-    else if constexpr (RB == 2) return launch_decode<MODE, true, (kPair ? 2 : 1), 2, 4, 4>(p, st);
+    else if constexpr (RB == 2) return launch_decode<MODE, true, (MODE == MODE_L1 ? 1 : 2), 2, 4, 4>(p, st);
     else return launch_decode<MODE, true, 2, 4, (kPair ? 3 : 2), (kPair ? 3 : 4)>(p, st);
   }
   if constexpr (!kPair) {

@@ -150,10 +150,8 @@ __global__ __launch_bounds__(256) void k_index_scatter(IndexParams p) {
   __shared__ int32_t off[kMaxExperts];     // first row of each expert
   __shared__ int32_t before[kMaxExperts];  // rows of each expert owned by earlier workgroups
   __shared__ int32_t tbase[kMaxExperts];   // first M-tile of each expert (workgroup 0)
-  __shared__ int32_t tallest;              // rows of the tallest M-tile (workgroup 0)
   const int E = p.s.E, R = p.s.R, k = p.s.k;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (threadIdx.x == 0) tallest = 0;
   int my_cnt = 0;
   {
     const int e = threadIdx.x;   // E <= 256 = threads
@@ -189,7 +187,6 @@ __global__ __launch_bounds__(256) void k_index_scatter(IndexParams p) {
     const int e = threadIdx.x;
     const int tail = e < E ? tail_height(my_cnt, p.tile_m) : 0;
     const int my_tiles = e < E ? my_cnt / p.tile_m + (tail > 0) : 0;
-    if (my_tiles > 0) atomicMax(&tallest, min(my_cnt, p.tile_m));   // (exclusive_scan_256 has barriers on both sides of it)
     const int n_tiles = exclusive_scan_256(tbase, my_tiles);
     const int waves = wave == 0 ? waves_now(p, lane) : 0;
     if (threadIdx.x == 0) {
@@ -199,7 +196,6 @@ __global__ __launch_bounds__(256) void k_index_scatter(IndexParams p) {
       p.ws.status[2] = n_tiles * p.n_tiles_n0;
       p.ws.status[3] = n_tiles * p.n_tiles_n1;
       p.ws.status[4] = 0;
-      p.ws.status[6] = tallest;
       p.ws.offsets[E] = total_rows;
     }
     if (threadIdx.x < 2 * kXcds) p.ws.status[8 + threadIdx.x] = 0;   // queue heads of both layers
@@ -861,14 +857,13 @@ __global__ __launch_bounds__(1024) void k_index_small(IndexParams p, int schedul
   __syncthreads();
   // offsets and first tiles of the experts: four experts per lane of the first wavefront
   if (wave == 0) {
-    int c[4], t[4], rows = 0, tiles = 0, tallest = 0;
+    int c[4], t[4], rows = 0, tiles = 0;
 #pragma unroll
     for (int i = 0; i < 4; i++) {
       c[i] = cnt[lane * 4 + i];
       t[i] = c[i] / p.tile_m + (c[i] % p.tile_m > 0);
       rows += c[i];
       tiles += t[i];
-      tallest = max(tallest, min(c[i], p.tile_m));
     }
     int rows_incl = rows, tiles_incl = tiles;
 #pragma unroll
@@ -878,7 +873,6 @@ __global__ __launch_bounds__(1024) void k_index_small(IndexParams p, int schedul
         rows_incl += ro;
         tiles_incl += to;
       }
-      tallest = max(tallest, __shfl_xor(tallest, d));
     }
     int ro = rows_incl - rows, to = tiles_incl - tiles;
 #pragma unroll
@@ -895,7 +889,6 @@ __global__ __launch_bounds__(1024) void k_index_small(IndexParams p, int schedul
       p.ws.status[2] = tiles_incl * p.n_tiles_n0;
       p.ws.status[3] = tiles_incl * p.n_tiles_n1;
       p.ws.status[4] = 0;
-      p.ws.status[6] = tallest;
       p.ws.offsets[E] = rows_incl;
     }
   } else if (wave == 1) {

@@ -231,11 +231,11 @@ int default_layer0_waves(const Shape& s, int ingest_gbps) {
 //                                      3072 (192 / 128) 83 / 49 -> 98 / 41; GELU, F = 3072 (96 / 128) 63 / 49 -> 47 / 43
 // So packed weights take it up to 16 rows per expert.  Plain weights, whose rows it reads in pieces of 128 bytes against
 // the tile kernel's 512, take it only where the tiles leave compute units idle -- half of them in layer0 with SwiGLU, whose
-// gate and up pieces lie apart.  It addresses an expert's matrix (K rows of ldb columns) with 32-bit byte offsets; the tile
-// kernel has no such limit.
+// gate and up pieces lie apart.  It addresses an expert's matrix (K rows of ldb columns) with 32-bit byte offsets and the rows of A
+// with 31-bit ones; the tile kernel has no such limits.
 bool decode_path(const moe_plan* p, int n_tiles_n, int64_t K, int64_t ldb, bool pair, int n_cu) {
   const Shape& s = p->s;
-  if (K * ldb * 2 >= 1ll << 32) return false;
+  if (K * ldb * 2 >= 1ll << 32 || (int64_t)s.T * s.H * 2 > 1ll << 31 || (int64_t)s.R * s.F * 2 > 1ll << 31) return false;
   if ((int64_t)s.R > (int64_t)kDecodeRowsPerExpert * s.E) return false;
   if (!p->weights_packed && expected_experts(s) * n_tiles_n * (pair ? 2 : 1) >= n_cu) return false;
   return p->layer1_order == 0 && !p->fuse_layers && p->n_prefetch <= 0 && !p->handoff_fences && !p->alias_experts &&
@@ -653,12 +653,11 @@ int forward_impl(moe_plan_t* p, const void* x, const int32_t* topk_ids, const fl
   if (decode0 || decode1) {
     memset(&d0, 0, sizeof(d0));
     d0.n_slots = decode_slots(s, p->tile_m, p->max_tiles);
-    d0.tile_m = s.R < p->tile_m ? s.R : p->tile_m;
     d0.T = s.T;
+    d0.R = s.R;
     d0.n_cu = p->n_cu;
     d0.experts = expected_experts(s);
     d0.n_tiles = g.n_tiles;
-    d0.tallest = ws.status + 6;
     d0.tile_expert = g.tile_expert;
     d0.tile_row0 = g.tile_row0;
     d0.tile_rows = g.tile_rows;

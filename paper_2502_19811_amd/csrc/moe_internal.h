@@ -38,7 +38,7 @@ struct ItemRec {
 struct Workspace {
   int32_t* status;        // [64]  0: device status word, 1: n_tiles, 2: items of layer0, 3: items of layer1,
                           //       4: combine unit counter, 5: serial number of the last forward that saw an expert
-                          //       id out of range; 6: rows of the tallest tile; 7: waves of the layer0 schedule; per XCD: 8..15 layer0 queue heads, 16..23 layer1 queue
+                          //       id out of range; 7: waves of the layer0 schedule; per XCD: 8..15 layer0 queue heads, 16..23 layer1 queue
                           //       heads, 24..31 layer0 queue lengths, 32..39 layer1 queue lengths, 40..47 layer1
                           //       queue bases, 48..55 layer0 queue bases (only with contiguous layer0 queues;
                           //       otherwise layer0's queue x is list positions x, x+8, ...)
@@ -162,11 +162,9 @@ struct DecodeParams {
   int32_t F;                // expert hidden size (gate/up split of W1 columns)
   int32_t n_slots;          // bound on the tiles of the table
   float experts;            // experts that even routing gives rows
-  int32_t tile_m;           // rows of the tallest tile there can be
-  int32_t T;
+  int32_t T, R;
   int32_t n_cu;
-  const int32_t* n_tiles;   // device scalars: tiles in the table, rows of the tallest
-  const int32_t* tallest;
+  const int32_t* n_tiles;   // device scalar: tiles in the table
   const int32_t* tile_expert;
   const int32_t* tile_row0;
   const int32_t* tile_rows;
