@@ -16,6 +16,7 @@
 //    the up columns of its hidden units.  Plain weights are loaded as they lie (rows of K, whole 128-byte lines) and
 //    transposed through LDS with ds_read_b64_tr_b16; with SwiGLU the two wavefronts of a workgroup take gate and up and
 //    exchange halves at the end (in 64-byte pieces, both in one wavefront: 61 us against 47 on layer0 of 33 tokens, F = 1792).
+//  * A unit of layer0 waits for the source segment of its tile alone; where that is missing for good the others are computed.
 //  * There is no schedule: wavefronts walk the units with a fixed stride.  An expert with more rows than a unit holds is several
 //    units per columns, next to each other on one XCD, so that its weights come from HBM once.  (With the parts of all experts
 //    one after the other they came once per part: 128 tokens of 64 experts, popularity falling as rank^-1.2, 450 / 247 us per
@@ -63,23 +64,20 @@ __global__ __launch_bounds__(kDecodeWaves * 64) __attribute__((amdgpu_waves_per_
   __shared__ __attribute__((aligned(16))) f32x4 swap_lds[kTwoWaves ? 2 : 1][2][kTwoWaves ? RR * 2 : 1][kTwoWaves ? 64 : 1];
   __shared__ __attribute__((aligned(128))) char operands[kDecodeWaves * kWaveBytes];
   __shared__ int32_t unit0[kDecodeWaves][kDecodeTileCap];
-  __shared__ int ok_lds;
+  __shared__ int given_up[2][2];   // [turn][wavefront]: no rows for this unit
 
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n_tiles = min(*p.n_tiles, kDecodeTileCap);
-  if (MODE != MODE_L1 && p.seg_ready != nullptr) {
-    // a small batch waits for every segment its tiles need before it starts on the first
-    if (tid == 0) ok_lds = 1;
-    __syncthreads();
-    for (int i = tid; i < n_tiles; i += kDecodeWaves * 64)
-      if (!spin_until_ge(&p.seg_ready[p.tile_ready[i]], p.ready_epoch, p.spin_limit)) ok_lds = 0;
-    __syncthreads();
-    if (!ok_lds) {
-      if (tid == 0) atomicExch(p.status, (int)MOE_ERR_TIMEOUT);
-      return;
-    }
+  // Source segments that have arrived.  A unit waits for its tile's segment only, and starts early where that is there.
+  uint64_t there = ~0ull;
+  bool patient = true;   // false once a wait has run out: what is missing then is not waited for again
+  auto look = [&]() {
+    const bool up = lane < p.n_segments && __hip_atomic_load(&p.seg_ready[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) >= p.ready_epoch;
+    there = __ballot(up);
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "");
-  }
+  };
+  const bool flagged = MODE != MODE_L1 && p.seg_ready != nullptr;
+  if (flagged) look();
 
   // Units: (tile, columns, row part), the parts fastest.  unit0[i]: the units of the tiles before tile i.
   const int nk = p.K / kStepK;
@@ -103,13 +101,13 @@ __global__ __launch_bounds__(kDecodeWaves * 64) __attribute__((amdgpu_waves_per_
   const int xcd = blockIdx.x % kXcds;
   const int stride = (gridDim.x / kXcds) * (kTwoWaves ? 1 : kDecodeWaves);
   struct Unit {
-    int turn, cg, row0, nrows, expert;   // nrows = 0: there is no further unit
+    int turn, cg, row0, nrows, expert, seg;   // nrows = 0: there is no further unit
     uint32_t a_off[RB];          // per lane: rows 8 g + lane / 8 of A, 16 bytes at lane % 8 of a line
   };
   auto find = [&](int turn) {
     Unit t;
     t.turn = turn;
-    t.nrows = 0;
+    t.nrows = t.seg = 0;
     const int index = (turn / kUnitChunk * kXcds + xcd) * kUnitChunk + turn % kUnitChunk;
     if (index < n_units) {
       int slot = -1;   // the last tile whose units begin at this one or before (every tile has some)
@@ -121,6 +119,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64) __attribute__((amdgpu_waves_per_
       t.row0 = p.tile_row0[slot] + part * ROWS;
       t.nrows = min(rows - part * ROWS, ROWS);
       t.expert = p.tile_expert[slot];
+      if (flagged) t.seg = p.tile_ready[slot];
 #pragma unroll
       for (int g = 0; g < RB; g++) {
         const int in_unit = g * 8 + (lane >> 3), r = t.row0 + min(in_unit, t.nrows - 1);
@@ -231,9 +230,24 @@ __global__ __launch_bounds__(kDecodeWaves * 64) __attribute__((amdgpu_waves_per_
     }
   };
 
+  auto arrived = [&](const Unit& t) { return MODE == MODE_L1 || ((there >> t.seg) & 1); };
+  // waits for the rows of a unit and starts it; false: they have not come
+  auto start_when_there = [&](const Unit& t) {
+    if (!arrived(t)) {
+      if (patient && !spin_until_ge(&p.seg_ready[t.seg], p.ready_epoch, p.spin_limit)) {
+        patient = false;
+        if (lane == 0) atomicExch(p.status, (int)MOE_ERR_TIMEOUT);
+      }
+      look();
+      if (!arrived(t)) return false;
+    }
+    start(t);
+    return true;
+  };
+
   const int first = kTwoWaves ? blockIdx.x / kXcds : blockIdx.x / kXcds * kDecodeWaves + w;
   Unit cur = find(first);
-  if (cur.nrows > 0) start(cur);
+  bool started = cur.nrows > 0 && start_when_there(cur);
   int turn = 0;
   while (cur.nrows > 0) {
 #pragma unroll
@@ -241,21 +255,24 @@ __global__ __launch_bounds__(kDecodeWaves * 64) __attribute__((amdgpu_waves_per_
 #pragma unroll
       for (int nb = 0; nb < NB; nb++) acc[r][nb] = (f32x4){0};
     const Unit next = find(cur.turn + stride);   // asked for now: its table entries are back when they are needed
-    if (kAhead) through_lds(0, 0);
-    int st = 0;
+    if (started) {
+      if (kAhead) through_lds(0, 0);
+      int st = 0;
 #pragma unroll 1
-    do {
+      do {
 #pragma unroll
-      for (int u = 0; u < U; u++) {
-        __builtin_amdgcn_sched_barrier(0);   // a step's loads reuse the registers just consumed
-        if (st + u < nk) multiply(u, cur.nrows);
-        __builtin_amdgcn_sched_barrier(0);
-        load(u, min(st + u + U, nk - 1));
-      }
-      st += U;
-    } while (st < nk);
+        for (int u = 0; u < U; u++) {
+          __builtin_amdgcn_sched_barrier(0);   // a step's loads reuse the registers just consumed
+          if (st + u < nk) multiply(u, cur.nrows);
+          __builtin_amdgcn_sched_barrier(0);
+          load(u, min(st + u + U, nk - 1));
+        }
+        st += U;
+      } while (st < nk);
+    }
     // the next unit's first loads are under way while this one is written
-    if (next.nrows > 0) start(next);
+    bool next_started = next.nrows > 0 && arrived(next);
+    if (next_started) start(next);
 
     // SwiGLU of plain weights: wavefront 0 gives the gate columns of the upper blocks away and gets the up columns of the
     // lower ones, wavefront 1 the reverse.
@@ -264,7 +281,9 @@ __global__ __launch_bounds__(kDecodeWaves * 64) __attribute__((amdgpu_waves_per_
       for (int r = 0; r < RR; r++)
 #pragma unroll
         for (int i = 0; i < 2; i++) swap_lds[turn][w][r * 2 + i][lane] = w == 0 ? acc[r][2 + i] : acc[r][i];
+      given_up[turn][w] = !started;
       __syncthreads();   // (this turn's buffer is written again two units on, behind the next unit's barrier)
+      started = started && !given_up[turn][w ^ 1];
     }
     // a lane holds, of row lane % 16 of a block, the 4 columns from 4 (lane / 16) on
 #pragma unroll
@@ -287,11 +306,13 @@ __global__ __launch_bounds__(kDecodeWaves * 64) __attribute__((amdgpu_waves_per_
         }
         const bf16x2 lo = {(__bf16)v[0], (__bf16)v[1]}, hi = {(__bf16)v[2], (__bf16)v[3]};
         const u32x2 pk = {__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
-        if (row < cur.nrows) *(u32x2*)(dst + nb * 16) = pk;
+        if (started && row < cur.nrows) *(u32x2*)(dst + nb * 16) = pk;
       }
     }
+    if (next.nrows > 0 && !next_started) next_started = start_when_there(next);
     turn ^= 1;
     cur = next;
+    started = next_started;
   }
 }
 
@@ -311,7 +332,7 @@ static hipError_t launch_decode(const DecodeParams& p, hipStream_t st) {
 // Columns of a wavefront, ring depth and wavefronts per SIMD by what fits the registers and measured best, us per launch:
 //   packed, up to 8 rows    SwiGLU 4 steps x 4 wavefronts 86, 6 x 2 87, 3 x 4 87; layer1 (512 wavefronts in all for one token) 16 columns
 //                           each, 8 x 2 44, 4 x 4 52; 32 columns 4 x 4 66   (1 token, Mixtral-shaped)
-//   packed, 9 to 16 rows    4 x 4 309 / 159, 2 x 4 319 / 159 (16 tokens)
+//   packed, 9 to 16 rows    4 x 3 / 4 x 4, 2 x 4 3 % and 3 x 4 0.4 % longer (16 tokens, Mixtral-shaped)
 //   packed, more            SwiGLU 3 x 3 404, 2 x 4 395, with skewed routing 390 / 414; layer1 32 columns 2 x 4 213, 3 x 3 208, 4 x 2 206, 16 columns 3 x 4 225 (48 tokens,
 //                           64 experts of F = 2560; skewed: 128 tokens, popularity falling as rank^-1.2, layer1 210 / 209 / 208 / 259)
 //   plain, SwiGLU           3 x 2 25, 2 x 2 33 (4 tokens); 4 x 1 47, 3 x 2 50 (33 tokens, 8 experts of F = 1792)
@@ -323,7 +344,7 @@ static hipError_t launch_decode_depth(const DecodeParams& p, int packed, hipStre
   constexpr bool kPair = MODE == MODE_L0_SWIGLU;
   if (packed) {
     if constexpr (RB == 1) return launch_decode<MODE, true, (kPair ? 2 : 1), 1, (kPair ? 4 : 8), (kPair ? 4 : 2)>(p, st);
-    else if constexpr (RB == 2) return launch_decode<MODE, true, (MODE == MODE_L1 ? 1 : 2), 2, 4, 4>(p, st);
+    else if constexpr (RB == 2) return launch_decode<MODE, true, (MODE == MODE_L1 ? 1 : 2), 2, 4, (MODE == MODE_L1 ? 4 : 3)>(p, st);
     else return launch_decode<MODE, true, 2, 4, (kPair ? 3 : 2), (kPair ? 3 : 4)>(p, st);
   }
   if constexpr (!kPair) {

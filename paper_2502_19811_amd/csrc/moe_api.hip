@@ -679,6 +679,7 @@ int forward_impl(moe_plan_t* p, const void* x, const int32_t* topk_ids, const fl
     d0.N = s.F;
     d0.seg_ready = seg_ready;
     d0.ready_epoch = ready_epoch;
+    d0.n_segments = s.S;
     d1.A = (const char*)ws.h;
     d1.lda_bytes = (uint32_t)s.F * 2;
     d1.B = (const char*)W2;

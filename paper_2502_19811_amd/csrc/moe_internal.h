@@ -171,6 +171,7 @@ struct DecodeParams {
   const int32_t* tile_ready;
   const uint32_t* seg_ready;
   uint32_t ready_epoch;
+  int32_t n_segments;
   uint32_t spin_limit;
   int32_t* status;
 };

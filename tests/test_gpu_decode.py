@@ -179,3 +179,55 @@ def test_every_row_part_of_crowded_experts(T, E, k, act, tile_m):
         np.testing.assert_array_equal(bits[0], bits[1])
     a, b = H.error_metrics(run.out, orc.moe_layer(inp.x, inp.W1, inp.W2, ids, w, act))
     assert a <= H.REL_TOL and b <= H.REL_TOL
+
+
+@pytest.mark.parametrize("packed", [False, True], ids=["plain", "packed"])
+def test_a_missing_segment_costs_its_own_rows_only(packed):
+    """Tokens of the first segment use the first experts, tokens of the second one the others; the second never arrives."""
+    import gpu_harness as H
+    cfg = wl.MoEConfig("decode_half", T=20, H=512, F=1152, E=8, k=2, act=wl.ACT_SWIGLU, S=2, seed=651)
+    inp = wl.make_inputs(cfg, threads=4)
+    half = int(inp.seg_offsets[1])
+    rng = np.random.default_rng(651)
+    ids = np.stack([rng.permutation(4)[:2] + (0 if t < half else 4) for t in range(cfg.T)]).astype(np.int32)
+    w = rng.uniform(0.1, 1.0, (cfg.T, 2)).astype(np.float32)
+    layer = H.GpuLayer(cfg, inp, ids, w, {"spin_limit": 200}, packed=packed)
+    layer.forward()
+    want = layer.results().out
+    layer.out.fill_(7.0)
+    print(f"decode, second of two segments missing, packed {packed}", flush=True)
+    layer.ws.zero_()
+    layer.forward(seg_ready=torch.tensor([3, 2], dtype=torch.int32, device="cuda"), epoch=3)
+    run = layer.results()
+    layer.close()
+    assert run.status == -6
+    np.testing.assert_array_equal(run.out[:half], want[:half])
+
+
+@pytest.mark.parametrize("packed", [False, True], ids=["plain", "packed"])
+def test_segments_that_arrive_during_the_forward(packed):
+    """The receive buffer is filled segment by segment while a small batch waits for it.  The wait is bounded, so that a lost segment
+    fails the test."""
+    import gpu_harness as H
+    import paper_2502_19811_amd as moe
+    cfg = wl.MoEConfig("decode_arrival", T=33, H=1024, F=1792, E=8, k=2, act=wl.ACT_SWIGLU, S=4, seed=652)
+    inp = wl.make_inputs(cfg, threads=4)
+    ids, w = orc.route_topk(inp.logits, cfg.k)
+    layer = H.GpuLayer(cfg, inp, ids, w, {"spin_limit": 1 << 21}, packed=packed)
+    want, _ = _bits(layer)
+    staging = layer.x.clone()
+    layer.x.zero_()
+    layer.out.zero_()
+    flags = torch.zeros(cfg.S, dtype=torch.int32, device="cuda")
+    counters = torch.zeros(cfg.S, dtype=torch.int32, device="cuda")
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    print(f"decode with arriving segments, packed {packed}", flush=True)
+    moe.moe_play_arrival(layer.plan, staging, layer.x, flags, counters, 3, 0.2, 2, side)   # 67 KB at 0.2 GB/s: 0.3 ms
+    layer.forward(seg_ready=flags, epoch=3)
+    torch.cuda.synchronize()
+    run = layer.results()
+    got = layer.out.view(torch.int16).cpu().numpy()
+    layer.close()
+    assert run.status == 0
+    np.testing.assert_array_equal(got, want)
