@@ -223,7 +223,8 @@ int32_t moe_plan_max_tiles(const moe_plan_t *plan);
  * positions named by the queues are meaningful.  queues: host int32 [24]: for XCD x the list position of its first
  * item (queues[x]), its number of items (queues[8+x]) and the distance between consecutive items (queues[16+x]); a
  * workgroup on XCD x takes its own queue front to back, then the others'.  Synchronises the stream.  The plan's
- * schedule options must be the ones the forward ran with. */
+ * schedule options must be the ones the forward ran with.  A small batch's forward may do without the schedules; this call
+ * then builds them in the workspace first. */
 int moe_get_schedule(const moe_plan_t *plan, const void *workspace, int32_t layer, int32_t *items, int32_t *queues,
                      void *hip_stream);
 int64_t moe_plan_schedule_capacity(const moe_plan_t *plan, int32_t layer);

@@ -196,6 +196,7 @@ __global__ __launch_bounds__(256) void k_index_scatter(IndexParams p) {
       p.ws.status[2] = n_tiles * p.n_tiles_n0;
       p.ws.status[3] = n_tiles * p.n_tiles_n1;
       p.ws.status[4] = 0;
+      p.ws.status[6] = 0;
       p.ws.offsets[E] = total_rows;
     }
     if (threadIdx.x < 2 * kXcds) p.ws.status[8 + threadIdx.x] = 0;   // queue heads of both layers
@@ -357,6 +358,7 @@ __global__ __launch_bounds__(1024) void k_index_schedule_large(IndexParams p) {
   __shared__ uint8_t keys[kTileCap];
   __shared__ uint8_t exp_lds[kTileCap];
   __shared__ uint16_t ord_lds[kTileCap];
+  if (p.only_if_owed && p.ws.status[6] != kScheduleOwed) return;
   const int n_tiles = p.ws.status[1];
   const int tid = threadIdx.x;
   const int S = p.s.S;
@@ -777,6 +779,7 @@ __device__ inline void build_schedules(ScheduleLds& L, const IndexParams& p, int
 __global__ __launch_bounds__(1024) void k_index_schedule(IndexParams p) {
   __shared__ __attribute__((aligned(16))) ScheduleLds L;
   __shared__ int32_t seg_lds[kMaxSegments + 1];
+  if (p.only_if_owed && p.ws.status[6] != kScheduleOwed) return;
   const int n_tiles = max(0, min(p.ws.status[1], p.max_tiles));
   const int tid = threadIdx.x;
   if (tid <= p.s.S) seg_lds[tid] = p.seg_offsets[tid];
@@ -889,6 +892,7 @@ __global__ __launch_bounds__(1024) void k_index_small(IndexParams p, int schedul
       p.ws.status[2] = tiles_incl * p.n_tiles_n0;
       p.ws.status[3] = tiles_incl * p.n_tiles_n1;
       p.ws.status[4] = 0;
+      p.ws.status[6] = schedule ? 0 : kScheduleOwed;
       p.ws.offsets[E] = rows_incl;
     }
   } else if (wave == 1) {
@@ -1002,19 +1006,20 @@ hipError_t launch_arrival_producer(const void* staging, void* x, const ArrivalPa
 
 // Queue heads, combine counter, panel counters and the status word back to zero: what the scatter kernel does at the
 // start of a forward, for a forward that runs the schedules of an earlier index build again.
-__global__ void k_reset_counters(Workspace ws, int n_tiles_n1, int max_tiles) {
+__global__ void k_reset_counters(Workspace ws, int n_tiles_n1, int max_tiles, int schedule_built) {
   const int t = threadIdx.x;
   for (int i = t; i < max_tiles + 1; i += 256) ws.tile_done[i] = 0;
   if (t == 0) {
     ws.status[0] = 0;
     ws.status[4] = 0;
+    if (schedule_built) ws.status[6] = 0;
   }
   if (t < 2 * kXcds) ws.status[8 + t] = 0;
   for (int i = t; i < n_tiles_n1; i += 256) ws.panel_done[i] = 0;
 }
 
-hipError_t launch_reset_counters(const Workspace& ws, int n_tiles_n1, int max_tiles, hipStream_t st) {
-  hipLaunchKernelGGL(k_reset_counters, dim3(1), dim3(256), 0, st, ws, n_tiles_n1, max_tiles);
+hipError_t launch_reset_counters(const Workspace& ws, int n_tiles_n1, int max_tiles, bool schedule_built, hipStream_t st) {
+  hipLaunchKernelGGL(k_reset_counters, dim3(1), dim3(256), 0, st, ws, n_tiles_n1, max_tiles, schedule_built ? 1 : 0);
   return hipGetLastError();
 }
 

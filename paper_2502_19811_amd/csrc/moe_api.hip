@@ -31,7 +31,6 @@ struct moe_plan {
   int32_t layer0_waves;          // 0: from the table below
   int32_t expected_ingest_gbps;  // 0: unknown
   int32_t last_layer0_order;     // what the last forward ran with (for moe_get_schedule)
-  int32_t schedule_owed;         // 1: the last index build left the tile schedules out (its GroupGEMMs run without them)
   int32_t layer1_order;
   int32_t spin_limit;
   int32_t phases;
@@ -222,6 +221,9 @@ int default_layer0_waves(const Shape& s, int ingest_gbps) {
   return waves < 1 ? 1 : waves;
 }
 
+// Batches whose GroupGEMMs may run as k_decode_gemm, without tile schedules.
+bool few_rows(const Shape& s) { return (int64_t)s.R <= (int64_t)kDecodeRowsPerExpert * s.E; }
+
 // Whether a GroupGEMM of n_tiles_n column tiles runs as k_decode_gemm (one pass over the weights for a few rows per
 // expert) or as the persistent tile kernel.  Measured, us per layer0 / layer1 launch, tile kernel -> decode kernel:
 //   packed, 8 experts of F = 14336     1 token 120 / 144 -> 89 / 44, 16 tokens 328 / 202 -> 320 / 160, 64: 336 / 208 -> 343 / 167,
@@ -236,7 +238,7 @@ int default_layer0_waves(const Shape& s, int ingest_gbps) {
 bool decode_path(const moe_plan* p, int n_tiles_n, int64_t K, int64_t ldb, bool pair, int n_cu) {
   const Shape& s = p->s;
   if (K * ldb * 2 >= 1ll << 32 || (int64_t)s.T * s.H * 2 > 1ll << 31 || (int64_t)s.R * s.F * 2 > 1ll << 31) return false;
-  if ((int64_t)s.R > (int64_t)kDecodeRowsPerExpert * s.E) return false;
+  if (!few_rows(s)) return false;
   if (!p->weights_packed && expected_experts(s) * n_tiles_n * (pair ? 2 : 1) >= n_cu) return false;
   return p->layer1_order == 0 && !p->fuse_layers && p->n_prefetch <= 0 && !p->handoff_fences && !p->alias_experts &&
          !p->large_schedule && !p->n_cu_set;
@@ -531,15 +533,17 @@ int forward_impl(moe_plan_t* p, const void* x, const int32_t* topk_ids, const fl
       ip.seg_ready = seg_ready;
       ip.ready_epoch = ready_epoch;
     }
-    p->schedule_owed = decode0 && decode1;
-    if (launch_index_build(ip, !p->schedule_owed, st) != hipSuccess) return MOE_ERR_HIP;
+    if (launch_index_build(ip, !(decode0 && decode1), st) != hipSuccess) return MOE_ERR_HIP;
   } else {
-    if (p->schedule_owed && !(decode0 && decode1)) {
-      if (launch_index_schedule(index_params(p, ws, topk_ids, order0), st) != hipSuccess) return MOE_ERR_HIP;
-      p->schedule_owed = 0;
+    // an index build for a forward that does without schedules left them out, which the workspace knows: they are made now
+    const bool make_up = few_rows(s) && !(decode0 && decode1);
+    if (make_up) {
+      IndexParams ip = index_params(p, ws, topk_ids, order0);
+      ip.only_if_owed = 1;
+      if (launch_index_schedule(ip, st) != hipSuccess) return MOE_ERR_HIP;
     }
     // the schedules of the last index build on this workspace are run again: their queue heads and counters start over
-    if (launch_reset_counters(ws, p->n_tiles_n1, p->max_tiles, st) != hipSuccess) return MOE_ERR_HIP;
+    if (launch_reset_counters(ws, p->n_tiles_n1, p->max_tiles, make_up, st) != hipSuccess) return MOE_ERR_HIP;
   }
 
   if (!mark(1)) return MOE_ERR_HIP;
@@ -855,9 +859,11 @@ int moe_get_schedule(const moe_plan_t* p, const void* workspace, int32_t layer, 
   Workspace ws = view(p, const_cast<void*>(workspace));
   hipStream_t st = (hipStream_t)hip_stream;
   int32_t status[64];
-  if (p->schedule_owed &&   // (the forward had no use for it)
-      launch_index_schedule(index_params(p, ws, nullptr, p->last_layer0_order), st) != hipSuccess)
-    return MOE_ERR_HIP;
+  if (few_rows(p->s) && p->s.R > 0) {   // a forward that did without schedules left them out
+    IndexParams ip = index_params(p, ws, nullptr, p->last_layer0_order);
+    ip.only_if_owed = 1;
+    if (launch_index_schedule(ip, st) != hipSuccess) return MOE_ERR_HIP;
+  }
   if (hipMemcpyAsync(status, ws.status, sizeof(status), hipMemcpyDeviceToHost, st) != hipSuccess) return MOE_ERR_HIP;
   if (items) {
     const size_t bytes = (size_t)moe_plan_schedule_capacity(p, layer) * sizeof(ItemRec);

@@ -28,6 +28,8 @@ constexpr int kScheduleTileCap = 2048;  // M-tiles up to which the multi-workgro
 // Which schedule builder a plan uses: the one-workgroup kernel has no size limit (and simpler orders).
 inline bool uses_large_schedule(int max_tiles, int force) { return force != 0 || max_tiles > kScheduleTileCap; }
 
+constexpr int32_t kScheduleOwed = 0x4f574544;   // (a workspace that no forward has seen is unlikely to hold it)
+
 // Item of a GroupGEMM schedule: one (M-tile, column tile) pair with the M-tile's table row copied in, so that a
 // workgroup needs a single 32-byte read to start on it.
 struct ItemRec {
@@ -38,7 +40,8 @@ struct ItemRec {
 struct Workspace {
   int32_t* status;        // [64]  0: device status word, 1: n_tiles, 2: items of layer0, 3: items of layer1,
                           //       4: combine unit counter, 5: serial number of the last forward that saw an expert
-                          //       id out of range; 7: waves of the layer0 schedule; per XCD: 8..15 layer0 queue heads, 16..23 layer1 queue
+                          //       id out of range; 6: kScheduleOwed where the index build left the tile schedules
+                          //       out; 7: waves of the layer0 schedule; per XCD: 8..15 layer0 queue heads, 16..23 layer1 queue
                           //       heads, 24..31 layer0 queue lengths, 32..39 layer1 queue lengths, 40..47 layer1
                           //       queue bases, 48..55 layer0 queue bases (only with contiguous layer0 queues;
                           //       otherwise layer0's queue x is list positions x, x+8, ...)
@@ -82,6 +85,7 @@ struct IndexParams {
   int32_t max_tiles;             // bound on the M-tiles of this plan
   int32_t force_large_schedule;  // 1: build the schedules with the one-workgroup kernel whatever the size
   int32_t block_m;               // M-tiles per block of the locality order (1..8)
+  int32_t only_if_owed;          // schedule builders: nothing to do where the index build made the schedules
   int32_t forward_serial;        // written to status[5] when an expert id is out of range
   int32_t seg_offsets[kMaxSegments + 1];
 };
@@ -199,7 +203,7 @@ struct CombineParams {
 hipError_t launch_route_topk(const float* logits, int T, int E, int k, int32_t* ids, float* w, hipStream_t st);
 hipError_t launch_index_build(const IndexParams& p, bool schedule, hipStream_t st);
 hipError_t launch_index_schedule(const IndexParams& p, hipStream_t st);
-hipError_t launch_reset_counters(const Workspace& ws, int n_tiles_n1, int max_tiles, hipStream_t st);
+hipError_t launch_reset_counters(const Workspace& ws, int n_tiles_n1, int max_tiles, bool schedule_built, hipStream_t st);
 hipError_t launch_layer0(const GemmParams& p, int act, int grid, hipStream_t st);
 hipError_t launch_layer1(const GemmParams& p, int grid, hipStream_t st);
 hipError_t launch_decode_gemm(const DecodeParams& p, int layer1, int act, int packed, hipStream_t st);

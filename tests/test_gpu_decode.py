@@ -231,3 +231,31 @@ def test_segments_that_arrive_during_the_forward(packed):
     layer.close()
     assert run.status == 0
     np.testing.assert_array_equal(got, want)
+
+
+def test_schedules_a_small_batch_did_without_belong_to_the_workspace():
+    """One plan, two workspaces: the first has seen a forward that needs no tile schedules, the second one that builds them.  The
+    steps after the index build, and the schedule itself, are then asked of the first with the option of the second, and the reverse."""
+    import gpu_harness as H
+    import paper_2502_19811_amd as moe
+    cfg = wl.MoEConfig("decode_two_ws", T=24, H=512, F=1152, E=8, k=2, act=wl.ACT_SWIGLU, S=2, seed=653)
+    inp = wl.make_inputs(cfg, threads=4)
+    ids, w = orc.route_topk(inp.logits, cfg.k)
+    layer = H.GpuLayer(cfg, inp, ids, w, packed=True)
+    want, run = _bits(layer)
+    first, second = layer.ws, torch.zeros_like(layer.ws)
+    moe.moe_plan_set_option(layer.plan, "handoff_fences", 1)      # the tile kernel
+    layer.ws = second
+    layer.forward()
+    for ws, fences in ((first, 1), (second, 0), (first, 0), (second, 1)):
+        print(f"phases without the index build, {'first' if ws is first else 'second'} workspace, fences {fences}", flush=True)
+        moe.moe_plan_set_option(layer.plan, "handoff_fences", fences)
+        moe.moe_plan_set_option(layer.plan, "phases", 14)
+        layer.ws = ws
+        layer.out.fill_(7.0)
+        got, _ = _bits(layer)
+        np.testing.assert_array_equal(got, want)
+        for l, n in ((0, cfg.F // 128), (1, cfg.H // 256)):
+            items, queues = layer.schedule(l)
+            H.check_schedule(items, queues, run.tiles, n)
+    layer.close()
