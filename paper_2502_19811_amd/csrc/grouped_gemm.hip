@@ -52,14 +52,15 @@ __device__ __forceinline__ void mfma_in_place(f32x4& acc, bf16x8 b, bf16x8 a) {
 // with s_waitcnt vmcnt.
 __device__ __forceinline__ void dma16(const void* sbase, uint32_t voff, uint32_t lds_base) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds_base)
-               : "memory");
+               : "memory", "m0");
 }
 // The same in two instructions with an MFMA between them (M0 wants a cycle before it is used): the LDS address, a base in a
-// scalar register plus a constant, and the load.  Nothing between the two may touch M0.
+// scalar register plus a constant, and the load.  Nothing between the two may touch M0:
+// the scheduling barriers around both leave the MFMA alone there, and the compiler has no other use for M0 in these kernels.
 template <int OFF>
 __device__ __forceinline__ void dma16_address(uint32_t lds_base) {
-  if constexpr (OFF == 0) asm volatile("s_mov_b32 m0, %0" ::"s"(lds_base) : "memory");
-  else asm volatile("s_add_u32 m0, %0, %1" ::"s"(lds_base), "n"(OFF) : "memory", "scc");
+  if constexpr (OFF == 0) asm volatile("s_mov_b32 m0, %0" ::"s"(lds_base) : "memory", "m0");
+  else asm volatile("s_add_u32 m0, %0, %1" ::"s"(lds_base), "n"(OFF) : "memory", "scc", "m0");
 }
 __device__ __forceinline__ void dma16_load(const void* sbase, uint32_t voff) {
   asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase) : "memory");
