@@ -52,7 +52,7 @@ __device__ __forceinline__ void mfma_in_place(f32x4& acc, bf16x8 b, bf16x8 a) {
 // with s_waitcnt vmcnt.
 __device__ __forceinline__ void dma16(const void* sbase, uint32_t voff, uint32_t lds_base) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds_base)
-               : "memory", "m0");
+               : "memory");
 }
 // The same in two instructions with an MFMA between them (M0 wants a cycle before it is used): the LDS address, a base in a
 // scalar register plus a constant, and the load.  Nothing between the two may touch M0:
