@@ -36,12 +36,18 @@ def test_small_batches_match_the_oracle(size, packed):
         print(f"decode {size} packed {packed} rows of the fullest expert {np.bincount(ids.ravel()).max()}", flush=True)
         ref = orc.moe_layer(inp.x, inp.W1, inp.W2, ids, w, act)
         layer = H.GpuLayer(cfg, inp, ids, w, packed=packed)
+        # nothing is written behind the output or the workspace (Y, layer1's output, is the last part of it)
+        n = layer.ws.numel()
+        ws = torch.full((n + (1 << 20),), 0x5A, dtype=torch.uint8, device="cuda")
+        out = torch.full((T + 64, Hd), 7.0, dtype=torch.bfloat16, device="cuda")
+        layer.ws, layer.out = ws[:n], out[:T]
         layer.forward(); run = layer.results()
         assert run.status == 0
+        assert bool((ws[n:] == 0x5A).all()) and bool((out[T:] == 7.0).all())
         a, b = H.error_metrics(run.out, ref)
         print(f"  err {a:.3e} {b:.3e}", flush=True)
         assert a <= H.REL_TOL and b <= H.REL_TOL
-        # ready flags that are all there, and no row written beyond the batch's
+        # ready flags that are all there
         layer.out.fill_(7.0)
         layer.forward(seg_ready=torch.ones(cfg.S, dtype=torch.int32, device="cuda"), epoch=1)
         np.testing.assert_array_equal(layer.results().out, run.out)
