@@ -102,7 +102,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64) __attribute__((amdgpu_waves_per_
   const int stride = (gridDim.x / kXcds) * (kTwoWaves ? 1 : kDecodeWaves);
   struct Unit {
     int turn, cg, row0, nrows, expert, seg;   // nrows = 0: there is no further unit
-    uint32_t a_off[RB];          // per lane: rows 8 g + lane / 8 of A, 16 bytes at lane % 8 of a line
+    int row[RB];                 // per lane: rows 8 g + lane / 8 of A (as loaded: used in start, so that nothing waits for them here)
   };
   auto find = [&](int turn) {
     Unit t;
@@ -122,9 +122,8 @@ __global__ __launch_bounds__(kDecodeWaves * 64) __attribute__((amdgpu_waves_per_
       if (flagged) t.seg = p.tile_ready[slot];
 #pragma unroll
       for (int g = 0; g < RB; g++) {
-        const int in_unit = g * 8 + (lane >> 3), r = t.row0 + min(in_unit, t.nrows - 1);
-        t.a_off[g] = (uint32_t)(MODE != MODE_L1 ? p.a_rows[r] : r) * p.lda_bytes + (lane & 7) * 16;
-        if (in_unit >= t.nrows) t.a_off[g] = kRowsEnd;
+        const int r = t.row0 + min(g * 8 + (lane >> 3), t.nrows - 1);
+        t.row[g] = MODE != MODE_L1 ? p.a_rows[r] : r;
       }
     }
     return t;
@@ -167,7 +166,8 @@ __global__ __launch_bounds__(kDecodeWaves * 64) __attribute__((amdgpu_waves_per_
   auto start = [&](const Unit& t) {
     const int col = t.cg * (OB * 16);   // of C
 #pragma unroll
-    for (int g = 0; g < RB; g++) a_off[g] = t.a_off[g];
+    for (int g = 0; g < RB; g++)
+      a_off[g] = g * 8 + (lane >> 3) < t.nrows ? (uint32_t)t.row[g] * p.lda_bytes + (lane & 7) * 16 : kRowsEnd;
     if (PK) {   // column tiles of 256 columns (SwiGLU: 128 gate and the 128 up columns of the same units)
       const int tile = kPair ? col >> 7 : col >> 8, in_tile = kPair ? col & 127 : col & 255;
       b_buf = buffer(p.B + ((uint64_t)t.expert * p.n_tiles_n + tile) * nk * (2 * kStageBytes) + (in_tile >> 5) * 1024 + ((in_tile >> 4) & 1) * 256);
@@ -333,8 +333,8 @@ static hipError_t launch_decode(const DecodeParams& p, hipStream_t st) {
 //   packed, up to 8 rows    SwiGLU 4 steps x 4 wavefronts 86, 6 x 2 87, 3 x 4 87; layer1 (512 wavefronts in all for one token) 16 columns
 //                           each, 8 x 2 44, 4 x 4 52; 32 columns 4 x 4 66   (1 token, Mixtral-shaped)
 //   packed, 9 to 16 rows    4 x 3 / 4 x 4, 2 x 4 3 % and 3 x 4 0.4 % longer (16 tokens, Mixtral-shaped)
-//   packed, more            SwiGLU 3 x 3 404, 2 x 4 395, with skewed routing 390 / 414; layer1 32 columns 2 x 4 213, 3 x 3 208, 4 x 2 206, 16 columns 3 x 4 225 (48 tokens,
-//                           64 experts of F = 2560; skewed: 128 tokens, popularity falling as rank^-1.2, layer1 210 / 209 / 208 / 259)
+//   packed, more            layer0 + layer1 of 48 tokens of 64 experts of F = 2560, gate and index build in it: SwiGLU 2 x 4 with layer1 3 x 3
+//                           611, 3 x 3 with 2 x 4 620, 4 x 2 with 4 x 2 615, 4 x 3 with 3 x 4 (spills) 694
 //   plain, SwiGLU           3 x 2 25, 2 x 2 33 (4 tokens); 4 x 1 47, 3 x 2 50 (33 tokens, 8 experts of F = 1792)
 // Plain weights without SwiGLU: 64 columns, whole lines (12 tokens, F = 2560, weights from HBM: layer1 33 us against 46 in
 // 64-byte pieces), but 32 where the wavefronts of 64 would leave compute units idle (one token, 120 wavefronts of 64 columns: layer1
@@ -345,7 +345,7 @@ static hipError_t launch_decode_depth(const DecodeParams& p, int packed, hipStre
   if (packed) {
     if constexpr (RB == 1) return launch_decode<MODE, true, (kPair ? 2 : 1), 1, (kPair ? 4 : 8), (kPair ? 4 : 2)>(p, st);
     else if constexpr (RB == 2) return launch_decode<MODE, true, (MODE == MODE_L1 ? 1 : 2), 2, 4, (MODE == MODE_L1 ? 4 : 3)>(p, st);
-    else return launch_decode<MODE, true, 2, 4, (kPair ? 3 : 2), (kPair ? 3 : 4)>(p, st);
+    else return launch_decode<MODE, true, 2, 4, (kPair ? 2 : 3), (kPair ? 4 : 3)>(p, st);
   }
   if constexpr (!kPair) {
     if (p.experts * (p.N / 64) < 0.75f * p.n_cu) return launch_decode<MODE, false, 2, RB, (RB == 1 ? 6 : 4), 2>(p, st);
