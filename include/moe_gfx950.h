@@ -53,7 +53,14 @@ typedef struct {
   int32_t act; /* moe_act_t */
 } moe_shape_t;
 
-/* Plan / variant selection (Section 3.2.2: the division point between data-movement and GEMM
+/* Small batches: with up to 16 rows per expert on average a GroupGEMM may run as a kernel made for the stream of weights,
+ * without tile schedules (packed weights always, plain ones where the tiles would leave compute units idle).  An output is the
+ * same fp32 sum in the same order there, so its bits depend neither on which kernel computes it nor on the batch around its
+ * token.  The options "n_cu", "layer1_order" 1 and 2, "n_prefetch" > 0, "fuse_layers", "handoff_fences", "alias_experts" and
+ * "large_schedule" take the tile kernel whatever the size: times measured with one of them are to be read against a
+ * forward that does too (any "n_cu", for instance).
+ *
+ * Plan / variant selection (Section 3.2.2: the division point between data-movement and GEMM
  * workgroups and the kernel variant are chosen per shape before launch and looked up at run time).
  * seg_offsets: host, [S+1], non-decreasing, seg_offsets[0] = 0, seg_offsets[S] = T; segment s is the
  * token range [seg_offsets[s], seg_offsets[s+1]) written by source s.  Copied into the plan.
@@ -64,7 +71,9 @@ int moe_plan_create(moe_plan_t **plan, const moe_shape_t *shape, const int32_t *
 int moe_plan_destroy(moe_plan_t *plan);
 
 /* Tunables.  Keys:
- *   "tile_m"       64 / 128 / 256: rows of the tallest GroupGEMM tile (default: chosen from T*k/E)
+ *   "tile_m"       64 / 128 / 256: rows of the tallest GroupGEMM tile (default: 256, or less where layer0's items -- from
+ *                  T*k/E, F and act -- are one round or less on 256 compute units; never one whose larger tables would
+ *                  push the plan out of the 32 MiB of moe_layer_forward_static)
  *   "n_dm"         data-movement workgroups of the layer1 kernel (default: table lookup per shape)
  *   "layer1_order" where the top-k reduction runs: 0 = a separate combine kernel after the layer1 kernel (default:
  *                  the fastest on every workload measured, see paper_2502_19811_amd/split_sweep.py);
@@ -76,7 +85,7 @@ int moe_plan_destroy(moe_plan_t *plan);
  *                  same bits
  *   "deep_short_tiles" 1 (default): the 64-row tiles of the ragged expert ends keep five K steps of operands in
  *                  flight instead of three (six LDS stages; their A blocks are small enough).  A K step of such a tile
- *                  is 8 MFMAs per wavefront, so with three steps of lead it spends half its time waiting for its
+ *                  is 256 cycles of MFMAs per wavefront, so with three steps of lead it spends half its time waiting for its
  *                  operands.  Same bits; 0 is kept for comparison
  *   "n_prefetch"   0, 8, ... 64 (a multiple of 8): that many of the workgroups of each GroupGEMM launch compute no
  *                  tiles but run ahead of the others of their XCD and read the packed weight panels of the items
@@ -258,8 +267,8 @@ int moe_plan_forward_times(moe_plan_t *plan, float *ms, int32_t capacity, int32_
  *   (overwritten).  tflops: host [1].
  * moe_probe_copy: plain device copy of bytes (multiple of 16, both pointers 16-byte aligned) from src to dst;
  *   gbytes_per_s: host [1], bytes read plus bytes written per second.
- * moe_probe_mix: the same MFMA loop on random data with the data movement of a GroupGEMM K step around it, arranged as
- *   the GroupGEMM's main loop is, to price each kind of traffic: mode is a bit mask -- 1: 16 ds_read_b128 per K step
+ * moe_probe_mix: the same MFMA loop on random data with the data movement of a GroupGEMM K step around it, in two half
+ *   steps of four groups, to price each kind of traffic: mode is a bit mask -- 1: 16 ds_read_b128 per K step
  *   (32 MFMAs of a wavefront) fetch the operand fragments of the next (half) step from LDS into a second register set;
  *   2: 8 global->LDS loads of 1 KiB per K step from an L2-resident region; 4: a workgroup barrier per K step; 8 (needs
  *   2): two loads in eight stream from HBM instead; 16: the MFMAs are 64 v_mfma_f32_16x16x32_bf16 per K step instead

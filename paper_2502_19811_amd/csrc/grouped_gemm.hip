@@ -392,7 +392,7 @@ struct LoadState {
 // bytes of one K step per row, 16 rows per instruction, is 1-2 % slower).  Block b = 2d + h holds rows [h*BM/2, (h+1)*BM/2) for
 // K steps 2d and 2d+1; a block per K step is loaded, NSX - 1 steps ahead like B.
 // NSX is 4 (three steps of lead) except for the 64-row tiles of the ragged expert ends, which get 6: a K step of
-// theirs is 8 MFMAs per wavefront, so three steps of lead are a third of a memory round trip and the tile would
+// theirs is 16 MFMAs of 16 cycles per wavefront, so three steps of lead are a third of a memory round trip and the tile would
 // spend half its time waiting for its operands; their small A blocks leave the LDS for two more B stages.
 constexpr int kDeepStages = 6;
 constexpr int a_block_bytes(int bm) { return bm * 64; }
@@ -1339,7 +1339,8 @@ hipError_t launch_layer1(const GemmParams& p, int grid, hipStream_t st) {
 // Weight packing (once per set of weights, outside the forward): B [E][K][ldb] row-major becomes, per expert, column
 // tile and K step of 32, the 16 KiB LDS image of that stage: 16 fragments of 1 KiB, fragment (kk, c) = 16 values of K
 // (kk-th half of the step) x 32 columns (c-th block of the tile), lane l of a wavefront owning the 8 K-consecutive
-// values k = kk*16 + (l/32)*8 .. +7 of column l%32 -- the operand layout of v_mfma_f32_32x32x16_bf16.  A tile's stages
+// values k = kk*16 + (l/32)*8 .. +7 of column l%32 -- the operand layout of v_mfma_f32_32x32x16_bf16; the 16 columns by 32
+// values that v_mfma_f32_16x16x32_bf16 takes are four pieces of 256 bytes of two of them.  A tile's stages
 // follow each other in memory, so a workgroup streams one contiguous run per tile.
 // Column blocks: plain layers, block c = columns [32c, 32c+32) of the tile.  SwiGLU W1 ([gate | up] column halves): tile
 // n covers hidden units [128n, 128n+128); blocks 0..3 are their gate columns, blocks 4..7 their up columns.

@@ -31,7 +31,8 @@ __device__ __forceinline__ const char* uniform(const char* ptr) {
 }
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
-// GELU in its erf form, 0.5 v (1 + erf(v / sqrt 2)).  erf is evaluated with the classic 5-term rational
+// GELU in its erf form, 0.5 v (1 + erf(v / sqrt 2)).  erf is evaluated with the 5-term formula 7.1.26 of Abramowitz and
+// Stegun's Handbook of Mathematical Functions, the rational
 // approximation 1 - (a1 t + ... + a5 t^5) exp(-z^2), t = 1 / (1 + 0.3275911 z) (absolute error below 1.5e-7,
 // far under the bf16 rounding of the result); it needs a handful of registers, which matters next to 256
 // live accumulators.

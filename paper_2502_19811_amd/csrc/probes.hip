@@ -69,8 +69,8 @@ __global__ __launch_bounds__(256) void k_probe_mfma(float* out, int iters) {
   out[blockIdx.x * 256 + threadIdx.x] = sum;
 }
 
-// The MFMA loop again, now with the data movement of a GroupGEMM K step around it, arranged as the GroupGEMM's main
-// loop arranges it, so that the price of each kind of traffic can be read off, in TFLOP/s, core clock and share of
+// The MFMA loop again, now with the data movement of a GroupGEMM K step around it, in two half steps of four groups, so
+// that the price of each kind of traffic can be read off, in TFLOP/s, core clock and share of
 // cycles the matrix cores are busy.  An iteration is one K step (32 values of K) of a wavefront's 128 x 128 outputs:
 // 32 v_mfma_f32_32x32x16_bf16 in 8 groups of 4 -- or, SHAPE16, 64 v_mfma_f32_16x16x32_bf16 in 8 groups of 8 -- and per
 // group optionally two ds_read_b128 that fetch operand fragments of the next (half) step from LDS into the other of
