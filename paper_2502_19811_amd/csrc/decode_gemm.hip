@@ -23,9 +23,9 @@
 //    layer0 / layer1 launch, now 390 / 200; the tile kernel 335 / 182.  256 tokens of 64 experts of F = 1408 116 / 131 ->
 //    96 / 52, tile kernel 95 / 51.)  The row blocks and rows of A that a unit does not have cost nothing: no MFMA, loads
 //    beyond the end of the buffer.
-// us for both layers, tile kernel -> K in 8 parts -> this one: Mixtral-shaped packed, 1 token 259 -> 130 -> 133 (704 MB: 5.3
-// TB/s), 16 tokens 530 -> 485 -> 484 (2.8 GB: 5.8 TB/s; a copy of 1 GiB moves 4.4 TB/s, half of it writes); 64 experts of
-// F = 2560, 48 tokens 634 -> 615 -> 623; plain, 8 experts of F = 1792, 33 tokens 102 -> 82 -> 74.
+// us for both layers, tile kernel -> K in 8 parts -> this one: Mixtral-shaped packed, 1 token 263 -> 135 -> 134 (704 MB: 5.3
+// TB/s), 16 tokens 532 -> 485 -> 490 (2.8 GB: 5.8 TB/s; a copy of 1 GiB moves 4.4 TB/s, half of it writes); 64 experts of
+// F = 2560, 48 tokens 636 -> 610 -> 614; plain, 8 experts of F = 1792, 33 tokens 102 -> 82 -> 77.
 #include "moe_device.h"
 
 namespace moe {

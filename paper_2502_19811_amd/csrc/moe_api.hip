@@ -226,20 +226,28 @@ bool few_rows(const Shape& s) { return (int64_t)s.R <= (int64_t)kDecodeRowsPerEx
 
 // Whether a GroupGEMM of n_tiles_n column tiles runs as k_decode_gemm (one pass over the weights for a few rows per
 // expert) or as the persistent tile kernel.  Measured, us per layer0 / layer1 launch, tile kernel -> decode kernel:
-//   packed, 8 experts of F = 14336     1 token 120 / 144 -> 89 / 44, 16 tokens 328 / 202 -> 320 / 160, 64: 336 / 208 -> 343 / 167,
-//                                      128 (32 rows per expert, a second part for half of them): 338 / 214 -> 525 / 256
-//   packed, 64 experts of F = 2560     1 token 67 / 45 -> 59 / 31, 48: 415 / 219 -> 404 / 219, 128 (16 rows): 424 / 224 -> 434 / 236
-//   plain, 8 experts, H = 4096, 64 tokens   F = 1792 (112 / 128 tiles) 68 / 36 -> 48 / 27, 2560 (160 / 128) 76 / 43 -> 98 / 36,
-//                                      3072 (192 / 128) 83 / 49 -> 98 / 41; GELU, F = 3072 (96 / 128) 63 / 49 -> 47 / 43
-// So packed weights take it up to 16 rows per expert.  Plain weights, whose rows it reads in pieces of 128 bytes against
-// the tile kernel's 512, take it only where the tiles leave compute units idle -- half of them in layer0 with SwiGLU, whose
-// gate and up pieces lie apart.  It addresses an expert's matrix (K rows of ldb columns) with 32-bit byte offsets and the rows of A
-// with 31-bit ones; the tile kernel has no such limits.
+//   packed, 8 experts of F = 14336     1 token 118 / 145 -> 89 / 45, 16 tokens 329 / 203 -> 326 / 164, 64: 326 / 188 -> 350 / 173,
+//                                      128 (32 rows per expert) 338 / 212 -> 525 / 271
+//   packed, 64 experts of F = 2560     1 token 67 / 45 -> 60 / 32, 48: 405 / 209 -> 413 / 213, 128 (16 rows): 409 / 214 -> 436 / 232,
+//                                      256: 421 / 225 -> 594 / 303
+//   plain, 8 experts, H = 4096, 64 tokens   F = 1792 (112 / 128 tiles) 68 / 35 -> 50 / 29, 2560 (160 / 128) 77 / 43 -> 98 / 36,
+//                                      3072 (192 / 128) 83 / 49 -> 98 / 41; GELU, F = 3072 (96 / 128) 68 / 52 -> 50 / 45
+// Where the tiles are no more than the compute units packed weights take it up to 16 rows per expert.  Where they are
+// more, up to 8: us per gate + layer, tile kernel against this one, 24 tokens of 16 experts of F = 6400 (3 rows) 447 / 406, 48 of 64 of
+// F = 2560 (6 rows) 638 / 614, 30 of 8 of F = 7168 (7.5 rows) 256 / 253, 40 of 8 of F = 14336 (layer0 alone, 10 rows) 494 / 498, 96 of 64
+// (12 rows) 640 / 637 -- but there with expert popularities falling as rank^-1.2 507 / 563, and 40 of 8 472 / 492: a crowded expert's
+// weights pass through the caches once per 32 rows here and once per 256 there.
+// Plain weights, whose rows it reads in pieces of 128 bytes against the tile kernel's 512, take it only where the tiles leave
+// compute units idle -- half of them in layer0 with SwiGLU, whose gate and up pieces lie apart.
+// It addresses an expert's matrix (K rows of ldb columns) with 32-bit byte offsets and the rows of A with 31-bit ones; the tile kernel
+// has no such limits.
 bool decode_path(const moe_plan* p, int n_tiles_n, int64_t K, int64_t ldb, bool pair, int n_cu) {
   const Shape& s = p->s;
   if (K * ldb * 2 >= 1ll << 32 || (int64_t)s.T * s.H * 2 > 1ll << 31 || (int64_t)s.R * s.F * 2 > 1ll << 31) return false;
   if (!few_rows(s)) return false;
-  if (!p->weights_packed && expected_experts(s) * n_tiles_n * (pair ? 2 : 1) >= n_cu) return false;
+  const double tiles = (double)expected_experts(s) * n_tiles_n;
+  if (!p->weights_packed && tiles * (pair ? 2 : 1) >= n_cu) return false;
+  if (tiles > n_cu && (int64_t)s.R > (int64_t)kDecodeRowsManyTiles * s.E) return false;
   return p->layer1_order == 0 && !p->fuse_layers && p->n_prefetch <= 0 && !p->handoff_fences && !p->alias_experts &&
          !p->large_schedule && !p->n_cu_set;
 }

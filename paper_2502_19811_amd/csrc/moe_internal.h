@@ -20,7 +20,8 @@ constexpr int kTileN = 256;         // columns of B staged per GroupGEMM tile
 constexpr int kTileK = 32;          // depth of one LDS stage
 constexpr int kStages = 4;          // LDS stages in flight
 constexpr int kCombineChunk = 256;  // tokens per unit of combine work
-constexpr int kDecodeRowsPerExpert = 16;   // rows per expert on average up to which the decode kernel is used
+constexpr int kDecodeRowsPerExpert = 16;   // rows per expert on average up to which the decode kernel is used ...
+constexpr int kDecodeRowsManyTiles = 8;    // ... and where the tile kernel has more tiles than compute units
 constexpr int kDefaultCus = 256;    // compute units a plan assumes before it has seen the device
 constexpr int kXcds = 8;            // XCDs of the device: workgroup i runs on XCD i % 8
 constexpr int kScheduleTileCap = 2048;  // M-tiles up to which the multi-workgroup schedule builder is used

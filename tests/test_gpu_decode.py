@@ -164,12 +164,13 @@ def test_a_small_batch_has_the_bits_of_every_other_way_to_compute_it(T, act):
     assert a <= H.REL_TOL and b <= H.REL_TOL
 
 
-@pytest.mark.parametrize("T,E,k,act,tile_m", [(256, 256, 16, wl.ACT_SWIGLU, 64), (256, 128, 8, wl.ACT_GELU, 256), (40, 20, 8, wl.ACT_SWIGLU, 128)])
-def test_every_row_part_of_crowded_experts(T, E, k, act, tile_m):
+@pytest.mark.parametrize("T,E,k,act,tile_m,Hd,F", [(256, 256, 16, wl.ACT_SWIGLU, 64, 256, 128), (128, 256, 16, wl.ACT_SWIGLU, 64, 512, 512),
+                                                   (256, 128, 8, wl.ACT_GELU, 256, 512, 512), (40, 20, 8, wl.ACT_SWIGLU, 128, 512, 512)])
+def test_every_row_part_of_crowded_experts(T, E, k, act, tile_m, Hd, F):
     """One expert with every token, others with a few or none: several row parts of one expert beside single ones of others, more
     tiles than a wavefront has lanes.  The tile kernel (option n_cu) gives the same bits."""
     import gpu_harness as H
-    cfg = wl.MoEConfig("decode_parts", T=T, H=512, F=512, E=E, k=k, act=act, S=1, seed=690)
+    cfg = wl.MoEConfig("decode_parts", T=T, H=Hd, F=F, E=E, k=k, act=act, S=1, seed=690)
     inp = wl.make_inputs(cfg, threads=4)
     rng = np.random.default_rng(690)
     ids = np.stack([np.concatenate([[E // 3], rng.permutation(np.delete(np.arange(E), E // 3))[:k - 1]]) for _ in range(T)]).astype(np.int32)
