@@ -26,6 +26,8 @@
 // us for both layers, tile kernel -> K in 8 parts -> this one: Mixtral-shaped packed, 1 token 263 -> 135 -> 134 (704 MB: 5.3
 // TB/s), 16 tokens 532 -> 485 -> 490 (2.8 GB: 5.8 TB/s; a copy of 1 GiB moves 4.4 TB/s, half of it writes); 64 experts of
 // F = 2560, 48 tokens 636 -> 610 -> 614; plain, 8 experts of F = 1792, 33 tokens 102 -> 82 -> 77.
+// Then with non-temporal loads of B (gate and layer together): 1 token 134 -> 121 (704 MB: 6.3 TB/s over the two launches), 16 tokens 480
+// -> 430 (6.8 TB/s), 48 of 64 experts 614 -> 560, 33 plain 82 -> 76.
 #include "moe_device.h"
 
 namespace moe {
@@ -37,6 +39,7 @@ constexpr int kDecodeTileCap = 384;                // tiles of a batch the kerne
 static_assert(kDecodeTileCap % 64 == 0 && kDecodeTileCap >= kDecodeRowsPerExpert * kMaxExperts / 64 + kMaxExperts, "tiles of the largest batch");
 constexpr int kStageBytes = kTileK * kTileN * 2;   // packed weights: one K step of one column tile
 constexpr int kPlainPitch = 144;                   // bytes between rows of K in the transposing buffer (64 columns + padding)
+constexpr int kNonTemporal = 2;                    // cache policy of a buffer load: the nt bit
 constexpr int kStepK = 64;                         // K of one ring slot: a whole 128-byte line of every row of A
 
 // The memory from ptr on (the same in every lane) as a buffer: loads then take one 32-bit offset per lane and one scalar
@@ -46,8 +49,9 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer(const char* ptr, uint32
 }
 
 // NB: 16-column blocks of weights of a wavefront (SwiGLU: half of them gate, half up columns of the same hidden units);
-// RB: 8-row groups of A that are loaded (a unit is up to 8 RB rows); U: steps in flight; EU: wavefronts a SIMD holds.
-template <int MODE, bool PK, int NB, int RB, int U, int EU>
+// RB: 8-row groups of A that are loaded (a unit is up to 8 RB rows); U: steps in flight; EU: wavefronts a SIMD holds; STREAM:
+// the loads of B are non-temporal (GemmParams::b_stream).
+template <int MODE, bool PK, int NB, int RB, int U, int EU, bool STREAM>
 __global__ __launch_bounds__(kDecodeWaves * 64) __attribute__((amdgpu_waves_per_eu(EU))) void k_decode_gemm(DecodeParams p) {
   constexpr bool kPair = MODE == MODE_L0_SWIGLU;
   constexpr int ROWS = 8 * RB;
@@ -157,7 +161,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64) __attribute__((amdgpu_waves_per_
       } else {
         at = bs + j * b_rows;
       }
-      breg[u][j] = __builtin_amdgcn_raw_buffer_load_b128(b_buf, b_off, at, 0);
+      breg[u][j] = __builtin_amdgcn_raw_buffer_load_b128(b_buf, b_off, at, STREAM ? kNonTemporal : 0);
     }
     if (!kAhead) load_a();
   };
@@ -325,7 +329,9 @@ static hipError_t launch_decode(const DecodeParams& p, hipStream_t st) {
   const int64_t most = ((int64_t)p.R / (8 * RB) + p.n_slots) * n_groups, resident = (int64_t)p.n_cu * 4 * EU / kUnitWaves;
   const int64_t per_xcd = ((most < resident ? most : resident) + kXcds * kUnitChunk - 1) / (kXcds * kUnitChunk) * kUnitChunk;
   const unsigned grid = (unsigned)(per_xcd * kUnitWaves / kDecodeWaves) * kXcds;
-  hipLaunchKernelGGL((k_decode_gemm<MODE, PK, NB, RB, U, EU>), dim3(grid), dim3(kDecodeWaves * 64), 0, st, p);
+  // (64-byte pieces of plain weights: the other half of a line is another wavefront's and should still be there)
+  if (p.b_stream && (PK || NB == 4)) hipLaunchKernelGGL((k_decode_gemm<MODE, PK, NB, RB, U, EU, (PK || NB == 4)>), dim3(grid), dim3(kDecodeWaves * 64), 0, st, p);
+  else hipLaunchKernelGGL((k_decode_gemm<MODE, PK, NB, RB, U, EU, false>), dim3(grid), dim3(kDecodeWaves * 64), 0, st, p);
   return hipGetLastError();
 }
 

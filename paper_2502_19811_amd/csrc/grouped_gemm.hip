@@ -50,9 +50,15 @@ __device__ __forceinline__ void mfma_in_place(f32x4& acc, bf16x8 b, bf16x8 a) {
 // 16 bytes per lane from sbase + voff straight into LDS at lds_base + lane * 16.  Written as asm so that the
 // compiler's wait-count pass does not serialise later LDS reads behind it; completion is awaited by hand
 // with s_waitcnt vmcnt.
+// STREAM: with the non-temporal hint (GemmParams::b_stream).
+template <bool STREAM = false>
 __device__ __forceinline__ void dma16(const void* sbase, uint32_t voff, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds_base)
-               : "memory");
+  if constexpr (STREAM)
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(voff), "s"(sbase), "s"(lds_base)
+                 : "memory");
+  else
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds_base)
+                 : "memory");
 }
 // The same in two instructions with an MFMA between them (M0 wants a cycle before it is used): the LDS address, a base in a
 // scalar register plus a constant, and the load.  Nothing between the two may touch M0:
@@ -62,8 +68,10 @@ __device__ __forceinline__ void dma16_address(uint32_t lds_base) {
   if constexpr (OFF == 0) asm volatile("s_mov_b32 m0, %0" ::"s"(lds_base) : "memory", "m0");
   else asm volatile("s_add_u32 m0, %0, %1" ::"s"(lds_base), "n"(OFF) : "memory", "scc", "m0");
 }
+template <bool STREAM = false>
 __device__ __forceinline__ void dma16_load(const void* sbase, uint32_t voff) {
-  asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase) : "memory");
+  if constexpr (STREAM) asm volatile("global_load_lds_dwordx4 %0, %1 nt" ::"v"(voff), "s"(sbase) : "memory");
+  else asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase) : "memory");
 }
 // Waits until at most N LDS reads are outstanding, in a form the compiler knows: it adds no waits of its own for the
 // fragments that have landed by then (one in front of every fragment's first MFMA otherwise).
@@ -426,7 +434,7 @@ __device__ __forceinline__ void load_arows(const GemmParams& p, Tile& t, int lan
 // A: lane l of a load fetches the 16 bytes at position (l & 7) ^ ((row / 2) & 7) of its row's 128-byte line, so that
 // the line lands in LDS (linearly, 16 bytes per lane) with its chunks XOR-swizzled by row: the 16 rows one pass of
 // ds_read_b128 touches then fall on distinct banks.
-template <int WM, int MT, int NT, int MODE, bool PK, int NSX>
+template <int WM, int MT, int NT, int MODE, bool PK, bool STREAM, int NSX>
 __device__ __forceinline__ void setup_and_issue(const GemmParams& p, uint32_t lds0, const Tile& t, LoadState& ls, int lane,
                                                 int w, bool issue) {
   constexpr int BM = WM * MT * 32;
@@ -475,7 +483,7 @@ __device__ __forceinline__ void setup_and_issue(const GemmParams& p, uint32_t ld
     };
     auto b_stage = [&](int st) {
 #pragma unroll
-      for (int j = 0; j < LB; j++) dma16(ls.Bb + st * bstep, ls.boff[j], lds0 + B_RING + st * B_STAGE + (w * LB + j) * 1024);
+      for (int j = 0; j < LB; j++) dma16<STREAM>(ls.Bb + st * bstep, ls.boff[j], lds0 + B_RING + st * B_STAGE + (w * LB + j) * 1024);
     };
     a_block(0);
     a_block(1);
@@ -518,7 +526,7 @@ __device__ __forceinline__ bool segment_ready(const GemmParams& p, const Tile& t
 // through LDS and the item record is requested.  A tile followed by one of the same height also starts the
 // successor's first operand stages during its own epilogue (next.pre = 1); otherwise only the rows of A the next
 // tile gathers are requested, after the epilogue.  next.idx = -1: no further tile.
-template <int WM, int MT, int NT, int MODE, bool PK, int NSX = NS>
+template <int WM, int MT, int NT, int MODE, bool PK, bool STREAM, int NSX = NS>
 __device__ __forceinline__ void run_tile(const GemmParams& p, char* smem, volatile int32_t* lds_slot, const Tile& cur,
                                          Tile& next, int xcd, const Queue& q, int& pending_panel,
                                          volatile int32_t* lds_panel_count_ptr, volatile uint32_t* lds_mask) {
@@ -573,7 +581,7 @@ __device__ __forceinline__ void run_tile(const GemmParams& p, char* smem, volati
   if (MODE == MODE_L1 && p.handoff_fences) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   // address set-up and the first loads (A blocks 0..2, B stages 0..2)
   LoadState ls;
-  setup_and_issue<WM, MT, NT, MODE, PK, NSX>(p, lds0, cur, ls, lane, w, !cur.pre);
+  setup_and_issue<WM, MT, NT, MODE, PK, STREAM, NSX>(p, lds0, cur, ls, lane, w, !cur.pre);
   const char* Ab = uniform(ls.Ab);
   const char* Bb = uniform(ls.Bb);
   const size_t bstep = PK ? (size_t)B_STAGE : (size_t)BK * p.ldb * 2;
@@ -768,7 +776,7 @@ __device__ __forceinline__ void run_tile(const GemmParams& p, char* smem, volati
     auto part = [&](auto gi) {
       constexpr int q = decltype(gi)::value - 4;
       group(par, gi, where, reads_next, [&]() { if (q == 3) advance_b(ring, next_ring); },   // the B ring's next positions
-            [&]() { if (do_issue) dma16_address<q * 1024>(dst); }, [&]() { if (do_issue) dma16_load(Bb, ls.boff[q]); });
+            [&]() { if (do_issue) dma16_address<q * 1024>(dst); }, [&]() { if (do_issue) dma16_load<STREAM>(Bb, ls.boff[q]); });
     };
     part(std::integral_constant<int, 4>{});
     part(std::integral_constant<int, 5>{});
@@ -940,7 +948,7 @@ __device__ __forceinline__ void run_tile(const GemmParams& p, char* smem, volati
       if (ma == kPreBlock && do_pre) {
         if (flags_on) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "");
         LoadState ls_next;
-        setup_and_issue<WM, MT, NT, MODE, PK, NSX>(p, lds0, next, ls_next, lane_e, w, true);
+        setup_and_issue<WM, MT, NT, MODE, PK, STREAM, NSX>(p, lds0, next, ls_next, lane_e, w, true);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
@@ -1044,7 +1052,7 @@ __device__ __forceinline__ void run_tile(const GemmParams& p, char* smem, volati
 #endif
 }
 
-template <int MODE, bool PK>
+template <int MODE, bool PK, bool STREAM>
 __global__ __launch_bounds__(256, 1) void k_group_gemm(GemmParams p) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   __shared__ int32_t lds_slot[2];
@@ -1100,10 +1108,10 @@ __global__ __launch_bounds__(256, 1) void k_group_gemm(GemmParams p) {
       continue;
     }
     next.idx = -1;
-    if (cur.rec.kind == 2) run_tile<2, 4, 4, MODE, PK>(p, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
-    else if (cur.rec.kind == 1) run_tile<2, 2, 4, MODE, PK>(p, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
-    else if (deep64) run_tile<1, 2, 2, MODE, PK, kDeepStages>(p, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
-    else run_tile<1, 2, 2, MODE, PK>(p, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
+    if (cur.rec.kind == 2) run_tile<2, 4, 4, MODE, PK, STREAM>(p, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
+    else if (cur.rec.kind == 1) run_tile<2, 2, 4, MODE, PK, STREAM>(p, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
+    else if (deep64) run_tile<1, 2, 2, MODE, PK, STREAM, kDeepStages>(p, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
+    else run_tile<1, 2, 2, MODE, PK, STREAM>(p, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
     cur = next;
   }
   if (MODE == MODE_L1 && p.fused_combine) {
@@ -1201,9 +1209,9 @@ __global__ __launch_bounds__(256, 1) void k_fused_layers(GemmParams p0, GemmPara
       }
       next.idx = -1;
       const int m_tile = cur.rec.m_tile;
-      if (cur.rec.kind == 2) run_tile<2, 4, 4, MODE0, PK>(p0, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
-      else if (cur.rec.kind == 1) run_tile<2, 2, 4, MODE0, PK>(p0, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
-      else run_tile<1, 2, 2, MODE0, PK>(p0, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
+      if (cur.rec.kind == 2) run_tile<2, 4, 4, MODE0, PK, false>(p0, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
+      else if (cur.rec.kind == 1) run_tile<2, 2, 4, MODE0, PK, false>(p0, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
+      else run_tile<1, 2, 2, MODE0, PK, false>(p0, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
       if (tid == 0 && (unsigned)m_tile < (unsigned)kScheduleTileCap) lds_tile_cnt[m_tile] += 1;
       cur = next;
       if (++since_publish >= f.publish_every && cur.idx >= 0) {
@@ -1255,9 +1263,9 @@ __global__ __launch_bounds__(256, 1) void k_fused_layers(GemmParams p0, GemmPara
         }
       }
       next.idx = -1;
-      if (cur.rec.kind == 2) run_tile<2, 4, 4, MODE_L1, PK>(q1, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
-      else if (cur.rec.kind == 1) run_tile<2, 2, 4, MODE_L1, PK>(q1, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
-      else run_tile<1, 2, 2, MODE_L1, PK>(q1, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
+      if (cur.rec.kind == 2) run_tile<2, 4, 4, MODE_L1, PK, false>(q1, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
+      else if (cur.rec.kind == 1) run_tile<2, 2, 4, MODE_L1, PK, false>(q1, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
+      else run_tile<1, 2, 2, MODE_L1, PK, false>(q1, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
       cur = next;
     }
   }
@@ -1319,7 +1327,7 @@ hipError_t launch_fused_layers(const GemmParams& p0, const GemmParams& p1, const
 template <int MODE, bool PK>
 static hipError_t launch_gemm(const GemmParams& p, int grid, hipStream_t st) {
   constexpr int lds = kLdsBytes;
-  auto kern = k_group_gemm<MODE, PK>;
+  auto kern = p.b_stream ? k_group_gemm<MODE, PK, true> : k_group_gemm<MODE, PK, false>;
   hipError_t e = allow_large_lds((const void*)kern, lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, st, p);

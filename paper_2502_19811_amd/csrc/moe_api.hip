@@ -252,6 +252,20 @@ bool decode_path(const moe_plan* p, int n_tiles_n, int64_t K, int64_t ldb, bool 
          !p->large_schedule && !p->n_cu_set;
 }
 
+// Whether the weight loads of a forward carry the non-temporal hint.  A plain read of 2.8 GB runs at 6.2-6.5 TB/s, one with the hint, which
+// leaves nothing in the Infinity Cache, at 7.0-7.4.  us per gate + layer, without / with it: small-batch kernel, 1 token of 8 experts of
+// F = 14336 133 / 121, 16 tokens 495 / 445, 48 of 64 experts of F = 2560 635 / 578; tile kernel, 509 tokens of 16 experts of F = 6400
+// 487 / 447, 64 tokens of 8 of F = 14336 516 / 462.
+// It does not pay where the caches would have the weights for somebody:
+//  * weights of less than half the Infinity Cache (256 MB), so that those of two layers in turn stay there: 3 plans in turn, 82 MB each
+//    36.3 / 37.1, plain weights 51.4 / 54.4; 145 MB 47.7 / 43.8, 130 MB 44.0 / 40.6;
+//  * tile kernel: experts of so many rows that several XCDs stream the same weights.  Rows per expert 187 (64 experts) 874 / 851, 275 (8) 1100 /
+//    1068, 312 (16) 1026 / 1021, 344 (64) 566 / 556, 375 (8) 1095 / 1135, (16) 1024 / 1037, (64) 1509 / 1489, 512 (8) 408 / 420,
+//    2048 (8) 4165 / 4211.
+bool weights_pass_caches(const Shape& s) {
+  return expected_experts(s) * ((double)s.H * s.F1 + (double)s.F * s.H) * 2 > kCachedWeightBytes;
+}
+
 bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 }  // namespace
@@ -587,6 +601,8 @@ int forward_impl(moe_plan_t* p, const void* x, const int32_t* topk_ids, const fl
   a.b_expert_bytes = (uint64_t)s.H * s.F1 * 2;
   a.ldb = (uint32_t)s.F1;
   a.b_packed = p->weights_packed;
+  const bool stream = weights_pass_caches(s);
+  a.b_stream = stream && s.R <= (int64_t)kStreamRowsPerExpert * s.E;
   if (p->alias_experts && !p->weights_packed) a.b_expert_bytes = 0;   // measurement aid, see the option
   a.n_tiles_n = p->n_tiles_n0;
   a.C = ws.h;
@@ -626,6 +642,7 @@ int forward_impl(moe_plan_t* p, const void* x, const int32_t* topk_ids, const fl
   b.b_expert_bytes = (uint64_t)s.F * s.H * 2;
   b.ldb = (uint32_t)s.H;
   b.b_packed = p->weights_packed;
+  b.b_stream = a.b_stream;
   if (p->alias_experts && !p->weights_packed) b.b_expert_bytes = 0;
   b.n_tiles_n = p->n_tiles_n1;
   b.C = ws.Y;
@@ -684,6 +701,7 @@ int forward_impl(moe_plan_t* p, const void* x, const int32_t* topk_ids, const fl
     d0.B = (const char*)W1;
     d0.b_expert_bytes = (uint64_t)s.H * s.F1 * 2;
     d0.ldb = (uint32_t)s.F1;
+    d0.b_stream = d1.b_stream = stream;
     d0.n_tiles_n = p->n_tiles_n0;
     d0.C = ws.h;
     d0.ldc = (uint32_t)s.F;

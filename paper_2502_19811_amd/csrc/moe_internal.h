@@ -22,6 +22,8 @@ constexpr int kStages = 4;          // LDS stages in flight
 constexpr int kCombineChunk = 256;  // tokens per unit of combine work
 constexpr int kDecodeRowsPerExpert = 16;   // rows per expert on average up to which the decode kernel is used ...
 constexpr int kDecodeRowsManyTiles = 8;    // ... and where the tile kernel has more tiles than compute units
+constexpr double kCachedWeightBytes = 128e6;   // weights read by a forward beyond which its loads of them are non-temporal ...
+constexpr int kStreamRowsPerExpert = 320;   // ... in the tile kernel up to this many rows per expert on average
 constexpr int kDefaultCus = 256;    // compute units a plan assumes before it has seen the device
 constexpr int kXcds = 8;            // XCDs of the device: workgroup i runs on XCD i % 8
 constexpr int kScheduleTileCap = 2048;  // M-tiles up to which the multi-workgroup schedule builder is used
@@ -99,6 +101,7 @@ struct GemmParams {
   uint64_t b_expert_bytes;  // bytes between experts
   uint32_t ldb;             // elements per row of B
   int32_t b_packed;         // 1: B is in the packed layout of moe_pack_weights (b_expert_bytes and ldb unused)
+  int32_t b_stream;         // 1: B is loaded with the non-temporal hint: nobody reads it again from the caches
   int32_t n_tiles_n;        // column tiles of this layer (addressing of packed B)
   int32_t handoff_fences;   // measurement aid: per-tile agent-scope release (layer0) / acquire (layer1)
   int32_t no_pre;           // 1: a tile never starts its successor's loads early (the successor's rows may not be there)
@@ -159,6 +162,7 @@ struct DecodeParams {
   const char* B;            // W1 or W2, plain or packed
   uint64_t b_expert_bytes;  // plain: bytes between experts
   uint32_t ldb;             // plain: elements per row of B
+  int32_t b_stream;         // 1: B is loaded with the non-temporal hint
   int32_t n_tiles_n;        // packed: column tiles of this layer
   uint16_t* C;              // h (layer0) or Y (layer1)
   uint32_t ldc;
