@@ -245,10 +245,13 @@ struct Queue {
 __device__ __forceinline__ int queue_pos(const GemmParams& p, int x, int i) {
   return (p.queue_base ? p.queue_base[x] : x) + i * p.queue_stride;
 }
+// The heads lie 256 bytes apart where there is room (Workspace::queue_heads): with all of them in one line the atomics of 256 workgroups that
+// end a tile together took several us (1000 tokens of 64 experts with F = 1408: 245 -> 241 us, and with late tickets 263 -> 237).
+constexpr int kLateRounds = 2;   // rounds at the end of a queue in which an item is taken late, see run_tile
 // Takes the next item of XCD x's queue; returns its list position or -1 when that queue is used up.
 __device__ __forceinline__ int take_from(const GemmParams& p, int x, int len, int base) {
   if (len == 0) return -1;
-  const int i = __hip_atomic_fetch_add(&p.queue_heads[x], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const int i = __hip_atomic_fetch_add(&p.queue_heads[x * p.head_stride], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return i < len ? base + i * p.queue_stride : -1;
 }
 // The other XCDs' leftovers, nearest first; -1 when every queue is used up.  All heads and lengths are read first
@@ -259,7 +262,7 @@ __device__ __forceinline__ int steal(const GemmParams& p, int xcd) {
 #pragma unroll
   for (int d = 1; d < kXcds; d++) {
     const int x = (xcd + d) & (kXcds - 1);
-    head[d] = __hip_atomic_load(&p.queue_heads[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    head[d] = __hip_atomic_load(&p.queue_heads[x * p.head_stride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     len[d] = p.queue_len[x];
   }
 #pragma unroll
@@ -289,7 +292,7 @@ __device__ __forceinline__ void prefetch_loop(const GemmParams& p, int xcd, int 
   int i = 0, last_expert = -1, last_n = -1;
   uint32_t idle = 0, sink = 0;
   while (i < len) {
-    const int head = uniform(__hip_atomic_load(&p.queue_heads[xcd], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    const int head = uniform(__hip_atomic_load(&p.queue_heads[xcd * p.head_stride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
     if (head >= len) break;   // everything handed out: nothing left to be ahead of
     // items handed out a while ago are being streamed by their workgroups already
     if (i < head - p.prefetch_behind) i = head - p.prefetch_behind;
@@ -789,8 +792,15 @@ __device__ __forceinline__ void run_tile(const GemmParams& p, char* smem, volati
 
   // The next item of this XCD's queue is requested before anything else of this tile is outstanding; the
   // operand loads of the first stages were issued before (by the previous tile, or by the kernel for the first).
+  // Not so in the last rounds of a queue (late): there an item goes to whoever ends first, and not, a tile ahead, to a workgroup that
+  // may be at the start of a tall tile while another runs out of short ones.  2047 tokens of 8 experts with F = 3584: 48 short
+  // tiles waited for the second round of tall ones, layer0 262 -> 225 us, the layer 414 -> 381; 1100 of 16 with F = 6400 568 -> 539;
+  // where all tiles take the same time it costs 0.3 %.  One round instead of two loses half of it.
   int next_raw = 0;
-  if (tid == 0) next_raw = take_from(p, xcd, q.own_len, q.own_base);
+  const int taken = (cur.idx - q.own_base) >> (p.queue_stride == 1 ? 0 : 3);   // position in the own queue (a stolen item: anything)
+  const int round = (int)(gridDim.x / kXcds);
+  const bool late = q.own_len > round && (uint32_t)(taken + kLateRounds * round) >= (uint32_t)q.own_len;   // (up to one round: all gone at the start)
+  if (tid == 0 && !late) next_raw = take_from(p, xcd, q.own_len, q.own_base);
   // A tile starts the loads of a successor of its own height during its epilogue, which needs the successor's
   // segment to be there already: the ready flags are sampled here (lane s of the first wavefront reads
   // flag s) and looked at when the successor is known.  A flag raised later than this only costs the early start.
@@ -865,8 +875,9 @@ __device__ __forceinline__ void run_tile(const GemmParams& p, char* smem, volati
     half2(P0{}, false, Last{}, true);
     kt++;
   }
+  if (tid == 0 && late) next_raw = take_from(p, xcd, q.own_len, q.own_base);
   half1(P1{}, false, Last{});
-  wait_vmcnt<LB>();   // younger than the last A block: the last B stage
+  wait_vmcnt<LB>();   // younger than the last A block: the last B stage (and a late ticket)
   block_barrier();
   half2(P1{}, false, Last{}, true);
   kt++;

@@ -199,7 +199,7 @@ __global__ __launch_bounds__(256) void k_index_scatter(IndexParams p) {
       p.ws.status[6] = 0;
       p.ws.offsets[E] = total_rows;
     }
-    if (threadIdx.x < 2 * kXcds) p.ws.status[8 + threadIdx.x] = 0;   // queue heads of both layers
+    if (threadIdx.x < 2 * kXcds) p.ws.queue_heads[threadIdx.x * p.ws.head_stride] = 0;
     for (int i = threadIdx.x; i < p.n_tiles_n1; i += 256) p.ws.panel_done[i] = 0;
     for (int i = threadIdx.x; i < p.max_tiles + 1; i += 256) p.ws.tile_done[i] = 0;
     if (e < E) {
@@ -896,7 +896,7 @@ __global__ __launch_bounds__(1024) void k_index_small(IndexParams p, int schedul
       p.ws.offsets[E] = rows_incl;
     }
   } else if (wave == 1) {
-    if (lane < 2 * kXcds) p.ws.status[8 + lane] = 0;   // queue heads of both layers
+    if (lane < 2 * kXcds) p.ws.queue_heads[lane * p.ws.head_stride] = 0;
     const int now = waves_now(p, lane);
     if (lane == 0) p.ws.status[7] = waves = now;
   } else if (wave < 4) {
@@ -1014,7 +1014,7 @@ __global__ void k_reset_counters(Workspace ws, int n_tiles_n1, int max_tiles, in
     ws.status[4] = 0;
     if (schedule_built) ws.status[6] = 0;
   }
-  if (t < 2 * kXcds) ws.status[8 + t] = 0;
+  if (t < 2 * kXcds) ws.queue_heads[t * ws.head_stride] = 0;
   for (int i = t; i < n_tiles_n1; i += 256) ws.panel_done[i] = 0;
 }
 

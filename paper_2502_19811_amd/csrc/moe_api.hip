@@ -10,6 +10,7 @@
 using namespace moe;
 
 constexpr int kProfSlots = 256;
+constexpr int kHeadStride = 64;   // words between queue heads: 256 bytes
 
 // Workspace of moe_layer_forward_static: device memory that exists from the moment the library is loaded, so that a
 // forward on it allocates nothing.  Every GPU the library runs on holds its own copy at its own address; in host code
@@ -32,6 +33,7 @@ struct moe_plan {
   int32_t expected_ingest_gbps;  // 0: unknown
   int32_t last_layer0_order;     // what the last forward ran with (for moe_get_schedule)
   int32_t layer1_order;
+  int32_t spread_heads;          // the last index build's schedules leave the room for spread queue heads, see view()
   int32_t spin_limit;
   int32_t phases;
   int32_t n_cu;          // 0: not queried yet
@@ -115,6 +117,15 @@ Workspace view(const moe_plan* p, void* base) {
   w.tile_order = (int32_t*)(b + p->off_tile_order);
   w.items0 = (ItemRec*)(b + p->off_items0);
   w.items1 = (ItemRec*)(b + p->off_items1);
+  // The heads of the queues, every workgroup's atomics on 8 words per launch: in cache lines of their own where the layer1 schedule
+  // leaves its room behind the items of all tiles unused (any order but the panel-major one and the large builder's).
+  w.queue_heads = w.status + 8;
+  w.head_stride = 1;
+  if (p->spread_heads) {
+    const int room = 3 * kXcds * p->n_tiles_n1 * (int)(sizeof(ItemRec) / 4);   // words; 12 per head and more
+    w.queue_heads = (int32_t*)(w.items1 + (size_t)p->max_tiles * p->n_tiles_n1);
+    w.head_stride = room / (2 * kXcds) < kHeadStride ? room / (2 * kXcds) : kHeadStride;
+  }
   w.panel_done = (uint32_t*)(b + p->off_panel_done);
   w.tile_done = (uint32_t*)(b + p->off_tile_done);
   w.arrive = (uint32_t*)(b + p->off_arrive);
@@ -531,11 +542,14 @@ int forward_impl(moe_plan_t* p, const void* x, const int32_t* topk_ids, const fl
     if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) return MOE_ERR_HIP;
     p->n_cu = n;
   }
+  const bool large = uses_large_schedule(p->max_tiles, p->large_schedule);
+  // (a launch of one item per workgroup has no use for it, and finds its heads and queue lengths in one line)
+  const int most_columns = p->n_tiles_n0 > p->n_tiles_n1 ? p->n_tiles_n0 : p->n_tiles_n1;
+  if (p->phases & 1) p->spread_heads = p->layer1_order != 1 && !large && (int64_t)p->max_tiles * most_columns > p->n_cu;
   Workspace ws = view(p, workspace);
   // The layer0 tile order of this forward: the schedule is built inside the forward, so it can follow what the
   // forward is given.  All rows resident: expert-major (weight reuse first).  Ready flags in use: waves of source
   // segments (Fig. 5).  The one-workgroup builder for very large tile tables knows orders 0 and 1 only.
-  const bool large = uses_large_schedule(p->max_tiles, p->large_schedule);
   int order0 = p->layer0_order >= 0 ? p->layer0_order : (seg_ready ? 2 : 0);
   if (order0 == 2 && large) order0 = 1;
   if (p->phases & 1) p->last_layer0_order = order0;
@@ -624,7 +638,8 @@ int forward_impl(moe_plan_t* p, const void* x, const int32_t* topk_ids, const fl
     a.prefetch_ahead = p->prefetch_ahead;
     a.prefetch_behind = p->prefetch_behind;
   }
-  a.queue_heads = ws.status + 8;
+  a.queue_heads = ws.queue_heads;
+  a.head_stride = ws.head_stride;
   a.queue_len = ws.status + 24;
   if (order0 != 1 && !large) {
     a.queue_base = ws.status + 48;   // contiguous per-XCD queues (locality order)
@@ -667,7 +682,8 @@ int forward_impl(moe_plan_t* p, const void* x, const int32_t* topk_ids, const fl
   b.topk_weights = topk_weights;
   b.out = (uint16_t*)out;
   b.combine_counter = ws.status + 4;
-  b.queue_heads = ws.status + 16;
+  b.queue_heads = ws.queue_heads + kXcds * ws.head_stride;
+  b.head_stride = ws.head_stride;
   b.queue_len = ws.status + 32;
   b.queue_base = ws.status + 40;
   b.queue_stride = 1;
