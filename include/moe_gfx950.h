@@ -219,9 +219,10 @@ int moe_get_index_outputs(const moe_plan_t *plan, const void *workspace, int32_t
 
 /* Tile table of the GroupGEMMs as built by the last forward (dev pointers, each [max_tiles], any may be
  * NULL, entries beyond *n_tiles untouched; n_tiles: dev int32 [1]): expert, first sorted row, rows, the
- * source segment the tile waits for, and the height (64 / 128 / 256 rows) of the kernel variant that
- * computes it.  An expert's rows are cut into tiles of "tile_m" rows; the remainder goes into shorter
- * tiles so that little of a tile is padding.  max_tiles >= moe_plan_max_tiles(plan). */
+ * source segment the tile waits for, and the height class (64 / 128 / 256 rows) it is scheduled in.  An
+ * expert's rows are cut into tiles of "tile_m" rows; the remainder is a tile of the same class, computed
+ * by the lowest kernel variant that holds its rows, so that little of a tile is padding; an expert of
+ * fewer rows has one tile of the lowest class that holds them.  max_tiles >= moe_plan_max_tiles(plan). */
 int moe_get_tile_table(const moe_plan_t *plan, const void *workspace, int32_t *n_tiles, int32_t *tile_expert,
                        int32_t *tile_row0, int32_t *tile_rows, int32_t *tile_ready_seg, int32_t *tile_height,
                        void *hip_stream);

@@ -386,7 +386,8 @@ struct Tile {
 };
 __device__ __forceinline__ ItemRec make_uniform(ItemRec r) {
   r.m_tile = uniform(r.m_tile); r.n_tile = uniform(r.n_tile); r.expert = uniform(r.expert); r.row0 = uniform(r.row0);
-  r.nrows = uniform(r.nrows); r.kind = uniform(r.kind); r.ready_seg = uniform(r.ready_seg);
+  r.nrows = uniform(r.nrows); r.ready_seg = uniform(r.ready_seg);
+  r.kind = r.nrows <= 64 ? 0 : (r.nrows <= 128 ? 1 : 2);   // the variant that computes it: the lowest that holds its rows, whatever its class in the table
   return r;
 }
 __device__ __forceinline__ ItemRec load_item(const GemmParams& p, int idx) { return make_uniform(p.items[idx]); }

@@ -88,15 +88,21 @@ __global__ __launch_bounds__(256) void k_index_hist(IndexParams p) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Tiling of an expert's rows: as many tiles of tile_m rows as fit, then one tile for the remainder, of the lowest
-// height that holds it.  (A remainder of 129 to 192 rows is not split into a 128- and a 64-row tile, for all that the ragged
-// tile pads it: tiles of different heights lie apart in the queues, tall ones first, so every height streams its
-// experts' weights from HBM once more, which costs what the matrix cores need for about 240 rows.  160 rows for each of 16
+// Tiling of an expert's rows: as many tiles of tile_m rows as fit, then one tile for the remainder.  Beside full tiles the
+// remainder's is of their height class, so that the schedule may put it next to them (see build_schedules), and light where
+// it has at most half as many rows: a GroupGEMM workgroup computes a tile with the lowest variant that holds its rows,
+// whatever its class.  An expert without full tiles has one tile of the lowest height that holds it.  (A remainder of
+// 129 to 192 rows is not split into a 128- and a 64-row tile, for all that the ragged tile pads it: every tile of a column streams
+// the expert's weights, which costs what the matrix cores need for about 240 rows.  160 rows for each of 16
 // experts with F = 6400: 941 -> 611 us, 400 rows 1385 -> 1022.)
 // ---------------------------------------------------------------------------------------------
+__device__ inline int height_class(int rows) { return rows <= 64 ? 0 : (rows <= 128 ? 1 : 2); }
+// (of the tallest class: the others' tiles are the lowest that hold their rows)
+__device__ inline bool is_light(int rows, int kind) { return height_class(rows) < kind; }
 __device__ inline int tail_height(int rows, int tile_m) {   // height of the tile that holds the remainder; 0: there is none
   const int rem = rows % tile_m;
   if (rem == 0) return 0;
+  if (rows > tile_m) return tile_m;   // beside full tiles
   return rem <= 64 || tile_m == 64 ? 64 : (rem <= 128 || tile_m == 128 ? 128 : 256);
 }
 
@@ -279,7 +285,7 @@ __global__ __launch_bounds__(256) void k_index_scatter(IndexParams p) {
 // workgroup takes the next position of its own XCD's share and, when that is used up, of the others'), so
 // consecutive positions should differ in the column tile and keep the M-tile: the workgroups of one XCD then
 // work on few column tiles of many M-tiles and share weight panels in their L2.  Tall tiles come first and the
-// short tiles of the ragged ends last, so that the short ones fill the gaps at the end of the kernel.
+// short tiles last, so that the short ones fill the gaps at the end of the kernel.
 // The orders (k_index_schedule, for up to 2048 M-tiles; see there for the locality order):
 // Layer0, order 0: locality order (blocks of an expert's M-tiles per XCD, column tiles ascending inside a block).
 // Order 1: per tile height, M-tiles by the segment they wait for (Fig. 5: rows that are local or arrive early first),
@@ -464,12 +470,13 @@ __global__ __launch_bounds__(1024) void k_index_schedule_large(IndexParams p) {
 // the size limit (and with simpler orders).
 //
 // Locality order (layer0 with order 0, layer1 with the separate combine kernel): per tile height, an expert's
-// M-tiles are cut into blocks of up to block_m (4 by default); the blocks are dealt to the XCDs, whose queues hold
+// M-tiles are cut into blocks of up to block_m (4 by default, a light tile beside them not counted); the blocks are dealt to the XCDs, whose queues hold
 // their blocks one after the other, tallest first.  Inside a block of G M-tiles the column tiles ascend and the block's M-tiles are the inner
 // loop.  The 32 workgroups of an XCD, taking consecutive items, then work on G M-tiles x about 32/G column tiles of
 // one expert wherever in the block they are, and share both operands in their L2; an expert with few rows is
 // streamed through one XCD only (its weight panels are fetched once).
 constexpr int kRankTiles = 96;       // M-tiles up to which they are ranked against each other
+constexpr int kBesideItems = 128;    // light items of a layer, of experts of one block, from which on light tiles lie beside full ones
 constexpr int kFewItems = 128;       // items of a layer up to which they are dealt out without blocks
 constexpr int kScheduleWgs = 64;   // at most; one per 1024 items up to there (8 for 35 k items: 44 us)
 
@@ -480,6 +487,7 @@ struct ScheduleLds {
   uint16_t ord0[kTileCap];     // layer0 order: position -> tile
   uint16_t ord1[kTileCap];     // layer1 order (height class, then table order)
   uint16_t blk_g[kTileCap];    // M-tiles of block b
+  uint16_t blk_first[kTileCap];   // position in the order of block b's first tile
   uint16_t blk_ord[kTileCap];  // blocks in dealing order: height class, then larger blocks first
   uint8_t blk_q[kTileCap];     // XCD queue of block b
   uint8_t blk_key[kTileCap + 4];
@@ -488,11 +496,13 @@ struct ScheduleLds {
   uint8_t ready[kTileCap];
   uint8_t key0[kTileCap + 4];   // (height class, segment) or the height class alone; padded with 0xff
   uint8_t key1[kTileCap + 4];   // height class
+  uint8_t key2[kTileCap + 4];   // the same with the light tiles of the tallest class behind it
   uint16_t sub_first[kTileCap];       // position in ord1 of the first tile of tile i's run (same height, expert, wave)
   uint16_t blk_of[kTileCap];          // block of the tile at position i of ord1
   int32_t scan_buf[16];               // scratch of the prefix scans
   int32_t cls_first[4];
   int32_t cls_count[3];
+  int32_t n_light, n_light_near;   // light tiles; those of experts of one block
   int32_t queue_pos[3][kXcds];
   int32_t q_len_t[kXcds], q_base_t[kXcds];   // locality order: M-tiles per XCD queue, and ahead of it
   int32_t n_blocks;
@@ -556,21 +566,25 @@ __device__ inline void scan_pairs(int32_t* buf, int& v0, int& v1) {
   v1 = join(before, v1);
 }
 
-// rank_sort for the three height classes alone, up to kTileCap tiles: two counts in one scan instead of a pass over all keys
-// per tile (the schedule kernel for 250 tiles of 64 experts: 21.6 us with that, 17.4 so; up to kRankTiles tiles the pass is the shorter).  n0, n1: tiles of the first two classes.
-__device__ inline void class_sort(const uint8_t* key, uint16_t* ord, int n, int n0, int n1, int32_t* buf) {
+// rank_sort for the height classes alone (n2 > 0: four classes), up to kTileCap tiles: two counts in one scan instead of a pass over all keys
+// per tile (the schedule kernel for 250 tiles of 64 experts: 21.6 us with that, 17.4 so; up to kRankTiles tiles the pass is the shorter).  n0, n1, n2: tiles of the first classes.
+__device__ inline void class_sort(const uint8_t* key, uint16_t* ord, int n, int n0, int n1, int n2, int32_t* buf) {
   static_assert(kTileCap <= 2048, "counts of 16 bits, two tiles per thread");
   const int i0 = 2 * threadIdx.x, i1 = i0 + 1;
-  const int k0 = i0 < n ? key[i0] : 2, k1 = i1 < n ? key[i1] : 2;
+  const int k0 = i0 < n ? key[i0] : 3, k1 = i1 < n ? key[i1] : 3;
   auto one = [](int k) { return k == 0 ? 1 : (k == 1 ? 1 << 16 : 0); };
   int s0 = one(k0), s1 = one(k1);
   scan_pairs<false>(buf, s0, s1);   // of the first and second class up to and including this tile
-  auto place = [&](int i, int k, int s) {
-    const int a = s & 0xffff, b = s >> 16;
-    ord[k == 0 ? a - 1 : (k == 1 ? n0 + b - 1 : n0 + n1 + i - a - b)] = (uint16_t)i;
+  int t0 = k0 == 2, t1 = k1 == 2;
+  if (n2 > 0) scan_pairs<false>(buf, t0, t1);   // ... of the third, where there may be a fourth
+  auto place = [&](int i, int k, int s, int t) {
+    const int a = s & 0xffff, b = s >> 16, rest = i - a - b;
+    int at = k == 0 ? a - 1 : (k == 1 ? n0 + b - 1 : n0 + n1 + rest);
+    if (n2 > 0 && k >= 2) at = k == 2 ? n0 + n1 + t - 1 : n0 + n1 + n2 + rest - t;
+    ord[at] = (uint16_t)i;
   };
-  if (i0 < n) place(i0, k0, s0);
-  if (i1 < n) place(i1, k1, s1);
+  if (i0 < n) place(i0, k0, s0, t0);
+  if (i1 < n) place(i1, k1, s1, t1);
 }
 
 // Items of one layer in the locality order (see above); n_tiles_n column tiles.
@@ -578,7 +592,7 @@ __device__ inline void emit_blocks(const ScheduleLds& L, const uint16_t* ord, It
                                    int block_m, int gtid, int gthreads) {
   for (int w = gtid; w < n_tiles * n_tiles_n; w += gthreads) {
     const int i = w / n_tiles_n, n = w % n_tiles_n;
-    const int b = L.blk_of[i], g = L.blk_g[b], jm = (i - L.sub_first[i]) % block_m;
+    const int b = L.blk_of[i], g = L.blk_g[b], jm = i - L.blk_first[b];
     const int pos = (L.q_base_t[L.blk_q[b]] + L.blk_off[b]) * n_tiles_n + n * g + jm;
     items[pos] = make_item_lds(L, ord[i], n);
   }
@@ -586,18 +600,19 @@ __device__ inline void emit_blocks(const ScheduleLds& L, const uint16_t* ord, It
 
 // Blocks of the locality order and their XCD queues.  The tiles (in ord1's order: height class, expert, source order)
 // fall into runs of the same height class, expert and wave -- a wave being a group of consecutive source segments,
-// n_waves of them over the S segments (1: no waves) -- and every run is cut into blocks of up to block_m M-tiles.
+// n_waves of them over the S segments (1: no waves) -- and every run is cut into blocks of up to block_m M-tiles.  beside: a
+// light tile is in its expert's last block; otherwise the light tiles are a class of their own.
 // The blocks are sorted by (wave, height class, larger first) and dealt to the XCD queues back and forth (0..7,
 // 7..0, ...): with the sizes descending this keeps the queues level even when the experts' loads differ a lot, which
 // round-robin does not (what is left uneven, the workgroups even out by taking from other XCDs' queues at the end).
 // With waves the queues are segment-major across waves (tiles whose rows arrive early come first, Fig. 5) and
 // weight-panel-major inside a wave (a block's M-tiles share every weight panel they sweep).
-__device__ inline void build_blocks(ScheduleLds& L, const uint16_t* ord1, int n_tiles, int block_m, int n_waves, int S) {
+__device__ inline void build_blocks(ScheduleLds& L, const uint16_t* ord1, int n_tiles, int block_m, int n_waves, int S, bool beside) {
   const int tid = threadIdx.x;
   auto run_key = [&](int i) {
     const int m = ord1[i];
     const int wave = n_waves > 1 ? (int)L.ready[m] * n_waves / S : 0;
-    return ((2 - (int)L.kind[m]) << 16) | ((int)L.expert[m] << 8) | wave;
+    return ((int)(beside ? L.key1[m] : L.key2[m]) << 16) | ((int)L.expert[m] << 8) | wave;
   };
   if (tid < kXcds) L.q_len_t[tid] = 0;
   const int i0 = 2 * tid, i1 = 2 * tid + 1;
@@ -606,8 +621,9 @@ __device__ inline void build_blocks(ScheduleLds& L, const uint16_t* ord1, int n_
   if (i1 < n_tiles && run_key(i1) != run_key(i1 - 1)) f1 = i1;
   scan_pairs<true>(L.scan_buf, f0, f1);
   int s0 = 0, s1 = 0;
-  if (i0 < n_tiles) { L.sub_first[i0] = (uint16_t)f0; s0 = (i0 - f0) % block_m == 0; }
-  if (i1 < n_tiles) { L.sub_first[i1] = (uint16_t)f1; s1 = (i1 - f1) % block_m == 0; }
+  auto starts = [&](int i, int f) { return (i - f) % block_m == 0 && !(i > f && beside && is_light(L.rows[ord1[i]], L.kind[ord1[i]])); };
+  if (i0 < n_tiles) { L.sub_first[i0] = (uint16_t)f0; s0 = starts(i0, f0); }
+  if (i1 < n_tiles) { L.sub_first[i1] = (uint16_t)f1; s1 = starts(i1, f1); }
   const int start0 = s0, start1 = s1;
   scan_pairs<false>(L.scan_buf, s0, s1);
   if (i0 < n_tiles) L.blk_of[i0] = (uint16_t)(s0 - 1);
@@ -617,10 +633,11 @@ __device__ inline void build_blocks(ScheduleLds& L, const uint16_t* ord1, int n_
   __syncthreads();
   auto describe = [&](int i, int b) {   // tile i starts block b
     int g = 1;
-    while (g < block_m && i + g < n_tiles && L.sub_first[i + g] == L.sub_first[i]) g++;
+    while (i + g < n_tiles && L.blk_of[i + g] == b) g++;
     const int key = run_key(i);
     L.blk_g[b] = (uint16_t)g;
-    L.blk_key[b] = (uint8_t)((key & 0xff) * 24 + (key >> 16) * 8 + (8 - g));   // wave, height class, larger blocks first
+    L.blk_first[b] = (uint16_t)i;
+    L.blk_key[b] = (uint8_t)((key & 0xff) * 32 + (key >> 16) * 8 + (8 - min(g, 8)));   // wave, class, larger blocks first
   };
   if (i0 < n_tiles && start0) describe(i0, s0 - 1);
   if (i1 < n_tiles && start1) describe(i1, s1 - 1);
@@ -665,7 +682,11 @@ __device__ inline void note_tile(ScheduleLds& L, const IndexParams& p, const int
   L.ready[m] = (uint8_t)s;
   L.key0[m] = (uint8_t)((2 - kind) * nseg + (nseg > 1 ? s : 0));
   L.key1[m] = (uint8_t)(2 - kind);
+  const bool light = is_light(nrows, kind);   // (only of the tallest class)
+  const int below = height_class(p.tile_m) - kind;
+  L.key2[m] = (uint8_t)(below == 0 ? light : below + 1);
   atomicAdd(&L.cls_count[2 - kind], 1);
+  if (light) atomicAdd(&L.n_light, 1);
   if (publish) p.ws.tile_ready[m] = s;
 }
 
@@ -678,12 +699,32 @@ __device__ inline void build_schedules(ScheduleLds& L, const IndexParams& p, int
   const bool local0 = p.layer0_order != 1, local1 = p.layer1_order == 0;
   const int n_waves0 = p.layer0_order == 2 ? max(1, min(waves, min(S, 8))) : 1;
   const int block_m = p.block_m;   // M-tiles per block of the locality order (1..8)
-  if (nseg > 1) rank_sort(L.key1, L.ord1, n_tiles, tid);
-  if (nseg > 1 || n_tiles <= kRankTiles) {
-    rank_sort(L.key0, L.ord0, n_tiles, tid);
-  } else {
-    class_sort(L.key1, L.ord0, n_tiles, L.cls_count[0], L.cls_count[1], L.scan_buf);
-  }
+  // Where the light tiles lie in the locality order of a layer: in the block of their expert's full tiles (beside), with which
+  // they then share the weights in the L2 instead of streaming them again, or behind all full tiles, where they fill the gaps at the
+  // end of the launch.  The first pays where there are enough of them, the second where a launch is few rounds of long tiles; and an
+  // expert of several blocks saves the least.  us per layer, behind / beside: 2 full tiles and a light one for each of 64 experts (9000
+  // tokens, top-4, F = 1408; 704 and 512 light items) 731 / 630, for half of them (8192 tokens; 319 and 232) 607 / 567, (4096 tokens, top-8, F =
+  // 2560; 580 and 406) 1707 / 1641; one full tile (1060 tokens of 8 experts of F = 7168) 545 / 497; 112 and 64 items (2047 tokens of 8 experts)
+  // 381 / 414; 8 full tiles (8192 tokens of 8 experts of F = 14336, 448 items in layer0) 4045 / 4088.
+  for (int m = tid; m < n_tiles; m += 1024)
+    if (is_light(L.rows[m], L.kind[m]) && !(m > block_m && L.expert[m - block_m - 1] == L.expert[m])) atomicAdd(&L.n_light_near, 1);
+  __syncthreads();
+  const bool beside0 = !local0 || L.n_light_near * p.n_tiles_n0 >= kBesideItems;
+  const bool beside1 = !local1 || L.n_light_near * p.n_tiles_n1 >= kBesideItems;
+  auto sort_tiles = [&](uint16_t* ord, bool beside) {   // tallest class first, then table order
+    if (n_tiles <= kRankTiles) {
+      rank_sort(beside ? L.key1 : L.key2, ord, n_tiles, tid);
+    } else if (beside) {
+      class_sort(L.key1, ord, n_tiles, L.cls_count[0], L.cls_count[1], 0, L.scan_buf);
+    } else {
+      const int top = 2 - height_class(p.tile_m), n0 = L.cls_count[top];
+      class_sort(L.key2, ord, n_tiles, n0 - L.n_light, L.n_light, top < 2 ? L.cls_count[top + 1] : 0, L.scan_buf);
+    }
+  };
+  if (nseg > 1) rank_sort(L.key0, L.ord0, n_tiles, tid);
+  else sort_tiles(L.ord0, beside0);
+  const bool two_orders = nseg > 1 || (L.n_light > 0 && beside0 != beside1);
+  if (two_orders) sort_tiles(L.ord1, beside1);
   if (tid == 0) {
     int pos = 0;
     for (int c = 0; c < 3; c++) {
@@ -712,7 +753,7 @@ __device__ inline void build_schedules(ScheduleLds& L, const IndexParams& p, int
     }
   }
   __syncthreads();
-  const uint16_t* ord1 = nseg > 1 ? L.ord1 : L.ord0;   // height class, then table order (expert-major)
+  const uint16_t* ord1 = two_orders ? L.ord1 : L.ord0;   // height class, then table order (expert-major)
   // So few items that most workgroups get none and none gets a second: there is no locality to arrange, the items are
   // dealt out one by one (the block tables cost 4 us, of 38 us for a layer of 128 tokens and H = 256).
   if (local0 && local1 && n_waves0 == 1 && n_tiles * max(p.n_tiles_n0, p.n_tiles_n1) <= kFewItems) {
@@ -731,21 +772,21 @@ __device__ inline void build_schedules(ScheduleLds& L, const IndexParams& p, int
     return;
   }
   if (local0) {
-    build_blocks(L, ord1, n_tiles, block_m, n_waves0, S);
+    build_blocks(L, L.ord0, n_tiles, block_m, n_waves0, S, beside0);
     if (first && tid < kXcds) {
       p.ws.status[24 + tid] = L.q_len_t[tid] * p.n_tiles_n0;
       p.ws.status[48 + tid] = L.q_base_t[tid] * p.n_tiles_n0;
     }
-    emit_blocks(L, ord1, p.ws.items0, n_tiles, p.n_tiles_n0, block_m, gtid, gthreads);
+    emit_blocks(L, L.ord0, p.ws.items0, n_tiles, p.n_tiles_n0, block_m, gtid, gthreads);
   } else {
     // by source segment (Fig. 5): all column tiles of an M-tile in a row; list position i belongs to XCD i % 8
     for (int i = gtid; i < n_tiles * p.n_tiles_n0; i += gthreads)
       p.ws.items0[i] = make_item_lds(L, L.ord0[i / p.n_tiles_n0], i % p.n_tiles_n0);
   }
   if (local1) {
-    if (!local0 || n_waves0 > 1) {
+    if (!local0 || n_waves0 > 1 || two_orders) {
       __syncthreads();   // the layer0 items are out: the block tables can be rebuilt without waves
-      build_blocks(L, ord1, n_tiles, block_m, 1, S);
+      build_blocks(L, ord1, n_tiles, block_m, 1, S, beside1);
     }
     if (first && tid < kXcds) {
       p.ws.status[32 + tid] = L.q_len_t[tid] * p.n_tiles_n1;
@@ -784,11 +825,13 @@ __global__ __launch_bounds__(1024) void k_index_schedule(IndexParams p) {
   const int tid = threadIdx.x;
   if (tid <= p.s.S) seg_lds[tid] = p.seg_offsets[tid];
   if (tid < 3) L.cls_count[tid] = 0;
+  if (tid == 3) L.n_light = L.n_light_near = 0;
   __syncthreads();
   for (int m = tid; m < n_tiles + 4; m += 1024) {
     if (m >= n_tiles) {
       L.key0[m] = 0xff;
       L.key1[m] = 0xff;
+      L.key2[m] = 0xff;
       continue;
     }
     const int r0 = p.ws.tile_row0[m], nr = p.ws.tile_rows[m], kd = p.ws.tile_kind[m];
@@ -824,6 +867,7 @@ __global__ __launch_bounds__(1024) void k_index_small(IndexParams p, int schedul
   for (int i = tid; i < n_runs * E; i += 1024) run_cnt[i] = 0;
   if (tid <= p.s.S) seg_lds[tid] = p.seg_offsets[tid];
   if (tid < 3) L.cls_count[tid] = 0;
+  if (tid == 3) L.n_light = L.n_light_near = 0;
   if (tid < kMaxExperts) cnt[tid] = 0;
   __syncthreads();
 #pragma unroll
@@ -926,6 +970,7 @@ __global__ __launch_bounds__(1024) void k_index_small(IndexParams p, int schedul
     if (m >= n_tiles) {
       L.key0[m] = 0xff;
       L.key1[m] = 0xff;
+      L.key2[m] = 0xff;
       continue;
     }
     int lo = 0, hi = E - 1;   // the last expert whose first tile is at most m (experts without tiles share the next one's)

@@ -270,9 +270,8 @@ bool decode_path(const moe_plan* p, int n_tiles_n, int64_t K, int64_t ldb, bool 
 // It does not pay where the caches would have the weights for somebody:
 //  * weights of less than half the Infinity Cache (256 MB), so that those of two layers in turn stay there: 3 plans in turn, 82 MB each
 //    36.3 / 37.1, plain weights 51.4 / 54.4; 145 MB 47.7 / 43.8, 130 MB 44.0 / 40.6;
-//  * tile kernel: experts of so many rows that several XCDs stream the same weights.  Rows per expert 187 (64 experts) 874 / 851, 275 (8) 1100 /
-//    1068, 312 (16) 1026 / 1021, 344 (64) 566 / 556, 375 (8) 1095 / 1135, (16) 1024 / 1037, (64) 1509 / 1489, 512 (8) 408 / 420,
-//    2048 (8) 4165 / 4211.
+//  * tile kernel: experts of more than one tile, whose tiles share the weights.  us with the hint / without at 200 rows per expert (64
+//    experts) 847 / 869, 206 316 / 323, 237 920 / 953, 250 391 / 368, (16 experts) 770 / 740, 320 (8) 1150 / 1004, 300 (64) 1503 / 1221.
 bool weights_pass_caches(const Shape& s) {
   return expected_experts(s) * ((double)s.H * s.F1 + (double)s.F * s.H) * 2 > kCachedWeightBytes;
 }

@@ -23,7 +23,7 @@ constexpr int kCombineChunk = 256;  // tokens per unit of combine work
 constexpr int kDecodeRowsPerExpert = 16;   // rows per expert on average up to which the decode kernel is used ...
 constexpr int kDecodeRowsManyTiles = 8;    // ... and where the tile kernel has more tiles than compute units
 constexpr double kCachedWeightBytes = 128e6;   // weights read by a forward beyond which its loads of them are non-temporal ...
-constexpr int kStreamRowsPerExpert = 320;   // ... in the tile kernel up to this many rows per expert on average
+constexpr int kStreamRowsPerExpert = 244;   // ... in the tile kernel up to this many rows per expert on average
 constexpr int kDefaultCus = 256;    // compute units a plan assumes before it has seen the device
 constexpr int kXcds = 8;            // XCDs of the device: workgroup i runs on XCD i % 8
 constexpr int kScheduleTileCap = 2048;  // M-tiles up to which the multi-workgroup schedule builder is used
@@ -57,7 +57,7 @@ struct Workspace {
   int32_t* tile_row0;     // [max_tiles]
   int32_t* tile_rows;     // [max_tiles]
   int32_t* tile_ready;    // [max_tiles] source segment the tile waits for
-  int32_t* tile_kind;     // [max_tiles] 0 / 1 / 2: the tile is computed by the 64 / 128 / 256-row kernel variant
+  int32_t* tile_kind;     // [max_tiles] height class 0 / 1 / 2 the tile is scheduled in: 64 / 128 / 256 rows
   int32_t* tile_order;    // [max_tiles] scratch of the schedule builder: tiles sorted tallest first
   ItemRec* items0;        // [max_tiles * n_tiles_n0] layer0 schedule
   ItemRec* items1;        // [(max_tiles + 24) * n_tiles_n1] layer1 schedule, one contiguous queue per XCD
