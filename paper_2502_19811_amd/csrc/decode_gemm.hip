@@ -36,7 +36,8 @@ constexpr int kDecodeWaves = 2;                    // of a workgroup
 constexpr int kUnitChunk = 2;                      // consecutive units on one XCD
 constexpr uint32_t kRowsEnd = 1u << 31;            // no row of A has an offset of this or more; past it a load returns zeros
 constexpr int kDecodeTileCap = 384;                // tiles of a batch the kernel is used for: at most 4096 / 64 full ones and 256 others
-static_assert(kDecodeTileCap % 64 == 0 && kDecodeTileCap >= kDecodeRowsPerExpert * kMaxExperts / 64 + kMaxExperts, "tiles of the largest batch");
+static_assert(kDecodeTileCap % 64 == 0 && kDecodeTileCap >= kDecodeRowsPerExpert * kMaxExperts / 64 + kMaxExperts &&
+              kDecodeTileCap >= kDecodeCachedRows / 64 + kMaxExperts && kDecodeCachedRows < 65536, "tiles of the largest batch");
 constexpr int kStageBytes = kTileK * kTileN * 2;   // packed weights: one K step of one column tile
 constexpr int kPlainPitch = 144;                   // bytes between rows of K in the transposing buffer (64 columns + padding)
 constexpr int kNonTemporal = 2;                    // cache policy of a buffer load: the nt bit
@@ -48,11 +49,178 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer(const char* ptr, uint32
   return __builtin_amdgcn_make_buffer_rsrc((void*)uniform(ptr), 0, bytes, 0x00020000);
 }
 
+// What a workgroup's wavefronts find their units in: the rows of the batch in slots, the tiles of the table or the experts.
+struct UnitTable {
+  int32_t unit0[kDecodeTileCap];   // units of the slots before
+  uint16_t row0[kDecodeTileCap], rows[kDecodeTileCap];
+  uint8_t expert[kDecodeTileCap], seg[kDecodeTileCap];
+  uint16_t token[kOwnIndexRows];   // own_index: row -> token
+  int32_t n_units;
+};
+
+// unit0 and n_units from the rows of n slots; for one wavefront.
+__device__ __forceinline__ void number_units(UnitTable& L, int n, int rows_per_unit, int n_groups) {
+  const int lane = threadIdx.x & 63;
+  int n_units = 0;
+#pragma unroll 1
+  for (int i0 = 0; i0 < n; i0 += 64) {
+    const int rows = i0 + lane < n ? L.rows[i0 + lane] : 0;
+    const int mine = (rows + rows_per_unit - 1) / rows_per_unit * n_groups;
+    int incl = mine;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int o = __shfl_up(incl, d);
+      if (lane >= d) incl += o;
+    }
+    L.unit0[i0 + lane] = n_units + incl - mine;   // (the capacity is a multiple of 64)
+    n_units += uniform(__shfl(incl, 63));
+  }
+  if (lane == 0) L.n_units = n_units;
+}
+
+// The tile table of the index build.  All of it is asked for at once, before the number of tiles is known.
+__device__ __forceinline__ int load_table(UnitTable& L, const DecodeParams& p, int rows_per_unit, int n_groups, bool flagged) {
+  const int n_tiles = min(*p.n_tiles, kDecodeTileCap);
+  for (int i = threadIdx.x; i < p.n_slots; i += kDecodeWaves * 64) {
+    L.row0[i] = (uint16_t)p.tile_row0[i];
+    L.rows[i] = (uint16_t)p.tile_rows[i];
+    L.expert[i] = (uint8_t)p.tile_expert[i];
+    if (flagged) L.seg[i] = (uint8_t)p.tile_ready[i];
+  }
+  __syncthreads();
+  if (threadIdx.x < 64) number_units(L, n_tiles, rows_per_unit, n_groups);
+  __syncthreads();
+  return n_tiles;
+}
+
+// The index of a batch of up to kOwnIndexRows pairs, by every workgroup for itself from the expert ids: stable ranks by ballots over runs
+// of 64 pairs, as k_index_small makes them.  The slots are the experts.  That launch of one workgroup takes 5 us whatever the batch, and the
+// table it leaves is three dependent round trips to memory at the start of a GroupGEMM launch; the ids are one.  out: the
+// workgroup that leaves the index of this forward in the workspace too, as k_index_small does without schedules, for the reduction and whoever
+// asks for it.  us per gate + layer, with k_index_small / so: 1 token of 8 experts of F = 1792 37.7 / 34.0, 16 tokens 70.2 / 67.5, 33 plain
+// 78.4 / 76.3, 1 token of F = 14336 121 / 119; 384 to 480 pairs 579 / 578, 194.2 / 195.3.
+__device__ __forceinline__ void own_index(UnitTable& L, const DecodeParams& p, int rows_per_unit, int n_groups, const IndexParams& ip, bool out) {
+  constexpr int kRuns = kOwnIndexRows / 64;
+  const int tid = threadIdx.x, lane = tid & 63, E = p.E, R = p.R;
+  __shared__ int32_t tile0[kMaxExperts + 1];   // out: tiles of the experts before
+  if (tid < 64) {
+    int key[kRuns], rank[kRuns];
+#pragma unroll
+    for (int i = 0; i < kRuns; i++) key[i] = i * 64 + lane < R ? p.topk_ids[i * 64 + lane] : -1;
+    for (int e = lane; e < E; e += 64) L.rows[e] = 0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+    for (int i = 0; i < kRuns; i++) {
+      if (i * 64 >= R) break;
+      const bool valid = i * 64 + lane < R;
+      int e = key[i];
+      if (valid && (unsigned)e >= (unsigned)E) {   // not an expert: reported through the status word, counted as the last expert
+        if (out) ip.ws.status[5] = ip.forward_serial;
+        e = E - 1;
+      }
+      uint64_t same = __ballot(valid);
+#pragma unroll
+      for (int bit = 0; bit < 8; bit++) {
+        const uint64_t b = __ballot((e >> bit) & 1);
+        same &= ((e >> bit) & 1) ? b : ~b;
+      }
+      const uint64_t below = same & ((1ull << lane) - 1ull);
+      const int before = valid ? L.rows[e] : 0;   // in the runs before
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      if (valid && below == 0) L.rows[e] = (uint16_t)(before + __popcll(same));
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      key[i] = e;
+      rank[i] = before + __popcll(below);
+    }
+    int rows_before = 0;
+#pragma unroll 1
+    for (int e0 = 0; e0 < E; e0 += 64) {
+      const int rows = e0 + lane < E ? L.rows[e0 + lane] : 0;
+      int incl = rows;
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const int o = __shfl_up(incl, d);
+        if (lane >= d) incl += o;
+      }
+      if (e0 + lane < E) {
+        L.row0[e0 + lane] = (uint16_t)(rows_before + incl - rows);
+        L.expert[e0 + lane] = (uint8_t)(e0 + lane);
+      }
+      rows_before += uniform(__shfl(incl, 63));
+    }
+    number_units(L, E, rows_per_unit, n_groups);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+    for (int i = 0; i < kRuns; i++) {
+      const int q = i * 64 + lane;
+      if (q < R) {
+        const int pos = L.row0[key[i]] + rank[i], t = q / p.k;
+        L.token[pos] = (uint16_t)t;
+        if (out) {
+          ip.ws.perm[pos] = q;
+          ip.ws.inv_perm[q] = pos;
+          ip.ws.row_token[pos] = t;
+        }
+      }
+    }
+    if (out) {
+      const int tile_m = ip.tile_m;
+      int tiles_before = 0;
+#pragma unroll 1
+      for (int e0 = 0; e0 < E; e0 += 64) {
+        const int rows = e0 + lane < E ? L.rows[e0 + lane] : 0, tiles = (rows + tile_m - 1) / tile_m;
+        int incl = tiles;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+          const int o = __shfl_up(incl, d);
+          if (lane >= d) incl += o;
+        }
+        if (e0 + lane < E) tile0[e0 + lane] = tiles_before + incl - tiles;
+        tiles_before += uniform(__shfl(incl, 63));
+      }
+      if (lane == 0) tile0[E] = tiles_before;
+      const int waves = waves_now(ip, lane);
+      if (lane == 0) ip.ws.status[7] = waves;
+    }
+  }
+  __syncthreads();
+  if (!out) return;
+  for (int i = tid; i < ip.n_tiles_n1; i += kDecodeWaves * 64) ip.ws.panel_done[i] = 0;
+  for (int i = tid; i < ip.max_tiles + 1; i += kDecodeWaves * 64) ip.ws.tile_done[i] = 0;
+  if (tid < 2 * kXcds) ip.ws.queue_heads[tid * ip.ws.head_stride] = 0;
+  if (tid == 0) {
+    const int n_tiles = tile0[E];
+    ip.ws.status[0] = 0;
+    ip.ws.status[1] = n_tiles;
+    ip.ws.status[2] = n_tiles * ip.n_tiles_n0;
+    ip.ws.status[3] = n_tiles * ip.n_tiles_n1;
+    ip.ws.status[4] = 0;
+    ip.ws.status[6] = kScheduleOwed;
+    ip.ws.offsets[E] = R;
+  }
+  for (int e = tid; e < E; e += kDecodeWaves * 64) {
+    const int rows = L.rows[e], row0 = L.row0[e], tile_m = ip.tile_m;
+    ip.ws.counts[e] = rows;
+    ip.ws.offsets[e] = row0;
+    for (int i = 0; i * tile_m < rows; i++) {
+      const int m = tile0[e] + i, n = min(rows - i * tile_m, tile_m);
+      const int last = L.token[row0 + i * tile_m + n - 1];
+      int s = 0;
+      while (s + 1 < ip.s.S && ip.seg_offsets[s + 1] <= last) s++;
+      ip.ws.tile_expert[m] = e;
+      ip.ws.tile_row0[m] = row0 + i * tile_m;
+      ip.ws.tile_rows[m] = n;
+      ip.ws.tile_kind[m] = height_class(n == tile_m ? tile_m : tail_height(rows, tile_m));
+      ip.ws.tile_ready[m] = s;
+    }
+  }
+}
+
 // NB: 16-column blocks of weights of a wavefront (SwiGLU: half of them gate, half up columns of the same hidden units);
 // RB: 8-row groups of A that are loaded (a unit is up to 8 RB rows); U: steps in flight; EU: wavefronts a SIMD holds; STREAM:
 // the loads of B are non-temporal (GemmParams::b_stream).
 template <int MODE, bool PK, int NB, int RB, int U, int EU, bool STREAM>
-__global__ __launch_bounds__(kDecodeWaves * 64) __attribute__((amdgpu_waves_per_eu(EU))) void k_decode_gemm(DecodeParams p) {
+__global__ __launch_bounds__(kDecodeWaves * 64) __attribute__((amdgpu_waves_per_eu(EU))) void k_decode_gemm(DecodeParams p, IndexParams ip) {
   constexpr bool kPair = MODE == MODE_L0_SWIGLU;
   constexpr int ROWS = 8 * RB;
   constexpr int RR = (RB + 1) / 2;                     // 16-row blocks
@@ -67,11 +235,10 @@ __global__ __launch_bounds__(kDecodeWaves * 64) __attribute__((amdgpu_waves_per_
   static_assert(!kAhead || U % 2 == 0, "the fragments of A alternate between two sets of registers");
   __shared__ __attribute__((aligned(16))) f32x4 swap_lds[kTwoWaves ? 2 : 1][2][kTwoWaves ? RR * 2 : 1][kTwoWaves ? 64 : 1];
   __shared__ __attribute__((aligned(128))) char operands[kDecodeWaves * kWaveBytes];
-  __shared__ int32_t unit0[kDecodeWaves][kDecodeTileCap];
+  __shared__ UnitTable L;
   __shared__ int given_up[2][2];   // [turn][wavefront]: no rows for this unit
 
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int n_tiles = min(*p.n_tiles, kDecodeTileCap);
   // Source segments that have arrived.  A unit waits for its tile's segment only, and starts early where that is there.
   uint64_t there = ~0ull;
   bool patient = true;   // false once a wait has run out: what is missing then is not waited for again
@@ -83,27 +250,29 @@ __global__ __launch_bounds__(kDecodeWaves * 64) __attribute__((amdgpu_waves_per_
   const bool flagged = MODE != MODE_L1 && p.seg_ready != nullptr;
   if (flagged) look();
 
-  // Units: (tile, columns, row part), the parts fastest.  unit0[i]: the units of the tiles before tile i.
+  // Units: (slot of the table, columns, row part), the parts fastest.
   const int nk = p.K / kStepK;
   const int n_groups = p.N / (OB * 16);
-  int n_units = 0;
-#pragma unroll 1
-  for (int i0 = 0; i0 < n_tiles; i0 += 64) {
-    const int rows = i0 + lane < n_tiles ? p.tile_rows[i0 + lane] : 0;
-    int incl = (rows + ROWS - 1) / ROWS * n_groups;
-    const int mine = incl;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int o = __shfl_up(incl, d);
-      if (lane >= d) incl += o;
-    }
-    unit0[w][i0 + lane] = n_units + incl - mine;
-    n_units += uniform(__shfl(incl, 63));
+  constexpr bool kMayWriteIndex = MODE != MODE_L1;
+  const int index_blocks = kMayWriteIndex && p.own_index ? kXcds : 0;   // at the front of the grid, see own_index
+  if (kMayWriteIndex && index_blocks && blockIdx.x > 0 && (int)blockIdx.x < index_blocks) return;
+  const int block = (int)blockIdx.x - index_blocks;
+  int n_slots;
+  if (p.own_index) {
+    n_slots = p.E;
+    own_index(L, p, ROWS, n_groups, ip, kMayWriteIndex && block < 0);
+    if (kMayWriteIndex && block < 0) return;
+  } else {
+    n_slots = load_table(L, p, ROWS, n_groups, flagged);
   }
+  const int n_units = uniform(L.n_units);
+  // the source segment of a token: those that end at it or before
+  const int seg_end = flagged && p.own_index && lane < p.n_segments - 1 ? ip.seg_offsets[lane + 1] : 0x7fffffff;
+  auto segment_of = [&](int token) { return (int)__popcll(__ballot(seg_end <= token)); };
   // Chunks of kUnitChunk consecutive units go to the XCDs in turn, so that the parts of an expert's rows read its weights at the
   // same time through one L2; inside an XCD its wavefronts (SwiGLU of plain weights: workgroups) take the units in turn.
-  const int xcd = blockIdx.x % kXcds;
-  const int stride = (gridDim.x / kXcds) * (kTwoWaves ? 1 : kDecodeWaves);
+  const int xcd = block % kXcds;
+  const int stride = ((int)gridDim.x - index_blocks) / kXcds * (kTwoWaves ? 1 : kDecodeWaves);
   struct Unit {
     int turn, cg, row0, nrows, expert, seg;   // nrows = 0: there is no further unit
     int row[RB];                 // per lane: rows 8 g + lane / 8 of A (as loaded: used in start, so that nothing waits for them here)
@@ -114,20 +283,20 @@ __global__ __launch_bounds__(kDecodeWaves * 64) __attribute__((amdgpu_waves_per_
     t.nrows = t.seg = 0;
     const int index = (turn / kUnitChunk * kXcds + xcd) * kUnitChunk + turn % kUnitChunk;
     if (index < n_units) {
-      int slot = -1;   // the last tile whose units begin at this one or before (every tile has some)
-      for (int i0 = 0; i0 < n_tiles; i0 += 64) slot += __popcll(__ballot(i0 + lane < n_tiles && unit0[w][i0 + lane] <= index));
+      int slot = -1;   // the last one whose units begin at this one or before (slots without units share the next one's)
+      for (int i0 = 0; i0 < n_slots; i0 += 64) slot += __popcll(__ballot(i0 + lane < n_slots && L.unit0[i0 + lane] <= index));
       slot = uniform(slot);
-      const int in_tile = index - uniform(unit0[w][slot]), rows = p.tile_rows[slot], parts = (rows + ROWS - 1) / ROWS;
-      const int part = in_tile % parts;
-      t.cg = in_tile / parts;
-      t.row0 = p.tile_row0[slot] + part * ROWS;
+      const int in_slot = index - uniform(L.unit0[slot]), rows = uniform((int)L.rows[slot]), parts = (rows + ROWS - 1) / ROWS;
+      const int part = in_slot % parts;
+      t.cg = in_slot / parts;
+      t.row0 = uniform((int)L.row0[slot]) + part * ROWS;
       t.nrows = min(rows - part * ROWS, ROWS);
-      t.expert = p.tile_expert[slot];
-      if (flagged) t.seg = p.tile_ready[slot];
+      t.expert = uniform((int)L.expert[slot]);
+      if (flagged) t.seg = p.own_index ? segment_of((int)L.token[t.row0 + t.nrows - 1]) : uniform((int)L.seg[slot]);
 #pragma unroll
       for (int g = 0; g < RB; g++) {
         const int r = t.row0 + min(g * 8 + (lane >> 3), t.nrows - 1);
-        t.row[g] = MODE != MODE_L1 ? p.a_rows[r] : r;
+        t.row[g] = MODE == MODE_L1 ? r : (p.own_index ? (int)L.token[r] : p.a_rows[r]);
       }
     }
     return t;
@@ -240,7 +409,8 @@ __global__ __launch_bounds__(kDecodeWaves * 64) __attribute__((amdgpu_waves_per_
     if (!arrived(t)) {
       if (patient && !spin_until_ge(&p.seg_ready[t.seg], p.ready_epoch, p.spin_limit)) {
         patient = false;
-        if (lane == 0) atomicExch(p.status, (int)MOE_ERR_TIMEOUT);
+        // (a launch that makes its index clears the status word itself, so it has a word of its own to say so)
+        if (lane == 0) atomicExch(p.own_index ? p.status + kTimedOutAt : p.status, p.own_index ? p.forward_serial : (int)MOE_ERR_TIMEOUT);
       }
       look();
       if (!arrived(t)) return false;
@@ -249,7 +419,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64) __attribute__((amdgpu_waves_per_
     return true;
   };
 
-  const int first = kTwoWaves ? blockIdx.x / kXcds : blockIdx.x / kXcds * kDecodeWaves + w;
+  const int first = kTwoWaves ? block / kXcds : block / kXcds * kDecodeWaves + w;
   Unit cur = find(first);
   bool started = cur.nrows > 0 && start_when_there(cur);
   int turn = 0;
@@ -321,17 +491,17 @@ __global__ __launch_bounds__(kDecodeWaves * 64) __attribute__((amdgpu_waves_per_
 }
 
 template <int MODE, bool PK, int NB, int RB, int U, int EU>
-static hipError_t launch_decode(const DecodeParams& p, hipStream_t st) {
+static hipError_t launch_decode(const DecodeParams& p, const IndexParams& ip, hipStream_t st) {
   constexpr bool kTwoWaves = MODE == MODE_L0_SWIGLU && !PK, kInWave = MODE == MODE_L0_SWIGLU && PK;
   constexpr int kUnitWaves = kTwoWaves ? kDecodeWaves : 1;   // wavefronts per unit
   const int64_t n_groups = p.N / (NB * 16 / (kInWave ? 2 : 1));
   // no more wavefronts than can be resident, or than there can be units (an expert's last part is not full)
   const int64_t most = ((int64_t)p.R / (8 * RB) + p.n_slots) * n_groups, resident = (int64_t)p.n_cu * 4 * EU / kUnitWaves;
   const int64_t per_xcd = ((most < resident ? most : resident) + kXcds * kUnitChunk - 1) / (kXcds * kUnitChunk) * kUnitChunk;
-  const unsigned grid = (unsigned)(per_xcd * kUnitWaves / kDecodeWaves) * kXcds;
+  const unsigned grid = (unsigned)(per_xcd * kUnitWaves / kDecodeWaves) * kXcds + (MODE != MODE_L1 && p.own_index ? kXcds : 0);
   // (64-byte pieces of plain weights: the other half of a line is another wavefront's and should still be there)
-  if (p.b_stream && (PK || NB == 4)) hipLaunchKernelGGL((k_decode_gemm<MODE, PK, NB, RB, U, EU, (PK || NB == 4)>), dim3(grid), dim3(kDecodeWaves * 64), 0, st, p);
-  else hipLaunchKernelGGL((k_decode_gemm<MODE, PK, NB, RB, U, EU, false>), dim3(grid), dim3(kDecodeWaves * 64), 0, st, p);
+  if (p.b_stream && (PK || NB == 4)) hipLaunchKernelGGL((k_decode_gemm<MODE, PK, NB, RB, U, EU, (PK || NB == 4)>), dim3(grid), dim3(kDecodeWaves * 64), 0, st, p, ip);
+  else hipLaunchKernelGGL((k_decode_gemm<MODE, PK, NB, RB, U, EU, false>), dim3(grid), dim3(kDecodeWaves * 64), 0, st, p, ip);
   return hipGetLastError();
 }
 
@@ -346,32 +516,32 @@ static hipError_t launch_decode(const DecodeParams& p, hipStream_t st) {
 // 64-byte pieces), but 32 where the wavefronts of 64 would leave compute units idle (one token, 120 wavefronts of 64 columns: layer1
 // of F = 1792 19 -> 16; 4 tokens of GELU layer0, 147: 33 -> 26, 210: 37 / 37, 252 and cold: 44 -> 67).
 template <int MODE, int RB>
-static hipError_t launch_decode_depth(const DecodeParams& p, int packed, hipStream_t st) {
+static hipError_t launch_decode_depth(const DecodeParams& p, const IndexParams& ip, int packed, hipStream_t st) {
   constexpr bool kPair = MODE == MODE_L0_SWIGLU;
   if (packed) {
-    if constexpr (RB == 1) return launch_decode<MODE, true, (kPair ? 2 : 1), 1, (kPair ? 4 : 8), (kPair ? 4 : 2)>(p, st);
-    else if constexpr (RB == 2) return launch_decode<MODE, true, (MODE == MODE_L1 ? 1 : 2), 2, 4, (MODE == MODE_L1 ? 4 : 3)>(p, st);
-    else return launch_decode<MODE, true, 2, 4, (kPair ? 2 : 3), (kPair ? 4 : 3)>(p, st);
+    if constexpr (RB == 1) return launch_decode<MODE, true, (kPair ? 2 : 1), 1, (kPair ? 4 : 8), (kPair ? 4 : 2)>(p, ip, st);
+    else if constexpr (RB == 2) return launch_decode<MODE, true, (MODE == MODE_L1 ? 1 : 2), 2, 4, (MODE == MODE_L1 ? 4 : 3)>(p, ip, st);
+    else return launch_decode<MODE, true, 2, 4, (kPair ? 2 : 3), (kPair ? 4 : 3)>(p, ip, st);
   }
   if constexpr (!kPair) {
-    if (p.experts * (p.N / 64) < 0.75f * p.n_cu) return launch_decode<MODE, false, 2, RB, (RB == 1 ? 6 : 4), 2>(p, st);
+    if (p.experts * (p.N / 64) < 0.75f * p.n_cu) return launch_decode<MODE, false, 2, RB, (RB == 1 ? 6 : 4), 2>(p, ip, st);
   }
-  return launch_decode<MODE, false, 4, RB, (RB == 1 ? 3 : 4), (RB == 4 ? 1 : 2)>(p, st);
+  return launch_decode<MODE, false, 4, RB, (RB == 1 ? 3 : 4), (RB == 4 ? 1 : 2)>(p, ip, st);
 }
 
 template <int MODE>
-static hipError_t launch_decode_rows(const DecodeParams& p, int packed, hipStream_t st) {
+static hipError_t launch_decode_rows(const DecodeParams& p, const IndexParams& ip, int packed, hipStream_t st) {
   // rows a unit holds: what most experts of the batch stay under
-  if (p.T <= 8) return launch_decode_depth<MODE, 1>(p, packed, st);
-  if (p.T <= 16) return launch_decode_depth<MODE, 2>(p, packed, st);
-  return launch_decode_depth<MODE, 4>(p, packed, st);
+  if (p.T <= 8) return launch_decode_depth<MODE, 1>(p, ip, packed, st);
+  if (p.T <= 16) return launch_decode_depth<MODE, 2>(p, ip, packed, st);
+  return launch_decode_depth<MODE, 4>(p, ip, packed, st);
 }
 
-hipError_t launch_decode_gemm(const DecodeParams& p, int layer1, int act, int packed, hipStream_t st) {
+hipError_t launch_decode_gemm(const DecodeParams& p, const IndexParams& ip, int layer1, int act, int packed, hipStream_t st) {
   if (p.n_slots == 0) return hipSuccess;
-  if (layer1) return launch_decode_rows<MODE_L1>(p, packed, st);
-  if (act == MOE_ACT_SWIGLU) return launch_decode_rows<MODE_L0_SWIGLU>(p, packed, st);
-  return launch_decode_rows<MODE_L0_GELU>(p, packed, st);
+  if (layer1) return launch_decode_rows<MODE_L1>(p, ip, packed, st);
+  if (act == MOE_ACT_SWIGLU) return launch_decode_rows<MODE_L0_SWIGLU>(p, ip, packed, st);
+  return launch_decode_rows<MODE_L0_GELU>(p, ip, packed, st);
 }
 
 }  // namespace moe

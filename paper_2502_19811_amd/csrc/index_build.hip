@@ -3,7 +3,7 @@
 // Row order (paper Section 3.1.2, Fig. 5): rows of the shared tensor are grouped by expert and, inside an
 // expert, sorted by source rank.  Source segment s owns a contiguous token range, so a stable counting sort of
 // the pair ids q = t*k + j by expert id gives exactly that order.
-#include "moe_internal.h"
+#include "moe_device.h"
 
 namespace moe {
 
@@ -87,25 +87,6 @@ __global__ __launch_bounds__(256) void k_index_hist(IndexParams p) {
   for (int e = threadIdx.x; e < E; e += 256) p.ws.block_hist[blockIdx.x * E + e] = hist[e];
 }
 
-// ---------------------------------------------------------------------------------------------
-// Tiling of an expert's rows: as many tiles of tile_m rows as fit, then one tile for the remainder.  Beside full tiles the
-// remainder's is of their height class, so that the schedule may put it next to them (see build_schedules), and light where
-// it has at most half as many rows: a GroupGEMM workgroup computes a tile with the lowest variant that holds its rows,
-// whatever its class.  An expert without full tiles has one tile of the lowest height that holds it.  (A remainder of
-// 129 to 192 rows is not split into a 128- and a 64-row tile, for all that the ragged tile pads it: every tile of a column streams
-// the expert's weights, which costs what the matrix cores need for about 240 rows.  160 rows for each of 16
-// experts with F = 6400: 941 -> 611 us, 400 rows 1385 -> 1022.)
-// ---------------------------------------------------------------------------------------------
-__device__ inline int height_class(int rows) { return rows <= 64 ? 0 : (rows <= 128 ? 1 : 2); }
-// (of the tallest class: the others' tiles are the lowest that hold their rows)
-__device__ inline bool is_light(int rows, int kind) { return height_class(rows) < kind; }
-__device__ inline int tail_height(int rows, int tile_m) {   // height of the tile that holds the remainder; 0: there is none
-  const int rem = rows % tile_m;
-  if (rem == 0) return 0;
-  if (rows > tile_m) return tile_m;   // beside full tiles
-  return rem <= 64 || tile_m == 64 ? 64 : (rem <= 128 || tile_m == 128 ? 128 : 256);
-}
-
 // Exclusive prefix sum over 256 values, one per thread of the workgroup, left in LDS; returns the total.
 __device__ inline int exclusive_scan_256(int32_t* buf, int v) {
   __shared__ int32_t wave_sum[4];
@@ -128,18 +109,6 @@ __device__ inline int exclusive_scan_256(int32_t* buf, int v) {
   buf[t] = before + incl - v;
   __syncthreads();
   return total;
-}
-
-// Waves of the layer0 schedule (order 2) of this forward, decided by one wavefront for everybody: the plan's number, or
-// one -- the order of resident input -- when every source segment has arrived by now (waves cost the weight reuse: layer0
-// of 16384 tokens of 16 experts with F = 6400 takes 3050 us against 2605, of 2047 tokens of 8 with F = 3584 284 against
-// 254).  A flag raised later than this only costs that.
-__device__ inline int waves_now(const IndexParams& p, int lane) {
-  if (p.seg_ready == nullptr) return p.layer0_waves;
-  bool missing = false;
-  if (lane < p.s.S && p.seg_offsets[lane + 1] > p.seg_offsets[lane])
-    missing = __hip_atomic_load(&p.seg_ready[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) < p.ready_epoch;
-  return __ballot(missing) != 0 ? p.layer0_waves : 1;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1057,6 +1026,7 @@ __global__ void k_reset_counters(Workspace ws, int n_tiles_n1, int max_tiles, in
   if (t == 0) {
     ws.status[0] = 0;
     ws.status[4] = 0;
+    ws.status[kTimedOutAt] = 0;
     if (schedule_built) ws.status[6] = 0;
   }
   if (t < 2 * kXcds) ws.queue_heads[t * ws.head_stride] = 0;

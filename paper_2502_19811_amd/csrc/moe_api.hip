@@ -233,7 +233,13 @@ int default_layer0_waves(const Shape& s, int ingest_gbps) {
 }
 
 // Batches whose GroupGEMMs may run as k_decode_gemm, without tile schedules.
-bool few_rows(const Shape& s) { return (int64_t)s.R <= (int64_t)kDecodeRowsPerExpert * s.E; }
+// Few rows per expert; or weights that all fit in the L2 of one XCD, where it costs nothing to pass them through it once per 32 rows, and no
+// schedule need be built.  us per gate + layer, 4 experts, H = 256, F = 512, tile kernel / this: 128 tokens 31.7 / 21.5, 500 33.7 / 25.4,
+// 1000 40.9 / 29.1, 2000 46.3 / 38.2.
+bool few_rows(const Shape& s) {
+  if ((int64_t)s.R <= (int64_t)kDecodeRowsPerExpert * s.E) return true;
+  return s.R <= kDecodeCachedRows && (int64_t)s.E * ((int64_t)s.H * s.F1 + (int64_t)s.F * s.H) * 2 <= kDecodeCachedBytes;
+}
 
 // Whether a GroupGEMM of n_tiles_n column tiles runs as k_decode_gemm (one pass over the weights for a few rows per
 // expert) or as the persistent tile kernel.  Measured, us per layer0 / layer1 launch, tile kernel -> decode kernel:
@@ -561,19 +567,20 @@ int forward_impl(moe_plan_t* p, const void* x, const int32_t* topk_ids, const fl
   auto mark = [&](int i) { return !ev || hipEventRecord(ev[i], st) == hipSuccess; };
   if (!mark(0)) return MOE_ERR_HIP;
 
-  if (p->phases & 1) {
-    IndexParams ip = index_params(p, ws, topk_ids, order0);
-    ip.forward_serial = ++p->serial;
-    if (p->layer0_order < 0) {   // the order is this library's choice
-      ip.seg_ready = seg_ready;
-      ip.ready_epoch = ready_epoch;
-    }
+  // Small batches: the GroupGEMMs make their index themselves, and layer0 leaves it in the workspace.
+  const bool own_index = (p->phases & 3) == 3 && decode0 && decode1 && s.R <= kOwnIndexRows;
+  IndexParams ip = index_params(p, ws, topk_ids, order0);
+  if (p->phases & 1) ip.forward_serial = ++p->serial;
+  if (p->layer0_order < 0) {   // the order is this library's choice
+    ip.seg_ready = seg_ready;
+    ip.ready_epoch = ready_epoch;
+  }
+  if ((p->phases & 1) && !own_index) {
     if (launch_index_build(ip, !(decode0 && decode1), st) != hipSuccess) return MOE_ERR_HIP;
-  } else {
+  } else if (!own_index) {
     // an index build for a forward that does without schedules left them out, which the workspace knows: they are made now
     const bool make_up = few_rows(s) && !(decode0 && decode1);
     if (make_up) {
-      IndexParams ip = index_params(p, ws, topk_ids, order0);
       ip.only_if_owed = 1;
       if (launch_index_schedule(ip, st) != hipSuccess) return MOE_ERR_HIP;
     }
@@ -709,6 +716,11 @@ int forward_impl(moe_plan_t* p, const void* x, const int32_t* topk_ids, const fl
     d0.status = g.status;
     d0.spin_limit = g.spin_limit;
     d0.F = s.F;
+    d0.own_index = own_index;
+    d0.topk_ids = topk_ids;
+    d0.E = s.E;
+    d0.k = s.k;
+    d0.forward_serial = ip.forward_serial;
     d1 = d0;
     d0.A = (const char*)x;
     d0.lda_bytes = (uint32_t)s.H * 2;
@@ -749,10 +761,10 @@ int forward_impl(moe_plan_t* p, const void* x, const int32_t* topk_ids, const fl
     if (launch_fused_layers(a, b, f, s.act, grid, st) != hipSuccess) return MOE_ERR_HIP;
     if (!mark(2)) return MOE_ERR_HIP;   // the whole launch is booked as the layer0 phase
   } else {
-    if ((p->phases & 2) && (decode0 ? launch_decode_gemm(d0, 0, s.act, p->weights_packed, st) : launch_layer0(a, s.act, grid0, st)) != hipSuccess)
+    if ((p->phases & 2) && (decode0 ? launch_decode_gemm(d0, ip, 0, s.act, p->weights_packed, st) : launch_layer0(a, s.act, grid0, st)) != hipSuccess)
       return MOE_ERR_HIP;
     if (!mark(2)) return MOE_ERR_HIP;
-    if ((p->phases & 4) && (decode1 ? launch_decode_gemm(d1, 1, s.act, p->weights_packed, st) : launch_layer1(b, grid1, st)) != hipSuccess)
+    if ((p->phases & 4) && (decode1 ? launch_decode_gemm(d1, ip, 1, s.act, p->weights_packed, st) : launch_layer1(b, grid1, st)) != hipSuccess)
       return MOE_ERR_HIP;
   }
   if (!mark(3)) return MOE_ERR_HIP;
@@ -949,10 +961,11 @@ int moe_play_arrival(const moe_plan_t* p, const void* staging, void* x, uint32_t
 int moe_last_device_status(const moe_plan_t* p, const void* workspace, void* hip_stream) {
   if (!p || !workspace) return MOE_ERR_INVALID_ARG;
   Workspace ws = view(p, const_cast<void*>(workspace));
-  int32_t v[6] = {0, 0, 0, 0, 0, 0};
+  int32_t v[kTimedOutAt + 1] = {0};
   if (hipMemcpyAsync(v, ws.status, sizeof(v), hipMemcpyDeviceToHost, (hipStream_t)hip_stream) != hipSuccess) return MOE_ERR_HIP;
   if (hipStreamSynchronize((hipStream_t)hip_stream) != hipSuccess) return MOE_ERR_HIP;
   if (v[0] != 0) return v[0];
+  if (v[kTimedOutAt] == p->serial) return MOE_ERR_TIMEOUT;
   return v[5] == p->serial ? MOE_ERR_INVALID_ARG : MOE_OK;
 }
 

@@ -53,6 +53,37 @@ __device__ __forceinline__ float silu(float v) {
   return v * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(v * -1.4426950408889634f));
 }
 
+// ---------------------------------------------------------------------------------------------
+// Tiling of an expert's rows: as many tiles of tile_m rows as fit, then one tile for the remainder.  Beside full tiles the
+// remainder's is of their height class, so that the schedule may put it next to them (see build_schedules), and light where
+// it has at most half as many rows: a GroupGEMM workgroup computes a tile with the lowest variant that holds its rows,
+// whatever its class.  An expert without full tiles has one tile of the lowest height that holds it.  (A remainder of
+// 129 to 192 rows is not split into a 128- and a 64-row tile, for all that the ragged tile pads it: every tile of a column streams
+// the expert's weights, which costs what the matrix cores need for about 240 rows.  160 rows for each of 16
+// experts with F = 6400: 941 -> 611 us, 400 rows 1385 -> 1022.)
+// ---------------------------------------------------------------------------------------------
+__device__ inline int height_class(int rows) { return rows <= 64 ? 0 : (rows <= 128 ? 1 : 2); }
+// (of the tallest class: the others' tiles are the lowest that hold their rows)
+__device__ inline bool is_light(int rows, int kind) { return height_class(rows) < kind; }
+__device__ inline int tail_height(int rows, int tile_m) {   // height of the tile that holds the remainder; 0: there is none
+  const int rem = rows % tile_m;
+  if (rem == 0) return 0;
+  if (rows > tile_m) return tile_m;   // beside full tiles
+  return rem <= 64 || tile_m == 64 ? 64 : (rem <= 128 || tile_m == 128 ? 128 : 256);
+}
+
+// Waves of the layer0 schedule (order 2) of this forward, decided by one wavefront for everybody: the plan's number, or
+// one -- the order of resident input -- when every source segment has arrived by now (waves cost the weight reuse: layer0
+// of 16384 tokens of 16 experts with F = 6400 takes 3050 us against 2605, of 2047 tokens of 8 with F = 3584 284 against
+// 254).  A flag raised later than this only costs that.
+__device__ inline int waves_now(const IndexParams& p, int lane) {
+  if (p.seg_ready == nullptr) return p.layer0_waves;
+  bool missing = false;
+  if (lane < p.s.S && p.seg_offsets[lane + 1] > p.seg_offsets[lane])
+    missing = __hip_atomic_load(&p.seg_ready[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) < p.ready_epoch;
+  return __ballot(missing) != 0 ? p.layer0_waves : 1;
+}
+
 // Wait until *flag >= want.  Returns false if the spin limit (when set) ran out.
 __device__ __forceinline__ bool spin_until_ge(const uint32_t* flag, uint32_t want, uint32_t spin_limit) {
   uint32_t polls = 0;

@@ -24,6 +24,10 @@ constexpr int kDecodeRowsPerExpert = 16;   // rows per expert on average up to w
 constexpr int kDecodeRowsManyTiles = 8;    // ... and where the tile kernel has more tiles than compute units
 constexpr double kCachedWeightBytes = 128e6;   // weights read by a forward beyond which its loads of them are non-temporal ...
 constexpr int kStreamRowsPerExpert = 244;   // ... in the tile kernel up to this many rows per expert on average
+constexpr int kOwnIndexRows = 512;   // pairs up to which the small-batch GroupGEMMs make their index themselves
+constexpr int kDecodeCachedRows = 4096;    // ... and pairs up to which it is used for weights of at most ...
+constexpr int64_t kDecodeCachedBytes = 4 << 20;   // ... the L2 of an XCD
+constexpr int kTimedOutAt = 56;       // status word: serial number of the last forward with an index of its own in which a wait ran out
 constexpr int kDefaultCus = 256;    // compute units a plan assumes before it has seen the device
 constexpr int kXcds = 8;            // XCDs of the device: workgroup i runs on XCD i % 8
 constexpr int kScheduleTileCap = 2048;  // M-tiles up to which the multi-workgroup schedule builder is used
@@ -46,7 +50,7 @@ struct Workspace {
                           //       id out of range; 6: kScheduleOwed where the index build left the tile schedules
                           //       out; 7: waves of the layer0 schedule; 8..23: room for queue_heads; per XCD: 24..31 layer0 queue lengths, 32..39 layer1 queue lengths, 40..47 layer1
                           //       queue bases, 48..55 layer0 queue bases (only with contiguous layer0 queues;
-                          //       otherwise layer0's queue x is list positions x, x+8, ...)
+                          //       otherwise layer0's queue x is list positions x, x+8, ...); 56: kTimedOutAt
   int32_t* counts;        // [E]
   int32_t* offsets;       // [E+1]
   int32_t* perm;          // [R] sorted row -> pair id
@@ -175,6 +179,10 @@ struct DecodeParams {
   float experts;            // experts that even routing gives rows
   int32_t T, R;
   int32_t n_cu;
+  int32_t own_index;        // 1: no table, the rows of the experts are made from topk_ids; layer0 leaves the index in the workspace
+  const int32_t* topk_ids;
+  int32_t E, k;
+  int32_t forward_serial;
   const int32_t* n_tiles;   // device scalar: tiles in the table
   const int32_t* tile_expert;
   const int32_t* tile_row0;
@@ -213,7 +221,7 @@ hipError_t launch_index_schedule(const IndexParams& p, hipStream_t st);
 hipError_t launch_reset_counters(const Workspace& ws, int n_tiles_n1, int max_tiles, bool schedule_built, hipStream_t st);
 hipError_t launch_layer0(const GemmParams& p, int act, int grid, hipStream_t st);
 hipError_t launch_layer1(const GemmParams& p, int grid, hipStream_t st);
-hipError_t launch_decode_gemm(const DecodeParams& p, int layer1, int act, int packed, hipStream_t st);
+hipError_t launch_decode_gemm(const DecodeParams& p, const IndexParams& ip, int layer1, int act, int packed, hipStream_t st);
 hipError_t launch_fused_layers(const GemmParams& p0, const GemmParams& p1, const FuseParams& f, int act, int grid, hipStream_t st);
 hipError_t launch_combine(const CombineParams& p, hipStream_t st);
 hipError_t launch_zero_u32(uint32_t* ptr, size_t n, hipStream_t st);
