@@ -11,6 +11,8 @@
 //    less than v_mfma_f32_32x32x16_bf16 (half the accumulator traffic; register-only loops: 2061 against 1835 TFLOP/s).  8192
 //    tokens of the Mixtral-shaped layer, 32x32x16 -> 16x16x32 and direct epilogue: main loop 91 -> 82 us per layer0
 //    tile (1140 cycles per K step in both, 1.60 -> 1.78 GHz), epilogue 5.4 -> 4.2 us, the layer 4338 -> 4077 us;
+//    Sweeping the blocks back and forth, one operand of two changing per MFMA, draws less again: 8192 tokens 4042 -> 4005 us, 16384 of
+//    them with plain weights 8035 -> 7960, 16384 of 16 experts of F = 6400 3830 -> 3800 (which operand stays longer makes no difference);
 //  * operands go global -> LDS directly (global_load_lds_dwordx4, 16 bytes per lane, no registers in between):
 //    B through a ring of 4 stages of depth 32, A through a ring of 5 blocks of half the tile's rows by depth 64, so
 //    that a load of A fetches whole 128-byte lines (8 rows per instruction); rows of A are gathered through
@@ -725,7 +727,10 @@ __device__ __forceinline__ void run_tile(const GemmParams& p, char* smem, volati
 #pragma unroll
       for (int i = decltype(lo)::value; i < decltype(hi)::value; i++) {
         // the operand half that was read last is the outer one: its fragments are needed one by one
-        const int m = (G & 1) * PER + i, ma = a0 + (Q < 2 ? m % HA : m / HB), nb = b0 + (Q < 2 ? m / HA : m % HB);
+        // ... and every other sweep of the inner one runs backwards, so that from one MFMA to the next one operand changes, never both
+        const int m = (G & 1) * PER + i, out = Q < 2 ? m / HA : m / HB, back = (out & 1) * ((Q < 2 ? HA : HB) - 1);
+        const int in = Q < 2 ? m % HA : m % HB, at = back ? back - in : in;
+        const int ma = a0 + (Q < 2 ? at : out), nb = b0 + (Q < 2 ? out : at);
         if constexpr (WHERE == Last::value && MA * NB == 64) mfma_in_place(acc[ma][nb], bfr[nb], af[ma]);
         else if constexpr (WHERE == First::value) acc[ma][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[nb], af[ma], (f32x4){0}, 0, 0, 0);
         else acc[ma][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[nb], af[ma], acc[ma][nb], 0, 0, 0);
