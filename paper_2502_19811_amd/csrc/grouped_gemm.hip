@@ -6,7 +6,7 @@
 //  * one persistent workgroup per compute unit walks a device-built tile schedule; a workgroup is either a
 //    GEMM workgroup or a data-movement workgroup, chosen by its index (the division point of Section 3.2.2); the
 //    data movement there is to do on one GPU: reducing finished column panels of layer1, prefetching weight panels;
-//  * a GEMM workgroup is 4 wavefronts, one per SIMD; a tile is BM x 256 outputs with BM = 256, 128 or 64, and
+//  * a GEMM workgroup is 4 wavefronts, one per SIMD; a tile is BM x 256 outputs with BM = 256, 192, 128 or 64, and
 //    accumulates in fp32 with v_mfma_f32_16x16x32_bf16.  What bounds the kernel is the power limit, and per flop this one draws
 //    less than v_mfma_f32_32x32x16_bf16 (half the accumulator traffic; register-only loops: 2061 against 1835 TFLOP/s).  8192
 //    tokens of the Mixtral-shaped layer, 32x32x16 -> 16x16x32 and direct epilogue: main loop 91 -> 82 us per layer0
@@ -389,7 +389,9 @@ struct Tile {
 __device__ __forceinline__ ItemRec make_uniform(ItemRec r) {
   r.m_tile = uniform(r.m_tile); r.n_tile = uniform(r.n_tile); r.expert = uniform(r.expert); r.row0 = uniform(r.row0);
   r.nrows = uniform(r.nrows); r.ready_seg = uniform(r.ready_seg);
-  r.kind = r.nrows <= 64 ? 0 : (r.nrows <= 128 ? 1 : 2);   // the variant that computes it: the lowest that holds its rows, whatever its class in the table
+  // (192 rows: a ragged tile of 129 to 192 rows was padded to 256.  us per gate + layer, 256 / 192: 150 rows for each of 16 experts of F = 6400 569 /
+  // 536, 162 for each of 64 of F = 2560 822 / 779, 425 for each of 64 of F = 1408 512 / 488, 412 for each of 64 of F = 2560 1412 / 1371)
+  r.kind = r.nrows <= 64 ? 0 : (r.nrows <= 128 ? 1 : (r.nrows <= 192 ? 3 : 2));   // the variant that computes it: the lowest that holds its rows, whatever its class in the table
   return r;
 }
 __device__ __forceinline__ ItemRec load_item(const GemmParams& p, int idx) { return make_uniform(p.items[idx]); }
@@ -416,18 +418,18 @@ constexpr int b_ring_offset(int bm, int nsx) { return (nsx + 1) * a_block_bytes(
 constexpr int kListBytes = 2048;
 constexpr int list_offset(int bm, int nsx) { return bm == 256 ? 3 * a_block_bytes(bm) : b_ring_offset(bm, nsx) + nsx * B_STAGE; }
 constexpr int kLdsBytes = b_ring_offset(256, NS) + NS * B_STAGE;   // 144 KiB; covers the smaller tiles' layouts too
-static_assert(list_offset(128, NS) + kListBytes <= kLdsBytes && list_offset(64, kDeepStages) + kListBytes <= kLdsBytes, "the list fits");
+static_assert(list_offset(192, NS) + kListBytes <= kLdsBytes && list_offset(128, NS) + kListBytes <= kLdsBytes && list_offset(64, kDeepStages) + kListBytes <= kLdsBytes, "the list fits");
 static_assert(kLdsBytes <= 160 * 1024 - 16384, "LDS of a compute unit, less the kernels' static variables");
 
-// Rows of A the lane loads for a tile of the given height class: LA = 1, 2 or 4 loads per block and two blocks (row
+// Rows of A the lane loads for a tile of the given variant: LA = 1, 2, 3 or 4 loads per block and two blocks (row
 // halves) per tile; a load covers 8 rows, 8 lanes per row.  arow[h * LA + j]: row half h, load j.
 template <int MODE>
 __device__ __forceinline__ void load_arows(const GemmParams& p, Tile& t, int lane, int w) {
-  const int la = 1 << t.rec.kind;
+  const int la = t.rec.kind == 3 ? 3 : 1 << t.rec.kind;
 #pragma unroll
   for (int i = 0; i < 8; i++) {
     if (i < 2 * la) {
-      const int h = i / la, j = i % la;
+      const int h = i >= la, j = i - h * la;
       const int r = h * (32 * la) + (w * la + j) * 8 + (lane >> 3);
       const int sr = t.rec.row0 + (r < t.rec.nrows ? r : t.rec.nrows - 1);   // past the ragged end: the last row again
       t.arow[i] = MODE != MODE_L1 ? p.a_rows[sr] : sr;
@@ -693,7 +695,7 @@ __device__ __forceinline__ void run_tile(const GemmParams& p, char* smem, volati
   // In-order issue and 16 cycles per MFMA: what stands between two MFMAs should be three instructions at most, so the
   // reads come behind the first MFMAs, the load behind the reads, in two parts.
   constexpr int PER = HA * HB / 2;                              // MFMAs of a group
-  constexpr int kLoadAt = PER == 8 ? 5 : (PER == 4 ? 2 : 1);   // ... ahead of the load
+  constexpr int kLoadAt = PER == 8 ? 5 : (PER == 6 ? 3 : (PER == 4 ? 2 : 1));   // ... ahead of the load
   auto group = [&](auto par, auto gi, auto where, bool reads_next, auto side, auto load_address, auto load) {
     constexpr int PAR = decltype(par)::value, G = decltype(gi)::value, Q = G / 2;
     constexpr int WHERE = decltype(where)::value;
@@ -811,7 +813,7 @@ __device__ __forceinline__ void run_tile(const GemmParams& p, char* smem, volati
   // segment to be there already: the ready flags are sampled here (lane s of the first wavefront reads
   // flag s) and looked at when the successor is known.  A flag raised later than this only costs the early start.
   constexpr bool kCanPre = true;   // (kept as a switch: the early start costs about 30 VGPRs)
-  constexpr int kKind = (WM == 2 && MT == 4) ? 2 : (WM == 2 ? 1 : 0);   // height class of this variant's tiles
+  constexpr int kKind = WM == 1 ? 0 : (MT == 4 ? 2 : (MT == 3 ? 3 : 1));   // what ItemRec::kind says of this variant's tiles
   const bool flags_on = MODE != MODE_L1 && p.seg_ready != nullptr;
   uint32_t flag_v = 0;
   if (kCanPre && flags_on && tid < p.n_segments)
@@ -1127,6 +1129,7 @@ __global__ __launch_bounds__(256, 1) void k_group_gemm(GemmParams p) {
     next.idx = -1;
     if (cur.rec.kind == 2) run_tile<2, 4, 4, MODE, PK, STREAM>(p, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
     else if (cur.rec.kind == 1) run_tile<2, 2, 4, MODE, PK, STREAM>(p, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
+    else if (cur.rec.kind == 3) run_tile<2, 3, 4, MODE, PK, STREAM>(p, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
     else if (deep64) run_tile<1, 2, 2, MODE, PK, STREAM, kDeepStages>(p, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
     else run_tile<1, 2, 2, MODE, PK, STREAM>(p, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
     cur = next;
@@ -1228,6 +1231,7 @@ __global__ __launch_bounds__(256, 1) void k_fused_layers(GemmParams p0, GemmPara
       const int m_tile = cur.rec.m_tile;
       if (cur.rec.kind == 2) run_tile<2, 4, 4, MODE0, PK, false>(p0, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
       else if (cur.rec.kind == 1) run_tile<2, 2, 4, MODE0, PK, false>(p0, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
+      else if (cur.rec.kind == 3) run_tile<2, 3, 4, MODE0, PK, false>(p0, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
       else run_tile<1, 2, 2, MODE0, PK, false>(p0, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
       if (tid == 0 && (unsigned)m_tile < (unsigned)kScheduleTileCap) lds_tile_cnt[m_tile] += 1;
       cur = next;
@@ -1282,6 +1286,7 @@ __global__ __launch_bounds__(256, 1) void k_fused_layers(GemmParams p0, GemmPara
       next.idx = -1;
       if (cur.rec.kind == 2) run_tile<2, 4, 4, MODE_L1, PK, false>(q1, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
       else if (cur.rec.kind == 1) run_tile<2, 2, 4, MODE_L1, PK, false>(q1, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
+      else if (cur.rec.kind == 3) run_tile<2, 3, 4, MODE_L1, PK, false>(q1, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
       else run_tile<1, 2, 2, MODE_L1, PK, false>(q1, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
       cur = next;
     }

@@ -58,7 +58,7 @@ __device__ __forceinline__ float silu(float v) {
 // remainder's is of their height class, so that the schedule may put it next to them (see build_schedules), and light where
 // it has at most half as many rows: a GroupGEMM workgroup computes a tile with the lowest variant that holds its rows,
 // whatever its class.  An expert without full tiles has one tile of the lowest height that holds it.  (A remainder of
-// 129 to 192 rows is not split into a 128- and a 64-row tile, for all that the ragged tile pads it: every tile of a column streams
+// 129 to 192 rows, for which there is a variant, is not split into a 128- and a 64-row tile: every tile of a column streams
 // the expert's weights, which costs what the matrix cores need for about 240 rows.  160 rows for each of 16
 // experts with F = 6400: 941 -> 611 us, 400 rows 1385 -> 1022.)
 // ---------------------------------------------------------------------------------------------
