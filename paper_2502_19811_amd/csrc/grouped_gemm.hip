@@ -1515,7 +1515,7 @@ hipError_t launch_combine(const CombineParams& p, hipStream_t st) {
 #ifdef MOE_TILE_TRACE
 // Measurement build only.  reset != 0: forget the tiles noted so far.  Otherwise copies out, per layer (0, 1) and
 // workgroup (256), the number of tiles noted, and per tile (128 slots) the four time stamps, the two cycle counts and the height class
-// (0 / 1 / 2 for 64 / 128 / 256 rows, +4 when the tile's first loads were started by its predecessor).  Host pointers.
+// (0 / 1 / 3 / 2 for 64 / 128 / 192 / 256 rows, +4 when the tile's first loads were started by its predecessor).  Host pointers.
 extern "C" int moe_debug_tile_trace(int reset, uint64_t* stamps, int32_t* kinds, int32_t* counts) {
   if (hipDeviceSynchronize() != hipSuccess) return MOE_ERR_HIP;
   if (reset) {

@@ -94,7 +94,7 @@ def main() -> int:
                    "share_of_launch_in_main_loops": round(float(main_total.mean() / (t_end - t_begin)), 3),
                    "truncated": bool((n >= N_SLOTS).any())}
             per_kind = {}
-            for kind, label in ((2, "256"), (1, "128"), (0, "64")):
+            for kind, label in ((2, "256"), (3, "192"), (1, "128"), (0, "64")):
                 for pre in (0, 1):
                     pro, mainl, epi, gap, sync, ghz = [], [], [], [], [], []
                     for g in wgs:
