@@ -247,6 +247,10 @@ __global__ __launch_bounds__(kDecodeWaves * 64) __attribute__((amdgpu_waves_per_
     there = __ballot(up);
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "");
   };
+  if (MODE == MODE_L1 && p.own_index && blockIdx.x == 0 && tid == 0) {   // what layer0 had to say of its waits, see start_when_there
+    if (p.status[kTimedOutAt] == p.forward_serial) p.status[0] = (int)MOE_ERR_TIMEOUT;
+    p.status[kTimedOutAt] = 0;
+  }
   const bool flagged = MODE != MODE_L1 && p.seg_ready != nullptr;
   if (flagged) look();
 
@@ -409,7 +413,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64) __attribute__((amdgpu_waves_per_
     if (!arrived(t)) {
       if (patient && !spin_until_ge(&p.seg_ready[t.seg], p.ready_epoch, p.spin_limit)) {
         patient = false;
-        // (a launch that makes its index clears the status word itself, so it has a word of its own to say so)
+        // (a launch that makes its index clears the status word itself: layer1 moves this one there)
         if (lane == 0) atomicExch(p.own_index ? p.status + kTimedOutAt : p.status, p.own_index ? p.forward_serial : (int)MOE_ERR_TIMEOUT);
       }
       look();

@@ -1075,7 +1075,6 @@ __global__ void k_reset_counters(Workspace ws, int n_tiles_n1, int max_tiles, in
   if (t == 0) {
     ws.status[0] = 0;
     ws.status[4] = 0;
-    ws.status[kTimedOutAt] = 0;
     if (schedule_built) ws.status[6] = 0;
   }
   if (t < 2 * kXcds) ws.queue_heads[t * ws.head_stride] = 0;

@@ -568,7 +568,7 @@ int forward_impl(moe_plan_t* p, const void* x, const int32_t* topk_ids, const fl
   if (!mark(0)) return MOE_ERR_HIP;
 
   // Small batches: the GroupGEMMs make their index themselves, and layer0 leaves it in the workspace.
-  const bool own_index = (p->phases & 3) == 3 && decode0 && decode1 && s.R <= kOwnIndexRows;
+  const bool own_index = (p->phases & 7) == 7 && decode0 && decode1 && s.R <= kOwnIndexRows;
   IndexParams ip = index_params(p, ws, topk_ids, order0);
   if (p->phases & 1) ip.forward_serial = ++p->serial;
   if (p->layer0_order < 0) {   // the order is this library's choice
@@ -961,11 +961,10 @@ int moe_play_arrival(const moe_plan_t* p, const void* staging, void* x, uint32_t
 int moe_last_device_status(const moe_plan_t* p, const void* workspace, void* hip_stream) {
   if (!p || !workspace) return MOE_ERR_INVALID_ARG;
   Workspace ws = view(p, const_cast<void*>(workspace));
-  int32_t v[kTimedOutAt + 1] = {0};
+  int32_t v[6] = {0, 0, 0, 0, 0, 0};
   if (hipMemcpyAsync(v, ws.status, sizeof(v), hipMemcpyDeviceToHost, (hipStream_t)hip_stream) != hipSuccess) return MOE_ERR_HIP;
   if (hipStreamSynchronize((hipStream_t)hip_stream) != hipSuccess) return MOE_ERR_HIP;
   if (v[0] != 0) return v[0];
-  if (v[kTimedOutAt] == p->serial) return MOE_ERR_TIMEOUT;
   return v[5] == p->serial ? MOE_ERR_INVALID_ARG : MOE_OK;
 }
 

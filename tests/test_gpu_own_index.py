@@ -86,3 +86,35 @@ def test_ids_out_of_range_and_time_outs_are_reported_once():
     assert run.status == 0
     a, b = H.error_metrics(run.out, orc.moe_layer(inp.x, inp.W1, inp.W2, ids, w, cfg.act))
     assert a <= H.REL_TOL and b <= H.REL_TOL
+
+
+def test_time_outs_of_a_replayed_graph_belong_to_their_replay():
+    """Replays of one captured forward, with and without a missing segment, and eager forwards of the plan in between: every one
+    reports its own waits (the captured launches carry the serial number of the forward that was captured)."""
+    import gpu_harness as H
+    cfg = wl.MoEConfig("own_index_graph", T=20, H=256, F=256, E=6, k=2, act=wl.ACT_SWIGLU, S=2, seed=871)
+    inp = wl.make_inputs(cfg, threads=2)
+    ids, w = orc.route_topk(inp.logits, cfg.k)
+    layer = H.GpuLayer(cfg, inp, ids, w, {"spin_limit": 200})
+    flags = torch.ones(cfg.S, dtype=torch.int32, device="cuda")
+    layer.ws.fill_(0x5A)
+    layer.forward(seg_ready=flags, epoch=1)
+    first = layer.results()
+    assert first.status == 0
+    graph, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.graph(graph, stream=stream):
+        layer.forward(seg_ready=flags, epoch=1, stream=stream)
+    for missing in (False, True, False, True, True, False):
+        print(f"own index, replay with a missing segment: {missing}", flush=True)
+        flags[1] = 0 if missing else 1
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        run = layer.results()
+        assert run.status == (-6 if missing else 0)
+        if not missing:
+            np.testing.assert_array_equal(run.out, first.out)
+        flags.fill_(1)
+        layer.forward(seg_ready=flags, epoch=1)
+        assert layer.results().status == 0
+    layer.close()
