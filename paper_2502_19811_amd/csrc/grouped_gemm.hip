@@ -247,7 +247,7 @@ struct Queue {
 __device__ __forceinline__ int queue_pos(const GemmParams& p, int x, int i) {
   return (p.queue_base ? p.queue_base[x] : x) + i * p.queue_stride;
 }
-// The heads lie 256 bytes apart where there is room (Workspace::queue_heads): with all of them in one line the atomics of 256 workgroups that
+// The heads lie 256 bytes apart in launches of more than a round (Workspace::queue_heads): with all of them in one line the atomics of 256 workgroups that
 // end a tile together took several us (1000 tokens of 64 experts with F = 1408: 245 -> 241 us, and with late tickets 263 -> 237).
 constexpr int kLateRounds = 2;   // rounds at the end of a queue in which an item is taken late, see run_tile
 // Takes the next item of XCD x's queue; returns its list position or -1 when that queue is used up.
@@ -807,7 +807,7 @@ __device__ __forceinline__ void run_tile(const GemmParams& p, char* smem, volati
   int next_raw = 0;
   const int taken = (cur.idx - q.own_base) >> (p.queue_stride == 1 ? 0 : 3);   // position in the own queue (a stolen item: anything)
   const int round = (int)(gridDim.x / kXcds);
-  const bool late = q.own_len > round && (uint32_t)(taken + kLateRounds * round) >= (uint32_t)q.own_len;   // (up to one round: all gone at the start)
+  const bool late = p.head_stride > 1 && q.own_len > round && (uint32_t)(taken + kLateRounds * round) >= (uint32_t)q.own_len;   // (up to one round: all gone at the start)
   if (tid == 0 && !late) next_raw = take_from(p, xcd, q.own_len, q.own_base);
   // A tile starts the loads of a successor of its own height during its epilogue, which needs the successor's
   // segment to be there already: the ready flags are sampled here (lane s of the first wavefront reads

@@ -11,6 +11,7 @@ using namespace moe;
 
 constexpr int kProfSlots = 256;
 constexpr int kHeadStride = 64;   // words between queue heads: 256 bytes
+constexpr size_t kHeadBytes = (size_t)2 * kXcds * kHeadStride * 4;
 
 // Workspace of moe_layer_forward_static: device memory that exists from the moment the library is loaded, so that a
 // forward on it allocates nothing.  Every GPU the library runs on holds its own copy at its own address; in host code
@@ -33,7 +34,6 @@ struct moe_plan {
   int32_t expected_ingest_gbps;  // 0: unknown
   int32_t last_layer0_order;     // what the last forward ran with (for moe_get_schedule)
   int32_t layer1_order;
-  int32_t spread_heads;          // the last index build's schedules leave the room for spread queue heads, see view()
   int32_t spin_limit;
   int32_t phases;
   int32_t n_cu;          // 0: not queried yet
@@ -56,7 +56,7 @@ struct moe_plan {
   int32_t serial;          // number of the last forward (tags the out-of-range report in the status words)
   int32_t n_tiles_n0, n_tiles_n1;
   size_t off_status, off_counts, off_offsets, off_perm, off_inv_perm, off_row_token, off_block_hist, off_tile_expert,
-      off_tile_row0, off_tile_rows, off_tile_ready, off_tile_kind, off_tile_order, off_items0, off_items1, off_panel_done, off_tile_done, off_arrive, off_h, off_Y, total_bytes;
+      off_tile_row0, off_tile_rows, off_tile_ready, off_tile_kind, off_tile_order, off_items0, off_items1, off_panel_done, off_tile_done, off_arrive, off_h, off_Y, off_heads, total_bytes;
 };
 
 namespace {
@@ -96,10 +96,16 @@ void layout(moe_plan* p) {
   p->off_arrive = take((size_t)s.T * p->n_tiles_n1 * 4);
   p->off_h = take((size_t)s.R * s.F * 2);
   p->off_Y = take((size_t)s.R * s.H * 2);
+  // Queue heads in cache lines of their own (see view).  They must not be what keeps a plan out of the library's own
+  // workspace: within 4 KiB of its size a plan does without them (off_heads = 0).
+  p->off_heads = 0;
+  if (o > kStaticScratchBytes || o + kHeadBytes <= kStaticScratchBytes) p->off_heads = take(kHeadBytes);
   p->total_bytes = o;
 }
 
-Workspace view(const moe_plan* p, void* base) {
+// spread_heads: the queue heads, every workgroup's atomics on 8 words per launch, lie in cache lines of their own; otherwise next
+// to the queue lengths in the status words.  Whoever uses the heads clears them in the same forward, so every forward chooses.
+Workspace view(const moe_plan* p, void* base, bool spread_heads = false) {
   char* b = (char*)base;
   Workspace w;
   w.status = (int32_t*)(b + p->off_status);
@@ -117,15 +123,9 @@ Workspace view(const moe_plan* p, void* base) {
   w.tile_order = (int32_t*)(b + p->off_tile_order);
   w.items0 = (ItemRec*)(b + p->off_items0);
   w.items1 = (ItemRec*)(b + p->off_items1);
-  // The heads of the queues, every workgroup's atomics on 8 words per launch: in cache lines of their own where the layer1 schedule
-  // leaves its room behind the items of all tiles unused (any order but the panel-major one and the large builder's).
-  w.queue_heads = w.status + 8;
-  w.head_stride = 1;
-  if (p->spread_heads) {
-    const int room = 3 * kXcds * p->n_tiles_n1 * (int)(sizeof(ItemRec) / 4);   // words; 12 per head and more
-    w.queue_heads = (int32_t*)(w.items1 + (size_t)p->max_tiles * p->n_tiles_n1);
-    w.head_stride = room / (2 * kXcds) < kHeadStride ? room / (2 * kXcds) : kHeadStride;
-  }
+  const bool apart = spread_heads && p->off_heads;
+  w.queue_heads = apart ? (int32_t*)(b + p->off_heads) : w.status + 8;
+  w.head_stride = apart ? kHeadStride : 1;
   w.panel_done = (uint32_t*)(b + p->off_panel_done);
   w.tile_done = (uint32_t*)(b + p->off_tile_done);
   w.arrive = (uint32_t*)(b + p->off_arrive);
@@ -550,8 +550,7 @@ int forward_impl(moe_plan_t* p, const void* x, const int32_t* topk_ids, const fl
   const bool large = uses_large_schedule(p->max_tiles, p->large_schedule);
   // (a launch of one item per workgroup has no use for it, and finds its heads and queue lengths in one line)
   const int most_columns = p->n_tiles_n0 > p->n_tiles_n1 ? p->n_tiles_n0 : p->n_tiles_n1;
-  if (p->phases & 1) p->spread_heads = p->layer1_order != 1 && !large && (int64_t)p->max_tiles * most_columns > p->n_cu;
-  Workspace ws = view(p, workspace);
+  Workspace ws = view(p, workspace, (int64_t)p->max_tiles * most_columns > p->n_cu);
   // The layer0 tile order of this forward: the schedule is built inside the forward, so it can follow what the
   // forward is given.  All rows resident: expert-major (weight reuse first).  Ready flags in use: waves of source
   // segments (Fig. 5).  The one-workgroup builder for very large tile tables knows orders 0 and 1 only.

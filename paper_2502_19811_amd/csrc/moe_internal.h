@@ -48,7 +48,7 @@ struct Workspace {
   int32_t* status;        // [64]  0: device status word, 1: n_tiles, 2: items of layer0, 3: items of layer1,
                           //       4: combine unit counter, 5: serial number of the last forward that saw an expert
                           //       id out of range; 6: kScheduleOwed where the index build left the tile schedules
-                          //       out; 7: waves of the layer0 schedule; 8..23: room for queue_heads; per XCD: 24..31 layer0 queue lengths, 32..39 layer1 queue lengths, 40..47 layer1
+                          //       out; 7: waves of the layer0 schedule; 8..23: queue_heads of short launches; per XCD: 24..31 layer0 queue lengths, 32..39 layer1 queue lengths, 40..47 layer1
                           //       queue bases, 48..55 layer0 queue bases (only with contiguous layer0 queues;
                           //       otherwise layer0's queue x is list positions x, x+8, ...); 56: kTimedOutAt
   int32_t* counts;        // [E]
@@ -65,7 +65,7 @@ struct Workspace {
   int32_t* tile_order;    // [max_tiles] scratch of the schedule builder: tiles sorted tallest first
   ItemRec* items0;        // [max_tiles * n_tiles_n0] layer0 schedule
   ItemRec* items1;        // [(max_tiles + 24) * n_tiles_n1] layer1 schedule, one contiguous queue per XCD
-  int32_t* queue_heads;   // [2 * 8] items taken from the queues of layer0 and layer1, head_stride words apart
+  int32_t* queue_heads;   // [2 * 8] items taken from the queues of layer0 and layer1, head_stride words apart: in the status words or behind Y
   int32_t head_stride;
   uint32_t* panel_done;   // [n_tiles_n1] finished M-tiles per column panel of layer1
   uint32_t* arrive;       // [T * n_tiles_n1] epilogue reduction: rows of a token already written, per column panel

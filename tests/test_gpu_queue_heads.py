@@ -3,6 +3,7 @@ less than a round, of a few rounds and of many), every tile is computed once.  T
 forward on one workspace, and the schedules of a forward are run again; all outputs have the same bits."""
 import numpy as np
 import pytest
+import torch
 
 import workloads as wl
 from oracle import moe_oracle as orc
@@ -44,4 +45,48 @@ def test_every_order_and_workgroup_count_gives_the_same_bits(Hd, F, act):
                 layer.forward()
                 np.testing.assert_array_equal(layer.results().out, first)
             moe.moe_plan_set_option(layer.plan, "phases", 15)
+    layer.close()
+
+
+@pytest.mark.parametrize("T,Hd,F", [(16, 256, 4096), (64, 256, 2048), (64, 768, 2048), (64, 1280, 2048)])
+def test_heads_of_a_schedule_made_later(T, Hd, F):
+    """A small batch leaves its schedules out; the steps after the index build, asked for with another kind of schedule, make them up in
+    the workspace, and a second workspace that has seen the usual kind comes in between.  Nothing is written behind the workspace
+    (Y and the queue heads are the last of it)."""
+    import gpu_harness as H
+    import paper_2502_19811_amd as moe
+    cfg = wl.MoEConfig("heads_later", T=T, H=Hd, F=F, E=8, k=2, act=wl.ACT_SWIGLU, S=2, seed=830)
+    inp = wl.make_inputs(cfg, threads=4)
+    ids, w = orc.route_topk(inp.logits, cfg.k)
+    layer = H.GpuLayer(cfg, inp, ids, w, packed=True)
+    n, guard = layer.ws.numel(), 1 << 20
+    spaces = [torch.full((n + guard,), 0x5A, dtype=torch.uint8, device="cuda") for _ in range(2)]
+    want = None
+
+    def forward(space, phases, **options):
+        nonlocal want
+        for name in ("layer1_order", "large_schedule"):
+            moe.moe_plan_set_option(layer.plan, name, options.get(name, 0))
+        moe.moe_plan_set_option(layer.plan, "phases", phases)
+        print(f"heads T {T} H {Hd} F {F} workspace {space} phases {phases} {options}", flush=True)
+        layer.ws = spaces[space][:n]
+        layer.out.fill_(7.0)
+        layer.forward()
+        run = layer.results()
+        assert run.status == 0
+        if want is None:
+            want = run.out
+            a, b = H.error_metrics(want, orc.moe_layer(inp.x, inp.W1, inp.W2, ids, w, cfg.act))
+            assert a <= H.REL_TOL and b <= H.REL_TOL
+        np.testing.assert_array_equal(run.out, want)
+        assert bool((spaces[space][n:] == 0x5A).all())
+
+    for options in ({"layer1_order": 1}, {"large_schedule": 1}):
+        forward(0, 15)                  # index build without schedules
+        forward(0, 14, **options)       # ... made up
+        forward(0, 14, **options)       # ... run again
+    forward(0, 15, layer1_order=1)
+    forward(1, 15)
+    forward(0, 14, layer1_order=1)      # the first workspace's schedule, after the usual kind on the second
+    forward(1, 14)
     layer.close()

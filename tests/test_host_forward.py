@@ -1,0 +1,126 @@
+"""What the host side launches, and on which memory, followed without a GPU (host_forward.hip: the library's host code with notes in
+the place of its launches)."""
+import ctypes as C
+import os
+import subprocess
+
+import pytest
+
+from conftest import ROOT
+
+INDEX, SCHEDULE, RESET, LAYER0, LAYER1, DECODE0, DECODE1 = range(1, 8)
+BASE = 1 << 40          # addresses are arithmetic here, nothing is accessed
+ITEM = 32               # bytes of a schedule record
+
+
+class Shape(C.Structure):
+    _fields_ = [(n, C.c_int32) for n in ("T", "H", "F", "E", "k", "S", "act")]
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("host") / "host_forward.so")
+    subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "--offload-arch=gfx950", "-O1", "-std=c++17", "-fPIC", "-shared",
+                    "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-I", os.path.join(ROOT, "include"),
+                    "-I", os.path.join(ROOT, "paper_2502_19811_amd", "csrc"), os.path.join(ROOT, "tests", "host_forward.hip"), "-o", so],
+                   check=True, capture_output=True)
+    lib = C.CDLL(so, mode=os.RTLD_LOCAL)
+    lib.moe_plan_workspace_bytes.restype = C.c_size_t
+    lib.moe_plan_schedule_capacity.restype = C.c_int64
+    return lib
+
+
+class Plan:
+    def __init__(self, lib, T, H, F, E, k, act=1, S=1, **options):
+        self.lib, self.act, self.p = lib, act, C.c_void_p()
+        seg = (C.c_int32 * (S + 1))(*[T * s // S for s in range(S + 1)])
+        assert lib.moe_plan_create(C.byref(self.p), C.byref(Shape(T, H, F, E, k, S, act)), seg) == 0
+        for name, value in options.items():
+            self.set(name, value)
+
+    def set(self, name, value):
+        assert self.lib.moe_plan_set_option(self.p, name.encode(), C.c_int64(value)) == 0
+
+    def bytes(self):
+        return self.lib.moe_plan_workspace_bytes(self.p)
+
+    def forward(self, base=BASE):
+        """The notes of one forward: tuples (kind, heads, stride, items0 or items, items1, own_index, stream)."""
+        at = C.c_void_p(BASE >> 8)
+        assert self.lib.moe_layer_forward(self.p, at, at, at, at, at, self.act, at, C.c_void_p(base), C.c_size_t(self.bytes()), None, 0, None) == 0
+        out = (C.c_int64 * (7 * 32))()
+        n = self.lib.host_forward_notes(out, 32)
+        assert 0 < n <= 32
+        return [tuple(out[7 * i:7 * i + 7]) for i in range(n)]
+
+    def close(self):
+        self.lib.moe_plan_destroy(self.p)
+
+
+def check_heads(plan, notes, base=BASE):
+    """Every launch of the forward has its queue heads where the launch that cleared them has, inside the workspace, and where no
+    schedule can be."""
+    heads = {n[1:3] for n in notes if n[0] in (INDEX, SCHEDULE, RESET, LAYER0, LAYER1) and not (n[0] == LAYER1)}
+    at, stride = heads.pop()
+    assert not heads
+    assert all(n[1:3] == (at + 8 * stride, stride) for n in notes if n[0] == LAYER1)   # layer1's lie behind layer0's
+    end = at + 15 * stride + 4
+    assert base <= at and end <= base + plan.bytes()
+    items = {n[3:5] for n in notes if n[0] in (INDEX, SCHEDULE, RESET)}
+    assert len(items) == 1
+    for layer, first in enumerate(items.pop()):
+        last = first + plan.lib.moe_plan_schedule_capacity(plan.p, layer) * ITEM
+        assert end <= first or at >= last, f"queue heads {at - base}..{end - base} inside the layer{layer} schedule {first - base}..{last - base}"
+
+
+SHAPES = [
+    # T, H, F, E, k, act
+    (64, 256, 2048, 8, 2, 1), (16, 256, 4096, 8, 2, 1), (64, 768, 2048, 8, 2, 1), (64, 1280, 2048, 8, 2, 1), (24, 512, 1152, 8, 2, 1),
+    (1111, 256, 512, 6, 2, 0), (1111, 1536, 640, 6, 2, 1), (8192, 4096, 14336, 8, 2, 1), (4096, 3584, 2560, 64, 8, 1), (1, 256, 256, 1, 1, 0),
+    (65536, 256, 128, 256, 16, 1),
+]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_queue_heads_lie_outside_every_schedule(lib, shape):
+    """Forwards with and without the index build, the options that choose the kind of schedule changed between them, on two
+    workspaces of one plan: a schedule may stem from any earlier forward."""
+    for tile_m in (64, 128, 256):
+        plan = Plan(lib, *shape, tile_m=tile_m, weights_packed=1)
+        for order in (0, 1, 2):
+            for large in (0, 1):
+                for phases in (15, 14, 1, 6):
+                    for base in (BASE, 2 * BASE):
+                        plan.set("layer1_order", order)
+                        plan.set("large_schedule", large)
+                        plan.set("phases", phases)
+                        notes = plan.forward(base)
+                        if any(n[0] in (INDEX, SCHEDULE, RESET) for n in notes):   # (a small batch makes its index itself, without queues)
+                            check_heads(plan, notes, base)
+        # a small batch leaves its schedules out; a forward without the index build makes them up with the options it finds
+        for name in ("layer1_order", "large_schedule", "handoff_fences"):
+            for other in ("layer1_order", "large_schedule", "handoff_fences"):
+                plan.set(other, 0)
+            plan.set("phases", 15)
+            plan.forward()
+            plan.set("phases", 14)
+            plan.set(name, 1)
+            check_heads(plan, plan.forward())
+        plan.close()
+
+
+def test_queue_heads_do_not_outgrow_the_static_workspace(lib):
+    """Just below 32 MiB a plan keeps to the room in the status words; every other one has its heads 256 bytes apart."""
+    limit, seen = 32 << 20, set()
+    for T in range(30000, 33000):
+        plan = Plan(lib, T, 256, 256, 4, 1, act=0, tile_m=256, n_cu=64)   # more than a round
+        total = plan.bytes()
+        stride = plan.forward()[0][2]
+        plan.close()
+        assert total % 256 == 0
+        if stride == 4:
+            assert limit - 4096 < total <= limit
+        else:
+            assert stride == 256 and not limit < total <= limit + 4096
+        seen.add((stride, total <= limit))
+    assert seen == {(4, True), (256, True), (256, False)}
