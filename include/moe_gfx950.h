@@ -219,10 +219,9 @@ int moe_get_index_outputs(const moe_plan_t *plan, const void *workspace, int32_t
 
 /* Tile table of the GroupGEMMs as built by the last forward (dev pointers, each [max_tiles], any may be
  * NULL, entries beyond *n_tiles untouched; n_tiles: dev int32 [1]): expert, first sorted row, rows, the
- * source segment the tile waits for, and the height class (64 / 128 / 256 rows) it is scheduled in.  An
- * expert's rows are cut into tiles of "tile_m" rows; the remainder is a tile of the same class, computed
- * by the lowest kernel variant that holds its rows, so that little of a tile is padding; an expert of
- * fewer rows has one tile of the lowest class that holds them.  max_tiles >= moe_plan_max_tiles(plan). */
+ * source segment the tile waits for, and the height (64 / 128 / 192 / 256 rows) of the kernel variant
+ * that computes it.  An expert's rows are cut into tiles of "tile_m" rows; the remainder goes into the
+ * lowest variant that holds it, so that little of a tile is padding.  max_tiles >= moe_plan_max_tiles(plan). */
 int moe_get_tile_table(const moe_plan_t *plan, const void *workspace, int32_t *n_tiles, int32_t *tile_expert,
                        int32_t *tile_row0, int32_t *tile_rows, int32_t *tile_ready_seg, int32_t *tile_height,
                        void *hip_stream);
@@ -230,7 +229,7 @@ int32_t moe_plan_max_tiles(const moe_plan_t *plan);
 
 /* The tile schedule of layer 0 or 1 as built by the last forward on this workspace (Fig. 5 / Fig. 6: the order in
  * which GroupGEMM tiles are taken), for tests of its invariants.  items: dev int32 [moe_plan_schedule_capacity(plan,
- * layer)][8] or NULL, records {m_tile, n_tile, expert, row0, nrows, height class 0/1/2, ready_seg, 0}; only the list
+ * layer)][8] or NULL, records {m_tile, n_tile, expert, row0, nrows, height class 0/1/2 (the lowest of 64 / 128 / 256 that holds its rows), ready_seg, 0}; only the list
  * positions named by the queues are meaningful.  queues: host int32 [24]: for XCD x the list position of its first
  * item (queues[x]), its number of items (queues[8+x]) and the distance between consecutive items (queues[16+x]); a
  * workgroup on XCD x takes its own queue front to back, then the others'.  Synchronises the stream.  The plan's

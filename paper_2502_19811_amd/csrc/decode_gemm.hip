@@ -210,7 +210,7 @@ __device__ __forceinline__ void own_index(UnitTable& L, const DecodeParams& p, i
       ip.ws.tile_expert[m] = e;
       ip.ws.tile_row0[m] = row0 + i * tile_m;
       ip.ws.tile_rows[m] = n;
-      ip.ws.tile_kind[m] = height_class(n == tile_m ? tile_m : tail_height(rows, tile_m));
+      ip.ws.tile_kind[m] = height_class(n);
       ip.ws.tile_ready[m] = s;
     }
   }

@@ -391,7 +391,7 @@ __device__ __forceinline__ ItemRec make_uniform(ItemRec r) {
   r.nrows = uniform(r.nrows); r.ready_seg = uniform(r.ready_seg);
   // (192 rows: a ragged tile of 129 to 192 rows was padded to 256.  us per gate + layer, 256 / 192: 150 rows for each of 16 experts of F = 6400 569 /
   // 536, 162 for each of 64 of F = 2560 822 / 779, 425 for each of 64 of F = 1408 512 / 488, 412 for each of 64 of F = 2560 1412 / 1371)
-  r.kind = r.nrows <= 64 ? 0 : (r.nrows <= 128 ? 1 : (r.nrows <= 192 ? 3 : 2));   // the variant that computes it: the lowest that holds its rows, whatever its class in the table
+  r.kind = r.nrows <= 64 ? 0 : (r.nrows <= 128 ? 1 : (r.nrows <= 192 ? 3 : 2));   // the variant that computes it: the lowest that holds its rows
   return r;
 }
 __device__ __forceinline__ ItemRec load_item(const GemmParams& p, int idx) { return make_uniform(p.items[idx]); }

@@ -209,7 +209,7 @@ __global__ __launch_bounds__(256) void k_index_scatter(IndexParams p) {
   const int total_rows = exclusive_scan_256(off, my_cnt);
   if (blockIdx.x == 0) {
     const int e = threadIdx.x;
-    const int tail = e < E ? tail_height(my_cnt, p.tile_m) : 0;
+    const int tail = my_cnt % p.tile_m;
     const int my_tiles = e < E ? my_cnt / p.tile_m + (tail > 0) : 0;
     const int n_tiles = exclusive_scan_256(tbase, my_tiles);
     const int waves = wave == 0 ? waves_now(p, lane) : 0;
@@ -229,20 +229,19 @@ __global__ __launch_bounds__(256) void k_index_scatter(IndexParams p) {
     if (e < E) {
       p.ws.counts[e] = my_cnt;
       p.ws.offsets[e] = off[e];
-      const int kind_full = p.tile_m == 256 ? 2 : (p.tile_m == 128 ? 1 : 0);
       const int nfull = my_cnt / p.tile_m;
       int ti = tbase[e], row = off[e];
       for (int i = 0; i < nfull; i++, ti++, row += p.tile_m) {
         p.ws.tile_expert[ti] = e;
         p.ws.tile_row0[ti] = row;
         p.ws.tile_rows[ti] = p.tile_m;
-        p.ws.tile_kind[ti] = kind_full;
+        p.ws.tile_kind[ti] = height_class(p.tile_m);
       }
       if (tail > 0) {
         p.ws.tile_expert[ti] = e;
         p.ws.tile_row0[ti] = row;
-        p.ws.tile_rows[ti] = my_cnt % p.tile_m;
-        p.ws.tile_kind[ti] = tail == 256 ? 2 : (tail == 128 ? 1 : 0);
+        p.ws.tile_rows[ti] = tail;
+        p.ws.tile_kind[ti] = height_class(tail);
       }
     }
   }
@@ -513,14 +512,13 @@ struct ScheduleLds {
   uint8_t kind[kTileCap];
   uint8_t ready[kTileCap];
   uint8_t key0[kTileCap + 4];   // (height class, segment) or the height class alone; padded with 0xff
-  uint8_t key1[kTileCap + 4];   // height class
-  uint8_t key2[kTileCap + 4];   // the same with the light tiles of the tallest class behind it
-  uint16_t sub_first[kTileCap];       // position in ord1 of the first tile of tile i's run (same height, expert, wave)
+  uint8_t key1[kTileCap + 4];   // height class, tallest first
+  uint8_t key2[kTileCap + 4];   // the same with the light tiles in the class of their expert's full ones
   uint16_t blk_of[kTileCap];          // block of the tile at position i of ord1
   int32_t scan_buf[16];               // scratch of the prefix scans
   int32_t cls_first[4];
-  int32_t cls_count[3];
-  int32_t n_light, n_light_near;   // light tiles; those of experts of one block
+  int32_t cls_count[3], beside_count[3];   // tiles by key1 and by key2
+  int32_t n_light_near;   // light tiles of experts of one block
   int32_t queue_pos[3][kXcds];
   int32_t q_len_t[kXcds], q_base_t[kXcds];   // locality order: M-tiles per XCD queue, and ahead of it
   int32_t n_blocks;
@@ -539,7 +537,7 @@ __device__ inline ItemRec make_item_lds(const ScheduleLds& L, int m, int n) {
   return r;
 }
 
-// ord[rank of tile m] = m for the stable order by key (keys < 0xff; the padding never counts).
+// ord[rank of tile m] = m for the stable order by key (keys < 0xff, so that the padding never counts).
 __device__ inline void rank_sort(const uint8_t* key, uint16_t* ord, int n, int tid) {
   const uint32_t* words = (const uint32_t*)key;
   const int nw = (n + 3) >> 2;
@@ -584,25 +582,22 @@ __device__ inline void scan_pairs(int32_t* buf, int& v0, int& v1) {
   v1 = join(before, v1);
 }
 
-// rank_sort for the height classes alone (n2 > 0: four classes), up to kTileCap tiles: two counts in one scan instead of a pass over all keys
-// per tile (the schedule kernel for 250 tiles of 64 experts: 21.6 us with that, 17.4 so; up to kRankTiles tiles the pass is the shorter).  n0, n1, n2: tiles of the first classes.
-__device__ inline void class_sort(const uint8_t* key, uint16_t* ord, int n, int n0, int n1, int n2, int32_t* buf) {
+// rank_sort for the three height classes alone, up to kTileCap tiles: two counts in one scan instead of a pass over all keys
+// per tile (the schedule kernel for 250 tiles of 64 experts: 21.6 us with that, 17.4 so; up to kRankTiles tiles the pass is the shorter).  count: tiles of each class.
+__device__ inline void class_sort(const uint8_t* key, uint16_t* ord, int n, const int32_t* count, int32_t* buf) {
   static_assert(kTileCap <= 2048, "counts of 16 bits, two tiles per thread");
+  const int n0 = count[0], n1 = count[1];
   const int i0 = 2 * threadIdx.x, i1 = i0 + 1;
-  const int k0 = i0 < n ? key[i0] : 3, k1 = i1 < n ? key[i1] : 3;
+  const int k0 = i0 < n ? key[i0] : 2, k1 = i1 < n ? key[i1] : 2;
   auto one = [](int k) { return k == 0 ? 1 : (k == 1 ? 1 << 16 : 0); };
   int s0 = one(k0), s1 = one(k1);
   scan_pairs<false>(buf, s0, s1);   // of the first and second class up to and including this tile
-  int t0 = k0 == 2, t1 = k1 == 2;
-  if (n2 > 0) scan_pairs<false>(buf, t0, t1);   // ... of the third, where there may be a fourth
-  auto place = [&](int i, int k, int s, int t) {
-    const int a = s & 0xffff, b = s >> 16, rest = i - a - b;
-    int at = k == 0 ? a - 1 : (k == 1 ? n0 + b - 1 : n0 + n1 + rest);
-    if (n2 > 0 && k >= 2) at = k == 2 ? n0 + n1 + t - 1 : n0 + n1 + n2 + rest - t;
-    ord[at] = (uint16_t)i;
+  auto place = [&](int i, int k, int s) {
+    const int a = s & 0xffff, b = s >> 16;
+    ord[k == 0 ? a - 1 : (k == 1 ? n0 + b - 1 : n0 + n1 + i - a - b)] = (uint16_t)i;
   };
-  if (i0 < n) place(i0, k0, s0, t0);
-  if (i1 < n) place(i1, k1, s1, t1);
+  if (i0 < n) place(i0, k0, s0);
+  if (i1 < n) place(i1, k1, s1);
 }
 
 // Items of one layer in the locality order (see above); n_tiles_n column tiles.
@@ -619,7 +614,7 @@ __device__ inline void emit_blocks(const ScheduleLds& L, const uint16_t* ord, It
 // Blocks of the locality order and their XCD queues.  The tiles (in ord1's order: height class, expert, source order)
 // fall into runs of the same height class, expert and wave -- a wave being a group of consecutive source segments,
 // n_waves of them over the S segments (1: no waves) -- and every run is cut into blocks of up to block_m M-tiles.  beside: a
-// light tile is in its expert's last block; otherwise the light tiles are a class of their own.
+// light tile is in its expert's last block; otherwise it is in the runs of its own height class.
 // The blocks are sorted by (wave, height class, larger first) and dealt to the XCD queues back and forth (0..7,
 // 7..0, ...): with the sizes descending this keeps the queues level even when the experts' loads differ a lot, which
 // round-robin does not (what is left uneven, the workgroups even out by taking from other XCDs' queues at the end).
@@ -630,7 +625,7 @@ __device__ inline void build_blocks(ScheduleLds& L, const uint16_t* ord1, int n_
   auto run_key = [&](int i) {
     const int m = ord1[i];
     const int wave = n_waves > 1 ? (int)L.ready[m] * n_waves / S : 0;
-    return ((int)(beside ? L.key1[m] : L.key2[m]) << 16) | ((int)L.expert[m] << 8) | wave;
+    return ((int)(beside ? L.key2[m] : L.key1[m]) << 16) | ((int)L.expert[m] << 8) | wave;
   };
   if (tid < kXcds) L.q_len_t[tid] = 0;
   const int i0 = 2 * tid, i1 = 2 * tid + 1;
@@ -639,9 +634,9 @@ __device__ inline void build_blocks(ScheduleLds& L, const uint16_t* ord1, int n_
   if (i1 < n_tiles && run_key(i1) != run_key(i1 - 1)) f1 = i1;
   scan_pairs<true>(L.scan_buf, f0, f1);
   int s0 = 0, s1 = 0;
-  auto starts = [&](int i, int f) { return (i - f) % block_m == 0 && !(i > f && beside && is_light(L.rows[ord1[i]], L.kind[ord1[i]])); };
-  if (i0 < n_tiles) { L.sub_first[i0] = (uint16_t)f0; s0 = starts(i0, f0); }
-  if (i1 < n_tiles) { L.sub_first[i1] = (uint16_t)f1; s1 = starts(i1, f1); }
+  auto starts = [&](int i, int f) { return (i - f) % block_m == 0 && !(i > f && beside && L.key2[ord1[i]] != L.key1[ord1[i]]); };
+  if (i0 < n_tiles) s0 = starts(i0, f0);
+  if (i1 < n_tiles) s1 = starts(i1, f1);
   const int start0 = s0, start1 = s1;
   scan_pairs<false>(L.scan_buf, s0, s1);
   if (i0 < n_tiles) L.blk_of[i0] = (uint16_t)(s0 - 1);
@@ -655,7 +650,7 @@ __device__ inline void build_blocks(ScheduleLds& L, const uint16_t* ord1, int n_
     const int key = run_key(i);
     L.blk_g[b] = (uint16_t)g;
     L.blk_first[b] = (uint16_t)i;
-    L.blk_key[b] = (uint8_t)((key & 0xff) * 32 + (key >> 16) * 8 + (8 - min(g, 8)));   // wave, class, larger blocks first
+    L.blk_key[b] = (uint8_t)((key & 0xff) * 24 + (key >> 16) * 8 + (8 - min(g, 8)));   // wave, class, larger blocks first
   };
   if (i0 < n_tiles && start0) describe(i0, s0 - 1);
   if (i1 < n_tiles && start1) describe(i1, s1 - 1);
@@ -687,9 +682,10 @@ __device__ inline void build_blocks(ScheduleLds& L, const uint16_t* ord1, int n_
   __syncthreads();
 }
 
-// M-tile m as the schedule builder sees it: its table row and the segment of its last row (of token `last_token`).
+// M-tile m as the schedule builder sees it: its table row and the segment of its last row (of token `last_token`).  ragged: it is the
+// remainder beside full tiles of its expert, light where its class is a lower one.
 __device__ inline void note_tile(ScheduleLds& L, const IndexParams& p, const int32_t* seg_lds, int m, int expert, int row0,
-                                 int nrows, int kind, int last_token, bool publish) {
+                                 int nrows, int kind, bool ragged, int last_token, bool publish) {
   const int S = p.s.S, nseg = p.layer0_order == 1 ? S : 1;
   int s = 0;
   while (s + 1 < S && seg_lds[s + 1] <= last_token) s++;
@@ -698,13 +694,12 @@ __device__ inline void note_tile(ScheduleLds& L, const IndexParams& p, const int
   L.kind[m] = (uint8_t)kind;
   L.expert[m] = (uint8_t)expert;
   L.ready[m] = (uint8_t)s;
+  const int beside = 2 - (ragged ? height_class(p.tile_m) : kind);
   L.key0[m] = (uint8_t)((2 - kind) * nseg + (nseg > 1 ? s : 0));
   L.key1[m] = (uint8_t)(2 - kind);
-  const bool light = is_light(nrows, kind);   // (only of the tallest class)
-  const int below = height_class(p.tile_m) - kind;
-  L.key2[m] = (uint8_t)(below == 0 ? light : below + 1);
+  L.key2[m] = (uint8_t)beside;
   atomicAdd(&L.cls_count[2 - kind], 1);
-  if (light) atomicAdd(&L.n_light, 1);
+  atomicAdd(&L.beside_count[beside], 1);
   if (publish) p.ws.tile_ready[m] = s;
 }
 
@@ -724,24 +719,20 @@ __device__ inline void build_schedules(ScheduleLds& L, const IndexParams& p, int
   // tokens, top-4, F = 1408; 704 and 512 light items) 731 / 630, for half of them (8192 tokens; 319 and 232) 607 / 567, (4096 tokens, top-8, F =
   // 2560; 580 and 406) 1707 / 1641; one full tile (1060 tokens of 8 experts of F = 7168) 545 / 497; 112 and 64 items (2047 tokens of 8 experts)
   // 381 / 414; 8 full tiles (8192 tokens of 8 experts of F = 14336, 448 items in layer0) 4045 / 4088.
+  // Other orders keep to the tiles' own classes (4096 tokens of 8 experts of F = 14336, light
+  // tiles among the full ones / behind: panel-major 2345 / 2257, large builder 2305 / 2230).
   for (int m = tid; m < n_tiles; m += 1024)
-    if (is_light(L.rows[m], L.kind[m]) && !(m > block_m && L.expert[m - block_m - 1] == L.expert[m])) atomicAdd(&L.n_light_near, 1);
+    if (L.key2[m] != L.key1[m] && !(m > block_m && L.expert[m - block_m - 1] == L.expert[m])) atomicAdd(&L.n_light_near, 1);
   __syncthreads();
-  const bool beside0 = !local0 || L.n_light_near * p.n_tiles_n0 >= kBesideItems;
-  const bool beside1 = !local1 || L.n_light_near * p.n_tiles_n1 >= kBesideItems;
+  const bool beside0 = local0 && L.n_light_near * p.n_tiles_n0 >= kBesideItems;
+  const bool beside1 = local1 && L.n_light_near * p.n_tiles_n1 >= kBesideItems;
   auto sort_tiles = [&](uint16_t* ord, bool beside) {   // tallest class first, then table order
-    if (n_tiles <= kRankTiles) {
-      rank_sort(beside ? L.key1 : L.key2, ord, n_tiles, tid);
-    } else if (beside) {
-      class_sort(L.key1, ord, n_tiles, L.cls_count[0], L.cls_count[1], 0, L.scan_buf);
-    } else {
-      const int top = 2 - height_class(p.tile_m), n0 = L.cls_count[top];
-      class_sort(L.key2, ord, n_tiles, n0 - L.n_light, L.n_light, top < 2 ? L.cls_count[top + 1] : 0, L.scan_buf);
-    }
+    if (n_tiles <= kRankTiles) rank_sort(beside ? L.key2 : L.key1, ord, n_tiles, tid);
+    else class_sort(beside ? L.key2 : L.key1, ord, n_tiles, beside ? L.beside_count : L.cls_count, L.scan_buf);
   };
   if (nseg > 1) rank_sort(L.key0, L.ord0, n_tiles, tid);
   else sort_tiles(L.ord0, beside0);
-  const bool two_orders = nseg > 1 || (L.n_light > 0 && beside0 != beside1);
+  const bool two_orders = nseg > 1 || beside0 != beside1;
   if (two_orders) sort_tiles(L.ord1, beside1);
   if (tid == 0) {
     int pos = 0;
@@ -842,8 +833,8 @@ __global__ __launch_bounds__(1024) void k_index_schedule(IndexParams p) {
   const int n_tiles = max(0, min(p.ws.status[1], p.max_tiles));
   const int tid = threadIdx.x;
   if (tid <= p.s.S) seg_lds[tid] = p.seg_offsets[tid];
-  if (tid < 3) L.cls_count[tid] = 0;
-  if (tid == 3) L.n_light = L.n_light_near = 0;
+  if (tid < 3) L.cls_count[tid] = L.beside_count[tid] = 0;
+  if (tid == 3) L.n_light_near = 0;
   __syncthreads();
   for (int m = tid; m < n_tiles + 4; m += 1024) {
     if (m >= n_tiles) {
@@ -853,7 +844,9 @@ __global__ __launch_bounds__(1024) void k_index_schedule(IndexParams p) {
       continue;
     }
     const int r0 = p.ws.tile_row0[m], nr = p.ws.tile_rows[m], kd = p.ws.tile_kind[m];
-    note_tile(L, p, seg_lds, m, p.ws.tile_expert[m], r0, nr, kd, p.ws.row_token[max(0, min(r0 + nr, p.s.R) - 1)], blockIdx.x == 0);
+    const int e = p.ws.tile_expert[m];
+    const bool ragged = nr < p.tile_m && m > 0 && p.ws.tile_expert[m - 1] == e;
+    note_tile(L, p, seg_lds, m, e, r0, nr, kd, ragged, p.ws.row_token[max(0, min(r0 + nr, p.s.R) - 1)], blockIdx.x == 0);
   }
   __syncthreads();
   build_schedules(L, p, n_tiles, p.ws.status[7], blockIdx.x == 0, blockIdx.x * 1024 + tid, gridDim.x * 1024);
@@ -884,8 +877,8 @@ __global__ __launch_bounds__(1024) void k_index_small(IndexParams p, int schedul
   }
   for (int i = tid; i < n_runs * E; i += 1024) run_cnt[i] = 0;
   if (tid <= p.s.S) seg_lds[tid] = p.seg_offsets[tid];
-  if (tid < 3) L.cls_count[tid] = 0;
-  if (tid == 3) L.n_light = L.n_light_near = 0;
+  if (tid < 3) L.cls_count[tid] = L.beside_count[tid] = 0;
+  if (tid == 3) L.n_light_near = 0;
   if (tid < kMaxExperts) cnt[tid] = 0;
   __syncthreads();
 #pragma unroll
@@ -999,31 +992,26 @@ __global__ __launch_bounds__(1024) void k_index_small(IndexParams p, int schedul
     }
     const int i = m - tbase[lo], full = cnt[lo] / p.tile_m;
     const int row0 = off[lo] + i * p.tile_m;
-    int rows = p.tile_m, height = p.tile_m;
-    if (i >= full) {
-      rows = cnt[lo] % p.tile_m;
-      height = tail_height(cnt[lo], p.tile_m);
-    }
-    const int kind = height == 256 ? 2 : (height == 128 ? 1 : 0);
+    const int rows = i < full ? p.tile_m : cnt[lo] % p.tile_m, kind = height_class(rows);
     p.ws.tile_expert[m] = lo;
     p.ws.tile_row0[m] = row0;
     p.ws.tile_rows[m] = rows;
     p.ws.tile_kind[m] = kind;
-    note_tile(L, p, seg_lds, m, lo, row0, rows, kind, token_of[row0 + rows - 1], true);
+    note_tile(L, p, seg_lds, m, lo, row0, rows, kind, i >= full && full > 0, token_of[row0 + rows - 1], true);
   }
   if (!schedule) return;
   __syncthreads();
   build_schedules(L, p, n_tiles, waves, true, tid, 1024);
 }
 
-__global__ void k_tile_heights(const int32_t* __restrict__ kind, int32_t* __restrict__ height, int n) {
+__global__ void k_tile_heights(const int32_t* __restrict__ rows, int32_t* __restrict__ height, int n) {
   const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < n) height[i] = 64 << kind[i];
+  if (i < n) height[i] = variant_rows(rows[i]);
 }
 
-hipError_t launch_tile_heights(const int32_t* kind, int32_t* height, int n, hipStream_t st) {
+hipError_t launch_tile_heights(const int32_t* rows, int32_t* height, int n, hipStream_t st) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_tile_heights, dim3((n + 255) / 256), dim3(256), 0, st, kind, height, n);
+  hipLaunchKernelGGL(k_tile_heights, dim3((n + 255) / 256), dim3(256), 0, st, rows, height, n);
   return hipGetLastError();
 }
 

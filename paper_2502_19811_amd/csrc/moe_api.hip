@@ -896,7 +896,7 @@ int moe_get_tile_table(const moe_plan_t* p, const void* workspace, int32_t* n_ti
   if (!cp(n_tiles, ws.status + 1, 4) || !cp(tile_expert, ws.tile_expert, tb) || !cp(tile_row0, ws.tile_row0, tb) ||
       !cp(tile_rows, ws.tile_rows, tb) || !cp(tile_ready_seg, ws.tile_ready, tb))
     return MOE_ERR_HIP;
-  if (tile_height && launch_tile_heights(ws.tile_kind, tile_height, p->max_tiles, st) != hipSuccess) return MOE_ERR_HIP;
+  if (tile_height && launch_tile_heights(ws.tile_rows, tile_height, p->max_tiles, st) != hipSuccess) return MOE_ERR_HIP;
   return MOE_OK;
 }
 

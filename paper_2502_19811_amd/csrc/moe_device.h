@@ -54,23 +54,15 @@ __device__ __forceinline__ float silu(float v) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Tiling of an expert's rows: as many tiles of tile_m rows as fit, then one tile for the remainder.  Beside full tiles the
-// remainder's is of their height class, so that the schedule may put it next to them (see build_schedules), and light where
-// it has at most half as many rows: a GroupGEMM workgroup computes a tile with the lowest variant that holds its rows,
-// whatever its class.  An expert without full tiles has one tile of the lowest height that holds it.  (A remainder of
+// Tiling of an expert's rows: as many tiles of tile_m rows as fit, then one tile for the remainder.  A tile's height class is the
+// lowest of 64, 128 and 256 rows that holds it.  (A remainder of
 // 129 to 192 rows, for which there is a variant, is not split into a 128- and a 64-row tile: every tile of a column streams
 // the expert's weights, which costs what the matrix cores need for about 240 rows.  160 rows for each of 16
 // experts with F = 6400: 941 -> 611 us, 400 rows 1385 -> 1022.)
 // ---------------------------------------------------------------------------------------------
 __device__ inline int height_class(int rows) { return rows <= 64 ? 0 : (rows <= 128 ? 1 : 2); }
-// (of the tallest class: the others' tiles are the lowest that hold their rows)
-__device__ inline bool is_light(int rows, int kind) { return height_class(rows) < kind; }
-__device__ inline int tail_height(int rows, int tile_m) {   // height of the tile that holds the remainder; 0: there is none
-  const int rem = rows % tile_m;
-  if (rem == 0) return 0;
-  if (rows > tile_m) return tile_m;   // beside full tiles
-  return rem <= 64 || tile_m == 64 ? 64 : (rem <= 128 || tile_m == 128 ? 128 : 256);
-}
+// Rows of the kernel variant that computes a tile.
+__device__ inline int variant_rows(int rows) { return rows <= 64 ? 64 : (rows <= 128 ? 128 : (rows <= 192 ? 192 : 256)); }
 
 // Waves of the layer0 schedule (order 2) of this forward, decided by one wavefront for everybody: the plan's number, or
 // one -- the order of resident input -- when every source segment has arrived by now (waves cost the weight reuse: layer0

@@ -61,7 +61,7 @@ struct Workspace {
   int32_t* tile_row0;     // [max_tiles]
   int32_t* tile_rows;     // [max_tiles]
   int32_t* tile_ready;    // [max_tiles] source segment the tile waits for
-  int32_t* tile_kind;     // [max_tiles] height class 0 / 1 / 2 the tile is scheduled in: 64 / 128 / 256 rows
+  int32_t* tile_kind;     // [max_tiles] height class 0 / 1 / 2: the lowest of 64 / 128 / 256 rows that holds the tile
   int32_t* tile_order;    // [max_tiles] scratch of the schedule builder: tiles sorted tallest first
   ItemRec* items0;        // [max_tiles * n_tiles_n0] layer0 schedule
   ItemRec* items1;        // [(max_tiles + 24) * n_tiles_n1] layer1 schedule, one contiguous queue per XCD
@@ -227,6 +227,6 @@ hipError_t launch_combine(const CombineParams& p, hipStream_t st);
 hipError_t launch_zero_u32(uint32_t* ptr, size_t n, hipStream_t st);
 hipError_t launch_pack_weights(const void* B, void* out, int E, int K, int ldb, int n_tiles_n, int swiglu_F, hipStream_t st);
 hipError_t launch_arrival_producer(const void* staging, void* x, const ArrivalParams& a, int n_wg, hipStream_t st);
-hipError_t launch_tile_heights(const int32_t* kind, int32_t* height, int n, hipStream_t st);
+hipError_t launch_tile_heights(const int32_t* rows, int32_t* height, int n, hipStream_t st);
 
 }  // namespace moe

@@ -103,16 +103,21 @@ def error_metrics(got: np.ndarray, ref: np.ndarray):
     return a, b
 
 
+def height_class(rows):
+    """0, 1, 2: the lowest of 64, 128, 256 rows that holds a tile."""
+    return np.where(rows <= 64, 0, np.where(rows <= 128, 1, 2))
+
+
 def check_tile_table(tiles, cfg, offsets, perm, seg_offsets, tile_m):
     """The M-tile table of a forward, checked through what any valid table has (the paper fixes no tile size or cut
-    rule: the rule is the library's): expert-major; the tiles of an expert partition its row range in order; heights
-    are kernel variants no taller than tile_m; a tile is full unless it is the expert's last; the segment it waits
-    for is the latest segment of its rows (Section 2.2.1), computed here from the oracle's row order."""
+    rule: the rule is the library's): expert-major; the tiles of an expert partition its row range in order; a tile has tile_m
+    rows unless it is the expert's last; its height is the lowest kernel variant (64, 128, 192, 256 rows) that holds its rows; the
+    segment it waits for is the latest segment of its rows (Section 2.2.1), computed here from the oracle's row order."""
     from oracle import moe_oracle as orc
     ex, r0, nr, rs, ht = (np.asarray(tiles[key], dtype=np.int64) for key in ("expert", "row0", "rows", "ready_seg", "height"))
     assert (np.diff(ex) >= 0).all(), "tile table is not expert-major"
-    assert np.isin(ht, (64, 128, 256)).all() and (ht <= tile_m).all()
-    assert (nr > 0).all() and (nr <= ht).all()
+    assert (nr > 0).all() and (nr <= tile_m).all()
+    np.testing.assert_array_equal(ht, -(-nr // 64) * 64)
     row_seg = orc.segment_of_token(seg_offsets, np.asarray(perm, dtype=np.int64) // cfg.k).astype(np.int64)
     pos = 0
     for e in range(cfg.E):
@@ -125,23 +130,26 @@ def check_tile_table(tiles, cfg, offsets, perm, seg_offsets, tile_m):
         pos += idx.size
         assert r0[idx[0]] == lo and r0[idx[-1]] + nr[idx[-1]] == hi
         assert (r0[idx[1:]] == r0[idx[:-1]] + nr[idx[:-1]]).all(), f"tiles of expert {e} leave a gap or overlap"
-        assert (nr[idx[:-1]] == ht[idx[:-1]]).all(), "only the last tile of an expert may be ragged"
-        # little padding: less than the smallest tile, unless the remainder needed a full-height ragged tile
-        pad = int(ht[idx].sum()) - (hi - lo)
-        assert 0 <= pad < 64 or ht[idx[-1]] == tile_m
+        assert (nr[idx[:-1]] == tile_m).all(), "only the last tile of an expert may be ragged"
     assert pos == ex.size
     for m in range(ex.size):
         assert rs[m] == row_seg[r0[m]:r0[m] + nr[m]].max(), f"tile {m} waits for the wrong segment"
 
 
-def check_schedule(items, queues, tiles, n_tiles_n, seg_major=False, panel_major=False, waves=None):
+def check_schedule(items, queues, tiles, n_tiles_n, seg_major=False, panel_major=False, waves=None, beside=False):
     """Invariants of a tile schedule (Fig. 5 / Fig. 6): the queues list every (M-tile, column tile) pair exactly once,
-    every record repeats its M-tile's table row, tall tiles come before short ones inside a queue; seg_major: inside
+    every record repeats its M-tile's table row, tall tiles come before short ones inside a queue; beside: but a light tile
+    (the remainder beside full tiles, of a lower class) comes right behind its expert's last full tile of the same column tile (with
+    waves: where both are in the same one) and counts as tall; seg_major: inside
     a height class of a queue the segment waited for never decreases (rows that arrive early first); panel_major:
     inside a height class of a queue the groups of 4 column panels ascend (all M-tiles finish a group before the
     next one starts); waves = (n_waves, S): the queue is wave-major (wave of a tile = ready_seg * n_waves // S), tall
     before short inside a wave, and the M-tiles of an expert inside a wave sweep the column tiles together."""
     n_tiles = len(tiles["row0"])
+    cls, expert = height_class(tiles["rows"]), tiles["expert"]
+    before = np.maximum(np.arange(n_tiles) - 1, 0)
+    light = (np.arange(n_tiles) > 0) & (expert[before] == expert) & (cls < cls[before])
+    rank = np.where(light & beside, cls[before], cls)       # what the order of a queue goes by
     seen = np.zeros((n_tiles, n_tiles_n), dtype=np.int32)
     for first, count, stride in queues:
         if count == 0:
@@ -154,15 +162,20 @@ def check_schedule(items, queues, tiles, n_tiles_n, seg_major=False, panel_major
         np.testing.assert_array_equal(q[:, 2], tiles["expert"][m])
         np.testing.assert_array_equal(q[:, 3], tiles["row0"][m])
         np.testing.assert_array_equal(q[:, 4], tiles["rows"][m])
-        np.testing.assert_array_equal(64 << q[:, 5], tiles["height"][m])
+        np.testing.assert_array_equal(q[:, 5], cls[m])
         np.testing.assert_array_equal(q[:, 6], tiles["ready_seg"][m])
+        if beside:
+            wave_of = (lambda i: tiles["ready_seg"][i] * waves[0] // waves[1]) if waves else (lambda i: 0)
+            for i in np.nonzero(light[m])[0]:
+                if wave_of(m[i]) == wave_of(m[i] - 1):
+                    assert i > 0 and m[i - 1] == m[i] - 1 and n[i - 1] == n[i], f"light tile {m[i]} is not beside its expert's full tiles"
         if waves:
             wave = q[:, 6] * waves[0] // waves[1]
             assert (np.diff(wave) >= 0).all(), "a tile of an earlier wave after one of a later wave"
             for wv in np.unique(wave):
-                assert (np.diff(q[wave == wv][:, 5]) <= 0).all(), "a taller tile after a shorter one inside a wave"
+                assert (np.diff(rank[m[wave == wv]]) <= 0).all(), "a taller tile after a shorter one inside a wave"
         else:
-            assert (np.diff(q[:, 5]) <= 0).all(), "a taller tile after a shorter one"
+            assert (np.diff(rank[m]) <= 0).all(), "a taller tile after a shorter one"
         for kind in (2, 1, 0):
             part = q[q[:, 5] == kind]
             if seg_major:
