@@ -218,7 +218,7 @@ __device__ __forceinline__ void own_index(UnitTable& L, const DecodeParams& p, i
 
 // NB: 16-column blocks of weights of a wavefront (SwiGLU: half of them gate, half up columns of the same hidden units);
 // RB: 8-row groups of A that are loaded (a unit is up to 8 RB rows); U: steps in flight; EU: wavefronts a SIMD holds; STREAM:
-// the loads of B are non-temporal (GemmParams::b_stream).
+// the loads of B are non-temporal (DecodeParams::b_stream).
 template <int MODE, bool PK, int NB, int RB, int U, int EU, bool STREAM>
 __global__ __launch_bounds__(kDecodeWaves * 64) __attribute__((amdgpu_waves_per_eu(EU))) void k_decode_gemm(DecodeParams p, IndexParams ip) {
   constexpr bool kPair = MODE == MODE_L0_SWIGLU;

@@ -52,7 +52,7 @@ __device__ __forceinline__ void mfma_in_place(f32x4& acc, bf16x8 b, bf16x8 a) {
 // 16 bytes per lane from sbase + voff straight into LDS at lds_base + lane * 16.  Written as asm so that the
 // compiler's wait-count pass does not serialise later LDS reads behind it; completion is awaited by hand
 // with s_waitcnt vmcnt.
-// STREAM: with the non-temporal hint (GemmParams::b_stream).
+// STREAM: with the non-temporal hint (GemmParams::stream_rows).
 template <bool STREAM = false>
 __device__ __forceinline__ void dma16(const void* sbase, uint32_t voff, uint32_t lds_base) {
   if constexpr (STREAM)
@@ -1094,6 +1094,15 @@ __global__ __launch_bounds__(256, 1) void k_group_gemm(GemmParams p) {
   }
   const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int xcd = blockIdx.x & (kXcds - 1);
+  // Whether weights are loaded with the hint is a fact of the expert: those of one tile (see stream_rows on the host side).  By the mean of the rows
+  // alone, every tile of a launch alike, the tiles of a crowded expert fetched its weights from HBM one after the other.  us per gate + layer,
+  // popularity falling as rank^-0.3, 3 sets of weights in turn, none / by the mean / so: 225 rows for each of 8 experts of F = 14336
+  // 824 / 882 / 814, 64 of F = 2560 949 / 1005 / 942; rank^-1.2, 125 rows for each of 16 of F = 6400 691 / 674 / 612; even, 200 for each of 64 of F =
+  // 2560 828 / 801 / 799; tiles of 128 rows for 150, 16 of F = 6400 641 / 814 / 641.
+  __shared__ uint64_t lds_stream[STREAM ? kMaxExperts / 64 : 1];   // a bit per expert
+  static_assert(kMaxExperts == 256, "an expert per thread");
+  int my_rows = 0;
+  if (STREAM) my_rows = p.counts[min(tid, p.E - 1)];
   Queue q;
   q.own_len = p.queue_len[xcd];
   q.own_base = queue_pos(p, xcd, 0);
@@ -1119,6 +1128,10 @@ __global__ __launch_bounds__(256, 1) void k_group_gemm(GemmParams p) {
     }
   };
   take_sync(cur);
+  if (STREAM) {
+    const uint64_t few = __ballot(my_rows <= p.stream_rows);
+    if (lane == 0) lds_stream[w] = few;
+  }
   while (cur.idx >= 0) {
     // every wavefront is done with the LDS of the previous tile before its slots are refilled
     __syncthreads();
@@ -1127,11 +1140,22 @@ __global__ __launch_bounds__(256, 1) void k_group_gemm(GemmParams p) {
       continue;
     }
     next.idx = -1;
-    if (cur.rec.kind == 2) run_tile<2, 4, 4, MODE, PK, STREAM>(p, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
-    else if (cur.rec.kind == 1) run_tile<2, 2, 4, MODE, PK, STREAM>(p, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
-    else if (cur.rec.kind == 3) run_tile<2, 3, 4, MODE, PK, STREAM>(p, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
-    else if (deep64) run_tile<1, 2, 2, MODE, PK, STREAM, kDeepStages>(p, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
-    else run_tile<1, 2, 2, MODE, PK, STREAM>(p, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
+    auto run = [&](auto hint) {
+      constexpr bool S = decltype(hint)::value;
+      if (cur.rec.kind == 2) run_tile<2, 4, 4, MODE, PK, S>(p, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
+      else if (cur.rec.kind == 1) run_tile<2, 2, 4, MODE, PK, S>(p, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
+      else if (cur.rec.kind == 3) run_tile<2, 3, 4, MODE, PK, S>(p, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
+      else if (deep64) run_tile<1, 2, 2, MODE, PK, S, kDeepStages>(p, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
+      else run_tile<1, 2, 2, MODE, PK, S>(p, smem, lds_slot, cur, next, xcd, q, pending_panel, lds_panel_count, lds_mask);
+    };
+    if constexpr (STREAM) {
+      const int e = cur.rec.expert;
+      const uint32_t few = ((const uint32_t*)lds_stream)[e >> 5];
+      if ((uniform((int)few) >> (e & 31)) & 1) run(std::true_type{});
+      else run(std::false_type{});
+    } else {
+      run(std::false_type{});
+    }
     cur = next;
   }
   if (MODE == MODE_L1 && p.fused_combine) {
@@ -1349,7 +1373,7 @@ hipError_t launch_fused_layers(const GemmParams& p0, const GemmParams& p1, const
 template <int MODE, bool PK>
 static hipError_t launch_gemm(const GemmParams& p, int grid, hipStream_t st) {
   constexpr int lds = kLdsBytes;
-  auto kern = p.b_stream ? k_group_gemm<MODE, PK, true> : k_group_gemm<MODE, PK, false>;
+  auto kern = p.stream_rows > 0 ? k_group_gemm<MODE, PK, true> : k_group_gemm<MODE, PK, false>;
   hipError_t e = allow_large_lds((const void*)kern, lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, st, p);

@@ -273,13 +273,26 @@ bool decode_path(const moe_plan* p, int n_tiles_n, int64_t K, int64_t ldb, bool 
 // leaves nothing in the Infinity Cache, at 7.0-7.4.  us per gate + layer, without / with it: small-batch kernel, 1 token of 8 experts of
 // F = 14336 133 / 121, 16 tokens 495 / 445, 48 of 64 experts of F = 2560 635 / 578; tile kernel, 509 tokens of 16 experts of F = 6400
 // 487 / 447, 64 tokens of 8 of F = 14336 516 / 462.
-// It does not pay where the caches would have the weights for somebody:
-//  * weights of less than half the Infinity Cache (256 MB), so that those of two layers in turn stay there: 3 plans in turn, 82 MB each
-//    36.3 / 37.1, plain weights 51.4 / 54.4; 145 MB 47.7 / 43.8, 130 MB 44.0 / 40.6;
-//  * tile kernel: experts of more than one tile, whose tiles share the weights.  us with the hint / without at 200 rows per expert (64
-//    experts) 847 / 869, 206 316 / 323, 237 920 / 953, 250 391 / 368, (16 experts) 770 / 740, 320 (8) 1150 / 1004, 300 (64) 1503 / 1221.
-bool weights_pass_caches(const Shape& s) {
-  return expected_experts(s) * ((double)s.H * s.F1 + (double)s.F * s.H) * 2 > kCachedWeightBytes;
+// It does not pay where the caches would have the weights for somebody: weights of less than half the Infinity Cache (256 MB), so that those
+// of two layers in turn stay there.  3 plans in turn, 82 MB each 36.3 / 37.1, plain weights 51.4 / 54.4; 145 MB 47.7 / 43.8, 130 MB 44.0 / 40.6.
+// (A single layer of up to 256 MB, forward after forward and nothing else, would find them there: 48 rows for each of 4 experts of F = 2048,
+// 201 MB, 65 / 92; with two more in turn 98 / 91.)
+double weight_bytes(const Shape& s) { return expected_experts(s) * ((double)s.H * s.F1 + (double)s.F * s.H) * 2; }
+bool weights_pass_caches(const Shape& s) { return weight_bytes(s) > kCachedWeightBytes; }
+
+// Tile kernel: nor does it pay for the weights that several tiles of an expert share, so it is for experts of up to this many rows, one tile; which
+// these are is known on the device (k_group_gemm).  Where an expert has two tiles of 64 rows and all tiles are one round, both stream its weights
+// at the same time and share them in the L2 all the same: us per gate + layer, one tile / two, 75 to 112 rows for each of 8 experts of F = 1792
+// 108 to 113 / 98 to 104 (none: 109 to 113), plain 111 to 115 / 104 to 109, 16 of F = 1024 123 to 129 / 110 to 115; 4 of F = 1408 (138 MB) plain
+// 86 to 92 / 91 to 95 (none: 84 to 91).  Three and more do not (4 of F = 2048, 160 and 220 rows: none 102 and 104, all 104 and 109), nor two
+// tiles of 128 (8 of F = 1792, 140 and 170 rows, plain: 133 and 133 / 145 and 140).  Beyond 244 rows on average few experts are left with one
+// tile (none / all: 250 rows 368 / 391, 300 of 64 experts 1221 / 1503).
+int stream_rows(const moe_plan* p) {
+  const Shape& s = p->s;
+  if (!weights_pass_caches(s) || s.R > (int64_t)kStreamRowsPerExpert * s.E) return 0;
+  const int experts = s.E < s.R ? s.E : s.R;
+  const bool two = p->tile_m == 64 && (int64_t)experts * p->n_tiles_n0 * 2 <= p->n_cu && weight_bytes(s) > kStreamPairBytes;
+  return two ? 128 : p->tile_m;
 }
 
 bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
@@ -621,7 +634,9 @@ int forward_impl(moe_plan_t* p, const void* x, const int32_t* topk_ids, const fl
   a.ldb = (uint32_t)s.F1;
   a.b_packed = p->weights_packed;
   const bool stream = weights_pass_caches(s);
-  a.b_stream = stream && s.R <= (int64_t)kStreamRowsPerExpert * s.E;
+  a.stream_rows = stream_rows(p);
+  a.counts = ws.counts;
+  a.E = s.E;
   if (p->alias_experts && !p->weights_packed) a.b_expert_bytes = 0;   // measurement aid, see the option
   a.n_tiles_n = p->n_tiles_n0;
   a.C = ws.h;
@@ -662,7 +677,9 @@ int forward_impl(moe_plan_t* p, const void* x, const int32_t* topk_ids, const fl
   b.b_expert_bytes = (uint64_t)s.F * s.H * 2;
   b.ldb = (uint32_t)s.H;
   b.b_packed = p->weights_packed;
-  b.b_stream = a.b_stream;
+  b.stream_rows = a.stream_rows;
+  b.counts = a.counts;
+  b.E = a.E;
   if (p->alias_experts && !p->weights_packed) b.b_expert_bytes = 0;
   b.n_tiles_n = p->n_tiles_n1;
   b.C = ws.Y;

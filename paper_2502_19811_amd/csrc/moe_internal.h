@@ -23,7 +23,8 @@ constexpr int kCombineChunk = 256;  // tokens per unit of combine work
 constexpr int kDecodeRowsPerExpert = 16;   // rows per expert on average up to which the decode kernel is used ...
 constexpr int kDecodeRowsManyTiles = 8;    // ... and where the tile kernel has more tiles than compute units
 constexpr double kCachedWeightBytes = 128e6;   // weights read by a forward beyond which its loads of them are non-temporal ...
-constexpr int kStreamRowsPerExpert = 244;   // ... in the tile kernel up to this many rows per expert on average
+constexpr int kStreamRowsPerExpert = 244;   // ... in the tile kernel up to this many rows per expert on average, for experts of one tile ...
+constexpr double kStreamPairBytes = 160e6;   // ... or two of 64 rows that run at the same time, beyond these weights
 constexpr int kOwnIndexRows = 512;   // pairs up to which the small-batch GroupGEMMs make their index themselves
 constexpr int kDecodeCachedRows = 4096;    // ... and pairs up to which it is used for weights of at most ...
 constexpr int64_t kDecodeCachedBytes = 4 << 20;   // ... the L2 of an XCD
@@ -106,7 +107,9 @@ struct GemmParams {
   uint64_t b_expert_bytes;  // bytes between experts
   uint32_t ldb;             // elements per row of B
   int32_t b_packed;         // 1: B is in the packed layout of moe_pack_weights (b_expert_bytes and ldb unused)
-  int32_t b_stream;         // 1: B is loaded with the non-temporal hint: nobody reads it again from the caches
+  int32_t stream_rows;      // B of an expert of up to this many rows is loaded with the non-temporal hint: nobody reads it again from the caches (0: none)
+  const int32_t* counts;    // rows of the experts, E of them
+  int32_t E;
   int32_t n_tiles_n;        // column tiles of this layer (addressing of packed B)
   int32_t handoff_fences;   // measurement aid: per-tile agent-scope release (layer0) / acquire (layer1)
   int32_t no_pre;           // 1: a tile never starts its successor's loads early (the successor's rows may not be there)

@@ -11,7 +11,8 @@
 
 enum { NOTE_INDEX = 1, NOTE_SCHEDULE, NOTE_RESET, NOTE_LAYER0, NOTE_LAYER1, NOTE_DECODE0, NOTE_DECODE1 };
 struct Note {
-  int64_t kind, heads, stride, items0, items1, own_index, stream;   // heads, items: addresses; stride: bytes
+  // heads, items: addresses; stride: bytes; stream: rows of an expert up to which its weights are loaded with the non-temporal hint, or (small batches) whether they are
+  int64_t kind, heads, stride, items0, items1, own_index, stream;
 };
 static std::vector<Note> notes;
 
@@ -20,7 +21,7 @@ static void note(int kind, const Workspace& ws) {
   notes.push_back({kind, (int64_t)ws.queue_heads, ws.head_stride * 4, (int64_t)ws.items0, (int64_t)ws.items1, 0, 0});
 }
 static void note(int kind, const GemmParams& p) {
-  notes.push_back({kind, (int64_t)p.queue_heads, p.head_stride * 4, (int64_t)p.items, 0, 0, p.b_stream});
+  notes.push_back({kind, (int64_t)p.queue_heads, p.head_stride * 4, (int64_t)p.items, 0, 0, p.stream_rows});
 }
 hipError_t launch_route_topk(const float*, int, int, int, int32_t*, float*, hipStream_t) { return hipSuccess; }
 hipError_t launch_index_build(const IndexParams& p, bool schedule, hipStream_t) {

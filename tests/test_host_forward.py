@@ -124,3 +124,25 @@ def test_queue_heads_do_not_outgrow_the_static_workspace(lib):
             assert stride == 256 and not limit < total <= limit + 4096
         seen.add((stride, total <= limit))
     assert seen == {(4, True), (256, True), (256, False)}
+
+
+@pytest.mark.parametrize("T, H, F, E, k, act, options, rows", [
+    (509, 4096, 6400, 16, 2, 1, {}, 256),                       # an expert's only tile
+    (509, 4096, 6400, 16, 2, 1, {"tile_m": 64}, 64),            # 64 rows per expert in 64-row tiles: some have two, one after the other
+    (1200, 4096, 6400, 16, 2, 1, {"tile_m": 128}, 128),         # two for each
+    (1200, 3584, 2560, 64, 8, 1, {"tile_m": 64, "weights_packed": 1}, 64),
+    (640, 4096, 1792, 8, 2, 1, {}, 128),                        # 160 rows per expert, 128-row tiles
+    (1952, 4096, 6400, 16, 2, 1, {}, 256),                      # 244 rows per expert on average
+    (1953, 4096, 6400, 16, 2, 1, {}, 0),
+    (448, 4096, 1792, 8, 2, 1, {}, 128),                        # one round of 64-row tiles, two for an expert, run at the same time
+    (448, 4096, 1792, 8, 2, 1, {"tile_m": 128}, 128),
+    (320, 4096, 2176, 8, 2, 1, {"tile_m": 64}, 64),             # 17 column tiles: no longer one round
+    (200, 4096, 1408, 4, 2, 1, {}, 64),                         # 138 MB: the second tile may still find them in the caches
+    (200, 4096, 1152, 4, 2, 1, {}, 0),                          # 113 MB
+])
+def test_weights_are_streamed_for_experts_of_one_tile(lib, T, H, F, E, k, act, options, rows):
+    """Whose weights are loaded non-temporally: those nobody fetches again, by the rows of the expert and the height of the tiles."""
+    plan = Plan(lib, T, H, F, E, k, act, **options)
+    notes = plan.forward()
+    assert [n[6] for n in notes if n[0] in (LAYER0, LAYER1)] == [rows, rows]
+    plan.close()
