@@ -55,7 +55,7 @@ typedef struct {
 
 /* Small batches: with up to 16 rows per expert on average a GroupGEMM may run as a kernel made for the stream of weights,
  * without tile schedules (packed weights, up to 8 rows where the tiles are more than the compute units; plain ones where the
- * tiles would leave compute units idle), and so may the layers whose weights take at most 4 MiB, up to 4096 pairs.  An output is the
+ * tiles would leave compute units idle), and so may the layers whose weights take at most 4 MiB, up to 4096 pairs, fewer with large experts.  An output is the
  * same fp32 sum in the same order there, so its bits depend neither on which kernel computes it nor on the batch around its
  * token.  The options "n_cu", "layer1_order" 1 and 2, "n_prefetch" > 0, "fuse_layers", "handoff_fences", "alias_experts" and
  * "large_schedule" take the tile kernel whatever the size: times measured with one of them are to be read against a

@@ -233,12 +233,17 @@ int default_layer0_waves(const Shape& s, int ingest_gbps) {
 }
 
 // Batches whose GroupGEMMs may run as k_decode_gemm, without tile schedules.
-// Few rows per expert; or weights that all fit in the L2 of one XCD, where it costs nothing to pass them through it once per 32 rows, and no
-// schedule need be built.  us per gate + layer, 4 experts, H = 256, F = 512, tile kernel / this: 128 tokens 31.7 / 21.5, 500 33.7 / 25.4,
-// 1000 40.9 / 29.1, 2000 46.3 / 38.2.
+// Few rows per expert; or weights that all fit in the L2 of one XCD, where passing them through it once per 32 rows costs little, and no
+// schedule need be built.  us per gate + layer, tile kernel / this, 4 experts, H = 256, F = 512, k = 2: 128 tokens 31.7 / 21.5, 500 33.7 / 25.4,
+// 1000 40.9 / 29.1, 2000 46.3 / 38.2.  It costs little up to 64 MiB of passes; with large experts and many rows the small tiles are
+// what counts.  One expert, H = F = 768, SwiGLU, plain: 758 rows (80 MiB) 41.1 / 34.5, 1536 44.0 / 46.3, 2304 45.4 / 53.7; H = F = 1024, GELU,
+// 640 rows (80 MiB) 49.0 / 33.9, 2304 55.6 / 56.1, 4096 61.4 / 80.4, packed 59.1 / 72.7; H = 4096, F = 256, 640 75.0 / 47.6, 4096 97.9 / 108.3;
+// 5 of H = 512, F = 256, 3072 pairs (72 MiB) 39.6 / 37.3, 4096 42.3 / 44.6; 7 of H = 256, F = 384, 4096 pairs (72 MiB) 40.7 / 42.5; 2 of H = 768,
+// F = 384, 1517 (80 MiB) 39.4 / 36.2, 3072 43.7 / 50.9.
 bool few_rows(const Shape& s) {
   if ((int64_t)s.R <= (int64_t)kDecodeRowsPerExpert * s.E) return true;
-  return s.R <= kDecodeCachedRows && (int64_t)s.E * ((int64_t)s.H * s.F1 + (int64_t)s.F * s.H) * 2 <= kDecodeCachedBytes;
+  const int64_t expert_bytes = ((int64_t)s.H * s.F1 + (int64_t)s.F * s.H) * 2;
+  return s.R <= kDecodeCachedRows && s.E * expert_bytes <= kDecodeCachedBytes && s.R * expert_bytes / 32 <= kDecodeCachedPassBytes;
 }
 
 // Whether a GroupGEMM of n_tiles_n column tiles runs as k_decode_gemm (one pass over the weights for a few rows per

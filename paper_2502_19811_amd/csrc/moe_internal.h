@@ -27,7 +27,8 @@ constexpr int kStreamRowsPerExpert = 244;   // ... in the tile kernel up to this
 constexpr double kStreamPairBytes = 160e6;   // ... or two of 64 rows that run at the same time, beyond these weights
 constexpr int kOwnIndexRows = 512;   // pairs up to which the small-batch GroupGEMMs make their index themselves
 constexpr int kDecodeCachedRows = 4096;    // ... and pairs up to which it is used for weights of at most ...
-constexpr int64_t kDecodeCachedBytes = 4 << 20;   // ... the L2 of an XCD
+constexpr int64_t kDecodeCachedBytes = 4 << 20;   // ... the L2 of an XCD, while the passes over them are ...
+constexpr int64_t kDecodeCachedPassBytes = 64 << 20;   // ... this much
 constexpr int kTimedOutAt = 56;       // status word: serial number of a forward with an index of its own from a wait that ran out in layer0 until its layer1
 constexpr int kDefaultCus = 256;    // compute units a plan assumes before it has seen the device
 constexpr int kXcds = 8;            // XCDs of the device: workgroup i runs on XCD i % 8

@@ -146,3 +146,25 @@ def test_weights_are_streamed_for_experts_of_one_tile(lib, T, H, F, E, k, act, o
     notes = plan.forward()
     assert [n[6] for n in notes if n[0] in (LAYER0, LAYER1)] == [rows, rows]
     plan.close()
+
+
+@pytest.mark.parametrize("T, H, F, E, k, act, small", [
+    (2048, 256, 512, 4, 2, 0, True),       # 4096 pairs, half a MiB per expert: 64 MiB
+    (2049, 256, 512, 4, 2, 0, False),
+    (512, 1024, 1024, 1, 1, 0, True),      # 4 MiB: 64 MiB at 512 rows
+    (513, 1024, 1024, 1, 1, 0, False),
+    (1536, 768, 768, 1, 1, 1, False),
+    (2048, 512, 256, 5, 2, 1, False),
+    (2048, 256, 384, 7, 2, 1, False),
+    (2048, 512, 128, 10, 2, 1, True),
+    (600, 768, 384, 2, 2, 1, True),
+    (64, 1024, 1280, 1, 1, 0, False),      # 5 MiB
+    (4097, 256, 256, 1, 1, 0, False),
+])
+@pytest.mark.parametrize("packed", [0, 1])
+def test_small_weights_take_the_small_batch_kernel_while_they_pass_the_cache_often_enough(lib, T, H, F, E, k, act, small, packed):
+    plan = Plan(lib, T, H, F, E, k, act, weights_packed=packed)
+    kinds = [n[0] for n in plan.forward()]
+    assert (DECODE0 in kinds and DECODE1 in kinds) == small
+    assert (LAYER0 in kinds and LAYER1 in kinds) == (not small)
+    plan.close()
