@@ -98,7 +98,10 @@ __device__ __forceinline__ int load_table(UnitTable& L, const DecodeParams& p, i
 // table it leaves is three dependent round trips to memory at the start of a GroupGEMM launch; the ids are one.  out: the
 // workgroup that leaves the index of this forward in the workspace too, as k_index_small does without schedules, for the reduction and whoever
 // asks for it.  us per gate + layer, with k_index_small / so: 1 token of 8 experts of F = 1792 37.7 / 34.0, 16 tokens 70.2 / 67.5, 33 plain
-// 78.4 / 76.3, 1 token of F = 14336 121 / 119; 384 to 480 pairs 579 / 578, 194.2 / 195.3.
+// 78.4 / 76.3, 1 token of F = 14336 121 / 119; 64 experts of F = 1408, 128 pairs 164.5 / 162.4, 256 184.6 / 183.5, 384 188.0 / 187.9, 512 193.1 /
+// 194.4; 4 of H = 256, F = 512, 256 24.5 / 22.2, 384 24.4 / 23.4, 512 24.4 / 24.7; 64 of H = F = 512, 384 35.0 / 34.4, 512 35.0 / 36.1.  With more
+// experts there is more to number: 128 of F = 1024, popularity falling as rank^-1.2, 256 pairs 75.3 / 74.6, 384 93.0 / 94.0,
+// 512 97.1 / 99.1; 256 experts of F = 1024 128 pairs 103.4 / 105.0, 256 144.4 / 146.8.
 __device__ __forceinline__ void own_index(UnitTable& L, const DecodeParams& p, int rows_per_unit, int n_groups, const IndexParams& ip, bool out) {
   constexpr int kRuns = kOwnIndexRows / 64;
   const int tid = threadIdx.x, lane = tid & 63, E = p.E, R = p.R;

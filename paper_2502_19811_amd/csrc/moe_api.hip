@@ -584,8 +584,9 @@ int forward_impl(moe_plan_t* p, const void* x, const int32_t* topk_ids, const fl
   auto mark = [&](int i) { return !ev || hipEventRecord(ev[i], st) == hipSuccess; };
   if (!mark(0)) return MOE_ERR_HIP;
 
-  // Small batches: the GroupGEMMs make their index themselves, and layer0 leaves it in the workspace.
-  const bool own_index = (p->phases & 7) == 7 && decode0 && decode1 && s.R <= kOwnIndexRows;
+  // Small batches: the GroupGEMMs make their index themselves, and layer0 leaves it in the workspace (see own_index for the limits).
+  const int own_index_rows = s.E <= 64 ? kOwnIndexRows : (s.E <= kOwnIndexExperts ? kOwnIndexRowsManyExperts : 0);
+  const bool own_index = (p->phases & 7) == 7 && decode0 && decode1 && s.R <= own_index_rows;
   IndexParams ip = index_params(p, ws, topk_ids, order0);
   if (p->phases & 1) ip.forward_serial = ++p->serial;
   if (p->layer0_order < 0) {   // the order is this library's choice

@@ -25,7 +25,9 @@ constexpr int kDecodeRowsManyTiles = 8;    // ... and where the tile kernel has 
 constexpr double kCachedWeightBytes = 128e6;   // weights read by a forward beyond which its loads of them are non-temporal ...
 constexpr int kStreamRowsPerExpert = 244;   // ... in the tile kernel up to this many rows per expert on average, for experts of one tile ...
 constexpr double kStreamPairBytes = 160e6;   // ... or two of 64 rows that run at the same time, beyond these weights
-constexpr int kOwnIndexRows = 512;   // pairs up to which the small-batch GroupGEMMs make their index themselves
+constexpr int kOwnIndexRows = 384;   // pairs up to which the small-batch GroupGEMMs make their index themselves ...
+constexpr int kOwnIndexRowsManyExperts = 256;   // ... with more than 64 experts ...
+constexpr int kOwnIndexExperts = 128;   // ... and at most this many
 constexpr int kDecodeCachedRows = 4096;    // ... and pairs up to which it is used for weights of at most ...
 constexpr int64_t kDecodeCachedBytes = 4 << 20;   // ... the L2 of an XCD, while the passes over them are ...
 constexpr int64_t kDecodeCachedPassBytes = 64 << 20;   // ... this much

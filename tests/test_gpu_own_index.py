@@ -16,8 +16,13 @@ CASES = [
     (1, 256, 256, 4, 1, wl.ACT_GELU),
     (63, 256, 128, 8, 1, wl.ACT_SWIGLU),
     (65, 512, 256, 5, 1, wl.ACT_SWIGLU),
-    (32, 256, 128, 256, 16, wl.ACT_SWIGLU),     # 512 pairs, the last batch with an index of its own
-    (171, 256, 128, 64, 3, wl.ACT_SWIGLU),      # 513 pairs
+    (32, 256, 128, 128, 8, wl.ACT_SWIGLU),      # 256 pairs, the last batch of so many experts with an index of its own
+    (65, 256, 128, 128, 4, wl.ACT_SWIGLU),
+    (32, 256, 128, 256, 16, wl.ACT_SWIGLU),
+    (128, 256, 128, 64, 3, wl.ACT_SWIGLU),      # 384 pairs, the last batch
+    (385, 256, 128, 25, 1, wl.ACT_SWIGLU),
+    (171, 256, 128, 64, 3, wl.ACT_SWIGLU),
+    (192, 256, 512, 4, 2, wl.ACT_GELU),         # 384 pairs, 96 rows per expert
     (256, 256, 512, 4, 2, wl.ACT_GELU),         # 512 pairs, 128 rows per expert
     (257, 256, 512, 4, 2, wl.ACT_GELU),
     (2048, 256, 512, 4, 2, wl.ACT_GELU),        # 4096 pairs, the last such batch; 1366 of 3 experts

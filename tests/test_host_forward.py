@@ -168,3 +168,13 @@ def test_small_weights_take_the_small_batch_kernel_while_they_pass_the_cache_oft
     assert (DECODE0 in kinds and DECODE1 in kinds) == small
     assert (LAYER0 in kinds and LAYER1 in kinds) == (not small)
     plan.close()
+
+
+@pytest.mark.parametrize("T, E, k, own", [(384, 24, 1, 1), (385, 25, 1, 0), (192, 4, 2, 1), (193, 4, 2, 0), (96, 64, 4, 1), (97, 64, 4, 0),
+                                          (64, 65, 4, 1), (65, 65, 4, 0), (32, 128, 8, 1), (33, 128, 8, 0), (1, 129, 8, 0)])
+def test_up_to_how_many_pairs_a_small_batch_makes_its_index_itself(lib, T, E, k, own):
+    plan = Plan(lib, T, 256, 256, E, k, act=0, weights_packed=1)
+    notes = plan.forward()
+    assert [n[5] for n in notes if n[0] in (DECODE0, DECODE1)] == [own, own]
+    assert any(n[0] == INDEX for n in notes) == (not own)
+    plan.close()
