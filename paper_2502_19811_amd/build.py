@@ -15,8 +15,8 @@ SOURCES = ["moe_api.hip", "index_build.hip", "grouped_gemm.hip", "decode_gemm.hi
 
 
 def build_library(verbose: bool = False, extra_flags=(), out_path: str = LIB_PATH) -> str:
-    """Compiles the library, its sources side by side.  extra_flags / out_path: builds with extra instrumentation go elsewhere
-    than in-tree."""
+    """Compiles the library, its sources side by side, to objects next to out_path.  extra_flags / out_path: builds with extra
+    instrumentation go elsewhere than in-tree; the flags are those of every compilation and of the link."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     common = [hipcc, "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
               "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",   # no packed-fp32 code generation
@@ -34,11 +34,11 @@ def build_library(verbose: bool = False, extra_flags=(), out_path: str = LIB_PAT
         if verbose and err.strip():
             print(err, file=sys.stderr)
 
-    with tempfile.TemporaryDirectory(prefix="moe_build_", dir=PKG_DIR) as tmp:
+    with tempfile.TemporaryDirectory(prefix="moe_build_", dir=os.path.dirname(os.path.abspath(out_path))) as tmp:
         objects = [os.path.join(tmp, s.replace(".hip", ".o")) for s in SOURCES]
         with ThreadPoolExecutor(len(SOURCES)) as pool:
             list(pool.map(run, [common + ["-c", os.path.join(CSRC, s), "-o", o] for s, o in zip(SOURCES, objects)]))
-        run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", out_path] + objects)
+        run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", out_path] + list(extra_flags) + objects)
     return out_path
 
 
