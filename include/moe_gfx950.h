@@ -218,7 +218,7 @@ int moe_get_index_outputs(const moe_plan_t *plan, const void *workspace, int32_t
                           int32_t *expert_offsets, int32_t *perm, int32_t *inv_perm, void *hip_stream);
 
 /* Tile table of the GroupGEMMs as built by the last forward (dev pointers, each [max_tiles], any may be
- * NULL, entries beyond *n_tiles untouched; n_tiles: dev int32 [1]): expert, first sorted row, rows, the
+ * NULL, entries beyond *n_tiles mean nothing; n_tiles: dev int32 [1]): expert, first sorted row, rows, the
  * source segment the tile waits for, and the height (64 / 128 / 192 / 256 rows) of the kernel variant
  * that computes it.  An expert's rows are cut into tiles of "tile_m" rows; the remainder goes into the
  * lowest variant that holds it, so that little of a tile is padding.  max_tiles >= moe_plan_max_tiles(plan). */
